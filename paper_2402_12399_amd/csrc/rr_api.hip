@@ -124,7 +124,8 @@ static int make_dims(const rr_config *c, bool need_ffn, Dims *D) {
     if (rows_max * kmax * 2 >= ((int64_t)1 << 31) || (int64_t)c->d_model * c->d_ff * 2 >= ((int64_t)1 << 31))
       return RR_ERR_UNSUPPORTED;
   }
-  D->BM = c->dtype == RR_BF16 ? 256 : 64;
+  if (need_ffn && (c->d_model >= 1 << 23 || c->d_ff >= 1 << 23)) return RR_ERR_UNSUPPORTED;  // a GEMM tile's rows: 32-bit byte offsets
+  D->BM = need_ffn ? ffn_row_tile(*D) : 0;
   D->max_mtiles = need_ffn ? D->Rmax / D->BM + c->E : 0;  // routing-only calls cut no GEMM row tiles
   return RR_OK;
 }
@@ -317,8 +318,7 @@ int rr_moe_forward(const rr_config *cfg, const void *x, const float *w_router, c
   D.cb = router_count_blocks(D);  // the router ranks and counts: per 32 tokens for small batches
   D.NBc = (D.T + kTokBlock / D.cb - 1) / (kTokBlock / D.cb);
   hipError_t e = launch_router(D, x, w_router, bias, lg, nullptr, nullptr, &tb, &W, s);
-  const bool direct = !routing_only && ffn_writes_single_rows(D);
-  if (e == hipSuccess) e = launch_dispatch(D, lg, tb, W, true, direct ? W.row_dest : nullptr, s);
+  if (e == hipSuccess) e = launch_dispatch(D, lg, tb, W, true, routing_only ? nullptr : W.row_dest, s);
   if (routing_only) return e == hipSuccess ? RR_OK : RR_ERR_HIP;
   if (e == hipSuccess && !ffn_fuses_gather(D)) e = launch_gather(D, x, tb, W, s);
   if (e == hipSuccess) e = launch_ffn(D, x, tb, w1, w3, w2, W, out, s);

@@ -5,10 +5,12 @@
 // Both are "A[rows,K] times B[N,K]^T" with K contiguous in both operands.  Rows of expert e are
 // row_base[e] .. row_base[e+1]-1 and are cut into row tiles when the routing tables are built (TileInfo).
 //
-// bf16 main path (K % 64 == 0, K >= 192): persistent kernel, one workgroup of 8 waves per CU, tiles of
-// 256 x 256 staged rows dealt in an XCD-aware panel order (see "Tile order" in the kernel).
-//   * v_mfma_f32_32x32x16_bf16, fp32 accumulate; 2 x 4 waves, wave tile 128 x 64; two waves per SIMD
-//     so that one wave's LDS reads overlap the other's MFMAs.
+// Large bf16 layers: persistent kernel, one workgroup of 8 waves per CU, tiles of 256 x 256 staged rows
+// dealt in an XCD-aware panel order (see "Tile order" in the kernel).
+//   * v_mfma_f32_16x16x32_bf16, fp32 accumulate; 2 x 4 waves, wave tile 128 x 64; two waves per SIMD
+//     so that one wave's LDS reads overlap the other's MFMAs.  (A loop of MFMAs alone on normally
+//     distributed operands sustains 2030 TFLOP/s with this shape and 1330 with 32x32x16, 2470 and 1670
+//     on zeros: the wide shape was the kernel's ceiling.)
 //   * K advances in chunks of 64 through LDS rings - two 32 KB stages of A, three of B, 160 KB in all
 //     - filled by buffer_load ... lds (16 bytes per lane straight into LDS, no staging registers);
 //     the chunks of a workgroup's successive tiles form one stream.  A wave instruction fills 1 KB = 8
@@ -23,8 +25,9 @@
 //     the dispatch gather is then a per-lane row offset of the LDS DMA and costs no pass over HBM.
 //   * While a tile's epilogue stores drain, the first K chunk of the workgroup's next tile is
 //     already in flight (its tile id and table entries were fetched during the K loop).
-// Other bf16 shapes take a register-staged kernel; fp32 workloads a plain fp32 FMA tile kernel
-// (the fp32 accuracy bar forbids bf16 products).
+// Layers with few rows or short rows, and all fp32 layers: gemm_tile_kernel, smaller tiles of several shapes
+// (pick_shape chooses per GEMM).
+#include <algorithm>
 #include <type_traits>
 
 #include "rr_device.h"
@@ -34,7 +37,7 @@ namespace rr {
 namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // Scheduling groups for the instruction scheduler (masks of sched_group_barrier: 0x008 MFMA,
 // 0x100 LDS read, 0x020 global or buffer load).  They order the instructions of the surrounding
@@ -48,23 +51,16 @@ __device__ __forceinline__ void sched_mfma_lds_read() {
     sched_mfma_lds_read<N - 1>();
   }
 }
-// N times "one MFMA, then up to PER global loads":
-template <int N, int PER>
-__device__ __forceinline__ void sched_mfma_global_load() {
+// N times "one MFMA, one LDS read, one MFMA, one LDS read, one global load":
+template <int N>
+__device__ __forceinline__ void sched_mfma_lds_read_dma() {
   if constexpr (N > 0) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, PER, 0);
-    sched_mfma_global_load<N - 1, PER>();
+    sched_mfma_lds_read<2>();
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    sched_mfma_lds_read_dma<N - 1>();
   }
 }
 
-__device__ inline u32 f32_to_bf16_bits(float f) {
-  u32 u = __builtin_bit_cast(u32, f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
-__device__ inline float silu(float g) { return g / (1.0f + __expf(-g)); }
 // for results that are rounded to bf16 right away: hardware reciprocal (1 ulp) instead of a division
 __device__ inline float silu_fast(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
@@ -76,6 +72,23 @@ __device__ inline u32 pack_bf16(float a, float b) {
   return __builtin_bit_cast(u32, __builtin_convertvector(f, bf16x2_t));
 }
 __device__ inline float gelu_erf(float g) { return 0.5f * g * (1.0f + erff(g * 0.70710678118654752f)); }
+// The same for results that are rounded to bf16 right away.  g Phi(g) from the complementary error function
+// erfc(x) = exp(-x^2) t P(t), t = 1 / (1 + 0.45 x), x = |g| / sqrt(2) >= 0, with P of degree 7 fitted to
+// exp(x^2) erfc(x) for least relative error over [0, 12]: 6e-7 evaluated in fp32, relative also in the negative
+// tail where 1 + erf cancels.  16 instructions; both branches of erff took 20 us of a 6161 x 2728 epilogue.
+__device__ inline float gelu_fast(float g) {
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.45f * 0.70710678118654752f, fabsf(g), 1.0f));
+  float p = 0.0682215769f;
+  p = fmaf(p, t, -0.246015257f);
+  p = fmaf(p, t, 0.218920928f);
+  p = fmaf(p, t, 0.0308424651f);
+  p = fmaf(p, t, 0.193736749f);
+  p = fmaf(p, t, 0.22651131f);
+  p = fmaf(p, t, 0.253890255f);
+  p = fmaf(p, t, 0.253892308f);
+  const float tail = 0.5f * g * (t * p) * __builtin_amdgcn_exp2f(g * g * -0.72134752044448170f);  // g Phi(-|g|)
+  return g < 0.0f ? tail : g - tail;
+}
 
 constexpr int GB_BK = 64;             // bf16 elements per K chunk = 128 B per LDS row
 constexpr int GB_ROW_BYTES = 128;
@@ -88,6 +101,7 @@ struct GemmArgs {
   void *Cout;           // [rows, N]
   int K, N;
   int NT;               // column tiles
+  int sub;              // small-tile kernel: row tiles per row tile of the table
   const TileInfo *tiles;
   const int32_t *ctl;   // [0] number of row tiles
   // GATHER only
@@ -101,71 +115,38 @@ struct GemmArgs {
   void *Out;
 };
 
-// Epilogue shared by the bf16 kernels: activation, round to bf16, store (masked on edge tiles).
-// Accumulator element v of a 32x32 fragment is row 8*(v/4) + 4*(lane/32) + v%4, column lane%32.
-// GATED: fragments j < WN/2 are gate columns, j >= WN/2 the matching up columns.
-template <int WM, int WN, bool GATED, int ACT>
-__device__ inline void store_tile(f32x16 (&acc)[WM][WN], uint16_t *Cb, int rbase, int rows_e, int m0, int n0, int N,
-                                  int wm, int wn, int lane) {
-  constexpr int NJ = GATED ? WN / 2 : WN;  // output column fragments per wave
-  const int fr = lane & 31, fh = lane >> 5;
-  const int wrow0 = m0 + wm * WM * 32, wcol0 = n0 + wn * NJ * 32;
-  const bool interior = wrow0 + WM * 32 <= rows_e && wcol0 + NJ * 32 <= N;
-  uint16_t *base = Cb + (size_t)(rbase + wrow0 + 4 * fh) * N + wcol0 + fr;
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      uint16_t *p = base + (size_t)(i * 32) * N + j * 32;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float c = acc[i][j][v];
-        if (GATED) c = silu(c) * acc[i][j + NJ][v];
-        if (ACT == RR_ACT_GELU) c = gelu_erf(c);
-        const int dr = 8 * (v >> 2) + (v & 3);
-        if (interior || (wrow0 + i * 32 + 4 * fh + dr < rows_e && wcol0 + j * 32 + fr < N))
-          p[(size_t)dr * N] = (uint16_t)f32_to_bf16_bits(c);
-      }
-    }
-  }
-}
-
 // Epilogue of the persistent kernel, which multiplies with the operands swapped (B fragment first):
-// the 32x32 accumulator then holds the transposed tile, i.e. a lane owns ONE output row (lane % 32
-// of the A fragment) and, per fragment, four groups of four consecutive columns
-// (8 * (v / 4) + 4 * (lane / 32) + v % 4): four 8-byte stores per fragment instead of sixteen
-// 2-byte ones.
+// the 16x16 accumulator then holds the transposed tile, i.e. a lane owns ONE output row (lane % 16 of
+// the A fragment) and four consecutive columns, 4 * (lane / 16) .. + 3 of the B fragment: one 8-byte
+// store per accumulator.
 // dest (DIRECT): per fragment row of this lane, the row of Ob that the same values are also stored to, or -1.
 template <int WM, int WN, bool GATED, int ACT, bool DIRECT = false>
-__device__ inline void store_tile_t(f32x16 (&acc)[WM][WN], uint16_t *Cb, int rbase, int rows_e, int m0, int n0, int N,
+__device__ inline void store_tile_t(f32x4 (&acc)[WM][WN], uint16_t *Cb, int rbase, int rows_e, int m0, int n0, int N,
                                     int wm, int wn, int lane, const int *dest = nullptr, uint16_t *Ob = nullptr) {
   constexpr int NJ = GATED ? WN / 2 : WN;  // output column fragments per wave
-  const int fr = lane & 31, fh = lane >> 5;
-  const int wrow0 = m0 + wm * WM * 32, wcol0 = n0 + wn * NJ * 32;
-  const bool cols_in = wcol0 + NJ * 32 <= N;  // N % 8 == 0: a group of four columns is inside or outside as a whole
+  const int fr = lane & 15, fg = lane >> 4;
+  const int wrow0 = m0 + wm * WM * 16, wcol0 = n0 + wn * NJ * 16;
+  const bool cols_in = wcol0 + NJ * 16 <= N;  // N % 8 == 0: a group of four columns is inside or outside as a whole
 #pragma unroll
   for (int i = 0; i < WM; ++i) {
-    const int row = wrow0 + i * 32 + fr;
+    const int row = wrow0 + i * 16 + fr;
     if (row >= rows_e) continue;
-    uint16_t *prow = Cb + (size_t)(rbase + row) * N + wcol0 + 4 * fh;
+    uint16_t *prow = Cb + (size_t)(rbase + row) * N + wcol0 + 4 * fg;
     uint16_t *orow = nullptr;
-    if (DIRECT && dest[i] >= 0) orow = Ob + (size_t)dest[i] * N + wcol0 + 4 * fh;
+    if (DIRECT && dest[i] >= 0) orow = Ob + (size_t)dest[i] * N + wcol0 + 4 * fg;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
+      float c[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float c[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c[u] = acc[i][j][4 * g + u];
-          if (GATED) c[u] = silu_fast(c[u]) * acc[i][j + NJ][4 * g + u];
-          if (ACT == RR_ACT_GELU) c[u] = gelu_erf(c[u]);
-        }
-        if (cols_in || wcol0 + j * 32 + 8 * g + 4 * fh < N) {
-          const uint2 val = make_uint2(pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3]));
-          *reinterpret_cast<uint2 *>(prow + j * 32 + 8 * g) = val;
-          if (DIRECT && orow) *reinterpret_cast<uint2 *>(orow + j * 32 + 8 * g) = val;
-        }
+      for (int u = 0; u < 4; ++u) {
+        c[u] = acc[i][j][u];
+        if (GATED) c[u] = silu_fast(c[u]) * acc[i][j + NJ][u];
+        if (ACT == RR_ACT_GELU) c[u] = gelu_fast(c[u]);
+      }
+      if (cols_in || wcol0 + j * 16 + 4 * fg < N) {
+        const uint2 val = make_uint2(pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3]));
+        *reinterpret_cast<uint2 *>(prow + j * 16) = val;
+        if (DIRECT && orow) *reinterpret_cast<uint2 *>(orow + j * 16) = val;
       }
     }
   }
@@ -184,13 +165,11 @@ __device__ inline void dma_barrier() {
 }
 
 // ------------------------------------------------------------------ bf16, persistent, LDS DMA
-constexpr int PK_WAVES_M = 2, PK_WAVES_N = 4, PK_WM = 4, PK_WN = 2;
+constexpr int PK_WAVES_M = 2, PK_WAVES_N = 4, PK_WM = 8, PK_WN = 4;  // waves, and 16-row fragments of a wave: 128 x 64
 constexpr int PK_NW = PK_WAVES_M * PK_WAVES_N;
 constexpr int PK_THREADS = PK_NW * 64;
-constexpr int PK_BM = PK_WAVES_M * PK_WM * 32;     // 256
-constexpr int PK_BROWS = PK_WAVES_N * PK_WN * 32;  // 256 staged B rows
-constexpr int PK_STAGE = (PK_BM + PK_BROWS) * GB_ROW_BYTES;  // one K chunk of A and B (the register-staged kernel)
-constexpr int PK_LDS = 2 * PK_STAGE;
+constexpr int PK_BM = PK_WAVES_M * PK_WM * 16;     // 256
+constexpr int PK_BROWS = PK_WAVES_N * PK_WN * 16;  // 256 staged B rows
 constexpr int PK_A_STAGE = PK_BM * GB_ROW_BYTES, PK_B_STAGE = PK_BROWS * GB_ROW_BYTES;
 constexpr int PK_A_STAGES = 2, PK_B_STAGES = 3;
 constexpr int PK_B_BASE = PK_A_STAGES * PK_A_STAGE;
@@ -207,7 +186,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "operand boundaries must fall between load instructions");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  const int K = P.K, N = P.N, NT = P.NT, KT = K / GB_BK;
+  const int K = P.K, N = P.N, NT = P.NT, KT = (K + GB_BK - 1) / GB_BK;
   // Tile order.  Workgroups are dealt to the 8 XCDs round-robin (workgroup g runs on XCD g % 8) and
   // each XCD has its own L2.  The tiles are numbered panel by panel - panels of pm x pn neighbouring
   // tiles (4 row tiles x 8 column tiles for 32 workgroups per XCD), column panels first, ragged at the
@@ -243,24 +222,14 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps LDS-DMA addressing scalar
   const int wm = w / PK_WAVES_N, wn = w % PK_WAVES_N;
-  const int fr = lane & 31, fh = lane >> 5;
+  const int fr = lane & 15, fg = lane >> 4;
 
-  // fragment addressing (the same for every tile): lane reads row (lane & 31), chunk 2*ks + (lane >> 5)
-  int a_off[WM], b_off[WN];
-  const int fsw = swz(fr);  // fragment rows start at multiples of 32, so the swizzle depends on fr only
-#pragma unroll
-  for (int i = 0; i < WM; ++i) a_off[i] = ((wm * WM + i) * 32 + fr) * GB_ROW_BYTES;
-#pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    int r;
-    if (GATED) {
-      constexpr int H = WN / 2;
-      r = (j < H) ? (wn * H + j) * 32 + fr : BN + (wn * H + (j - H)) * 32 + fr;
-    } else {
-      r = (wn * WN + j) * 32 + fr;
-    }
-    b_off[j] = r * GB_ROW_BYTES;
-  }
+  // fragment addressing (the same for every tile): lane reads row (lane & 15), chunk 4*ks + (lane >> 4)
+  const int fsw = swz(fr);  // fragment rows start at multiples of 16, so the swizzle depends on fr only
+  const int a_off = (wm * WM * 16 + fr) * GB_ROW_BYTES;  // fragment i: + i * 16 rows
+  // gated: the first half of a wave's column fragments are gate columns, the second the matching up columns
+  const int b_off = (wn * (GATED ? WN / 2 : WN) * 16 + fr) * GB_ROW_BYTES;
+  auto b_frag = [&](int j) { return (GATED && j >= WN / 2 ? BN + (j - WN / 2) * 16 : j * 16) * GB_ROW_BYTES; };
 
   // per-tile state.  A tile's table entry is fetched two tiles ahead and (GATHER) its token indices
   // one tile ahead, as plain vector loads issued right after a tile's first barrier: they complete
@@ -292,7 +261,9 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   };
   const int lrow = w * 8 + (lane >> 3);            // stage row of this lane in instruction 0
   const int lcol = ((lane & 7) ^ swz(lrow)) * 16;  // byte position of its 16-byte chunk in the global row
-  const int rstep = NW * 8 * K * 2;                // bytes between the rows of consecutive instructions
+  const unsigned rstep = NW * 8 * K * 2;           // bytes between the rows of consecutive instructions
+  // this lane's piece of the last chunk lies past the end of the row (K no multiple of the chunk)
+  const bool past = (KT - 1) * GB_BK * 2 + lcol >= K * 2;
   const char *Ab = static_cast<const char *>(P.A);
   auto raw_load = [&](int Lt, int4 &ra, int4 &rb) {
     const int4 *q = reinterpret_cast<const int4 *>(P.tiles + Lt / NT);
@@ -327,7 +298,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   };
   auto make_tile = [&](const Info &f, const int (&tok)[NIA], Tile &t) {
     t.e = f.e; t.m0 = f.m0; t.rbase = f.rbase; t.rows_e = f.rows_e; t.n0 = f.n0;
-    t.live = min(WM, max(0, (f.rows_e - f.m0 - wm * WM * 32 + 31) >> 5));
+    t.live = min(WM, max(0, (f.rows_e - f.m0 - wm * WM * 16 + 15) >> 4));
     const char *B0b = static_cast<const char *>(P.B0) + (size_t)f.e * N * K * 2;
     const char *B1b = GATED ? static_cast<const char *>(P.B1) + (size_t)f.e * N * K * 2 : B0b;
     if (GATHER) {
@@ -350,32 +321,51 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     }
     t.vb = (f.n0 + lrow) * K * 2 + lcol;  // gate and up rows (GATED) sit at the same offsets of W1 and W3
   };
-  // One K chunk of A (NIA instructions per wave) or of B (NIB) into a stage of its ring.
+  // The stream of K chunks that the LDS rings are filled from: where the next chunk of A (NIA instructions
+  // per wave) and of B (NIB) comes from.  It runs ahead of the multiplication into the next tile; past the
+  // last tile its ranges are 0, so that every chunk issues the same number of loads.
   constexpr int NIB = NI - NIA;
-  auto issue_a = [&](const Tile &t, int kt, int stage) {
+  unsigned sva[NVA], svb;  // offsets of this lane
+  int ska, skb, sna, snb;  // byte positions in K, ranges
+  unsigned long long spa, spb0, spb1;
+  auto stream_a = [&](const Tile &t, bool real) {
+#pragma unroll
+    for (int i = 0; i < NVA; ++i) sva[i] = t.va[i];
+    spa = t.pa;
+    sna = real ? t.na : 0;
+    ska = 0;
+  };
+  auto stream_b = [&](const Tile &t, bool real) {
+    svb = t.vb;
+    spb0 = t.pb0;
+    spb1 = t.pb1;
+    snb = real ? N * K * 2 : 0;
+    skb = 0;
+  };
+  auto issue_a = [&](int stage) {
     char *st = smem + stage * PK_A_STAGE + w * 1024;
-    const int koff = kt * (GB_BK * 2);
-    const __amdgpu_buffer_rsrc_t rsA = rsrc_of(t.pa, t.na);
+    const __amdgpu_buffer_rsrc_t rsA = rsrc_of(spa, sna);
 #pragma unroll
     for (int i = 0; i < NIA; ++i) {
       auto lp = (__attribute__((address_space(3))) void *)(st + i * NW * 1024);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, lp, 16, GATHER ? t.va[i < NVA ? i : 0] : t.va[0] + i * rstep, koff, 0,
-                                               0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, lp, 16, GATHER ? sva[i < NVA ? i : 0] : sva[0] + i * rstep, ska, 0, 0);
     }
+    ska += GB_BK * 2;
   };
-  auto issue_b = [&](const Tile &t, int kt, int stage) {
+  auto issue_b = [&](int stage, int i0, int i1) {  // instructions i0 .. i1 - 1 of the chunk
     char *st = smem + PK_B_BASE + stage * PK_B_STAGE + w * 1024;
-    const int koff = kt * (GB_BK * 2);
-    const __amdgpu_buffer_rsrc_t rsB0 = rsrc_of(t.pb0, N * K * 2), rsB1 = rsrc_of(t.pb1, N * K * 2);
+    const __amdgpu_buffer_rsrc_t rsB0 = rsrc_of(spb0, snb), rsB1 = rsrc_of(spb1, snb);
 #pragma unroll
     for (int i = 0; i < NIB; ++i) {
+      if (i < i0 || i >= i1) continue;
       // which weight matrix instruction i reads is known at compile time
       auto lp = (__attribute__((address_space(3))) void *)(st + i * NW * 1024);
       if (!GATED || i < NIB0)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB0, lp, 16, t.vb + i * rstep, koff, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB0, lp, 16, svb + i * rstep, skb, 0, 0);
       else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB1, lp, 16, t.vb + (i - NIB0) * rstep, koff, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB1, lp, 16, svb + (i - NIB0) * rstep, skb, 0, 0);
     }
+    if (i1 == NIB) skb += GB_BK * 2;
   };
   auto next_b = [](int sb) { return sb == PK_B_STAGES - 1 ? 0 : sb + 1; };
 
@@ -385,7 +375,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   // fetched two chunks ahead, the activations (mostly L2 hits: a row tile is shared by all column
   // tiles) one.  Each chunk issues A(c+1) and then B(c+2), so the barrier that publishes chunk c+1
   // waits for everything but the NIB youngest loads.  KT >= 3.
-  f32x16 acc[WM][WN];
+  f32x4 acc[WM][WN];
   Tile cur, nxt;
   Info info1{}, info2{};                              // table entries of this workgroup's next two tiles
   int4 ra2 = make_int4(0, 0, 0, 0), rb2 = ra2;        // raw table entry of the tile after next
@@ -404,9 +394,11 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
       raw_load(L1, ra, rb);
       info1 = finalize(L1, ra, rb);
     }
-    issue_a(cur, 0, sa);
-    issue_b(cur, 0, sb);
-    issue_b(cur, 1, next_b(sb));
+    stream_a(cur, true);
+    stream_b(cur, true);
+    issue_a(sa);
+    issue_b(sb, 0, NIB);
+    issue_b(next_b(sb), 0, NIB);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIB) : "memory");  // own A(0), B(0) have landed
   }
   while (true) {
@@ -414,9 +406,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+      for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // Everybody's A(0), B(0) have landed: each wave saw its own arrive before it stored the previous
     // tile's results, so the barrier itself waits for no memory operation (the stores and B(1) may
     // still be on their way).
@@ -430,60 +420,90 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     for (int i = 0; i < WM; ++i) {
       dest[i] = -1;
       if (DIRECT) {
-        const int row = cur.m0 + (wm * WM + i) * 32 + fr;
+        const int row = cur.m0 + (wm * WM + i) * 16 + fr;
         dest[i] = P.row_dest[cur.rbase + min(row, cur.rows_e - 1)];
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    issue_a(cur, 1, sa ^ 1);
-    issue_b(cur, 2, next_b(next_b(sb)));
+    issue_a(sa ^ 1);
+    issue_b(next_b(next_b(sb)), 0, NIB);
 
     // Ragged row tiles: the last tile of an expert is mostly padding.  A wave skips the fragment
-    // loads and MFMAs of its 32-row fragments that lie wholly past the expert's last row (a
+    // loads and MFMAs of its 16-row fragments that lie wholly past the expert's last row (a
     // wave-uniform test), so a padded tile costs MFMA time in proportion to its real rows.  Full
     // tiles take a branch-free copy of the loop (FULL), which keeps its counted LDS waits exact.
     const int live = cur.live;
     auto k_loop = [&](auto full_tag) {
       constexpr bool FULL = decltype(full_tag)::value;
-      bf16x8 af[2][WM], bfr[2][WN];
-      auto load_frags = [&](const char *sta, const char *stb, int ks, int slot) {
-        const int pos = ((2 * ks + fh) ^ fsw) << 4;
+      // A chunk is four steps: k-step ks (of two), half hf of the wave's A rows.  A step multiplies half of the
+      // A fragments with all B fragments of its k-step: 16 MFMAs.
+      constexpr int HM = WM / 2;
+      bf16x8 af[2][HM], bfr[2][WN];
+      auto load_a = [&](const char *sta, int ks, int hf) {
+        const char *p = sta + a_off + (((4 * ks + fg) ^ fsw) << 4);
 #pragma unroll
-        for (int i = 0; i < WM; ++i)
-          if (FULL || i < live) af[slot][i] = *reinterpret_cast<const bf16x8 *>(sta + a_off[i] + pos);
+        for (int i = 0; i < HM; ++i)
+          if (FULL || hf * HM + i < live)
+            af[hf][i] = *reinterpret_cast<const bf16x8 *>(p + (hf * HM + i) * 16 * GB_ROW_BYTES);
+      };
+      auto load_b = [&](const char *stb, int ks) {
+        const char *p = stb + b_off + (((4 * ks + fg) ^ fsw) << 4);
         if (FULL || live > 0) {
 #pragma unroll
-          for (int j = 0; j < WN; ++j) bfr[slot][j] = *reinterpret_cast<const bf16x8 *>(stb + b_off[j] + pos);
+          for (int j = 0; j < WN; ++j) bfr[ks][j] = *reinterpret_cast<const bf16x8 *>(p + b_frag(j));
         }
       };
-      auto mfma_step = [&](int slot) {
+      auto mfma_step = [&](int ks, int hf) {
 #pragma unroll
-        for (int i = 0; i < WM; ++i)
-          if (FULL || i < live) {
+        for (int i = 0; i < HM; ++i)
+          if (FULL || hf * HM + i < live) {
 #pragma unroll
             for (int j = 0; j < WN; ++j)
               // B fragment first: the accumulator holds the transposed tile (see store_tile_t)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
+              acc[hf * HM + i][j] =
+                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ks][j], af[hf][i], acc[hf * HM + i][j], 0, 0, 0);
           }
       };
-      // Software pipeline: the fragment loads of the NEXT k-step are spread over the MFMAs of the
-      // current one, one LDS read behind each of the first MFMAs.  (With all the reads in front
-      // of the MFMAs the LDS pipe is asked for 6 KB per wave in one burst and is then idle for the
-      // rest of the step; both waves of a SIMD doing so in turn leaves MFMA slots empty.)  The
-      // last k-step of a chunk runs after the barrier; the global loads of the stream go behind
-      // its last two MFMAs.  The loop is rotated so that its body starts at the barrier (the
-      // compiler's wait counting is exact only inside one basic block).
-      auto step = [&](const char *sta, const char *stb, int ks_next, int slot_next, int slot_now) {
-        load_frags(sta, stb, ks_next, slot_next);
-        mfma_step(slot_now);
-        sched_mfma_lds_read<WM + WN>();
+      // The chunk's LDS-DMA loads are spread over its steps, one behind every second MFMA: A(kt+1) in the step
+      // after the barrier, B(kt+2) in the two after it.  (All eight in one place - 64 per CU, 16 clocks of the
+      // load unit each - kept the waves waiting at the issue: down projection at 8 K tokens x 5632 296 -> 275 us.
+      // It takes straight-line code, hence the stream of chunks that runs past the tile's end.)
+      // Software pipeline: the fragments that the NEXT step needs and this one does not hold are read
+      // under the MFMAs of this one, one LDS read behind each of the first MFMAs.  (With all the reads in
+      // front of the MFMAs the LDS pipe is asked for several KB per wave in one burst and is then idle
+      // for the rest of the step; both waves of a SIMD doing so in turn leaves MFMA slots empty.)  The
+      // last step of a chunk runs after the barrier; the global loads of the stream go behind its last
+      // MFMAs.  The loop is rotated so that its body starts at the barrier (the compiler's wait
+      // counting is exact only inside one basic block).
+      // the first three steps of a chunk; the B loads of the stream ride in the first two of them
+      auto steps = [&](const char *sta, const char *stb, auto dma_tag, int bstage) {
+        constexpr bool DMA = decltype(dma_tag)::value;
+        load_a(sta, 0, 1);
+        if (DMA) issue_b(bstage, 0, NIB / 2);
+        mfma_step(0, 0);
+        if (DMA) sched_mfma_lds_read_dma<NIB / 2>();
+        else sched_mfma_lds_read<HM>();
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(sta, 1, 0);
+        load_b(stb, 1);
+        if (DMA) issue_b(bstage, NIB / 2, NIB);
+        mfma_step(0, 1);
+        if (DMA) {
+          sched_mfma_lds_read_dma<NIB / 2>();
+          sched_mfma_lds_read<HM + WN - NIB>();
+        } else {
+          sched_mfma_lds_read<HM + WN>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(sta, 1, 1);
+        mfma_step(1, 0);
+        sched_mfma_lds_read<HM>();
         __builtin_amdgcn_sched_barrier(0);
       };
       const char *sta = smem + sa * PK_A_STAGE, *stb = smem + PK_B_BASE + sb * PK_B_STAGE;
-      load_frags(sta, stb, 0, 0);
-      step(sta, stb, 1, 1, 0);
-      step(sta, stb, 2, 0, 1);
-      step(sta, stb, 3, 1, 0);
+      load_a(sta, 0, 0);
+      load_b(stb, 0);
+      steps(sta, stb, std::false_type{}, 0);
       // The looked-up values are consumed here, unconditionally, rather than where they are first
       // needed: in straight-line code after the lookups the compiler's wait for them is a counted
       // one (the A(1) and B(2) loads behind them stay in flight), and nothing it tracks is pending
@@ -496,35 +516,32 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
         for (int i = 0; i < WM; ++i) asm volatile("" : "+v"(dest[i]));
       }
       for (int kt = 1; kt < KT; ++kt) {
+        // the stream moves on to the next tile: A one chunk, B two chunks before this tile ends
+        if (kt == KT - 2) stream_b(nxt, have1);
+        if (kt == KT - 1) stream_a(nxt, have1);
+        if (K % GB_BK) {  // in the last chunk of a row, pieces past its end are sent out of range: they read as zero
+          if (kt == KT - 3 && past) svb = 0x7ffffff0;
+          if (kt == KT - 2 && past) {
+#pragma unroll
+            for (int i = 0; i < NVA; ++i) sva[i] = 0x7ffffff0;
+          }
+        }
         // A(kt) and B(kt) have landed - the B issued after A(kt) may still be on its way - and
         // nobody reads the stages of chunk kt-1 any more
-        if (kt + 1 < KT || have1) dma_barrier<NIB>();
-        else dma_barrier<0>();
+        dma_barrier<NIB>();
         sa ^= 1;
         sb = next_b(sb);
         sta = smem + sa * PK_A_STAGE;
         stb = smem + PK_B_BASE + sb * PK_B_STAGE;
-        load_frags(sta, stb, 0, 0);
-        mfma_step(1);  // last k-step of chunk kt-1
-        sched_mfma_lds_read<WM + WN>();
-        sched_mfma_global_load<2, 8>();
-        // the stream's next loads: the rest of this tile, then the first two chunks of the next one
-        if (kt + 2 < KT) {
-          issue_a(cur, kt + 1, sa ^ 1);
-          issue_b(cur, kt + 2, next_b(next_b(sb)));
-        } else if (kt + 2 == KT) {
-          issue_a(cur, kt + 1, sa ^ 1);
-          if (have1) issue_b(nxt, 0, next_b(next_b(sb)));
-        } else if (have1) {
-          issue_a(nxt, 0, sa ^ 1);
-          issue_b(nxt, 1, next_b(next_b(sb)));
-        }
+        load_a(sta, 0, 0);
+        load_b(stb, 0);
+        issue_a(sa ^ 1);
+        mfma_step(1, 1);  // last step of chunk kt-1
+        sched_mfma_lds_read_dma<NIA>();
         __builtin_amdgcn_sched_barrier(0);
-        step(sta, stb, 1, 1, 0);
-        step(sta, stb, 2, 0, 1);
-        step(sta, stb, 3, 1, 0);
+        steps(sta, stb, std::true_type{}, next_b(next_b(sb)));
       }
-      mfma_step(1);
+      mfma_step(1, 1);
     };
     if (live == WM)
       k_loop(std::true_type{});
@@ -533,12 +550,15 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 
     // own A(0), B(0) of the next tile have landed (they were issued one and two chunks ago), before
     // the stores below join the queue of outstanding memory operations
-    if (have1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIB) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIB) : "memory");
     sa ^= 1;
     sb = next_b(sb);
     store_tile_t<WM, WN, GATED, ACT, DIRECT>(acc, static_cast<uint16_t *>(P.Cout), cur.rbase, cur.rows_e, cur.m0, cur.n0,
                                              N, wm, wn, lane, dest, static_cast<uint16_t *>(P.Out));
-    if (!have1) break;
+    if (!have1) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stream's loads past the last tile still write this LDS
+      break;
+    }
     cur = nxt;
     L = L1;
     L1 = L2;
@@ -549,194 +569,220 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 #endif
 }
 
-// ------------------------------------------------------------------ bf16, any K % 8 == 0
-// Register-staged loads (global -> registers -> LDS), 4 waves, tile 256 x 256 staged rows, one
-// workgroup per tile.  Handles K tails by zero-filling whole 16-byte chunks.
-constexpr int GS_THREADS = 256;
-template <bool GATED, int ACT>
-__global__ __launch_bounds__(GS_THREADS) void gemm_bf16_staged_kernel(GemmArgs P) {
-  constexpr int WAVES_N = 2, WM = 4, WN = 4;
-  constexpr int BM = 256, BROWS = 256;
-  constexpr int BN = GATED ? BROWS / 2 : BROWS;
-  constexpr int A_LD = BM / 32, B_LD = BROWS / 32;  // 16-byte loads per thread per chunk
-  constexpr int STAGE_BYTES = (BM + BROWS) * GB_ROW_BYTES;
+// ------------------------------------------------------------------ small tiles, bf16 and fp32, any K % 8 == 0
+// Everything the 256 x 256 kernel is not made for: fp32 layers, row lengths that are no multiple of the
+// K chunk or shorter than three of them, and batches whose experts get few rows.  One workgroup per tile,
+// several workgroups per CU: one's epilogue, table lookups and barrier waits run under another's MFMAs.
+//   * K advances in chunks of 128 bytes of every staged row through a ring of ST stages filled by
+//     buffer_load ... lds with the same row layout and swizzle as above; a chunk is requested ST - 1 chunks
+//     ahead, into the stage that the barrier at the top of the chunk has just freed, and every chunk
+//     issues the same number of loads (past the end: out of range, which costs no traffic), so one
+//     counted wait serves any K.  Pieces past the end of a row are sent out of range as well: they read as zero.
+//   * bf16: v_mfma_f32_16x16x32_bf16.  fp32: v_mfma_f32_16x16x4_f32, fp32 products and accumulation; a
+//     lane's 16-byte piece is its operand of four MFMAs - the K order inside a chunk is then a
+//     permutation, the same for both operands.
+// Measured, before (register-staged bf16 kernel, fp32 FMA kernel) -> now: 6161 rows, 1000 x 2728, bf16 GELU: up 169 -> 58 us,
+// down 120 -> 66; 3931 rows, 1024 x 2816, fp32 SwiGLU: up 612 -> 354 us (128 TFLOP/s; the fp32 MFMA pipe sustains 154),
+// down 397 -> 184.  bf16 tiles of this size are bound by the operand bytes per flop (L2 -> LDS), fp32 ones by the MFMAs.
+// WM x WN: 16-row fragments of a wave.
+template <bool BF16_, int WAVES_M_, int WAVES_N_, int WM_, int WN_, int ST_, int OCC_>
+struct TileShape {
+  static constexpr bool BF16 = BF16_;
+  static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, WM = WM_, WN = WN_, ST = ST_, OCC = OCC_;
+  static constexpr int NW = WAVES_M * WAVES_N, THREADS = NW * 64;
+  static constexpr int BM = WAVES_M * WM * 16, BROWS = WAVES_N * WN * 16;
+  static constexpr int STAGE = (BM + BROWS) * GB_ROW_BYTES, SMEM = ST * STAGE;
+};
+
+template <class S, bool GATED, int ACT, bool GATHER, bool DIRECT>
+__global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs P) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int WM = S::WM, WN = S::WN, NW = S::NW, BM = S::BM, ST = S::ST;
+  constexpr int BN = GATED ? S::BROWS / 2 : S::BROWS;
+  constexpr int NIA = BM / 8 / NW, NIB = S::BROWS / 8 / NW, NI = NIA + NIB, NIB0 = BN / 8 / NW;
+  constexpr int ES = S::BF16 ? 2 : 4, CE = GB_ROW_BYTES / ES, PE = 16 / ES;  // elements per chunk of a row, per piece
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "operand boundaries must fall between load instructions");
+  static_assert((8 * NW) % 16 == 0, "swizzle must not depend on the instruction index");
+  static_assert(!GATED || WN % 2 == 0, "a wave holds the gate and the up columns of its outputs");
+  constexpr int kPanel = 8;  // row tiles that share a column tile of weights before the next column tile
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  const int mt = blockIdx.x / P.NT;
-  if (mt >= P.ctl[0]) return;
-  const TileInfo ti = P.tiles[mt];
-  const int e = ti.expert, m0 = ti.row0, rbase = ti.rbase, rows_e = ti.rows;
-  const int n0 = (blockIdx.x - mt * P.NT) * BN;
-  const int K = P.K, N = P.N;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w / WAVES_N, wn = w % WAVES_N;
+  // tile number: each XCD (workgroup g runs on XCD g % 8) takes a contiguous run; panels of kPanel row
+  // tiles, column tiles inside a panel, row tiles inside a column: neighbours share weights
+  // (the table's row tiles are P.sub times as high as this kernel's)
+  const int MT = P.ctl[0] * P.sub, NT = P.NT, total = MT * NT;
+  const int per = (total + 7) >> 3, run = blockIdx.x >> 3, t = (blockIdx.x & 7) * per + run;
+  if (run >= per || t >= total) return;
+  const int panel = t / (kPanel * NT), r = t - panel * kPanel * NT, h = min(kPanel, MT - panel * kPanel);
+  const int nt = r / h, mt = panel * kPanel + r - nt * h;
+  const TileInfo ti = P.tiles[mt / P.sub];
+  const int m0 = ti.row0 + mt % P.sub * BM;
+  if (m0 >= ti.rows) return;
+  const int K = P.K, N = P.N, KT = (K + CE - 1) / CE;
+  const int e = ti.expert, rbase = ti.rbase, rows_e = ti.rows, n0 = nt * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w / S::WAVES_N, wn = w % S::WAVES_N;
+  const int fr = lane & 15, fg = lane >> 4;
+  constexpr unsigned PAST = 0x7ffffff0u;  // past every operand's range: reads as zero
 
-  const char *Ab = static_cast<const char *>(P.A);
-  const char *B0b = static_cast<const char *>(P.B0) + (size_t)e * N * K * 2;
-  const char *B1b = GATED ? static_cast<const char *>(P.B1) + (size_t)e * N * K * 2 : nullptr;
-
-  // per-thread global sources: chunk id q = tid + 256 i -> row q / 8, chunk q % 8
-  const int lc = tid & 7;
-  const char *a_src[A_LD];
-  const char *b_src[B_LD];
-  int lds_off_a[A_LD], lds_off_b[B_LD];
+  // ---- operands: buffers that start at the tile's first row (GATHER: at x) and end with its last one
+  const int lrow = w * 8 + (lane >> 3);            // stage row of this lane in instruction 0
+  const int piece = (lane & 7) ^ swz(lrow);        // 16-byte piece of the row's chunk that belongs at its position
+  const unsigned rowb = (unsigned)K * ES;
+  const unsigned rstep = NW * 8 * rowb;            // between the rows of consecutive instructions
+  auto rsrc = [](const char *base, size_t off, long long range) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base) + off, 0,
+                                             __builtin_amdgcn_readfirstlane((int)range), BUF_FLAGS);
+  };
+  const size_t mat = (size_t)e * N * K * ES + (size_t)n0 * rowb;
+  const long long brange = (long long)min(BN, N - n0) * rowb;
+  const __amdgpu_buffer_rsrc_t rsB0 = rsrc(static_cast<const char *>(P.B0), mat, brange);
+  const __amdgpu_buffer_rsrc_t rsB1 = GATED ? rsrc(static_cast<const char *>(P.B1), mat, brange) : rsB0;
+  const __amdgpu_buffer_rsrc_t rsA =
+      GATHER ? rsrc(static_cast<const char *>(P.A), 0, P.a_bytes)
+             : rsrc(static_cast<const char *>(P.A), (size_t)(rbase + m0) * rowb, (long long)min(BM, rows_e - m0) * rowb);
+  unsigned va[GATHER ? NIA : 1];
+  if (GATHER) {
 #pragma unroll
-  for (int i = 0; i < A_LD; ++i) {
-    int r = (tid >> 3) + 32 * i;
-    int gr = min(m0 + r, rows_e - 1);
-    a_src[i] = Ab + ((size_t)(rbase + gr) * K + lc * 8) * 2;
-    lds_off_a[i] = r * GB_ROW_BYTES + ((lc ^ swz(r)) << 4);
-  }
+    for (int i = 0; i < NIA; ++i) {
+      const int lr = m0 + i * NW * 8 + lrow;  // row within the expert: capacity slots first, then its Intra-GPU rows
+      const int32_t *src = lr < ti.fill ? P.slot_token + ((size_t)e * P.C + lr) : P.ir_token + (ti.ir_offset + lr - ti.fill);
+      if (P.row_token) src = P.row_token + (rbase + lr);
+      if (lr >= rows_e) src = P.slot_token;  // a valid dummy: the lookups of all instructions are in flight together
+      va[i] = (unsigned)*src;
+    }
 #pragma unroll
-  for (int i = 0; i < B_LD; ++i) {
-    int r = (tid >> 3) + 32 * i;
-    const char *bb = B0b;
-    int nr = r;
-    if (GATED && r >= BN) { bb = B1b; nr = r - BN; }
-    int gn = min(n0 + nr, N - 1);
-    b_src[i] = bb + ((size_t)gn * K + lc * 8) * 2;
-    lds_off_b[i] = BM * GB_ROW_BYTES + r * GB_ROW_BYTES + ((lc ^ swz(r)) << 4);
+    for (int i = 0; i < NIA; ++i) va[i] = m0 + i * NW * 8 + lrow < rows_e ? va[i] * rowb + piece * 16 : PAST;
+  } else {
+    va[0] = lrow * rowb + piece * 16;
   }
+  const unsigned vb = lrow * rowb + piece * 16;
+  auto issue = [&](int kt, int stage) {
+    char *st = smem + stage * S::STAGE + w * 1024;
+    const bool past = kt * CE + piece * PE >= K;  // the last chunk of a ragged K, and chunks past the end
+    const int koff = min(kt, KT - 1) * GB_ROW_BYTES;
+#pragma unroll
+    for (int i = 0; i < NIB; ++i) {
+      auto lp = (__attribute__((address_space(3))) void *)(st + BM * GB_ROW_BYTES + i * NW * 1024);
+      const unsigned v = vb + (GATED && i >= NIB0 ? i - NIB0 : i) * rstep;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(!GATED || i < NIB0 ? rsB0 : rsB1, lp, 16, past ? PAST : v, koff, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NIA; ++i) {
+      auto lp = (__attribute__((address_space(3))) void *)(st + i * NW * 1024);
+      const unsigned v = GATHER ? va[GATHER ? i : 0] : va[0] + i * rstep;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, lp, 16, past ? PAST : v, koff, 0, 0);
+    }
+  };
 
-  f32x16 acc[WM][WN];
+  // ---- fragments: lane reads row (lane & 15), piece 4 ks + (lane >> 4) of k-step ks (two per chunk)
+  int a_off[WM], b_off[WN];
+  const int fsw = swz(fr);  // fragment rows start at multiples of 16, so the swizzle depends on fr only
+#pragma unroll
+  for (int i = 0; i < WM; ++i) a_off[i] = ((wm * WM + i) * 16 + fr) * GB_ROW_BYTES;
+#pragma unroll
+  for (int j = 0; j < WN; ++j) {
+    constexpr int H = WN / 2;
+    int row = (wn * WN + j) * 16 + fr;
+    if (GATED) row = (j < H) ? (wn * H + j) * 16 + fr : BN + (wn * H + (j - H)) * 16 + fr;
+    b_off[j] = (BM + row) * GB_ROW_BYTES;
+  }
+  using Frag = typename std::conditional<S::BF16, bf16x8, f32x4>::type;
+  f32x4 acc[WM][WN];
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < WN; ++j)
+    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  Frag af[2][WM], bfr[2][WN];
+  auto load_frags = [&](const char *st, int ks) {
+    const int pos = ((4 * ks + fg) ^ fsw) << 4;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  uint4 ra[A_LD], rb[B_LD];
-  const int KT = (K + GB_BK - 1) / GB_BK;
-  auto load_global = [&](int kt) {
-    const int kbyte = kt * GB_BK * 2;
-    const bool in = (kt * GB_BK + lc * 8) < K;
+    for (int i = 0; i < WM; ++i) af[ks][i] = *reinterpret_cast<const Frag *>(st + a_off[i] + pos);
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) ra[i] = in ? *reinterpret_cast<const uint4 *>(a_src[i] + kbyte) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) rb[i] = in ? *reinterpret_cast<const uint4 *>(b_src[i] + kbyte) : make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < WN; ++j) bfr[ks][j] = *reinterpret_cast<const Frag *>(st + b_off[j] + pos);
   };
-  auto store_lds = [&](int buf) {
-    char *st = smem + buf * STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i) *reinterpret_cast<uint4 *>(st + lds_off_a[i]) = ra[i];
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) *reinterpret_cast<uint4 *>(st + lds_off_b[i]) = rb[i];
-  };
-
-  const int fr = lane & 31, fh = lane >> 5;
-  const int fsw = swz(fr);
-  int a_row_off[WM], b_row_off[WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i) a_row_off[i] = ((wm * WM + i) * 32 + fr) * GB_ROW_BYTES;
-#pragma unroll
-  for (int j = 0; j < WN; ++j) {
-    int r;
-    if (GATED) {
-      constexpr int H = WN / 2;
-      r = (j < H) ? (wn * H + j) * 32 + fr : BN + (wn * H + (j - H)) * 32 + fr;
-    } else {
-      r = (wn * WN + j) * 32 + fr;
-    }
-    b_row_off[j] = (BM + r) * GB_ROW_BYTES;
-  }
-
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    if (kt + 1 < KT) load_global(kt + 1);
-    const char *st = smem + (kt & 1) * STAGE_BYTES;
-#pragma unroll
-    for (int ks = 0; ks < GB_BK / 16; ++ks) {
-      bf16x8 af[WM], bfr[WN];
-      const int pos = ((2 * ks + fh) ^ fsw) << 4;
-#pragma unroll
-      for (int i = 0; i < WM; ++i) af[i] = *reinterpret_cast<const bf16x8 *>(st + a_row_off[i] + pos);
-#pragma unroll
-      for (int j = 0; j < WN; ++j) bfr[j] = *reinterpret_cast<const bf16x8 *>(st + b_row_off[j] + pos);
+  // B fragment first: the accumulator holds the transposed tile, a lane owns row (lane & 15) of the A
+  // fragment and four consecutive columns, 4 * (lane >> 4) .. + 3 of the B fragment
+  auto mfma_step = [&](int ks) {
+    if constexpr (S::BF16) {
 #pragma unroll
       for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < WN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ks][j], af[ks][i], acc[i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+          for (int j = 0; j < WN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bfr[ks][j][q], af[ks][i][q], acc[i][j], 0, 0, 0);
     }
-    if (kt + 1 < KT) store_lds((kt + 1) & 1);
-    __syncthreads();
+  };
+
+#pragma unroll
+  for (int q = 0; q < ST - 1; ++q) issue(q, q);
+  int dest[WM];
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    dest[i] = -1;
+    if (DIRECT) dest[i] = P.row_dest[rbase + min(m0 + (wm * WM + i) * 16 + fr, rows_e - 1)];
   }
-  store_tile<WM, WN, GATED, ACT>(acc, static_cast<uint16_t *>(P.Cout), rbase, rows_e, m0, n0, N, wm, wn, lane);
-}
-
-// ------------------------------------------------------------------ fp32 path
-constexpr int GF_BM = 64, GF_BN = 64, GF_BK = 16, GF_LD = GF_BM + 4;
-
-// ACT: -1 none, RR_ACT_GELU, RR_ACT_SWIGLU (gated: B0 = gate, B1 = up)
-template <int ACT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs P) {
-  constexpr bool GATED = ACT == RR_ACT_SWIGLU;
-  __shared__ float As[GF_BK][GF_LD], Bs0[GF_BK][GF_LD], Bs1[GATED ? GF_BK : 1][GF_LD];
-  const int mt = blockIdx.x / P.NT;
-  if (mt >= P.ctl[0]) return;
-  const TileInfo ti = P.tiles[mt];
-  const int e = ti.expert, m0 = ti.row0, rbase = ti.rbase, rows_e = ti.rows;
-  const int n0 = (blockIdx.x - mt * P.NT) * GF_BN;
-  const int K = P.K, N = P.N;
-  const float *A = static_cast<const float *>(P.A);
-  const float *B0 = static_cast<const float *>(P.B0) + (size_t)e * N * K;
-  const float *B1 = GATED ? static_cast<const float *>(P.B1) + (size_t)e * N * K : nullptr;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int lr = tid >> 2, lc = tid & 3;
-  const float *a_src = A + (size_t)(rbase + min(m0 + lr, rows_e - 1)) * K + lc * 4;
-  const size_t b_off = (size_t)min(n0 + lr, N - 1) * K + lc * 4;
-
-  float g[4][4], u[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) { g[a][b] = 0.0f; u[a][b] = 0.0f; }
-
-  for (int k0 = 0; k0 < K; k0 += GF_BK) {
-    const bool in = k0 + lc * 4 < K;
-    float4 va = in ? *reinterpret_cast<const float4 *>(a_src + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 vb = in ? *reinterpret_cast<const float4 *>(B0 + b_off + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-    As[lc * 4 + 0][lr] = va.x; As[lc * 4 + 1][lr] = va.y; As[lc * 4 + 2][lr] = va.z; As[lc * 4 + 3][lr] = va.w;
-    Bs0[lc * 4 + 0][lr] = vb.x; Bs0[lc * 4 + 1][lr] = vb.y; Bs0[lc * 4 + 2][lr] = vb.z; Bs0[lc * 4 + 3][lr] = vb.w;
-    if (GATED) {
-      float4 vc = in ? *reinterpret_cast<const float4 *>(B1 + b_off + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-      Bs1[lc * 4 + 0][lr] = vc.x; Bs1[lc * 4 + 1][lr] = vc.y; Bs1[lc * 4 + 2][lr] = vc.z; Bs1[lc * 4 + 3][lr] = vc.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < GF_BK; ++kk) {
-      float av[4], bv[4], cv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = As[kk][ty * 4 + a];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) { bv[b] = Bs0[kk][tx * 4 + b]; cv[b] = GATED ? Bs1[kk][tx * 4 + b] : 0.0f; }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          g[a][b] = fmaf(av[a], bv[b], g[a][b]);
-          if (GATED) u[a][b] = fmaf(av[a], cv[b], u[a][b]);
-        }
-    }
-    __syncthreads();
+  int cur = 0, fill = ST - 1;
+  for (int kt = 0; kt < KT; ++kt) {
+    // own loads of chunk kt have landed (ST - 2 younger chunks may be on their way), own reads of chunk kt - 1 too
+    dma_barrier<(ST - 2) * NI>();
+    const char *st = smem + cur * S::STAGE;
+    // software pipeline: the fragments of the next k-step are read under the MFMAs of this one
+    load_frags(st, 0);
+    if (kt > 0) mfma_step(1);  // last k-step of chunk kt - 1
+    issue(kt + ST - 1, fill);
+    __builtin_amdgcn_sched_barrier(0);
+    load_frags(st, 1);
+    mfma_step(0);
+    if constexpr (S::BF16) sched_mfma_lds_read<(WM + WN < WM * WN ? WM + WN : WM * WN)>();
+    __builtin_amdgcn_sched_barrier(0);
+    cur = cur == ST - 1 ? 0 : cur + 1;
+    fill = fill == ST - 1 ? 0 : fill + 1;
   }
-  float *Cf = static_cast<float *>(P.Cout);
+  mfma_step(1);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // loads past the last chunk still write this LDS
+
+  // ---- epilogue
+  constexpr int NJ = GATED ? WN / 2 : WN;
+  const int wrow0 = m0 + wm * WM * 16, wcol0 = n0 + wn * NJ * 16 + 4 * fg;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int row = m0 + ty * 4 + a;
+  for (int i = 0; i < WM; ++i) {
+    const int row = wrow0 + i * 16 + fr;
     if (row >= rows_e) continue;
+    char *prow = static_cast<char *>(P.Cout) + (size_t)(rbase + row) * N * ES;
+    char *orow = DIRECT && dest[i] >= 0 ? static_cast<char *>(P.Out) + (size_t)dest[i] * N * ES : nullptr;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int col = n0 + tx * 4 + b;
-      if (col >= N) continue;
-      float c = g[a][b];
-      if (ACT == RR_ACT_SWIGLU) c = c / (1.0f + expf(-c)) * u[a][b];
-      if (ACT == RR_ACT_GELU) c = gelu_erf(c);
-      Cf[(size_t)(rbase + row) * N + col] = c;
+    for (int j = 0; j < NJ; ++j) {
+      const int col = wcol0 + j * 16;
+      float c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        c[u] = acc[i][j][u];
+        if (GATED) c[u] = (S::BF16 ? silu_fast(c[u]) : c[u] / (1.0f + expf(-c[u]))) * acc[i][j + NJ][u];
+        if (ACT == RR_ACT_GELU) c[u] = S::BF16 ? gelu_fast(c[u]) : gelu_erf(c[u]);
+      }
+      if (col < N) {  // N % 8 == 0: a group of four columns is inside or outside as a whole
+        if constexpr (S::BF16) {
+          const uint2 val = make_uint2(pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3]));
+          *reinterpret_cast<uint2 *>(prow + (size_t)col * ES) = val;
+          if (DIRECT && orow) *reinterpret_cast<uint2 *>(orow + (size_t)col * ES) = val;
+        } else {
+          const float4 val = make_float4(c[0], c[1], c[2], c[3]);
+          *reinterpret_cast<float4 *>(prow + (size_t)col * ES) = val;
+          if (DIRECT && orow) *reinterpret_cast<float4 *>(orow + (size_t)col * ES) = val;
+        }
+      }
     }
   }
+#endif
 }
 
 template <typename Kern>
@@ -754,11 +800,126 @@ int cu_count() {
   return n;
 }
 
-bool persistent_ok(int K) { return K % GB_BK == 0 && K >= 3 * GB_BK; }  // whole K chunks, at least three
+// Whole K chunks, at least three (the rings); a ragged row needs one more, so that its last chunk is requested inside the K loop.
+bool persistent_ok(int K) { return K % GB_BK == 0 ? K >= 3 * GB_BK : K > 3 * GB_BK; }
+
+//                         BF16   waves  frags ring waves per SIMD
+using TileF64 = TileShape<false, 2, 2, 2, 4, 2, 2>;     // fp32, 64 rows x 128 staged weight rows
+using TileF32 = TileShape<false, 2, 2, 1, 4, 2, 2>;     // fp32, 32 x 128
+using TileF32n = TileShape<false, 2, 2, 1, 2, 3, 2>;    // fp32, 32 x 64
+using TileB256 = TileShape<true, 4, 2, 4, 4, 3, 2>;     // bf16, 256 x 128, 8 waves
+using TileB128 = TileShape<true, 2, 4, 4, 2, 4, 2>;     // bf16, 128 x 128, 8 waves
+using TileB64 = TileShape<true, 2, 2, 2, 4, 3, 2>;      // bf16, 64 x 128
+using TileB32 = TileShape<true, 1, 2, 2, 4, 4, 2>;      // bf16, 32 x 128
+using TileB32n = TileShape<true, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
+
+// Which tiles a GEMM uses.  Time of a launch = rounds of tiles over the CUs x K chunks x time of a chunk, so the shape is
+// the one with the least ceil(tiles / CUs) x cost, cost = microseconds per chunk and CU, measured: large tiles move the
+// fewest operand bytes per flop, small ones leave no CU idle when a layer has few rows or few columns.  At 8 experts,
+// 4096 x 11008, K = 11008, us: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255; 540 rows 230, 160, 202
+// (128 x 128: 157); 34 rows 219, 153, 144 (32 x 64: 134).
+enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_F64, FFN_F32, FFN_F32N };
+struct ShapeInfo { int bm, brows; float cost; };
+constexpr ShapeInfo kShape[] = {{256, 256, 1.45f}, {256, 128, 1.0f}, {128, 128, 0.75f}, {64, 128, 0.5f}, {32, 128, 0.38f},
+                                {32, 64, 0.3f},    {64, 128, 0.97f}, {32, 128, 0.5f},  {32, 64, 0.26f}};
+
+FfnShape pick_shape(const Dims &D, int K, int N, bool gated) {
+  constexpr int kCUs = 256;
+  // dispatched rows: the top-k assignments (a dropped token's re-routed row stands for its dropped ones)
+  const long long want = (long long)D.T * D.k, R = want < D.Rmax ? want : D.Rmax, used = R < D.E ? R : D.E;
+  const bool bf16 = D.dtype == RR_BF16;
+  FfnShape best = bf16 ? FFN_32N : FFN_F32N;
+  float least = 0.0f;
+  for (int q = bf16 ? FFN_P256 : FFN_F64; q <= (bf16 ? FFN_32N : FFN_F32N); ++q) {
+    const ShapeInfo &s = kShape[q];
+    if (q == FFN_P256 && !persistent_ok(K)) continue;
+    // a tile's rows are addressed with 32-bit byte offsets (rr_config bounds rows so that the narrowest shape always fits)
+    if ((long long)K * std::max(s.bm, s.brows) * (bf16 ? 2 : 4) >= 1ll << 31) continue;
+    const int bn = gated ? s.brows / 2 : s.brows;
+    const long long mt = 4 * R <= 3ll * s.bm * used ? used : R / s.bm + used / 2;
+    const long long tiles = mt * ((N + bn - 1) / bn);
+    const float cost = (float)((tiles + kCUs - 1) / kCUs) * s.cost;
+    if (least == 0.0f || cost < least) { least = cost; best = (FfnShape)q; }
+  }
+  return best;
+}
+struct FfnPlan { FfnShape up, down; };
+FfnPlan ffn_plan(const Dims &D) {
+  return {pick_shape(D, D.d, D.F, D.act == RR_ACT_SWIGLU), pick_shape(D, D.F, D.d, false)};
+}
+
+template <class S>
+struct Tag { using type = S; };
+
+template <class F>
+void for_each_tile_kernel(F f) {
+  auto shape = [&](auto tag) {
+    using S = typename decltype(tag)::type;
+    f(gemm_tile_kernel<S, true, -1, true, false>, S::SMEM);
+    f(gemm_tile_kernel<S, true, -1, false, false>, S::SMEM);
+    f(gemm_tile_kernel<S, false, RR_ACT_GELU, true, false>, S::SMEM);
+    f(gemm_tile_kernel<S, false, RR_ACT_GELU, false, false>, S::SMEM);
+    f(gemm_tile_kernel<S, false, -1, false, true>, S::SMEM);
+  };
+  shape(Tag<TileF64>{});
+  shape(Tag<TileF32>{});
+  shape(Tag<TileF32n>{});
+  shape(Tag<TileB256>{});
+  shape(Tag<TileB128>{});
+  shape(Tag<TileB64>{});
+  shape(Tag<TileB32>{});
+  shape(Tag<TileB32n>{});
+}
+
+// One GEMM (UP or down) with tiles of shape S; grid: the most tiles there can be, in whole XCD runs.
+template <class S, bool UP>
+void launch_tiles(const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
+  const bool gated = UP && D.act == RR_ACT_SWIGLU;
+  const int bn = gated ? S::BROWS / 2 : S::BROWS;
+  g.NT = (g.N + bn - 1) / bn;
+  g.sub = D.BM / S::BM;
+  const dim3 grid((unsigned)(((long long)g.NT * D.max_mtiles * g.sub + 7) / 8 * 8));
+  if constexpr (UP) {
+    if (gated && fuse) gemm_tile_kernel<S, true, -1, true, false><<<grid, S::THREADS, S::SMEM, s>>>(g);
+    else if (gated) gemm_tile_kernel<S, true, -1, false, false><<<grid, S::THREADS, S::SMEM, s>>>(g);
+    else if (fuse) gemm_tile_kernel<S, false, RR_ACT_GELU, true, false><<<grid, S::THREADS, S::SMEM, s>>>(g);
+    else gemm_tile_kernel<S, false, RR_ACT_GELU, false, false><<<grid, S::THREADS, S::SMEM, s>>>(g);
+  } else {
+    gemm_tile_kernel<S, false, -1, false, true><<<grid, S::THREADS, S::SMEM, s>>>(g);
+  }
+}
+
+template <bool UP>
+void launch_gemm(FfnShape shape, const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
+  switch (shape) {
+    case FFN_P256: {
+      const bool gated = UP && D.act == RR_ACT_SWIGLU;
+      g.NT = gated ? (g.N + 127) / 128 : (g.N + 255) / 256;
+      const int cus = cu_count();
+      if constexpr (UP) {
+        if (gated && fuse) gemm_bf16_persistent_kernel<true, -1, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        else if (gated) gemm_bf16_persistent_kernel<true, -1, false><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        else if (fuse) gemm_bf16_persistent_kernel<false, RR_ACT_GELU, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        else gemm_bf16_persistent_kernel<false, RR_ACT_GELU, false><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+      } else {
+        gemm_bf16_persistent_kernel<false, -1, false, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+      }
+      break;
+    }
+    case FFN_256: launch_tiles<TileB256, UP>(D, g, fuse, s); break;
+    case FFN_128: launch_tiles<TileB128, UP>(D, g, fuse, s); break;
+    case FFN_64: launch_tiles<TileB64, UP>(D, g, fuse, s); break;
+    case FFN_32: launch_tiles<TileB32, UP>(D, g, fuse, s); break;
+    case FFN_32N: launch_tiles<TileB32n, UP>(D, g, fuse, s); break;
+    case FFN_F64: launch_tiles<TileF64, UP>(D, g, fuse, s); break;
+    case FFN_F32: launch_tiles<TileF32, UP>(D, g, fuse, s); break;
+    case FFN_F32N: launch_tiles<TileF32n, UP>(D, g, fuse, s); break;
+  }
+}
 
 }  // namespace
 
-// The bf16 kernels use more dynamic LDS than the default limit.  Raising it is host-side set-up of the
+// The GEMM kernels use more dynamic LDS than the default limit.  Raising it is host-side set-up of the
 // loaded code object on the current device (no stream work); the caller runs it once per device.
 hipError_t ffn_kernel_attributes() {
   hipError_t e = hipSuccess;
@@ -769,74 +930,34 @@ hipError_t ffn_kernel_attributes() {
   set(gemm_bf16_persistent_kernel<true, -1, false>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<false, RR_ACT_GELU, true>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<false, RR_ACT_GELU, false>, PK_SMEM);
-  set(gemm_bf16_persistent_kernel<false, -1, false>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<false, -1, false, true>, PK_SMEM);
-  set(gemm_bf16_staged_kernel<true, -1>, PK_LDS);
-  set(gemm_bf16_staged_kernel<false, RR_ACT_GELU>, PK_LDS);
-  set(gemm_bf16_staged_kernel<false, -1>, PK_LDS);
+  for_each_tile_kernel(set);
   return e;
 }
 
-bool ffn_writes_single_rows(const Dims &D) { return D.dtype == RR_BF16 && persistent_ok(D.F); }
-
-bool ffn_fuses_gather(const Dims &D) {
-  return D.dtype == RR_BF16 && persistent_ok(D.d) && (long long)D.T * D.d * 2 < 0x7ffffff0ll;
+// Row-tile height of the layer's tile table: the higher of the two GEMMs' tiles.
+int ffn_row_tile(const Dims &D) {
+  const FfnPlan plan = ffn_plan(D);
+  return std::max(kShape[plan.up].bm, kShape[plan.down].bm);
 }
 
-// which: bit 0 = up projection (+ activation), bit 1 = down projection
-hipError_t launch_ffn_part(const Dims &D, const void *x, const rr_tables &tb, const void *w1, const void *w3,
-                           const void *w2, const Work &W, void *out, hipStream_t s, int which) {
-  const bool fuse = ffn_fuses_gather(D);
-  GemmArgs up{fuse ? x : W.x_disp, w1, w3, W.h, D.d, D.F, 0, W.tiles, W.tile_ctl,
-              tb.slot_token, tb.ir_token, D.quota ? W.row_token : nullptr, D.C, (long long)D.T * D.d * 2, nullptr, nullptr};
-  GemmArgs down{W.h, w2, nullptr, W.y, D.F, D.d, 0, W.tiles, W.tile_ctl, nullptr, nullptr, nullptr, 0, 0, W.row_dest, out};
-  if (D.dtype == RR_BF16) {
-    const bool gated = D.act == RR_ACT_SWIGLU;
-    up.NT = gated ? (D.F + 127) / 128 : (D.F + 255) / 256;
-    down.NT = (D.d + 255) / 256;
-    const int cus = cu_count();
-    if (which & 1) {
-      prof_begin(K_FFN_UP, s);
-      if (persistent_ok(D.d)) {
-        if (gated && fuse) gemm_bf16_persistent_kernel<true, -1, true><<<cus, PK_THREADS, PK_SMEM, s>>>(up);
-        else if (gated) gemm_bf16_persistent_kernel<true, -1, false><<<cus, PK_THREADS, PK_SMEM, s>>>(up);
-        else if (fuse) gemm_bf16_persistent_kernel<false, RR_ACT_GELU, true><<<cus, PK_THREADS, PK_SMEM, s>>>(up);
-        else gemm_bf16_persistent_kernel<false, RR_ACT_GELU, false><<<cus, PK_THREADS, PK_SMEM, s>>>(up);
-      } else {
-        if (gated) gemm_bf16_staged_kernel<true, -1><<<up.NT * D.max_mtiles, GS_THREADS, PK_LDS, s>>>(up);
-        else gemm_bf16_staged_kernel<false, RR_ACT_GELU><<<up.NT * D.max_mtiles, GS_THREADS, PK_LDS, s>>>(up);
-      }
-      prof_end(K_FFN_UP, s);
-    }
-    if (which & 2) {
-      prof_begin(K_FFN_DOWN, s);
-      if (persistent_ok(D.F)) gemm_bf16_persistent_kernel<false, -1, false, true><<<cus, PK_THREADS, PK_SMEM, s>>>(down);
-      else gemm_bf16_staged_kernel<false, -1><<<down.NT * D.max_mtiles, GS_THREADS, PK_LDS, s>>>(down);
-      prof_end(K_FFN_DOWN, s);
-    }
-  } else {
-    up.NT = (D.F + GF_BN - 1) / GF_BN;
-    down.NT = (D.d + GF_BN - 1) / GF_BN;
-    if (which & 1) {
-      prof_begin(K_FFN_UP, s);
-      if (D.act == RR_ACT_SWIGLU)
-        gemm_f32_kernel<RR_ACT_SWIGLU><<<up.NT * D.max_mtiles, 256, 0, s>>>(up);
-      else
-        gemm_f32_kernel<RR_ACT_GELU><<<up.NT * D.max_mtiles, 256, 0, s>>>(up);
-      prof_end(K_FFN_UP, s);
-    }
-    if (which & 2) {
-      prof_begin(K_FFN_DOWN, s);
-      gemm_f32_kernel<-1><<<down.NT * D.max_mtiles, 256, 0, s>>>(down);
-      prof_end(K_FFN_DOWN, s);
-    }
-  }
-  return hipGetLastError();
-}
+bool ffn_fuses_gather(const Dims &D) { return (long long)D.T * D.d * (D.dtype == RR_BF16 ? 2 : 4) < 0x7ffffff0ll; }
 
 hipError_t launch_ffn(const Dims &D, const void *x, const rr_tables &tb, const void *w1, const void *w3,
                       const void *w2, const Work &W, void *out, hipStream_t s) {
-  return launch_ffn_part(D, x, tb, w1, w3, w2, W, out, s, 3);
+  const bool fuse = ffn_fuses_gather(D);
+  const FfnPlan plan = ffn_plan(D);
+  const GemmArgs up{fuse ? x : W.x_disp, w1, w3, W.h, D.d, D.F, 0, 1, W.tiles, W.tile_ctl,
+                    tb.slot_token, tb.ir_token, D.quota ? W.row_token : nullptr, D.C,
+                    (long long)D.T * D.d * (D.dtype == RR_BF16 ? 2 : 4), nullptr, nullptr};
+  const GemmArgs down{W.h, w2, nullptr, W.y, D.F, D.d, 0, 1, W.tiles, W.tile_ctl, nullptr, nullptr, nullptr, 0, 0, W.row_dest, out};
+  prof_begin(K_FFN_UP, s);
+  launch_gemm<true>(plan.up, D, up, fuse, s);
+  prof_end(K_FFN_UP, s);
+  prof_begin(K_FFN_DOWN, s);
+  launch_gemm<false>(plan.down, D, down, fuse, s);
+  prof_end(K_FFN_DOWN, s);
+  return hipGetLastError();
 }
 
 }  // namespace rr

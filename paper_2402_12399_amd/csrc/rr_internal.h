@@ -123,8 +123,8 @@ hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &
 hipError_t launch_gather(const Dims &D, const void *x, const rr_tables &tb, const Work &W, hipStream_t s);
 hipError_t router_kernel_attributes();  // raises the dynamic-LDS limit of the streaming router on the current device
 hipError_t ffn_kernel_attributes();     // raises the dynamic-LDS limit of the bf16 GEMM kernels on the current device
-bool ffn_fuses_gather(const Dims &D);
-bool ffn_writes_single_rows(const Dims &D);  // the down projection writes the output row of a token with one processed assignment itself  // the up projection reads x through the dispatch tables: no gather pass
+int ffn_row_tile(const Dims &D);          // row-tile height of the layer's GEMMs (Dims::BM)
+bool ffn_fuses_gather(const Dims &D);     // the up projection reads x through the dispatch tables: no gather pass
 hipError_t launch_ffn(const Dims &D, const void *x, const rr_tables &tb, const void *w1, const void *w3,
                       const void *w2, const Work &W, void *out, hipStream_t s);
 hipError_t launch_combine(const Dims &D, const rr_tables &tb, const Work &W, void *out, hipStream_t s);

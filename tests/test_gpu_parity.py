@@ -730,3 +730,30 @@ def test_forward_random_grouped_gemm_shapes():
         except AssertionError as err:
             raise AssertionError(f"{what}: {err}") from None
         done += 1
+
+
+# The grouped GEMM in small tiles: every shape of tile for either type, with ragged rows, columns and K (one chunk and
+# less, a last chunk of one piece, exactly whole chunks), experts without rows, and both activations.
+TILE_SHAPES = [
+    # tile of the up / down projection, T, d_model, d_ff, E, G, k, dtype, act
+    ("32x64 one row", 1, 64, 8, 4, 1, 1, "bf16", "swiglu"),
+    ("32x64 K 8", 40, 8, 72, 4, 2, 2, "bf16", "gelu"),
+    ("32x64 ragged", 70, 200, 136, 8, 2, 2, "bf16", "swiglu"),
+    ("64x128 32x128", 900, 456, 1000, 6, 2, 2, "bf16", "gelu"),
+    ("128x128 32x128", 900, 456, 1032, 6, 2, 2, "bf16", "gelu"),
+    ("256x256 64x128", 1500, 264, 4104, 4, 1, 2, "bf16", "swiglu"),
+    ("256x256 128x128", 2600, 584, 2056, 4, 2, 2, "bf16", "swiglu"),
+    ("256x256 256x128 ragged K", 9001, 264, 2312, 4, 1, 2, "bf16", "gelu"),
+    ("256x128 256x256 ragged K", 9001, 2312, 264, 4, 1, 1, "bf16", "swiglu"),
+    ("f32 32x64 one row", 1, 8, 40, 4, 1, 1, "f32", "gelu"),
+    ("f32 32x64", 129, 800, 264, 4, 1, 2, "f32", "swiglu"),
+    ("f32 32x128", 1900, 104, 1208, 4, 2, 2, "f32", "swiglu"),
+    ("f32 64x128", 4032, 40, 3032, 2, 1, 1, "f32", "gelu"),
+]
+
+
+@pytest.mark.parametrize("case", TILE_SHAPES, ids=[c[0] for c in TILE_SHAPES])
+def test_forward_tile_shapes(case):
+    name, T, d, F, E, G, k, dtype, act = case
+    w = wl.Workload(name, T, d, F, E, G, k, 1.0, dtype, act, "zipf:1.1", 40 + T % 97)
+    _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
