@@ -26,6 +26,7 @@ static int device_setup() {
   std::call_once(g_dev_once[dev], [dev] {
     hipError_t e = ffn_kernel_attributes();
     if (e == hipSuccess) e = router_kernel_attributes();
+    if (e == hipSuccess) e = dispatch_kernel_attributes();
     void *p = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     g_scratch_ptr[dev] = e == hipSuccess ? p : nullptr;
@@ -43,7 +44,7 @@ static hipEvent_t g_open[K_COUNT];
 static const char *const g_kernel_names[K_COUNT] = {
     "router_scores", "topk_rank", "scan_candidates", "scatter_candidates", "select_slot",
     "ir_count", "ir_scan", "ir_weights", "dispatch_gather", "ffn_gate_up", "ffn_down", "combine",
-    "router_backward"};
+    "router_backward", "route_small"};
 
 static hipEvent_t get_event() {
   if (!g_free_events.empty()) {
@@ -164,6 +165,7 @@ static size_t carve(const Dims &D, bool forward, void *ws, Work *W) {
   W->row_base = cv.take<int32_t>(E + 1);
   W->tiles = cv.take<TileInfo>(D.max_mtiles + 1);
   W->tile_ctl = cv.take<int32_t>(4);
+  W->part = cv.take<float>(T * E * router_parts(D));
   if (forward) {
     size_t K1 = D.k + 1, es = D.dtype == RR_BF16 ? 2 : 4;
     W->logits = cv.take<float>(T * E);
@@ -285,6 +287,7 @@ int rr_rectified_dispatch(const rr_config *cfg, const float *logits, const rr_ta
   memset(&W, 0, sizeof(W));
   rc = check_ws(D, false, workspace, workspace_bytes, &W);
   if (rc != RR_OK) return rc;
+  if (device_setup() < 0) return RR_ERR_HIP;
   hipError_t e = launch_dispatch(D, logits, *out, W, false, nullptr, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? RR_OK : RR_ERR_HIP;
 }
@@ -315,15 +318,25 @@ int rr_moe_forward(const rr_config *cfg, const void *x, const float *w_router, c
   hipStream_t s = static_cast<hipStream_t>(stream);
   const rr_tables &tb = tables ? *tables : W.tables;
   float *lg = logits ? logits : W.logits;
+  auto finish = [&](hipError_t e) {  // after the tables: the experts
+    if (!routing_only) {
+      if (e == hipSuccess && !ffn_fuses_gather(D)) e = launch_gather(D, x, tb, W, s);
+      if (e == hipSuccess) e = launch_ffn(D, x, tb, w1, w3, w2, W, out, s);
+      if (e == hipSuccess) e = launch_combine(D, tb, W, out, s);
+    }
+    return e == hipSuccess ? RR_OK : RR_ERR_HIP;
+  };
+  const int parts = router_parts(D);
+  if (parts) {  // small batch: the router only splits K, the tables' workgroup sums and ranks
+    hipError_t e = launch_router_parts(D, x, w_router, W.part, parts, s);
+    if (e == hipSuccess) e = launch_route_small(D, W.part, parts, bias, lg, tb, W, false, routing_only ? nullptr : W.row_dest, s);
+    return finish(e);
+  }
   D.cb = router_count_blocks(D);  // the router ranks and counts: per 32 tokens for small batches
   D.NBc = (D.T + kTokBlock / D.cb - 1) / (kTokBlock / D.cb);
   hipError_t e = launch_router(D, x, w_router, bias, lg, nullptr, nullptr, &tb, &W, s);
   if (e == hipSuccess) e = launch_dispatch(D, lg, tb, W, true, routing_only ? nullptr : W.row_dest, s);
-  if (routing_only) return e == hipSuccess ? RR_OK : RR_ERR_HIP;
-  if (e == hipSuccess && !ffn_fuses_gather(D)) e = launch_gather(D, x, tb, W, s);
-  if (e == hipSuccess) e = launch_ffn(D, x, tb, w1, w3, w2, W, out, s);
-  if (e == hipSuccess) e = launch_combine(D, tb, W, out, s);
-  return e == hipSuccess ? RR_OK : RR_ERR_HIP;
+  return finish(e);
 }
 
 int rr_router_backward(const rr_config *cfg, const void *dout, const float *logits, const rr_tables *tables,

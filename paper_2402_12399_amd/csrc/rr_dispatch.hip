@@ -21,7 +21,11 @@
 // Plans that are a few dozen numbers (array bases, kept counts, row layout) are recomputed by every
 // workgroup that needs them instead of being a launch of their own: a dependent launch costs about
 // 6 us on this part, more than any of these kernels needs for a small batch.
+// Batches of up to 1024 tokens skip all of it: one workgroup builds every table (route_small_kernel).
 // Every table is a deterministic function of the logits: integer atomics are only used for counts.
+#include <algorithm>
+#include <type_traits>
+
 #include "rr_device.h"
 
 namespace rr {
@@ -1012,6 +1016,57 @@ __global__ __launch_bounds__(256) void row_token_kernel(DispatchArgs A, const in
   for (int t = threadIdx.x; t < nir; t += 256) row_token[first + t] = ir_token[ir_offset[e] + t];
 }
 
+// Every dispatched row belongs to one (token, assignment): the token marks each of its rows - with its own
+// index if this is the token's only row (Eq. 2 / Eq. 3 then give it weight exactly 1 and the expert's
+// output row IS the layer's output row: the down projection stores it there), else with -1.
+// row_of_slot(e, slot): the dispatched row of a slot; ir_row: that of the token's Intra-GPU row.
+template <class RowOfSlot>
+__device__ inline void mark_rows(int i, int NR, const int (&slot_r)[kMaxRank], const int (&e_r)[kMaxRank], bool has_ir,
+                                 int ir_row, RowOfSlot row_of_slot, int32_t *__restrict__ row_dest) {
+  int nrows = has_ir ? 1 : 0;
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r) nrows += (r < NR && slot_r[r] >= 0) ? 1 : 0;
+  const int mark = nrows == 1 ? i : -1;
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r)
+    if (r < NR && slot_r[r] >= 0) row_dest[row_of_slot(e_r[r], slot_r[r])] = mark;
+  if (has_ir) row_dest[ir_row] = mark;
+}
+
+// Eq. 2 / Eq. 3: softmax over the successfully routed experts, a placed Fill-in expert, and the
+// Intra-GPU expert counted (k - |R_i|) times
+__device__ inline void write_weights(int i, int k, int NR, const int (&slot_r)[kMaxRank], const u32 (&key_r)[kMaxRank],
+                                     bool has_ir, int ndrop, float score_h, float *__restrict__ combine_w) {
+  const float a_h = has_ir ? score_h : 0.0f;
+  float a_r[kMaxRank];
+  bool kept[kMaxRank];
+  float mx = has_ir ? a_h : -INFINITY;
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r) {
+    kept[r] = false;
+    a_r[r] = 0.0f;
+    if (r < NR) {
+      kept[r] = slot_r[r] >= 0;
+      if (kept[r]) {
+        a_r[r] = key_score(key_r[r]);
+        mx = fmaxf(mx, a_r[r]);
+      }
+    }
+  }
+  float term[kMaxRank], t_ir = has_ir ? (float)ndrop * expf(a_h - mx) : 0.0f, Z = t_ir;
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r) {
+    term[r] = kept[r] ? expf(a_r[r] - mx) : 0.0f;
+    Z += term[r];
+  }
+  const float inv = Z > 0.0f ? 1.0f / Z : 0.0f;
+  float *cw = combine_w + (size_t)i * (k + 2);
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r)
+    if (r <= k) cw[r] = term[r] * inv;
+  cw[k + 1] = t_ir * inv;
+}
+
 // Per token: Intra-GPU list position (Sec. 4.1) and the Eq. 2 / Eq. 3 weights.
 __global__ __launch_bounds__(kTokBlock) void ir_weights_kernel(DispatchArgs A, const int32_t *__restrict__ slot,
                                                                const u32 *__restrict__ key,
@@ -1093,7 +1148,6 @@ __global__ __launch_bounds__(kTokBlock) void ir_weights_kernel(DispatchArgs A, c
     row_plan_wave(A, blockIdx.x == 0, fill_total, self ? s_cnt : ir_cnt, s_off, s_rbase, ir_offset, row_base, tiles, tile_ctl);
   __syncthreads();
   if (!valid) return;
-  float a_h = 0.0f;
   int my_ir_row = -1;
   if (has_ir) {
     int row = (A.ir_self ? s_before[h] : ir_blk_off[(size_t)h * A.NB + b]) + below;
@@ -1101,73 +1155,525 @@ __global__ __launch_bounds__(kTokBlock) void ir_weights_kernel(DispatchArgs A, c
     ir_expert[i] = h;
     ir_row[i] = row;
     ir_token[s_off[h] + row] = i;
-    a_h = score_h;
     my_ir_row = row;
   } else {
     ir_expert[i] = -1;
     ir_row[i] = -1;
   }
-  if (row_dest) {
-    // Every dispatched row belongs to one (token, assignment): the token marks each of its rows - with
-    // its own index if this is the token's only row (Eq. 2 / Eq. 3 then give it weight exactly 1 and the
-    // expert's output row IS the layer's output row: the down projection stores it there), else with -1.
-    int nrows = has_ir ? 1 : 0;
-#pragma unroll
-    for (int r = 0; r < kMaxRank; ++r) nrows += (r < A.NR && slot_r[r] >= 0) ? 1 : 0;
-    const int mark = nrows == 1 ? i : -1;
-#pragma unroll
-    for (int r = 0; r < kMaxRank; ++r) {
-      if (r < A.NR && slot_r[r] >= 0) {
-        const int e = e_r[r], g = slot_r[r] / A.Cq;
-        row_dest[s_rbase[e] + grp_off[e * A.Gq + g] + (slot_r[r] - g * A.Cq)] = mark;
-      }
-    }
-    if (has_ir) row_dest[s_rbase[h] + fill_total[h] + my_ir_row] = mark;
-  }
-  // Eq. 2 / Eq. 3: softmax over the successfully routed experts, a placed Fill-in expert, and the
-  // Intra-GPU expert counted (k - |R_i|) times
-  float a_r[kMaxRank];
-  bool kept[kMaxRank];
-  float mx = has_ir ? a_h : -INFINITY;
+  if (row_dest)
+    mark_rows(i, A.NR, slot_r, e_r, has_ir, has_ir ? s_rbase[h] + fill_total[h] + my_ir_row : 0,
+              [&](int e, int s) {
+                const int g = s / A.Cq;
+                return s_rbase[e] + grp_off[e * A.Gq + g] + (s - g * A.Cq);
+              },
+              row_dest);
+  write_weights(i, A.k, A.NR, slot_r, key_r, has_ir, ndrop, score_h, combine_w);
+}
+
+// ------------------------------------------------------------------ small batches: all tables in one workgroup
+// Up to kOneT tokens (and kOneEntries candidates) one workgroup of 1024 threads builds every table: a batch of
+// a few hundred tokens is three or four dependent launches of 4 - 14 us otherwise, most of it latency.  Thread
+// tid owns tokens u * 1024 + tid, so (u, wave) is token order.  Steps, a barrier between any two:
+//   ranking (SRC: by the router already; or from logits; or from partial scores, which are summed here)
+//   candidate counts per (round, expert, 64 tokens) by ballot matching; exclusive scans over the 64-token rows
+//   stable split of the candidates into per-list arrays in LDS
+//   one wave per list: kept count from the counts; threshold of the kept set by 4-ary search on the keys (as many
+//     rounds as it takes to separate m of n keys; no histogram, no barrier); slots by ballots
+//   Intra-GPU lists by the same matching and scan, row plan, weights
+enum { ROUTE_RANKED = 0, ROUTE_LOGITS = 1, ROUTE_PARTS = 2 };
+constexpr int OR_THREADS = 1024, OR_WAVES = OR_THREADS / kWave;
+constexpr int kOneT = OR_THREADS, kOneSlots = 32768, kOneTile = 16384;  // kOneTile: T * E with the ranking done here
+constexpr int kMaxParts = 16;  // parts of the router's K
+
+struct OneLayout {  // dynamic LDS: the score tile, later the candidate arrays; slots; counts
+  int tops, ctok, slot, wcnt, wir, plan, plan_topk, total;
+};
+__host__ __device__ inline OneLayout one_layout(int T, int E, int NR, int Gq, bool tile) {
+  const int rows = (T + kWave - 1) / kWave, n = NR * T;
+  // the tile, and behind it the ranked lists of tokens that several lanes rank
+  const int cand = n * 4 + (n * 2 + 3) / 4 * 4, tops = (T * (E + 1) * 4 + 7) / 8 * 8;
+  const int tile_bytes = tile ? tops + (T <= 512 ? T * kMaxRank * 8 : 0) : 0;
+  OneLayout L;
+  L.tops = tops;
+  L.ctok = n * 4;
+  L.slot = cand > tile_bytes ? cand : tile_bytes;
+  L.wcnt = L.slot + (n * 2 + 3) / 4 * 4;
+  L.wir = L.wcnt + (NR * rows * E * 2 + 3) / 4 * 4;
+  L.plan = L.wir + (rows * E * 2 + 3) / 4 * 4;
+  L.plan_topk = L.plan + NR * E * Gq * 4;
+  L.total = L.plan_topk + (Gq > 1 ? E * Gq * 4 : 0);
+  return L;
+}
+
+// Smallest value of the wave, in a scalar (data-parallel moves: no LDS round trips).
+__device__ inline u32 wave_min(u32 v) {
+  auto step = [&](auto ctrl, auto row_mask) {
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)0xffffffff, (int)v, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false));
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast 15 into rows 1 and 3
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast 31 into rows 2 and 3
+  return (u32)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+template <int SRC>
+__global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
+    DispatchArgs A, const float *__restrict__ part, int kparts, const float *__restrict__ bias, float *__restrict__ logits,
+    int32_t *__restrict__ rank_expert, const u32 *__restrict__ key, const float *__restrict__ ir_score,
+    const int32_t *__restrict__ ir_cand, int32_t *__restrict__ slot, int32_t *__restrict__ slot_token,
+    int32_t *__restrict__ grp_fill, int32_t *__restrict__ grp_off, int32_t *__restrict__ fill_topk,
+    int32_t *__restrict__ fill_total, int32_t *__restrict__ ir_offset, int32_t *__restrict__ row_base,
+    TileInfo *__restrict__ tiles, int32_t *__restrict__ tile_ctl, int32_t *__restrict__ ir_expert,
+    int32_t *__restrict__ ir_row, int32_t *__restrict__ ir_token, float *__restrict__ combine_w,
+    int32_t *__restrict__ row_dest) {
+  constexpr u32 NOSLOT = 0xffffu;  // handed-out slots lie below kMaxRounds * kOneT, counted from the first of the capacity block
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ int s_cnt[kMaxRounds * kMaxE], s_base[kMaxRounds * kMaxE];
+  __shared__ int s_fill[kMaxE], s_ircnt[kMaxE], s_off[kMaxE], s_rbase[kMaxE];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int i = tid, row = w;  // this thread's token, its row of 64 tokens
+  const unsigned long long below_mask = (1ull << lane) - 1ull;
+  const int T = A.T, E = A.E, NR = A.NR, rows = (T + kWave - 1) / kWave;
+  const OneLayout L = one_layout(T, E, NR, A.Gq, SRC != ROUTE_RANKED);
+  float *const tile = reinterpret_cast<float *>(lds);
+  unsigned long long *const tops = reinterpret_cast<unsigned long long *>(lds + L.tops);
+  u32 *const ckey = reinterpret_cast<u32 *>(lds);                  // [NR][T] keys, lists of a round in expert order
+  uint16_t *const ctok = reinterpret_cast<uint16_t *>(lds + L.ctok);  // [NR][T] tokens of the same
+  uint16_t *const s_slot = reinterpret_cast<uint16_t *>(lds + L.slot);  // [NR][T] slot of the token, relative (see below)
+  uint16_t *const wcnt = reinterpret_cast<uint16_t *>(lds + L.wcnt);  // [NR][rows][E] candidates, scanned over rows
+  uint16_t *const wir = reinterpret_cast<uint16_t *>(lds + L.wir);    // [rows][E] the same for the Intra-GPU lists
+  u32 *const plan = reinterpret_cast<u32 *>(lds + L.plan);            // [NL] kept count << 16 | slots of earlier rounds
+  u32 *const plan_topk = reinterpret_cast<u32 *>(lds + L.plan_topk);  // [E][Gq] (quotas) occupied after all rounds << 16 | after the top-k ones
+
+  // ---- everything from global memory first: one round trip
+  int e_r[kMaxRank], cand_h = 0;
+  u32 key_r[kMaxRank];
+  float score_h = 0.0f;
 #pragma unroll
   for (int r = 0; r < kMaxRank; ++r) {
-    kept[r] = false;
-    a_r[r] = 0.0f;
-    if (r < A.NR) {
-      kept[r] = slot_r[r] >= 0;
-      if (kept[r]) {
-        a_r[r] = key_score(key_r[r]);
-        mx = fmaxf(mx, a_r[r]);
+    e_r[r] = 0;
+    key_r[r] = 0;
+    if (SRC == ROUTE_RANKED && i < T && r < NR) {
+      e_r[r] = rank_expert[(size_t)i * (A.k + 1) + r];
+      key_r[r] = key[(size_t)i * NR + r];
+    }
+  }
+  if (SRC == ROUTE_RANKED && i < T && A.ir) {
+    score_h = ir_score[i];
+    cand_h = ir_cand[i];
+  }
+  for (int c = tid; c < (L.plan - L.wcnt) / 4; c += OR_THREADS) reinterpret_cast<u32 *>(lds + L.wcnt)[c] = 0;
+  if constexpr (SRC != ROUTE_RANKED) {
+    // (all loads of an element, or of several, in flight together: one CU's latency is what this kernel consists of)
+    if constexpr (SRC == ROUTE_PARTS) {
+      for (int idx = tid; idx < T * E; idx += OR_THREADS) {  // the partial sums in order, then the bias
+        float p[kMaxParts];
+#pragma unroll
+        for (int q = 0; q < kMaxParts; ++q) p[q] = part[(size_t)(q < kparts ? q : 0) * T * E + idx];
+        const int row = idx / E, e = idx - row * E;
+        const float b = bias ? bias[e] : 0.0f;
+        float v = p[0];
+#pragma unroll
+        for (int q = 1; q < kMaxParts; ++q) v += q < kparts ? p[q] : 0.0f;
+        v += b;
+        logits[idx] = v;
+        tile[row * (E + 1) + e] = v;
+      }
+    } else {
+      constexpr int AHEAD = 8;
+      for (int i0 = tid; i0 < T * E; i0 += AHEAD * OR_THREADS) {
+        float v[AHEAD];
+#pragma unroll
+        for (int q = 0; q < AHEAD; ++q) v[q] = logits[min(i0 + q * OR_THREADS, T * E - 1)];
+#pragma unroll
+        for (int q = 0; q < AHEAD; ++q) {
+          const int idx = i0 + q * OR_THREADS, row = idx / E, e = idx - row * E;
+          if (idx < T * E) tile[row * (E + 1) + e] = v[q];
+        }
+      }
+    }
+    __syncthreads();
+    // Ranking.  With fewer tokens than threads several lanes share a token: each ranks a part of its row (at
+    // least eight experts), the lists are merged by shuffles and handed to the token's thread through LDS.
+    const int share = min(E >> 3, T <= 128 ? 8 : (T <= 256 ? 4 : (T <= 512 ? 2 : 1)));
+    const int lpt = share >= 8 ? 8 : (share >= 4 ? 4 : (share >= 2 ? 2 : 1)), per = (E + lpt - 1) / lpt;
+    auto rank = [&](auto tag) {
+      constexpr int N = decltype(tag)::value;  // list length: at least k + 1 and NR
+      const int n = min(A.k + 1, E);
+      unsigned long long top[N];
+      auto rank_part = [&](const float *row, int e0, int e1) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) top[q] = 0ull;
+        for (int eb = e0; eb < e1; eb += 8) {
+          float v[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = row[min(eb + q, E - 1)];
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if (eb + q < e1) insert_key(top, rank_key(v[q], eb + q));
+        }
+      };
+      if (lpt > 1) {
+        const int tok = tid / lpt, sub = tid & (lpt - 1);
+        if (tok < T) {  // (T * lpt is a multiple of lpt: the lanes of a token are all here)
+          rank_part(tile + tok * (E + 1), sub * per, min(E, (sub + 1) * per));
+          for (int off = 1; off < lpt; off <<= 1) {
+            unsigned long long o[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) {  // the other list, fetched whole before this one changes
+              const u32 l = __shfl_xor((u32)top[q], off), h = __shfl_xor((u32)(top[q] >> 32), off);
+              o[q] = ((unsigned long long)h << 32) | l;
+            }
+#pragma unroll
+            for (int q = 0; q < N; ++q) insert_key(top, o[q]);
+          }
+          if (sub == 0)
+#pragma unroll
+            for (int q = 0; q < N; ++q) tops[q * T + tok] = top[q];
+        }
+        __syncthreads();
+        if (i < T)
+#pragma unroll
+          for (int q = 0; q < N; ++q) top[q] = tops[q * T + i];
+      } else if (i < T) {
+        rank_part(tile + i * (E + 1), 0, E);
+      }
+      if (i < T) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+          const int e = rank_key_expert(top[q]);  // -1 past the number of experts
+          if (q <= A.k) rank_expert[(size_t)i * (A.k + 1) + q] = q < n ? e : -1;
+          if (q < NR) {
+            e_r[q] = e;
+            key_r[q] = rank_key_score(top[q]);
+          }
+        }
+        const int g = i / A.Tg;
+        best_in_group(tile + i * (E + 1), g * A.Eg, (g + 1) * A.Eg, score_h, cand_h);
+      }
+    };
+    if (A.k == 1) rank(std::integral_constant<int, 2>{});
+    else if (A.k == 2) rank(std::integral_constant<int, 3>{});
+    else rank(std::integral_constant<int, kMaxRank>{});
+  }
+  __syncthreads();  // counts are zero, the tile has been read
+  // ---- candidates per (round, 64 tokens, expert)
+  int below[kMaxRank];
+#pragma unroll
+  for (int r = 0; r < kMaxRank; ++r) {
+    below[r] = 0;
+    if (r < NR && row < rows) {
+      const unsigned long long mask = same_expert_mask(i < T, e_r[r]);
+      below[r] = __popcll(mask & below_mask);
+      if (i < T && below[r] == 0) wcnt[(r * rows + row) * E + e_r[r]] = (uint16_t)__popcll(mask);
+      if (i < T) s_slot[r * T + i] = (uint16_t)NOSLOT;
+    }
+  }
+  __syncthreads();
+  for (int c = tid; c < A.NCAT; c += OR_THREADS) {
+    const int r = c / E, e = c - r * E;
+    uint16_t *p = wcnt + r * rows * E + e;
+    int sum = 0;
+    for (int q = 0; q < rows; ++q) {
+      const int v = p[q * E];
+      p[q * E] = (uint16_t)sum;
+      sum += v;
+    }
+    s_cnt[c] = sum;
+  }
+  __syncthreads();
+  // first candidate of every list of round w, by wave w; meanwhile the last waves plan the rounds (kept =
+  // min(candidates, free slots) round after round): one thread per (expert, capacity block)
+  const int rpg = rows / A.Gq;  // 64-token rows per capacity block (quotas: groups end on 128 tokens)
+  auto piece = [&](int rr, int j, int g, int &lo, int &hi) {
+    lo = g == 0 ? 0 : wcnt[(rr * rows + g * rpg) * E + j];
+    hi = g == A.Gq - 1 ? s_cnt[rr * E + j] : wcnt[(rr * rows + (g + 1) * rpg) * E + j];
+  };
+  if (w < NR) {
+    const int c = lane < E ? s_cnt[w * E + lane] : 0;
+    int incl = c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(incl, off);
+      if (lane >= off) incl += t;
+    }
+    if (lane < E) s_base[w * E + lane] = w * T + incl - c;
+  } else {
+    for (int c = OR_THREADS - 1 - tid; c < E * A.Gq; c += OR_THREADS - NR * kWave) {
+      const int j = c / A.Gq, g = c - j * A.Gq;
+      int fill = 0, topk = 0;
+#pragma unroll
+      for (int r = 0; r < kMaxRounds; ++r)
+        if (r < NR) {
+          int lo, hi;
+          piece(r, j, g, lo, hi);
+          const int m = min(hi - lo, A.Cq - fill);
+          plan[(r * E + j) * A.Gq + g] = (u32)m << 16 | (u32)fill;
+          fill += m;
+          if (r == A.k - 1) topk = fill;
+        }
+      grp_fill[c] = fill;
+      if (A.Gq == 1) {
+        grp_off[j] = 0;
+        s_fill[j] = fill;
+        fill_total[j] = fill;
+        fill_topk[j] = topk;
+      } else {
+        plan_topk[c] = (u32)fill << 16 | (u32)topk;
       }
     }
   }
-  float term[kMaxRank], t_ir = has_ir ? (float)ndrop * expf(a_h - mx) : 0.0f, Z = t_ir;
+  __syncthreads();
+  if (A.Gq > 1) {  // quotas: one wave per expert adds up its blocks
+    for (int j = w; j < E; j += OR_WAVES) {
+      const u32 v = lane < A.Gq ? plan_topk[j * A.Gq + lane] : 0u;
+      const int total = v >> 16;
+      int incl = total, sum_topk = v & 0xffffu;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) sum_topk += __shfl_xor(sum_topk, off);
+      if (lane < A.Gq) grp_off[j * A.Gq + lane] = incl - total;
+      if (lane == 63) {
+        fill_total[j] = incl;
+        s_fill[j] = incl;
+      }
+      if (lane == 0) fill_topk[j] = sum_topk;
+    }
+  }
+  if (i < T) {
+#pragma unroll
+    for (int r = 0; r < kMaxRank; ++r)
+      if (r < NR) {
+        const int at = s_base[r * E + e_r[r]] + wcnt[(r * rows + row) * E + e_r[r]] + below[r];
+        ckey[at] = key_r[r];
+        ctok[at] = (uint16_t)i;
+      }
+  }
+  __syncthreads();
+  // ---- the lists.  A slot is kept in LDS as its offset from the first slot of the list's capacity block.
+  for (int c = tid; c < E * A.C; c += OR_THREADS) {  // zero padding (Sec. 3)
+    const int j = c / A.C, sl = c - j * A.C, g = A.Gq == 1 ? 0 : sl / A.Cq;
+    const u32 last = plan[((NR - 1) * E + j) * A.Gq + g];
+    if (sl - g * A.Cq >= (int)((last >> 16) + (last & 0xffffu))) slot_token[c] = -1;
+  }
+  for (int lst = w; lst < A.NL; lst += OR_WAVES) {
+    const int cat = lst / A.Gq, g = lst - cat * A.Gq, r = cat / E, j = cat - r * E;
+    int lo, hi;
+    piece(r, j, g, lo, hi);
+    const u32 pl = plan[lst];
+    const int n = __builtin_amdgcn_readfirstlane(hi - lo), m = __builtin_amdgcn_readfirstlane((int)(pl >> 16));
+    const int fill = pl & 0xffffu;
+    if (m == 0) continue;
+    const u32 *keys = ckey + s_base[cat] + lo;
+    const uint16_t *toks = ctok + s_base[cat] + lo;
+    int32_t *queue = slot_token + (size_t)j * A.C + g * A.Cq;
+    const int trips = (n + kWave - 1) / kWave;
+    const bool all = m == n, by_pos = m < n && A.arrival && r < A.k;
+    auto place = [&](auto tag) {
+      constexpr int NQ = decltype(tag)::value;  // at least `trips`: candidate q * 64 + lane is element q of the lane
+      u32 kr[NQ], tr[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int idx = min(q * kWave + lane, n - 1);
+        kr[q] = keys[idx];
+        tr[q] = toks[idx];
+      }
+      // kept: keys above `thr`, and the first need_eq of those equal to it (by_pos: the first m)
+      u32 thr = 0;
+      int need_eq = by_pos ? m : 0;
+      if (!all && !by_pos) {
+        u32 a = 0xffffffffu, b = 0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {  // (copies of the last key past the end of the list)
+          a = min(a, kr[q]);
+          b = max(b, kr[q]);
+          if (q * kWave + lane >= n) kr[q] = 0u;  // below every probe
+        }
+        a = wave_min(a);
+        b = ~wave_min(~b) + 1;  // keys of finite scores stay below the largest u32
+        // count(key >= a) >= m > count(key >= b) = cb; three probes a round, independent of each other
+        int cb = 0;
+        bool exact = false;
+        while (b - a > 1) {
+          const u32 h = (b - a) / 4, x1 = a + (h ? h : 1), x2 = a + (b - a) / 2, x3 = b - (h ? h : 1);
+          int c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q)
+            if (q < trips) {
+              c1 += __popcll(__ballot(kr[q] >= x1));
+              c2 += __popcll(__ballot(kr[q] >= x2));
+              c3 += __popcll(__ballot(kr[q] >= x3));
+            }
+          if (c1 == m || c2 == m || c3 == m) {
+            thr = (c1 == m ? x1 : (c2 == m ? x2 : x3)) - 1;  // exactly the keys above it; nothing equal to it is taken
+            exact = true;
+            break;
+          }
+          if (c3 >= m) a = x3;
+          else if (c2 >= m) { a = x2; b = x3; cb = c3; }
+          else if (c1 >= m) { a = x1; b = x2; cb = c2; }
+          else { b = x1; cb = c1; }
+        }
+        if (!exact) {
+          thr = a;
+          need_eq = m - cb;
+        }
+      }
+      int run = 0, run_eq = 0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < trips) {
+          const bool valid = q * kWave + lane < n;
+          const bool gt = valid && (all || (!by_pos && kr[q] > thr)), eq = valid && !all && (by_pos || kr[q] == thr);
+          const unsigned long long beq = __ballot(eq);
+          const bool kept = gt || (eq && run_eq + (int)__popcll(beq & below_mask) < need_eq);
+          const unsigned long long bk = __ballot(kept);
+          if (kept) {
+            const int sl = fill + run + __popcll(bk & below_mask);
+            s_slot[r * T + tr[q]] = (uint16_t)sl;
+            queue[sl] = tr[q];
+          }
+          run += __popcll(bk);
+          run_eq += __popcll(beq);
+        }
+    };
+    if (trips <= 1) place(std::integral_constant<int, 1>{});
+    else if (trips <= 4) place(std::integral_constant<int, 4>{});
+    else place(std::integral_constant<int, OR_WAVES>{});
+  }
+  __syncthreads();
+  // ---- the tokens' slots; Intra-GPU candidates (Sec. 4.1)
+  int slot_r[kMaxRank], ndrop = 0, ir_below = 0;
 #pragma unroll
   for (int r = 0; r < kMaxRank; ++r) {
-    term[r] = kept[r] ? expf(a_r[r] - mx) : 0.0f;
-    Z += term[r];
+    slot_r[r] = -1;
+    if (r < NR && i < T) {
+      const u32 s = s_slot[r * T + i];
+      if (s != NOSLOT) slot_r[r] = (A.Gq == 1 ? 0 : i / A.Tg * A.Cq) + (int)s;
+      if (r < A.k) ndrop += s == NOSLOT;
+      slot[(size_t)i * (A.k + 1) + r] = slot_r[r];
+    }
   }
-  const float inv = Z > 0.0f ? 1.0f / Z : 0.0f;
-  float *cw = combine_w + (size_t)i * (A.k + 2);
-#pragma unroll
-  for (int r = 0; r < kMaxRank; ++r)
-    if (r <= A.k) cw[r] = term[r] * inv;
-  cw[A.k + 1] = t_ir * inv;
+  if (i < T && !A.fr) slot[(size_t)i * (A.k + 1) + A.k] = -1;
+  const bool has_ir = A.ir && ndrop > 0;
+  if (row < rows) {
+    const unsigned long long mask = same_expert_mask(has_ir, cand_h);
+    ir_below = __popcll(mask & below_mask);
+    if (has_ir && ir_below == 0) wir[row * E + cand_h] = (uint16_t)__popcll(mask);
+  }
+  __syncthreads();
+  if (tid < E) {
+    int sum = 0;
+    for (int q = 0; q < rows; ++q) {
+      const int v = wir[q * E + tid];
+      wir[q * E + tid] = (uint16_t)sum;
+      sum += v;
+    }
+    s_ircnt[tid] = sum;
+  }
+  __syncthreads();
+  if (w == 0) row_plan_wave(A, true, s_fill, s_ircnt, s_off, s_rbase, ir_offset, row_base, tiles, tile_ctl);
+  __syncthreads();
+  if (i >= T) return;
+  const int at = has_ir ? wir[row * E + cand_h] + ir_below : -1;
+  ir_expert[i] = has_ir ? cand_h : -1;
+  ir_row[i] = at;
+  if (has_ir) ir_token[s_off[cand_h] + at] = i;
+  if (row_dest)
+    mark_rows(i, NR, slot_r, e_r, has_ir, has_ir ? s_rbase[cand_h] + s_fill[cand_h] + at : 0,
+              [&](int e, int s) {
+                const int g = s / A.Cq;
+                return s_rbase[e] + (A.Gq == 1 ? 0 : grp_off[e * A.Gq + g]) + (s - g * A.Cq);
+              },
+              row_dest);
+  write_weights(i, A.k, NR, slot_r, key_r, has_ir, ndrop, score_h, combine_w);
 }
 
 }  // namespace
 
+static DispatchArgs dispatch_args(const Dims &D) {
+  return {D.T, D.E, D.k, D.C, D.NR, D.NCAT, D.NB, D.Eg, D.Tg, D.ir, D.fr, D.arrival, D.BM, D.max_mtiles,
+          D.Cq, D.Gq, D.NL, D.NBc, D.cb, D.E * D.NB <= kIrSelfMax ? 1 : 0,
+          D.Gq == 1 && D.T <= kDirectMaxT ? 1 : 0};
+}
+
+// One CU's throughput sets the limits: at 1024 tokens and 64 experts one workgroup takes as long as the launches it
+// replaces (tables from logits, us, before -> now: 256 x 8, k 1: 22 -> 12; 512 x 16, k 2: 24 -> 17; 1024 x 16, k 4:
+// 27 -> 27; 256 x 64, k 2: 30 -> 20).
+bool route_in_one(const Dims &D) {
+  return D.T <= kOneT && (long long)D.E * D.C <= kOneSlots;
+}
+
+// The forward call's router splits K over workgroups (of four waves) while they leave most CUs idle and the partial
+// scores, which one workgroup reads, stay small: 16 tokens x 4096, 8 experts, router + tables 34 us with the router
+// that ranks (one workgroup) and three table kernels, 26 us with it and one, 15 us with K split; 300 tokens x 2048,
+// 16 experts 46, 31, 27 us.  Short rows gain less from the split, so that it ends at half as many scores for them.
+int router_parts(const Dims &D) {
+  const int tiles = (D.T + 31) / 32, steps = (D.d + (D.dtype == RR_BF16 ? 63 : 31)) / (D.dtype == RR_BF16 ? 64 : 32);
+  if (!route_in_one(D) || D.T * D.E > (steps >= 32 ? 8192 : 4096)) return 0;
+  return std::max(1, std::min({kMaxParts, 256 / tiles, steps / 4, 65536 / (D.T * D.E)}));
+}
+
+static void launch_row_token(const Dims &D, const DispatchArgs &A, const rr_tables &tb, const Work &W, hipStream_t s) {
+  if (D.quota && D.max_mtiles > 0)  // the forward pass addresses dispatched rows through row_token
+    row_token_kernel<<<D.E, 256, 0, s>>>(A, tb.slot_token, W.grp_fill, W.grp_off, tb.fill_total, tb.ir_offset,
+                                         tb.ir_token, W.row_base, W.row_token);
+}
+
+hipError_t launch_route_small(const Dims &D, const float *part, int kparts, const float *bias, float *logits,
+                              const rr_tables &tb, const Work &W, bool ranked, int32_t *row_dest, hipStream_t s) {
+  const DispatchArgs A = dispatch_args(D);
+  const int src = ranked ? ROUTE_RANKED : (kparts ? ROUTE_PARTS : ROUTE_LOGITS);
+  const OneLayout L = one_layout(D.T, D.E, D.NR, D.Gq, src != ROUTE_RANKED);
+  prof_begin(K_ROUTE_SMALL, s);
+  auto go = [&](auto kern) {
+    kern<<<1, OR_THREADS, L.total, s>>>(A, part, kparts, bias, logits, tb.rank_expert, W.key, W.ir_score, W.ir_cand, tb.slot,
+                                        tb.slot_token, W.grp_fill, W.grp_off, tb.fill_topk, tb.fill_total, tb.ir_offset,
+                                        W.row_base, W.tiles, W.tile_ctl, tb.ir_expert, tb.ir_row, tb.ir_token,
+                                        tb.combine_w, row_dest);
+  };
+  if (src == ROUTE_RANKED) go(route_small_kernel<ROUTE_RANKED>);
+  else if (src == ROUTE_LOGITS) go(route_small_kernel<ROUTE_LOGITS>);
+  else go(route_small_kernel<ROUTE_PARTS>);
+  prof_end(K_ROUTE_SMALL, s);
+  launch_row_token(D, A, tb, W, s);
+  return hipGetLastError();
+}
+
+// route_small_kernel's dynamic LDS can exceed the default limit: raised once per device by the caller.
+hipError_t dispatch_kernel_attributes() {
+  hipError_t e = hipSuccess;
+  auto set = [&e](auto kern) {
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+  };
+  set(route_small_kernel<ROUTE_RANKED>);
+  set(route_small_kernel<ROUTE_LOGITS>);
+  set(route_small_kernel<ROUTE_PARTS>);
+  return e;
+}
+
 hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &tb, const Work &W, bool ranked,
                            int32_t *row_dest, hipStream_t s) {
-  DispatchArgs A{D.T, D.E, D.k, D.C, D.NR, D.NCAT, D.NB, D.Eg, D.Tg, D.ir, D.fr, D.arrival, D.BM, D.max_mtiles,
-                 D.Cq, D.Gq, D.NL, D.NBc, D.cb, D.E * D.NB <= kIrSelfMax ? 1 : 0,
-                 D.Gq == 1 && D.T <= kDirectMaxT ? 1 : 0};
+  const DispatchArgs A = dispatch_args(D);
+  const bool in_one = route_in_one(D);
+  if (in_one && !ranked && D.T * D.E <= kOneTile)
+    return launch_route_small(D, nullptr, 0, nullptr, const_cast<float *>(logits), tb, W, false, row_dest, s);
   if (!ranked) {  // otherwise the router's epilogue has already written what topk_rank writes
     prof_begin(K_TOPK, s);
     topk_rank_kernel<<<D.NB, kTokBlock, 0, s>>>(logits, A, tb.rank_expert, tb.slot, W.key, W.ir_score, W.ir_cand,
                                                 W.blk_cnt);
     prof_end(K_TOPK, s);
   }
+  if (in_one) return launch_route_small(D, nullptr, 0, nullptr, nullptr, tb, W, true, row_dest, s);
   if (A.direct) {
     prof_begin(K_SELECT_SLOT, s);
     select_direct_kernel<<<D.NCAT, SS_THREADS, 0, s>>>(A, tb.rank_expert, W.key, tb.slot, tb.slot_token, W.grp_fill,
@@ -1206,9 +1712,7 @@ hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &
                                                tb.ir_expert, tb.ir_row, tb.ir_token, tb.combine_w, tb.rank_expert,
                                                W.grp_off, row_dest);
   prof_end(K_IR_WEIGHTS, s);
-  if (D.quota && D.max_mtiles > 0)  // the forward pass addresses dispatched rows through row_token
-    row_token_kernel<<<D.E, 256, 0, s>>>(A, tb.slot_token, W.grp_fill, W.grp_off, tb.fill_total, tb.ir_offset,
-                                         tb.ir_token, W.row_base, W.row_token);
+  launch_row_token(D, A, tb, W, s);
   return hipGetLastError();
 }
 

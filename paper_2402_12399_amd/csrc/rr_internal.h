@@ -77,6 +77,7 @@ struct Work {
   int32_t *tile_ctl;     // [4] [0] = number of row tiles
   // forward only
   float   *logits;       // [T,E] when the caller passes none
+  float   *part;         // [parts,T,E] partial scores of a small batch (router_parts)
   rr_tables tables;      // storage when the caller passes none
   int32_t *row_dest;     // [Rmax] token whose ONLY processed row this is (its output row is written by the down projection), else -1
   void    *x_disp;       // [Rmax, d]
@@ -91,7 +92,7 @@ struct Launch {
 // Kernel ids for the profiling record.
 enum KernelId {
   K_ROUTER = 0, K_TOPK, K_SCAN_CAND, K_SCATTER_CAND, K_SELECT_SLOT,
-  K_IR_COUNT, K_IR_SCAN, K_IR_WEIGHTS, K_GATHER, K_FFN_UP, K_FFN_DOWN, K_COMBINE, K_ROUTER_BWD,
+  K_IR_COUNT, K_IR_SCAN, K_IR_WEIGHTS, K_GATHER, K_FFN_UP, K_FFN_DOWN, K_COMBINE, K_ROUTER_BWD, K_ROUTE_SMALL,
   K_COUNT
 };
 
@@ -117,6 +118,16 @@ int router_count_blocks(const Dims &D);
 hipError_t launch_router(const Dims &D, const void *x, const float *w_router, const float *bias,
                          float *logits, float *probs, int32_t *rank_expert, const rr_tables *tb, const Work *W,
                          hipStream_t s);
+// Batches whose routing tables one workgroup builds (rr_dispatch.hip, route_small_kernel), and the parts that the
+// forward call's router then splits K into (0: it ranks the tokens itself).
+bool route_in_one(const Dims &D);
+int router_parts(const Dims &D);
+hipError_t launch_router_parts(const Dims &D, const void *x, const float *w_router, float *part, int kparts, hipStream_t s);
+// logits: source of the ranking; or, with kparts > 0, destination of the scores: part[kparts][T][E] summed, plus bias.
+// ranked: the router has ranked the tokens (neither is read).
+hipError_t launch_route_small(const Dims &D, const float *part, int kparts, const float *bias, float *logits,
+                              const rr_tables &tb, const Work &W, bool ranked, int32_t *row_dest, hipStream_t s);
+hipError_t dispatch_kernel_attributes();
 // row_dest: only in the forward call (see Work::row_dest), else nullptr
 hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &tb, const Work &W, bool ranked,
                            int32_t *row_dest, hipStream_t s);

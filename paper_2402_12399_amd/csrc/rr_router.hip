@@ -14,13 +14,15 @@
 // fp32 x anyway): x.w_hi + x.w_lo for bf16 x, x_hi.w_hi + x_hi.w_lo + x_lo.w_hi for fp32 x.
 // This keeps the kernel near the one pass over x in HBM instead of bound by fp32 FMA throughput.
 //
-// A workgroup of 4 waves owns TM*32 tokens; the waves split K four ways and each streams its K slice
+// Up to 16 K tokens: a workgroup of NW waves owns 32 tokens; the waves split K and each streams its slice
 // straight from global memory into MFMA operand registers (no LDS in the main loop, no barriers):
 // lane (row r = lane%32, half h = lane/32) loads 64 contiguous bytes of row r per macro-step, the
 // two halves taking adjacent segments, so every row is read in whole 128-byte lines.  The order in
 // which K is fed to the MFMAs is permuted by that, identically for x and w, which a dot product does
-// not see.  The four partial tiles are summed through LDS in a fixed order (deterministic), then the
-// finished [token][expert] tile leaves as coalesced logits / probs rows and one lane per token ranks.
+// not see.  Up to 16 experts the scores come from v_mfma_f32_16x16x4_f32 instead, on the fp32 weights as
+// they are (two 16-token fragments, four lanes per row).  The partial tiles are summed through LDS in a
+// fixed order (deterministic), then the finished [token][expert] tile leaves as coalesced logits rows and
+// probabilities, and several lanes per token rank.
 #include <type_traits>
 
 #include "rr_device.h"
@@ -31,9 +33,11 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-constexpr int RT_THREADS = 256;
+constexpr int RT_THREADS = 256;  // streaming kernel
 constexpr int RT_NW = RT_THREADS / kWave;
+constexpr int RS_TB = 32;        // tokens per workgroup of the K-split kernel
 
 union Frag {
   u32 w[4];
@@ -149,18 +153,80 @@ __device__ inline void rank_row(const float *row, int tok, int half, int E, int 
   }
 }
 
+// The same with LPT neighbouring lanes per token (sub = lane % LPT): each takes the experts sub, sub + LPT, ...,
+// the lists are merged in log2(LPT) exchanges; the best local expert is the greatest key of the group.
+template <bool FUSE, int LPT>
+__device__ inline void rank_row_shared(const float *row, int tok, int sub, int E, int k, int32_t *rank_expert,
+                                       const RankOut &R, int *cnt) {
+  const int n = min(k + 1, E);
+  int32_t *ranks = FUSE ? R.rank_expert : rank_expert;
+  auto fetch = [&](unsigned long long v, int off) {
+    const u32 lo = __shfl_xor((u32)v, off), hi = __shfl_xor((u32)(v >> 32), off);
+    return ((unsigned long long)hi << 32) | lo;
+  };
+  auto rank = [&](auto tag) {
+    constexpr int N = decltype(tag)::value;  // list length: at least n
+    unsigned long long b[N], o[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) b[q] = 0ull;
+#pragma unroll
+    for (int m = 0; m < kMaxE / LPT; ++m) {
+      const int e = sub + m * LPT;
+      if (e < E) insert_key(b, rank_key(row[e], e));
+    }
+#pragma unroll
+    for (int off = 1; off < LPT; off <<= 1) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) o[q] = fetch(b[q], off);  // the other list, fetched whole before this one changes
+#pragma unroll
+      for (int q = 0; q < N; ++q) insert_key(b, o[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < kMaxRank; ++q) {
+      if (sub != q % LPT) continue;  // all lanes hold the list: each writes its entries
+      const unsigned long long key = q < N ? b[q < N ? q : 0] : 0ull;
+      const int e = rank_key_expert(key);  // -1 past the number of experts
+      if (q <= k) ranks[(size_t)tok * (k + 1) + q] = (q < n) ? e : -1;
+      if (FUSE && q < R.NR) {
+        R.key[(size_t)tok * R.NR + q] = rank_key_score(key);
+        atomicAdd(&cnt[q * E + e], 1);
+      }
+    }
+    if (FUSE && !R.fr && sub == 0) R.slot[(size_t)tok * (k + 1) + k] = -1;
+  };
+  if (n <= 3) rank(std::integral_constant<int, 3>{});
+  else rank(std::integral_constant<int, kMaxRank>{});
+  if (FUSE) {
+    const int e0 = tok / R.Tg * R.Eg;
+    unsigned long long best = 0ull;
+    for (int m = sub; m < R.Eg; m += LPT) {
+      const unsigned long long key = rank_key(row[e0 + m], e0 + m);
+      best = key > best ? key : best;
+    }
+#pragma unroll
+    for (int off = 1; off < LPT; off <<= 1) {
+      const unsigned long long o = fetch(best, off);
+      best = o > best ? o : best;
+    }
+    if (sub == 0) {
+      R.ir_score[tok] = key_score(rank_key_score(best));
+      R.ir_cand[tok] = rank_key_expert(best);
+    }
+  }
+}
+
 // The same per-token results as rank_row from a [tokens][experts] tile in LDS, with every thread
 // of the workgroup at work: the thread of (token, expert e) counts the experts that beat e - a
 // greater score, or an equal one at a lower index (Eq. 1 argtopk, ties -> lower expert index) - and
 // that count is e's rank; the same count inside the token's own group finds the best local expert
 // (Sec. 4.1).  E^2 comparisons per token instead of E insertion steps, but no serial chain: the
 // small-batch kernel's epilogue is latency, not arithmetic.
-template <bool FUSE>
+template <bool FUSE, int THREADS>
 __device__ inline void rank_tile(const float *tile, int TS, int ntok, int t0, int E, int k, int32_t *rank_expert,
                                  const RankOut &R, int *cnt) {
   const int n = min(k + 1, E);
   int32_t *ranks = FUSE ? R.rank_expert : rank_expert;
-  for (int idx = threadIdx.x; idx < ntok * E; idx += RT_THREADS) {
+  for (int idx = threadIdx.x; idx < ntok * E; idx += THREADS) {
     const int row = idx / E, e = idx - row * E, tok = t0 + row;
     const float *a = tile + row * TS;
     const float v = a[e];
@@ -197,177 +263,253 @@ __device__ inline void rank_tile(const float *tile, int TS, int ntok, int t0, in
   }
 }
 
-template <bool BF16, int TM, int NJ, bool FUSE>
-__global__ __launch_bounds__(RT_THREADS) void router_kernel(const void *__restrict__ xv, const float *__restrict__ wr,
+// NW waves split K.  Dynamic LDS: the NW partial tiles.
+constexpr int rs_width(int NJ) { return NJ == 0 ? 16 : NJ * 32; }  // experts of a partial tile
+constexpr int rs_smem(int NW, int NJ) { return NW * RS_TB * (rs_width(NJ) + 1) * 4; }
+
+template <bool BF16, int NW, int NJ, bool FUSE>
+__global__ __launch_bounds__(NW *kWave) void router_kernel(const void *__restrict__ xv, const float *__restrict__ wr,
                                                             const float *__restrict__ bias, float *__restrict__ logits,
                                                             float *__restrict__ probs, int32_t *__restrict__ rank_expert,
                                                             int T, int d, int E, int k, RankOut R) {
-  constexpr int TB = TM * 32;                 // tokens per workgroup = one candidate-count block (FUSE)
+  constexpr int TB = RS_TB, THREADS = NW * kWave;  // TB tokens: one candidate-count block (FUSE)
   constexpr int S = BF16 ? 32 : 16;           // elements in a lane's 64-byte segment
   constexpr int KM = 2 * S;                   // K advance per macro-step
   constexpr int MS = S / 8;                   // MFMA k-steps per macro-step
   constexpr int ES = BF16 ? 2 : 4;
-  constexpr int TS = NJ * 32 + 1;             // LDS row stride of a [token][expert] tile
-  __shared__ float red[RT_NW][TB * TS];
-  __shared__ float row_max[TB], row_inv[TB];
+  constexpr int TS = rs_width(NJ) + 1;        // LDS row stride of a [token][expert] tile
+  extern __shared__ __attribute__((aligned(16))) float red[];  // [NW][TB * TS]
   __shared__ int cnt[kMaxRounds * kMaxE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int fr = lane & 31, fh = lane >> 5;
   const int t0 = blockIdx.x * TB;
 
   // this wave's K slice, in whole macro-steps
-  const int steps_total = (d + KM - 1) / KM;
-  const int steps_per_wave = (steps_total + RT_NW - 1) / RT_NW;
-  const int kbeg = min(w * steps_per_wave, steps_total) * KM;
-  const int kend = min(min((w + 1) * steps_per_wave, steps_total) * KM, d);
+  // (a grid of several rows splits K over its rows as well: row y stores the partial scores of its share)
+  const int steps_total = (d + KM - 1) / KM, slice = blockIdx.y * NW + w;
+  const int steps_per_wave = (steps_total + NW * gridDim.y - 1) / (NW * gridDim.y);
+  const int kbeg = min(slice * steps_per_wave, steps_total) * KM;
+  const int kend = min(min((slice + 1) * steps_per_wave, steps_total) * KM, d);
+  logits += (size_t)blockIdx.y * T * E;
 
-  const char *xrow[TM];
+  float *mine = red + w * TB * TS;
+  if constexpr (NJ == 0) {
+    // Up to 16 experts: v_mfma_f32_16x16x4_f32 on the fp32 weights as they are; the tokens are two row
+    // fragments.  Lane (row r = lane % 16, quarter q = lane / 16) holds the q-th quarter of the macro-step's
+    // 128 bytes of every row and feeds it element by element.
+    constexpr int SQ = S / 2;  // elements of a lane's quarter: 16 (bf16 x) or 8
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const char *xrow[2];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-    xrow[i] = static_cast<const char *>(xv) + (size_t)min(t0 + i * 32 + fr, T - 1) * d * ES;
-  const float *wrow[NJ];
-  bool wok[NJ];
+    for (int i = 0; i < 2; ++i)
+      xrow[i] = static_cast<const char *>(xv) + ((size_t)min(t0 + i * 16 + r16, T - 1) * d + q4 * SQ) * ES;
+    const bool wok = r16 < E;
+    const float *wrow = wr + (size_t)min(r16, E - 1) * d + q4 * SQ;
+    f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+    auto load = [&](int kb, uint4 (&x)[2][2], float4 (&wv)[SQ / 4]) {
+      const int k0 = kb + q4 * SQ;
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    wok[j] = j * 32 + fr < E;
-    wrow[j] = wr + (size_t)min(j * 32 + fr, E - 1) * d;
-  }
+      for (int p = 0; p < 2; ++p) {
+        const bool in = k0 + p * (16 / ES) < kend;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          x[i][p] = in ? *reinterpret_cast<const uint4 *>(xrow[i] + (size_t)kb * ES + p * 16) : make_uint4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int p = 0; p < SQ / 4; ++p)
+        wv[p] = wok && k0 + p * 4 < kend ? *reinterpret_cast<const float4 *>(wrow + kb + p * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    uint4 xc[2][2], xn[2][2];
+    float4 wc[SQ / 4], wn[SQ / 4];
+    if (kbeg < kend) load(kbeg, xc, wc);
+    for (int kb = kbeg; kb < kend; kb += KM) {
+      if (kb + KM < kend) load(kb + KM, xn, wn);
+#pragma unroll
+      for (int m = 0; m < SQ; ++m) {
+        const float wm = (&wc[m / 4].x)[m % 4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float xm;
+          if (BF16) {
+            const u32 pair = (&xc[i][m / 8].x)[m % 8 / 2];
+            xm = m % 2 ? hi_half(pair) : lo_half(pair);
+          } else {
+            xm = __builtin_bit_cast(float, (&xc[i][m / 4].x)[m % 4]);
+          }
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(xm, wm, acc[i], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) xc[i][p] = xn[i][p];
+#pragma unroll
+      for (int p = 0; p < SQ / 4; ++p) wc[p] = wn[p];
+    }
+    // accumulator element v is token 16 i + 4 (lane / 16) + v, expert lane % 16
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) mine[(i * 16 + 4 * q4 + v) * TS + r16] = acc[i][v];
+  } else {
+    const char *xrow = static_cast<const char *>(xv) + (size_t)min(t0 + fr, T - 1) * d * ES;
+    const float *wrow[NJ];
+    bool wok[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      wok[j] = j * 32 + fr < E;
+      wrow[j] = wr + (size_t)min(j * 32 + fr, E - 1) * d;
+    }
 
-  f32x16 acc[TM][NJ];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
+    f32x16 acc[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+      for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
 
-  uint4 xr[TM][4], xn[TM][4];
-  auto load_x = [&](int kb, uint4 (&dst)[TM][4]) {
-    const int k0 = kb + fh * S;  // first element of this lane's segment
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
+    uint4 xr[4], xn[4];
+    auto load_x = [&](int kb, uint4 (&dst)[4]) {
+      const int k0 = kb + fh * S;  // first element of this lane's segment
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int kq = k0 + q * (16 / ES);
-        dst[i][q] = kq < kend ? *reinterpret_cast<const uint4 *>(xrow[i] + (size_t)kq * ES) : make_uint4(0, 0, 0, 0);
+        dst[q] = kq < kend ? *reinterpret_cast<const uint4 *>(xrow + (size_t)kq * ES) : make_uint4(0, 0, 0, 0);
       }
-  };
+    };
 
-  // w of a macro-step: per k-step 8 consecutive fp32 of row (expert) fr.  Fetched one macro-step
-  // ahead like x (the weights sit in L2, but an L2 round trip per macro-step is most of a small
-  // batch's run time when it is not hidden).
-  uint4 wc[MS][NJ][2], wnx[MS][NJ][2];
-  auto load_wm = [&](int kb, uint4 (&dst)[MS][NJ][2]) {
-#pragma unroll
-    for (int m = 0; m < MS; ++m) {
+    // w of a macro-step: per k-step 8 consecutive fp32 of row (expert) fr.  Fetched one macro-step
+    // ahead like x (the weights sit in L2, but an L2 round trip per macro-step is most of a small
+    // batch's run time when it is not hidden).  Sixteen waves hide most of it by themselves and have fewer
+    // registers: they fetch a macro-step's weights at its start, with two column fragments one k-step ahead.
+    constexpr bool AHEAD = NW < 16, BY_STEP = NW >= 16 && NJ > 1;
+    uint4 wc[BY_STEP ? 2 : MS][NJ][2], wnx[AHEAD ? MS : 1][NJ][2];
+    auto load_w = [&](int kb, int m, uint4 (&dst)[NJ][2]) {
       const int kw = kb + fh * S + m * 8;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        dst[m][j][0] = dst[m][j][1] = make_uint4(0, 0, 0, 0);
+        dst[j][0] = dst[j][1] = make_uint4(0, 0, 0, 0);
         if (wok[j] && kw < kend) {
-          dst[m][j][0] = *reinterpret_cast<const uint4 *>(wrow[j] + kw);
-          dst[m][j][1] = *reinterpret_cast<const uint4 *>(wrow[j] + kw + 4);
+          dst[j][0] = *reinterpret_cast<const uint4 *>(wrow[j] + kw);
+          dst[j][1] = *reinterpret_cast<const uint4 *>(wrow[j] + kw + 4);
         }
       }
+    };
+    auto load_wm = [&](int kb, auto &dst) {
+#pragma unroll
+      for (int m = 0; m < MS; ++m) load_w(kb, m, dst[m]);
+    };
+    if (kbeg < kend) {
+      load_x(kbeg, xr);
+      if constexpr (AHEAD) load_wm(kbeg, wc);
+      if constexpr (BY_STEP) load_w(kbeg, 0, wc[0]);
     }
-  };
-  if (kbeg < kend) {
-    load_x(kbeg, xr);
-    load_wm(kbeg, wc);
-  }
-  for (int kb = kbeg; kb < kend; kb += KM) {
-    if (kb + KM < kend) {
-      load_x(kb + KM, xn);
-      load_wm(kb + KM, wnx);
-    }
+    for (int kb = kbeg; kb < kend; kb += KM) {
+      if constexpr (!AHEAD && !BY_STEP) load_wm(kb, wc);
+      if (kb + KM < kend) {
+        load_x(kb + KM, xn);
+        if constexpr (AHEAD) load_wm(kb + KM, wnx);
+      }
 #pragma unroll
-    for (int m = 0; m < MS; ++m) {
-      Frag wh[NJ], wl[NJ], wl2[NJ];
+      for (int m = 0; m < MS; ++m) {
+        Frag wh[NJ], wl[NJ], wl2[NJ];
+        if constexpr (BY_STEP) load_w(m + 1 < MS ? kb : kb + KM, (m + 1) % MS, wc[(m + 1) & 1]);  // MS is even
+        const auto &wm = wc[BY_STEP ? m & 1 : m];
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) split3x8(wc[m][j][0], wc[m][j][1], wh[j], wl[j], wl2[j]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
+        for (int j = 0; j < NJ; ++j) split3x8(wm[j][0], wm[j][1], wh[j], wl[j], wl2[j]);
         if (BF16) {
           Frag xf;
-          xf.w[0] = xr[i][m].x; xf.w[1] = xr[i][m].y; xf.w[2] = xr[i][m].z; xf.w[3] = xr[i][m].w;
+          xf.w[0] = xr[m].x; xf.w[1] = xr[m].y; xf.w[2] = xr[m].z; xf.w[3] = xr[m].w;
 #pragma unroll
           for (int j = 0; j < NJ; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wl2[j].v, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wl[j].v, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wh[j].v, acc[i][j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wl2[j].v, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wl[j].v, acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v, wh[j].v, acc[j], 0, 0, 0);
           }
         } else {
           Frag xh, xl;
-          split2x8(xr[i][2 * m], xr[i][2 * m + 1], xh, xl);
+          split2x8(xr[(2 * m) % 4], xr[(2 * m + 1) % 4], xh, xl);  // m < 2 here
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) acc[i][j] = mfma5(xh, xl, wh[j], wl[j], wl2[j], acc[i][j]);
+          for (int j = 0; j < NJ; ++j) acc[j] = mfma5(xh, xl, wh[j], wl[j], wl2[j], acc[j]);
         }
       }
-    }
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int q = 0; q < 4; ++q) xr[q] = xn[q];
+      if constexpr (AHEAD) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) xr[i][q] = xn[i][q];
+        for (int m = 0; m < MS; ++m)
 #pragma unroll
-    for (int m = 0; m < MS; ++m)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        wc[m][j][0] = wnx[m][j][0];
-        wc[m][j][1] = wnx[m][j][1];
+          for (int j = 0; j < NJ; ++j) {
+            wc[m][j][0] = wnx[m][j][0];
+            wc[m][j][1] = wnx[m][j][1];
+          }
       }
-  }
+    }
 
-  // ---- partial tiles to LDS: accumulator element v is token 8*(v/4) + 4*(lane/32) + v%4, expert lane%32
-  float *mine = red[w];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
+    // ---- partial tiles to LDS: accumulator element v is token 8*(v/4) + 4*(lane/32) + v%4, expert lane%32
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        mine[(i * 32 + 8 * (v >> 2) + 4 * fh + (v & 3)) * TS + j * 32 + fr] = acc[i][j][v];
+      for (int v = 0; v < 16; ++v) mine[(8 * (v >> 2) + 4 * fh + (v & 3)) * TS + j * 32 + fr] = acc[j][v];
+  }
   __syncthreads();
-  // ---- fixed-order sum of the four K slices, plus bias
-  float *tile = red[0];
-  for (int idx = tid; idx < TB * E; idx += RT_THREADS) {
+  // ---- fixed-order sum of the K slices, plus bias
+  float *tile = red;
+  for (int idx = tid; idx < TB * E; idx += THREADS) {
     const int row = idx / E, e = idx - row * E;
     const int o = row * TS + e;
-    tile[o] = ((red[0][o] + red[1][o]) + (red[2][o] + red[3][o])) + (bias ? bias[e] : 0.0f);
+    float p[NW];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) p[q] = red[q * TB * TS + o];
+#pragma unroll
+    for (int h = 1; h < NW; h *= 2)  // pairwise
+#pragma unroll
+      for (int q = 0; q + h < NW; q += 2 * h) p[q] += p[q + h];
+    tile[o] = p[0] + (bias ? bias[e] : 0.0f);
   }
   if (FUSE)
-    for (int c = tid; c < R.NCAT; c += RT_THREADS) cnt[c] = 0;
+    for (int c = tid; c < R.NCAT; c += THREADS) cnt[c] = 0;
   __syncthreads();
 
   const int ntok = min(TB, T - t0);
   // logits rows of this tile are contiguous in memory
-  for (int idx = tid; idx < ntok * E; idx += RT_THREADS) {
+  for (int idx = tid; idx < ntok * E; idx += THREADS) {
     int row = idx / E, e = idx - row * E;
     logits[(size_t)t0 * E + idx] = tile[row * TS + e];
   }
-  if (tid < ntok && probs) {
-    const float *row = tile + tid * TS;
-    float m = row[0];
-    for (int e = 1; e < E; ++e) m = fmaxf(m, row[e]);
-    float s = 0.0f;
-    for (int e = 0; e < E; ++e) s += expf(row[e] - m);
-    row_max[tid] = m;
-    row_inv[tid] = 1.0f / s;
-  }
-  // more than 16 experts: two lanes per token, each scanning half the row (the E^2 comparisons of
-  // rank_tile then cost more than the serial insertion saves); lanes l and l + 32 of wave 0 share token l
-  static_assert(TB <= 32, "the two lanes of a token sit in one wave");
-  if ((rank_expert || FUSE) && E > 16 && tid < 64 && (tid & 31) < ntok)
-    rank_row<FUSE>(tile + (tid & 31) * TS, t0 + (tid & 31), tid >> 5, E, k, rank_expert, R, cnt);
-  if ((rank_expert || FUSE) && E <= 16) rank_tile<FUSE>(tile, TS, ntok, t0, E, k, rank_expert, R, cnt);
-  if (probs || FUSE) __syncthreads();
-  if (probs) {
-    for (int idx = tid; idx < ntok * E; idx += RT_THREADS) {
-      int row = idx / E, e = idx - row * E;
-      probs[(size_t)t0 * E + idx] = expf(tile[row * TS + e] - row_max[row]) * row_inv[row];
+  if (probs) {  // softmax: THREADS / 32 lanes per token
+    constexpr int LPT = THREADS / TB;
+    const int tok = tid / LPT, sub = tid % LPT;
+    const float *row = tile + tok * TS;
+    float v[(kMaxE + LPT - 1) / LPT], m = -INFINITY, sum = 0.0f;
+#pragma unroll
+    for (int q = 0; q < kMaxE / LPT; ++q) {
+      const int e = sub + q * LPT;
+      v[q] = e < E ? row[e] : -INFINITY;
+      m = fmaxf(m, v[q]);
     }
+#pragma unroll
+    for (int off = 1; off < LPT; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
+#pragma unroll
+    for (int q = 0; q < kMaxE / LPT; ++q) {
+      v[q] = sub + q * LPT < E ? expf(v[q] - m) : 0.0f;
+      sum += v[q];
+    }
+#pragma unroll
+    for (int off = 1; off < LPT; off <<= 1) sum += __shfl_xor(sum, off);
+    const float inv = 1.0f / sum;
+#pragma unroll
+    for (int q = 0; q < kMaxE / LPT; ++q)
+      if (tok < ntok && sub + q * LPT < E) probs[(size_t)(t0 + tok) * E + sub + q * LPT] = v[q] * inv;
   }
+  // more than 16 experts: eight lanes per token (the E^2 comparisons of rank_tile then cost more than the
+  // serial insertion saves)
+  static_assert(8 * TB <= 256, "the tokens' lanes fit the smallest workgroup");
+  if ((rank_expert || FUSE) && E > 16 && tid < 8 * ntok)
+    rank_row_shared<FUSE, 8>(tile + (tid >> 3) * TS, t0 + (tid >> 3), tid & 7, E, k, rank_expert, R, cnt);
+  if ((rank_expert || FUSE) && E <= 16) rank_tile<FUSE, THREADS>(tile, TS, ntok, t0, E, k, rank_expert, R, cnt);
+  if (FUSE) __syncthreads();
   if (FUSE)
-    for (int c = tid; c < R.NCAT; c += RT_THREADS) R.blk_cnt[(size_t)c * R.NBc + blockIdx.x] = cnt[c];
+    for (int c = tid; c < R.NCAT; c += THREADS) R.blk_cnt[(size_t)c * R.NBc + blockIdx.x] = cnt[c];
 }
 
 // ------------------------------------------------------------------ large batches
@@ -677,18 +819,34 @@ __global__ __launch_bounds__(RT_THREADS, 2) void router_lds_kernel(const void *_
 #endif
 }
 
-template <bool BF16, int TM>
-void launch_one(const Dims &D, const void *x, const float *w_router, const float *bias, float *logits, float *probs,
-                int32_t *rank_expert, const RankOut *R, hipStream_t s) {
-  dim3 grid((D.T + TM * 32 - 1) / (TM * 32)), block(RT_THREADS);
+template <bool BF16, int NW>
+void launch_split(const Dims &D, const void *x, const float *w_router, const float *bias, float *logits, float *probs,
+                  int32_t *rank_expert, const RankOut *R, int kparts, hipStream_t s) {
+  dim3 grid((D.T + RS_TB - 1) / RS_TB, kparts), block(NW * kWave);
   RankOut none{};
-  if (D.E <= 32) {
-    if (R) router_kernel<BF16, TM, 1, true><<<grid, block, 0, s>>>(x, w_router, bias, logits, probs, rank_expert, D.T, D.d, D.E, D.k, *R);
-    else router_kernel<BF16, TM, 1, false><<<grid, block, 0, s>>>(x, w_router, bias, logits, probs, rank_expert, D.T, D.d, D.E, D.k, none);
-  } else if constexpr (TM == 1) {  // two column fragments: the partial tiles of two token fragments would not fit LDS
-    if (R) router_kernel<BF16, TM, 2, true><<<grid, block, 0, s>>>(x, w_router, bias, logits, probs, rank_expert, D.T, D.d, D.E, D.k, *R);
-    else router_kernel<BF16, TM, 2, false><<<grid, block, 0, s>>>(x, w_router, bias, logits, probs, rank_expert, D.T, D.d, D.E, D.k, none);
-  }
+#define RR_LAUNCH_SPLIT(NJ)                                                                                            \
+  do {                                                                                                                 \
+    constexpr int smem = rs_smem(NW, NJ);                                                                              \
+    if (R) router_kernel<BF16, NW, NJ, true><<<grid, block, smem, s>>>(x, w_router, bias, logits, probs, rank_expert,  \
+                                                                       D.T, D.d, D.E, D.k, *R);                        \
+    else router_kernel<BF16, NW, NJ, false><<<grid, block, smem, s>>>(x, w_router, bias, logits, probs, rank_expert,   \
+                                                                      D.T, D.d, D.E, D.k, none);                       \
+  } while (0)
+  if (D.E <= 16) RR_LAUNCH_SPLIT(0);
+  else if (D.E <= 32) RR_LAUNCH_SPLIT(1);
+  else RR_LAUNCH_SPLIT(2);
+#undef RR_LAUNCH_SPLIT
+}
+
+// Waves that split K: as many as leave each of them two macro-steps, and as a full chip holds (16 waves per CU).
+// 4096 tokens x 4096 bf16, 8 experts: 4 waves 28 us, 16 waves 20; 8192 x 2048, 16 experts: 18, 16.
+template <bool BF16>
+void launch_small(const Dims &D, const void *x, const float *w_router, const float *bias, float *logits, float *probs,
+                  int32_t *rank_expert, const RankOut *R, hipStream_t s) {
+  const int steps = (D.d + (BF16 ? 63 : 31)) / (BF16 ? 64 : 32);
+  if (steps >= 32 && D.T <= 8192) launch_split<BF16, 16>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
+  else if (steps >= 16) launch_split<BF16, 8>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
+  else launch_split<BF16, 4>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
 }
 
 template <bool BF16>
@@ -726,6 +884,16 @@ hipError_t router_kernel_attributes() {
   set(router_lds_kernel<false, 1, false>, RxLayout<false, 1>::SMEM);
   set(router_lds_kernel<false, 2, true>, RxLayout<false, 2>::SMEM);
   set(router_lds_kernel<false, 2, false>, RxLayout<false, 2>::SMEM);
+  auto split = [&set](auto nw, auto nj) {
+    constexpr int NW = decltype(nw)::value, NJ = decltype(nj)::value;
+    set(router_kernel<true, NW, NJ, true>, rs_smem(NW, NJ));
+    set(router_kernel<true, NW, NJ, false>, rs_smem(NW, NJ));
+    set(router_kernel<false, NW, NJ, true>, rs_smem(NW, NJ));
+    set(router_kernel<false, NW, NJ, false>, rs_smem(NW, NJ));
+  };
+  split(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+  split(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});
+  split(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{});
   return e;
 }
 
@@ -734,6 +902,15 @@ hipError_t router_kernel_attributes() {
 // K-split kernel 115 us; at 16 K tokens the K-split kernel is still ahead, 47 against 55 us).
 static bool router_small(const Dims &D) { return D.T <= 16 * 1024; }
 int router_count_blocks(const Dims &D) { return router_small(D) ? kTokBlock / 32 : 1; }
+
+// Partial scores of small batches: part[kparts][T][E], summed by whoever ranks them.
+hipError_t launch_router_parts(const Dims &D, const void *x, const float *w_router, float *part, int kparts, hipStream_t s) {
+  prof_begin(K_ROUTER, s);
+  if (D.dtype == RR_BF16) launch_split<true, 4>(D, x, w_router, nullptr, part, nullptr, nullptr, nullptr, kparts, s);
+  else launch_split<false, 4>(D, x, w_router, nullptr, part, nullptr, nullptr, nullptr, kparts, s);
+  prof_end(K_ROUTER, s);
+  return hipGetLastError();
+}
 
 hipError_t launch_router(const Dims &D, const void *x, const float *w_router, const float *bias, float *logits,
                          float *probs, int32_t *rank_expert, const rr_tables *tb, const Work *W, hipStream_t s) {
@@ -747,8 +924,8 @@ hipError_t launch_router(const Dims &D, const void *x, const float *w_router, co
                 D.k, D.NR, D.fr, D.Eg, D.Tg, D.NCAT, D.NBc};
   if (small) {
     const RankOut *Rp = tb && W ? &R : nullptr;
-    if (D.dtype == RR_BF16) launch_one<true, 1>(D, x, w_router, bias, logits, probs, rank_expert, Rp, s);
-    else launch_one<false, 1>(D, x, w_router, bias, logits, probs, rank_expert, Rp, s);
+    if (D.dtype == RR_BF16) launch_small<true>(D, x, w_router, bias, logits, probs, rank_expert, Rp, s);
+    else launch_small<false>(D, x, w_router, bias, logits, probs, rank_expert, Rp, s);
   } else {
     if (D.dtype == RR_BF16) launch_stream<true>(D, x, w_router, bias, logits, probs, rank_expert, tb && W ? &R : nullptr, s);
     else launch_stream<false>(D, x, w_router, bias, logits, probs, rank_expert, tb && W ? &R : nullptr, s);

@@ -757,3 +757,45 @@ def test_forward_tile_shapes(case):
     name, T, d, F, E, G, k, dtype, act = case
     w = wl.Workload(name, T, d, F, E, G, k, 1.0, dtype, act, "zipf:1.1", 40 + T % 97)
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
+
+
+# Batches whose tables one workgroup builds, and their borders: one token, a wave and one more or less, the most tokens
+# (and one more), lists of one candidate and of all tokens, ranks shared by 1, 2, 4 and 8 lanes, every source of the ranking
+# (logits; the router's partial scores or its own ranking in the forward call).
+ONE_WORKGROUP = [
+    # T, E, G, k, cf, quota
+    (1, 2, 1, 1, 1.0, False),
+    (63, 9, 1, 1, 0.5, False),
+    (64, 64, 8, 2, 0.75, False),
+    (65, 5, 1, 4, 1.0, False),
+    (130, 64, 2, 4, 0.3, False),
+    (256, 8, 2, 1, 40.0, False),     # queues far longer than the batch
+    (512, 32, 4, 2, 1.0, True),
+    (513, 24, 1, 3, 1.25, False),
+    (1023, 16, 1, 2, 0.05, False),
+    (1024, 3, 1, 2, 1.0, False),     # whole-batch lists, nothing placed in the last round
+    (1024, 64, 8, 4, 0.5, True),
+    (1025, 6, 1, 2, 1.0, False),
+]
+
+
+@pytest.mark.parametrize("T,E,G,k,cf,quota", ONE_WORKGROUP)
+def test_small_batch_tables(T, E, G, k, cf, quota):
+    for arrival in (False, True):
+        for ties in (False, True):
+            a = wl.synthetic_logits(T, E, seed=T + E, bias_std=1.5, ties=ties)
+            cfg = rr.RRConfig(T, 64, 0, E, k, G, cf, rr.RR_F32, rr.RR_ACT_SWIGLU,
+                              gu.flags_of(("ir", "fr"), arrival, quota))
+            gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), arrival, quota))
+    rng = np.random.default_rng(T + 7 * E)
+    for d in (72, 4160):  # one part of K, and as many as it is split into
+        x = (rng.integers(-8, 9, (T, d)) / 8.0).astype(np.float32)  # dyadic: the scores are exact in any order
+        wr = (rng.integers(-8, 9, (E, d)) / 16.0).astype(np.float32)
+        cfg = rr.RRConfig(T, d, 0, E, k, G, cf, rr.RR_BF16, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), False, quota))
+        tables, logits, ws = rr.alloc_tables(cfg), torch.empty((T, E), device="cuda"), rr.alloc_workspace(cfg)
+        rr.rr_moe_forward(cfg, torch.from_numpy(x).cuda().bfloat16(), torch.from_numpy(wr).cuda(), None, None, None, None,
+                          None, tables, logits, ws)
+        torch.cuda.synchronize()
+        a = logits.cpu().numpy()
+        assert np.array_equal(a, (x.astype(np.float64) @ wr.astype(np.float64).T).astype(np.float32))
+        gu.assert_tables_equal(tables.to_host(), _oracle_tables(a, cfg, ("ir", "fr"), False, quota))
