@@ -23,6 +23,10 @@
 //     every LDS read right before its first use.
 //   * The up projection can read its A rows straight from x through the dispatch tables (GATHER):
 //     the dispatch gather is then a per-lane row offset of the LDS DMA and costs no pass over HBM.
+//   * The last round of tiles rarely fills the chip: where its tiles are at most half as many as the
+//     workgroups they are cut by rows into up to eight parts (see "cut").  8 K tokens top-1, 2048 x 5632: down
+//     projection 292 -> 249 us (384 tiles for 256 CUs); 4 K tokens 4096 x 11008, top-2: down 829 -> 695 (576 tiles).
+//     The waves of a column take turns at the 16-row fragments, so that a short tile keeps all four SIMDs busy.
 //   * While a tile's epilogue stores drain, the first K chunk of the workgroup's next tile is
 //     already in flight (its tile id and table entries were fetched during the K loop).
 // Layers with few rows or short rows, and all fp32 layers: gemm_tile_kernel, smaller tiles of several shapes
@@ -51,13 +55,20 @@ __device__ __forceinline__ void sched_mfma_lds_read() {
     sched_mfma_lds_read<N - 1>();
   }
 }
-// N times "one MFMA, one LDS read, one MFMA, one LDS read, one global load":
-template <int N>
-__device__ __forceinline__ void sched_mfma_lds_read_dma() {
-  if constexpr (N > 0) {
-    sched_mfma_lds_read<2>();
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    sched_mfma_lds_read_dma<N - 1>();
+// The step's R LDS reads and D global loads behind its first MFMAs: two LDS reads, then one global load, each
+// behind an MFMA of its own while there are any left of M.
+template <int M, int R, int D>
+__device__ __forceinline__ void sched_step() {
+  if constexpr (M > 0 && (R > 0 || D > 0)) {
+    constexpr int r = R < 2 ? R : 2, m = r > 0 ? (r < M ? r : M) : 1;
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    if constexpr (r > 1) {
+      if constexpr (m > 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    if constexpr (D > 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    sched_step<M - m, R - r, (D > 0 ? D - 1 : 0)>();
   }
 }
 
@@ -120,16 +131,17 @@ struct GemmArgs {
 // the A fragment) and four consecutive columns, 4 * (lane / 16) .. + 3 of the B fragment: one 8-byte
 // store per accumulator.
 // dest (DIRECT): per fragment row of this lane, the row of Ob that the same values are also stored to, or -1.
-template <int WM, int WN, bool GATED, int ACT, bool DIRECT = false>
+// The WAVES_M waves of a column take turns at the 16-row fragments of the tile.
+template <int WM, int WN, int WAVES_M, bool GATED, int ACT, bool DIRECT = false>
 __device__ inline void store_tile_t(f32x4 (&acc)[WM][WN], uint16_t *Cb, int rbase, int rows_e, int m0, int n0, int N,
                                     int wm, int wn, int lane, const int *dest = nullptr, uint16_t *Ob = nullptr) {
   constexpr int NJ = GATED ? WN / 2 : WN;  // output column fragments per wave
   const int fr = lane & 15, fg = lane >> 4;
-  const int wrow0 = m0 + wm * WM * 16, wcol0 = n0 + wn * NJ * 16;
+  const int wrow0 = m0 + wm * 16, wcol0 = n0 + wn * NJ * 16;
   const bool cols_in = wcol0 + NJ * 16 <= N;  // N % 8 == 0: a group of four columns is inside or outside as a whole
 #pragma unroll
   for (int i = 0; i < WM; ++i) {
-    const int row = wrow0 + i * 16 + fr;
+    const int row = wrow0 + i * WAVES_M * 16 + fr;
     if (row >= rows_e) continue;
     uint16_t *prow = Cb + (size_t)(rbase + row) * N + wcol0 + 4 * fg;
     uint16_t *orow = nullptr;
@@ -171,6 +183,7 @@ constexpr int PK_THREADS = PK_NW * 64;
 constexpr int PK_BM = PK_WAVES_M * PK_WM * 16;     // 256
 constexpr int PK_BROWS = PK_WAVES_N * PK_WN * 16;  // 256 staged B rows
 constexpr int PK_A_STAGE = PK_BM * GB_ROW_BYTES, PK_B_STAGE = PK_BROWS * GB_ROW_BYTES;
+[[maybe_unused]] constexpr int PK_MAX_CUT = 8;
 constexpr int PK_A_STAGES = 2, PK_B_STAGES = 3;
 constexpr int PK_B_BASE = PK_A_STAGES * PK_A_STAGE;
 constexpr int PK_SMEM = PK_B_BASE + PK_B_STAGES * PK_B_STAGE;  // 160 KB: all of a CU's LDS
@@ -211,14 +224,23 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     const int dm = r2 / wd, dn = r2 - dm * wd;
     return (qm * pm + dm) * NT + qn * pn + dn;
   };
-  // this workgroup's i-th tile is number (i * nX + xcd) * S + slot
-  int kk = xcd * S + slot;
-  const int kstep = nX * S;
-  if (kk >= total) return;
-  int L = tile_at(kk), L1 = -1, L2 = -1;  // this workgroup's current tile and the two after it
-  if (kk + kstep < total) L1 = tile_at(kk + kstep);
-  if (kk + 2 * kstep < total) L2 = tile_at(kk + 2 * kstep);
-  kk += 2 * kstep;  // number of L2
+  // This workgroup's i-th tile is number (i * nX + xcd) * S + slot.  The tiles of the last, partial round are
+  // spread over the XCDs and, where they are at most half as many as the workgroups, cut by rows into up to
+  // PK_MAX_CUT parts that different workgroups take.
+  const int rounds = total / G, left = total - rounds * G;
+  const int cut = left > 0 ? min(G / left, PK_MAX_CUT) : 1;
+  const int units = left * cut, per_xcd = (units + nX - 1) / nX;
+  // tile of round i and, in the last round, which part of it; -1: none
+  struct Unit { int L, part; };
+  auto unit_at = [&](int i) {
+    if (i < rounds) return Unit{tile_at((i * nX + xcd) * S + slot), -1};
+    const int u = xcd * per_xcd + slot;
+    if (i > rounds || slot >= per_xcd || u >= units) return Unit{-1, -1};
+    return Unit{tile_at(rounds * G + u / cut), cut > 1 ? u % cut : -1};
+  };
+  int round = 0;
+  Unit U = unit_at(0), U1 = unit_at(1), U2 = unit_at(2);  // this workgroup's current tile and the two after it
+  if (U.L < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps LDS-DMA addressing scalar
   const int wm = w / PK_WAVES_N, wn = w % PK_WAVES_N;
@@ -226,7 +248,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 
   // fragment addressing (the same for every tile): lane reads row (lane & 15), chunk 4*ks + (lane >> 4)
   const int fsw = swz(fr);  // fragment rows start at multiples of 16, so the swizzle depends on fr only
-  const int a_off = (wm * WM * 16 + fr) * GB_ROW_BYTES;  // fragment i: + i * 16 rows
+  const int a_off = (wm * 16 + fr) * GB_ROW_BYTES;  // fragment i: + i * PK_WAVES_M * 16 rows
   // gated: the first half of a wave's column fragments are gate columns, the second the matching up columns
   const int b_off = (wn * (GATED ? WN / 2 : WN) * 16 + fr) * GB_ROW_BYTES;
   auto b_frag = [&](int j) { return (GATED && j >= WN / 2 ? BN + (j - WN / 2) * 16 : j * 16) * GB_ROW_BYTES; };
@@ -270,7 +292,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     ra = q[0];
     rb = q[1];
   };
-  auto finalize = [&](int Lt, const int4 &ra, const int4 &rb) {
+  auto finalize = [&](const Unit &u, const int4 &ra, const int4 &rb) {
     Info f;
     f.e = __builtin_amdgcn_readfirstlane(ra.x);
     f.m0 = __builtin_amdgcn_readfirstlane(ra.y);
@@ -278,7 +300,12 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     f.rows_e = __builtin_amdgcn_readfirstlane(ra.w);
     f.fill_e = __builtin_amdgcn_readfirstlane(rb.x);
     f.iroff_e = __builtin_amdgcn_readfirstlane(rb.y);
-    f.n0 = (Lt % NT) * BN;
+    f.n0 = (u.L % NT) * BN;
+    if (u.part >= 0) {  // an equal share of the tile's rows, in whole fragments of both waves; past the last row: empty
+      const int h = (min(BM, f.rows_e - f.m0) + cut * 32 - 1) / (cut * 32) * 32;
+      f.m0 += u.part * h;
+      f.rows_e = min(f.rows_e, f.m0 + h);
+    }
     return f;
   };
   // the dispatch gather (Sec. 3: tokens travel to their experts): the tokens behind this lane's A
@@ -298,7 +325,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   };
   auto make_tile = [&](const Info &f, const int (&tok)[NIA], Tile &t) {
     t.e = f.e; t.m0 = f.m0; t.rbase = f.rbase; t.rows_e = f.rows_e; t.n0 = f.n0;
-    t.live = min(WM, max(0, (f.rows_e - f.m0 - wm * WM * 16 + 15) >> 4));
+    t.live = (min(BM, f.rows_e - f.m0) + PK_WAVES_M * 16 - 1) / (PK_WAVES_M * 16);
     const char *B0b = static_cast<const char *>(P.B0) + (size_t)f.e * N * K * 2;
     const char *B1b = GATED ? static_cast<const char *>(P.B1) + (size_t)f.e * N * K * 2 : B0b;
     if (GATHER) {
@@ -383,16 +410,17 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
   int sa = 0, sb = 0;   // ring stages of the current chunk
   {
     int4 ra, rb;
-    raw_load(L, ra, rb);
-    const Info f0 = finalize(L, ra, rb);
+    raw_load(U.L, ra, rb);
+    const Info f0 = finalize(U, ra, rb);
+    if (f0.m0 >= f0.rows_e) return;  // an empty part
     int tok0[NIA];
 #pragma unroll
     for (int i = 0; i < NIA; ++i) tok0[i] = -1;
     if (GATHER) lookup_tokens(f0, tok0);
     make_tile(f0, tok0, cur);
-    if (L1 >= 0) {
-      raw_load(L1, ra, rb);
-      info1 = finalize(L1, ra, rb);
+    if (U1.L >= 0) {
+      raw_load(U1.L, ra, rb);
+      info1 = finalize(U1, ra, rb);
     }
     stream_a(cur, true);
     stream_b(cur, true);
@@ -402,7 +430,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIB) : "memory");  // own A(0), B(0) have landed
   }
   while (true) {
-    const bool have1 = L1 >= 0;
+    const bool have1 = U1.L >= 0 && info1.m0 < info1.rows_e;  // (only a workgroup's last tile can be an empty part)
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -414,13 +442,13 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     // table lookups for the tiles to come, issued before this chunk's loads so that they are older
     // than anything a counted wait lets pass
     if (GATHER) lookup_tokens(info1, tok1);
-    raw_load(L2 >= 0 ? L2 : L, ra2, rb2);
+    raw_load(U2.L >= 0 ? U2.L : U.L, ra2, rb2);
     int dest[WM];  // DIRECT: where the rows that this lane will store also go (this tile's, used in its epilogue)
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
       dest[i] = -1;
       if (DIRECT) {
-        const int row = cur.m0 + (wm * WM + i) * 16 + fr;
+        const int row = cur.m0 + (i * PK_WAVES_M + wm) * 16 + fr;
         dest[i] = P.row_dest[cur.rbase + min(row, cur.rows_e - 1)];
       }
     }
@@ -428,41 +456,33 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
     issue_a(sa ^ 1);
     issue_b(next_b(next_b(sb)), 0, NIB);
 
-    // Ragged row tiles: the last tile of an expert is mostly padding.  A wave skips the fragment
-    // loads and MFMAs of its 16-row fragments that lie wholly past the expert's last row (a
-    // wave-uniform test), so a padded tile costs MFMA time in proportion to its real rows.  Full
-    // tiles take a branch-free copy of the loop (FULL), which keeps its counted LDS waits exact.
-    const int live = cur.live;
-    auto k_loop = [&](auto full_tag) {
-      constexpr bool FULL = decltype(full_tag)::value;
+    // Ragged and cut row tiles: the two waves of a column take turns at the tile's 16-row fragments, and
+    // the K loop comes in copies for 2, 4, 6 and 8 fragments per wave (branch-free, which keeps the counted
+    // LDS waits exact), so a short tile costs MFMA time in proportion to its rows on all four SIMDs.
+    auto k_loop = [&](auto live_tag) {
       // A chunk is four steps: k-step ks (of two), half hf of the wave's A rows.  A step multiplies half of the
-      // A fragments with all B fragments of its k-step: 16 MFMAs.
-      constexpr int HM = WM / 2;
+      // A fragments with all B fragments of its k-step: 16 MFMAs in a full tile.
+      constexpr int HM = decltype(live_tag)::value / 2, MF = HM * WN;
       bf16x8 af[2][HM], bfr[2][WN];
       auto load_a = [&](const char *sta, int ks, int hf) {
         const char *p = sta + a_off + (((4 * ks + fg) ^ fsw) << 4);
 #pragma unroll
         for (int i = 0; i < HM; ++i)
-          if (FULL || hf * HM + i < live)
-            af[hf][i] = *reinterpret_cast<const bf16x8 *>(p + (hf * HM + i) * 16 * GB_ROW_BYTES);
+          af[hf][i] = *reinterpret_cast<const bf16x8 *>(p + (hf * HM + i) * PK_WAVES_M * 16 * GB_ROW_BYTES);
       };
       auto load_b = [&](const char *stb, int ks) {
         const char *p = stb + b_off + (((4 * ks + fg) ^ fsw) << 4);
-        if (FULL || live > 0) {
 #pragma unroll
-          for (int j = 0; j < WN; ++j) bfr[ks][j] = *reinterpret_cast<const bf16x8 *>(p + b_frag(j));
-        }
+        for (int j = 0; j < WN; ++j) bfr[ks][j] = *reinterpret_cast<const bf16x8 *>(p + b_frag(j));
       };
       auto mfma_step = [&](int ks, int hf) {
 #pragma unroll
         for (int i = 0; i < HM; ++i)
-          if (FULL || hf * HM + i < live) {
 #pragma unroll
-            for (int j = 0; j < WN; ++j)
-              // B fragment first: the accumulator holds the transposed tile (see store_tile_t)
-              acc[hf * HM + i][j] =
-                  __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ks][j], af[hf][i], acc[hf * HM + i][j], 0, 0, 0);
-          }
+          for (int j = 0; j < WN; ++j)
+            // B fragment first: the accumulator holds the transposed tile (see store_tile_t)
+            acc[hf * HM + i][j] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ks][j], af[hf][i], acc[hf * HM + i][j], 0, 0, 0);
       };
       // The chunk's LDS-DMA loads are spread over its steps, one behind every second MFMA: A(kt+1) in the step
       // after the barrier, B(kt+2) in the two after it.  (All eight in one place - 64 per CU, 16 clocks of the
@@ -481,23 +501,17 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
         load_a(sta, 0, 1);
         if (DMA) issue_b(bstage, 0, NIB / 2);
         mfma_step(0, 0);
-        if (DMA) sched_mfma_lds_read_dma<NIB / 2>();
-        else sched_mfma_lds_read<HM>();
+        sched_step<MF, HM, DMA ? NIB / 2 : 0>();
         __builtin_amdgcn_sched_barrier(0);
         load_a(sta, 1, 0);
         load_b(stb, 1);
         if (DMA) issue_b(bstage, NIB / 2, NIB);
         mfma_step(0, 1);
-        if (DMA) {
-          sched_mfma_lds_read_dma<NIB / 2>();
-          sched_mfma_lds_read<HM + WN - NIB>();
-        } else {
-          sched_mfma_lds_read<HM + WN>();
-        }
+        sched_step<MF, HM + WN, DMA ? NIB - NIB / 2 : 0>();
         __builtin_amdgcn_sched_barrier(0);
         load_a(sta, 1, 1);
         mfma_step(1, 0);
-        sched_mfma_lds_read<HM>();
+        sched_step<MF, HM, 0>();
         __builtin_amdgcn_sched_barrier(0);
       };
       const char *sta = smem + sa * PK_A_STAGE, *stb = smem + PK_B_BASE + sb * PK_B_STAGE;
@@ -510,7 +524,7 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
       // when the loop is entered or the tile ends - there it would drain every outstanding load
       // and store.  Without a next tile the values are unused.
       make_tile(info1, tok1, nxt);
-      info2 = finalize(L2 >= 0 ? L2 : L, ra2, rb2);
+      info2 = finalize(U2.L >= 0 ? U2 : U, ra2, rb2);
       if (DIRECT) {  // consumed here like the other lookups, so that no load is pending when the loop is entered
 #pragma unroll
         for (int i = 0; i < WM; ++i) asm volatile("" : "+v"(dest[i]));
@@ -537,33 +551,33 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
         load_b(stb, 0);
         issue_a(sa ^ 1);
         mfma_step(1, 1);  // last step of chunk kt-1
-        sched_mfma_lds_read_dma<NIA>();
+        sched_step<MF, HM + WN, NIA>();
         __builtin_amdgcn_sched_barrier(0);
         steps(sta, stb, std::true_type{}, next_b(next_b(sb)));
       }
       mfma_step(1, 1);
     };
-    if (live == WM)
-      k_loop(std::true_type{});
-    else
-      k_loop(std::false_type{});
+    const int live = cur.live;
+    if (live > 6) k_loop(std::integral_constant<int, 8>{});
+    else if (live > 4) k_loop(std::integral_constant<int, 6>{});
+    else if (live > 2) k_loop(std::integral_constant<int, 4>{});
+    else k_loop(std::integral_constant<int, 2>{});
 
     // own A(0), B(0) of the next tile have landed (they were issued one and two chunks ago), before
     // the stores below join the queue of outstanding memory operations
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NIB) : "memory");
     sa ^= 1;
     sb = next_b(sb);
-    store_tile_t<WM, WN, GATED, ACT, DIRECT>(acc, static_cast<uint16_t *>(P.Cout), cur.rbase, cur.rows_e, cur.m0, cur.n0,
+    store_tile_t<WM, WN, PK_WAVES_M, GATED, ACT, DIRECT>(acc, static_cast<uint16_t *>(P.Cout), cur.rbase, cur.rows_e, cur.m0, cur.n0,
                                              N, wm, wn, lane, dest, static_cast<uint16_t *>(P.Out));
     if (!have1) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stream's loads past the last tile still write this LDS
       break;
     }
     cur = nxt;
-    L = L1;
-    L1 = L2;
-    kk += kstep;
-    L2 = kk < total ? tile_at(kk) : -1;
+    U = U1;
+    U1 = U2;
+    U2 = unit_at(++round + 2);
     info1 = info2;
   }
 #endif
@@ -813,39 +827,92 @@ using TileB64 = TileShape<true, 2, 2, 2, 4, 3, 2>;      // bf16, 64 x 128
 using TileB32 = TileShape<true, 1, 2, 2, 4, 4, 2>;      // bf16, 32 x 128
 using TileB32n = TileShape<true, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
 
-// Which tiles a GEMM uses.  Time of a launch = rounds of tiles over the CUs x K chunks x time of a chunk, so the shape is
-// the one with the least ceil(tiles / CUs) x cost, cost = microseconds per chunk and CU, measured: large tiles move the
-// fewest operand bytes per flop, small ones leave no CU idle when a layer has few rows or few columns.  At 8 experts,
-// 4096 x 11008, K = 11008, us: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255; 540 rows 230, 160, 202
-// (128 x 128: 157); 34 rows 219, 153, 144 (32 x 64: 134).
+// Which tiles a GEMM uses: the shape with the least estimated time.  A CU works through ceil(tiles / CUs) tiles of
+// (K chunks x time of a chunk + prologue and epilogue); a chunk takes the longer of
+//   cost     its MFMAs and LDS traffic, us per chunk with the CU full, and
+//   fetch    its weight bytes that come from HBM (row tiles of one expert share them through L2) at kCuFetch: what
+//            one CU sustains against HBM, however deep its ring (a 64 x 128 ring of 6 chunks is no faster than one
+//            of 3), so weight-bound layers need their bytes spread evenly over the CUs;
+// and no launch is faster than its weights at kHbm.  Large tiles move the fewest operand bytes per flop, small ones
+// leave no CU idle.  Measured against the estimate, us: 300 tokens Zipf(1.1), 16 experts, down 5632 -> 2048:
+// 32 x 128 92, 64 x 128 108 (one expert has more than 64 rows: 272 tiles), 128 x 128 74; fp32, up / down: 64 x 128
+// 213 / 238, 32 x 128 188 / 213, 32 x 64 165 / 168; 16 tokens, 8 experts, down 11008 -> 4096: 32 x 128 141, 32 x 64 133;
+// 8 experts 4096 x 11008, K = 11008: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255.
 enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_F64, FFN_F32, FFN_F32N };
-struct ShapeInfo { int bm, brows; float cost; };
-constexpr ShapeInfo kShape[] = {{256, 256, 1.45f}, {256, 128, 1.0f}, {128, 128, 0.75f}, {64, 128, 0.5f}, {32, 128, 0.38f},
-                                {32, 64, 0.3f},    {64, 128, 0.97f}, {32, 128, 0.5f},  {32, 64, 0.26f}};
+struct ShapeInfo { int bm, brows; float cost, fixed; };
+constexpr ShapeInfo kShape[] = {{256, 256, 1.45f, 5.0f}, {256, 128, 1.0f, 3.0f}, {128, 128, 0.62f, 2.0f},
+                                {64, 128, 0.5f, 1.0f},   {32, 128, 0.4f, 1.0f},  {32, 64, 0.3f, 0.3f},
+                                {64, 128, 1.05f, 1.0f},  {32, 128, 0.5f, 0.7f},  {32, 64, 0.26f, 0.5f}};
+constexpr float kCuFetch = 26e3f, kHbm = 5.9e6f;  // bytes per us
+// the 256 x 256 kernel: its start, and a chunk of a tile of the last round cut into 1 .. PK_MAX_CUT parts
+constexpr float kPersistentStart = 6.0f, kCutCost[] = {1.0f, 0.72f, 0.6f, 0.53f, 0.5f, 0.47f, 0.45f, 0.43f};
+static_assert(sizeof(kCutCost) / sizeof(float) == PK_MAX_CUT);
+// the activation of a tile whose workgroup has the CU to itself (256 x 256: in `fixed`; smaller ones overlap theirs)
+constexpr float kAct256 = 4.0f, kAct128 = 3.0f;
 
-FfnShape pick_shape(const Dims &D, int K, int N, bool gated) {
-  constexpr int kCUs = 256;
+// Row tiles of height bm that the layer's rows are expected to make.
+long long expected_row_tiles(const Dims &D, int bm) {
   // dispatched rows: the top-k assignments (a dropped token's re-routed row stands for its dropped ones)
   const long long want = (long long)D.T * D.k, R = want < D.Rmax ? want : D.Rmax, used = R < D.E ? R : D.E;
-  const bool bf16 = D.dtype == RR_BF16;
-  FfnShape best = bf16 ? FFN_32N : FFN_F32N;
-  float least = 0.0f;
-  for (int q = bf16 ? FFN_P256 : FFN_F64; q <= (bf16 ? FFN_32N : FFN_F32N); ++q) {
-    const ShapeInfo &s = kShape[q];
-    if (q == FFN_P256 && !persistent_ok(K)) continue;
-    // a tile's rows are addressed with 32-bit byte offsets (rr_config bounds rows so that the narrowest shape always fits)
-    if ((long long)K * std::max(s.bm, s.brows) * (bf16 ? 2 : 4) >= 1ll << 31) continue;
-    const int bn = gated ? s.brows / 2 : s.brows;
-    const long long mt = 4 * R <= 3ll * s.bm * used ? used : R / s.bm + used / 2;
-    const long long tiles = mt * ((N + bn - 1) / bn);
-    const float cost = (float)((tiles + kCUs - 1) / kCUs) * s.cost;
-    if (least == 0.0f || cost < least) { least = cost; best = (FfnShape)q; }
-  }
-  return best;
+  // a popular expert: its capacity and three times an even share of re-routed tokens; one expert in eight is one
+  const long long popular = std::min((long long)D.T, D.C + (D.ir ? 3ll * D.T / D.E : 0)), n_popular = (used + 7) / 8;
+  return 4 * R <= 3ll * bm * used ? used + n_popular * ((popular - 1) / bm) : R / bm + used / 2;
 }
+
+// Estimated time of a GEMM with tiles of shape q, us; < 0: not possible.
+float shape_cost(const Dims &D, int K, int N, bool up, int q) {
+  constexpr int kCUs = 256;
+  const bool bf16 = D.dtype == RR_BF16, gated = up && D.act == RR_ACT_SWIGLU;
+  const ShapeInfo &s = kShape[q];
+  if (q == FFN_P256 && !persistent_ok(K)) return -1.0f;
+  const int es = bf16 ? 2 : 4, KT = (int)(((long long)K * es + GB_ROW_BYTES - 1) / GB_ROW_BYTES);
+  // a tile's rows are addressed with 32-bit byte offsets (rr_config bounds rows so that the narrowest shape always fits)
+  if ((long long)K * std::max(s.bm, s.brows) * es >= 1ll << 31) return -1.0f;
+  const float used = (float)std::min<long long>({(long long)D.T * D.k, D.Rmax, D.E});
+  const float stream = used * N * K * es * (gated ? 2 : 1) / kHbm;
+  const int bn = gated ? s.brows / 2 : s.brows;
+  const long long mt = expected_row_tiles(D, s.bm), tiles = mt * ((N + bn - 1) / bn), rounds = tiles / kCUs, left = tiles - rounds * kCUs;
+  const float fetch = (float)(s.brows * GB_ROW_BYTES) / kCuFetch * used / (float)mt, chunk = std::max(s.cost, fetch);
+  const float filled = std::min(1.0f, (float)std::min<long long>((long long)D.T * D.k, D.Rmax) / (float)(mt * s.bm));
+  const float fixed = s.fixed + filled * (up && q == FFN_256 ? kAct256 : (up && q == FFN_128 ? kAct128 : 0.0f));
+  float busy = (float)rounds * (KT * chunk + fixed);
+  if (q == FFN_P256) {
+    busy += kPersistentStart;
+    if (left > 0)
+      busy += KT * std::max(s.cost * kCutCost[std::min<long long>(kCUs / left, PK_MAX_CUT) - 1], fetch) + fixed;
+  } else if (left > 0) {  // several workgroups per CU: a round that is nearly empty runs partly under the one before
+    busy += (KT * chunk + fixed) * (rounds ? std::min(1.0f, (float)left / kCUs + 0.5f) : 1.0f);
+  }
+  return std::max(busy, stream) + 0.1f * busy;
+}
+
 struct FfnPlan { FfnShape up, down; };
+// The pair of shapes with the least cost.  Both GEMMs walk one table of row tiles, as high as the higher of the two: a
+// lower shape cuts every row tile of the table (GemmArgs::sub) and launches a workgroup for the cuts that turn out
+// to be empty too, about 30 ns each (300 tokens, up 2048 -> 5632: 32-row tiles in a table of 128 rows 269 us, 140 alone).
 FfnPlan ffn_plan(const Dims &D) {
-  return {pick_shape(D, D.d, D.F, D.act == RR_ACT_SWIGLU), pick_shape(D, D.F, D.d, false)};
+  constexpr float kEmpty = 0.031f;
+  const int q0 = D.dtype == RR_BF16 ? FFN_P256 : FFN_F64, q1 = D.dtype == RR_BF16 ? FFN_32N : FFN_F32N;
+  auto empty = [&](int q, int N, bool gated, int bm) {
+    const ShapeInfo &s = kShape[q];
+    const int bn = gated ? s.brows / 2 : s.brows;
+    const long long cuts = expected_row_tiles(D, bm) * (bm / s.bm) - expected_row_tiles(D, s.bm);
+    return kEmpty * (float)(std::max(0ll, cuts) * ((N + bn - 1) / bn));
+  };
+  FfnPlan best{(FfnShape)q1, (FfnShape)q1};
+  float least = -1.0f, up[FFN_F32N + 1], down[FFN_F32N + 1];
+  for (int q = q0; q <= q1; ++q) {
+    up[q] = shape_cost(D, D.d, D.F, true, q);
+    down[q] = shape_cost(D, D.F, D.d, false, q);
+  }
+  for (int u = q0; u <= q1; ++u)
+    for (int w = q0; w <= q1; ++w) {
+      if (up[u] < 0.0f || down[w] < 0.0f) continue;
+      const int bm = std::max(kShape[u].bm, kShape[w].bm);
+      const float cost = up[u] + down[w] + empty(u, D.F, D.act == RR_ACT_SWIGLU, bm) + empty(w, D.d, false, bm);
+      if (least < 0.0f || cost <= least) { least = cost; best = {(FfnShape)u, (FfnShape)w}; }
+    }
+  return best;
 }
 
 template <class S>

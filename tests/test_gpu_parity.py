@@ -740,11 +740,12 @@ TILE_SHAPES = [
     ("32x64 K 8", 40, 8, 72, 4, 2, 2, "bf16", "gelu"),
     ("32x64 ragged", 70, 200, 136, 8, 2, 2, "bf16", "swiglu"),
     ("64x128 32x128", 900, 456, 1000, 6, 2, 2, "bf16", "gelu"),
-    ("128x128 32x128", 900, 456, 1032, 6, 2, 2, "bf16", "gelu"),
+    ("128x128 ragged K", 1300, 2056, 1032, 2, 1, 1, "bf16", "swiglu"),
     ("256x256 64x128", 1500, 264, 4104, 4, 1, 2, "bf16", "swiglu"),
     ("256x256 128x128", 2600, 584, 2056, 4, 2, 2, "bf16", "swiglu"),
     ("256x256 256x128 ragged K", 9001, 264, 2312, 4, 1, 2, "bf16", "gelu"),
-    ("256x128 256x256 ragged K", 9001, 2312, 264, 4, 1, 1, "bf16", "swiglu"),
+    ("256x128 ragged K", 9001, 2312, 264, 4, 1, 1, "bf16", "swiglu"),
+    ("256x256 ragged K", 3000, 2056, 776, 3, 1, 2, "bf16", "swiglu"),
     ("f32 32x64 one row", 1, 8, 40, 4, 1, 1, "f32", "gelu"),
     ("f32 32x64", 129, 800, 264, 4, 1, 2, "f32", "swiglu"),
     ("f32 32x128", 1900, 104, 1208, 4, 2, 2, "f32", "swiglu"),
@@ -799,3 +800,27 @@ def test_small_batch_tables(T, E, G, k, cf, quota):
         a = logits.cpu().numpy()
         assert np.array_equal(a, (x.astype(np.float64) @ wr.astype(np.float64).T).astype(np.float32))
         gu.assert_tables_equal(tables.to_host(), _oracle_tables(a, cfg, ("ir", "fr"), False, quota))
+
+
+# The 256 x 256 kernel's last round: its tiles are cut by rows into as many parts as leave no CU idle.  First choices
+# only, capacity T / E: the experts' rows, and so the cut of the up projection, follow from the tables.
+CUT_TILES = [
+    # T, d_model, d_ff, E, parts of a tile of the last round
+    (4030, 232, 1336, 8, 2),  # no whole round before it; an expert without rows, and parts that are empty (27 rows)
+    (5003, 232, 1048, 3, 3),  # the same; an expert of 5 rows
+    (3500, 232, 4000, 5, 2),
+    (3917, 232, 3352, 6, 3),  # experts of 7 and 10 rows
+    (3500, 232, 3352, 5, 6),
+    (3500, 232, 2992, 5, 8),
+]
+
+
+@pytest.mark.parametrize("T,d,F,E,parts", CUT_TILES)
+def test_forward_cut_row_tiles(T, d, F, E, parts):
+    w = wl.Workload(f"cut {parts}", T, d, F, E, 1, 1, 1.0, "bf16", "swiglu", "normal:0.5", 40 + T % 97)
+    inputs = wl.make_inputs(w)
+    first = orc.router_scores(wl.values_f32(inputs["x"], "bf16"), inputs["w_router"], inputs["bias"]).argmax(axis=1)
+    rows = np.minimum(np.bincount(first, minlength=E), -(-T // E))
+    left = int((-(-rows // 256)).sum()) * -(-F // 128) % 256
+    assert min(256 // left, 8) == parts
+    _forward_case(w, (), inputs)
