@@ -297,31 +297,73 @@ constexpr int SS_PER = kSelectRegMax / SS_THREADS;  // keys a thread keeps in re
 constexpr int kHistCopies = 32;  // counters per histogram bin (see radix_select)
 constexpr int kHistWords = 256 * (1 + kHistCopies);
 
-// m-th largest key among those that `each` enumerates, by 8-bit digits from the top (Sec. 3: the
-// lowest scores are dropped).  Returns the threshold key; need_eq = how many of the keys equal to it
-// are kept (the first ones in token order).  `each(f)` calls f(key, valid) for every key slot of the
+// Smallest value of the wave, in a scalar (data-parallel moves: no LDS round trips).
+__device__ inline u32 wave_min(u32 v) {
+  auto step = [&](auto ctrl, auto row_mask) {
+    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)0xffffffff, (int)v, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false));
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast 15 into rows 1 and 3
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast 31 into rows 2 and 3
+  return (u32)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// m-th largest key among those that `each` enumerates (Sec. 3: the lowest scores are dropped), by 8-bit digits
+// from the highest bit in which the keys differ at all.  Returns the threshold key; need_eq = how many of the keys
+// equal to it are kept (the first ones in token order).  `each(f)` calls f(key, valid) for every key slot of the
 // calling thread, the same number of times in every lane of a wave (invalid slots with valid = false);
 // all threads of the workgroup call this together.
-// Scores of one list share their leading digits, so most lanes of a wave hit the same histogram
-// bin, and LDS atomics of one instruction on one address are served one lane after the other: every
-// bin has kHistCopies counters, lane l adds to copy l % kHistCopies (consecutive words, different
-// banks), and the copies are added up before the bins are scanned.
-// last_pass > 0 stops after the digits above it: the result is then the threshold with its lower digits
-// cleared - a lower bound of the m-th largest key that is off by less than one step of the last digit
-// taken (need_eq is meaningless then).
+// A digit pass is four barriers and an LDS histogram, 1.6 us; a few thousand scores differ in 24 or 25 bits, and
+// two digits below their common prefix as a rule leave a bin of which every key is kept: the threshold is then
+// the key below the bin, and the passes end (3001 tokens, 6 experts: four fixed passes 6.5 us, now 4.2; all of
+// select_slot_kernel at 4096 tokens with per-group capacity 21.0 -> 17.5).
+// Most lanes of a wave can hit the same histogram bin (scores tied or close), and LDS atomics of one instruction on
+// one address are served one lane after the other: every bin has kHistCopies counters, lane l adds to copy
+// l % kHistCopies (consecutive words, different banks), and the copies are added up before the bins are scanned.
+// passes: at most that many digits; the result is then a lower bound of the m-th largest key, off by less than
+// one step of the last digit taken (need_eq is meaningless then).
 template <class Each>
-__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq, int last_pass = 0) {
+__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq, int passes = 4) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   u32 *copies = hist + 256;  // [256][kHistCopies]
-  u32 prefix = 0, remaining = (u32)m;
-  for (int pass = 3; pass >= last_pass; --pass) {
-    const int shift = pass * 8;
+  u32 prefix, remaining = (u32)m;
+  int left;  // bits below the prefix
+  {
+    u32 lo = 0xffffffffu, nhi = 0xffffffffu;  // smallest key, smallest complement
+    each([&](u32 kx, bool valid) {
+      if (valid) {
+        lo = min(lo, kx);
+        nhi = min(nhi, ~kx);
+      }
+    });
+    lo = wave_min(lo);
+    nhi = wave_min(nhi);
+    if (lane == 0) {
+      hist[w] = lo;
+      hist[SS_WAVES + w] = nhi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SS_WAVES; ++q) {
+      lo = min(lo, hist[q]);
+      nhi = min(nhi, hist[SS_WAVES + q]);
+    }
+    const u32 diff = lo ^ ~nhi;
+    left = diff ? 32 - __clz((int)diff) : 0;
+    prefix = left < 32 ? lo >> left << left : 0u;
+  }  // (hist is next written two barriers from here)
+  while (left > 0 && passes-- > 0) {
+    const int bits = min(left, 8), shift = left - bits;
 #pragma unroll
     for (int q = 0; q < 256 * kHistCopies / SS_THREADS; ++q) copies[q * SS_THREADS + tid] = 0;
     __syncthreads();
     each([&](u32 kx, bool valid) {
-      if (valid && (pass == 3 || ((kx ^ prefix) >> (shift + 8)) == 0))
-        atomicAdd(&copies[((kx >> shift) & 255u) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
+      const u32 digit = (kx ^ prefix) >> shift;  // (the prefix has zeros there: past 8 bits only in keys of another prefix)
+      if (valid && digit >> bits == 0) atomicAdd(&copies[digit * kHistCopies + (lane & (kHistCopies - 1))], 1u);
     });
     __syncthreads();
     {  // thread t adds up a quarter of the copies of bin t / 4
@@ -346,18 +388,24 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
       }
       u32 excl = incl - sum;
       if (excl < remaining && remaining <= incl) {
-        u32 rem = remaining - excl;
+        u32 rem = remaining - excl, in_bin = c0;
         int bkt = 255 - 4 * lane;
-        if (rem > c0) { rem -= c0; --bkt;
-          if (rem > c1) { rem -= c1; --bkt;
-            if (rem > c2) { rem -= c2; --bkt; } } }
+        if (rem > c0) { rem -= c0; --bkt; in_bin = c1;
+          if (rem > c1) { rem -= c1; --bkt; in_bin = c2;
+            if (rem > c2) { rem -= c2; --bkt; in_bin = c3; } } }
         s_pick[0] = (u32)bkt;
         s_pick[1] = rem;
+        s_pick[2] = in_bin;
       }
     }
-    __syncthreads();  // the picks are next written two barriers from here: no barrier needed after reading them
+    __syncthreads();  // the picks are next written three barriers from here: no barrier needed after reading them
     prefix |= s_pick[0] << shift;
     remaining = s_pick[1];
+    left = shift;
+    if (s_pick[2] == remaining && prefix > 0) {  // the whole bin is kept
+      need_eq = 0;
+      return prefix - 1;
+    }
   }
   need_eq = remaining;
   return prefix;
@@ -366,7 +414,7 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
 // Shared memory of the selection kernels.
 struct SelectSmem {
   u32 hist[kHistWords];
-  u32 pick[2];
+  u32 pick[3];
   int2 wtot[SS_PER][SS_WAVES];  // (kept-for-sure, equal-to-threshold) counts per (trip, wave)
   int2 wsum[8];
 };
@@ -374,7 +422,7 @@ struct SelectSmem {
 // Selection and slotting of a list of n <= SS_THREADS * SS_PER candidates held in registers: candidate
 // idx = u * SS_THREADS + tid is element u of thread tid (`load(idx, key, tok)` fetches it), so the
 // candidates are met in token order.  by_score: the m highest keys are kept, equal keys in token order
-// (radix select of the threshold, four digit passes on registers); otherwise the first m in token
+// (radix select of the threshold, digit passes on registers); otherwise the first m in token
 // order.  Kept candidates take slots fill0, fill0 + 1, ... in token order: one scan over the
 // (trip, wave) totals of the kept flags.  Only kept candidates are written (every slot entry starts
 // as -1).
@@ -453,8 +501,8 @@ __device__ inline void select_in_registers(const DispatchArgs &A, int n, int m, 
   }
 }
 
-// The same for a list of any length, streamed from memory by one workgroup: the threshold by four
-// digit passes over the keys, then a pass that hands out the slots 1024 candidates at a time.  The
+// The same for a list of any length, streamed from memory by one workgroup: the threshold by digit
+// passes over the keys, then a pass that hands out the slots 1024 candidates at a time.  The
 // path for lists that fit neither the registers nor the split scheme below; exact for any input.
 __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, bool by_score, int r, int j, int fill0,
                                         const u32 *__restrict__ keys, const int32_t *__restrict__ toks, SelectSmem &S,
@@ -699,8 +747,8 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) sk[u] = keys[(size_t)(u * SS_WAVES + w) * run + lane];
     u32 dummy;
-    // the two leading digits are enough: L only has to lie below the list's m-th highest key, and the keys of
-    // one 16-bit step (2^-7 of a score) are a handful of candidates more
+    // two digits are enough: L only has to lie below the list's m-th highest key, and the keys of one step of the
+    // second (2^-16 of the sample's range) are a handful of candidates more
     L = radix_select(qsel, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kSegPer; ++u) f(sk[u], true);
@@ -816,7 +864,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
                                                                    int32_t *__restrict__ fill_topk,
                                                                    int32_t *__restrict__ fill_total) {
   __shared__ u32 hist[kHistWords];
-  __shared__ u32 s_pick[2];
+  __shared__ u32 s_pick[3];
   __shared__ int2 wtot[SS_PER][SS_WAVES];
   __shared__ int2 wsum[8];
   __shared__ int s_cnt[kMaxRounds];
@@ -1203,21 +1251,6 @@ __host__ __device__ inline OneLayout one_layout(int T, int E, int NR, int Gq, bo
   L.plan_topk = L.plan + NR * E * Gq * 4;
   L.total = L.plan_topk + (Gq > 1 ? E * Gq * 4 : 0);
   return L;
-}
-
-// Smallest value of the wave, in a scalar (data-parallel moves: no LDS round trips).
-__device__ inline u32 wave_min(u32 v) {
-  auto step = [&](auto ctrl, auto row_mask) {
-    v = min(v, (u32)__builtin_amdgcn_update_dpp((int)0xffffffff, (int)v, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false));
-  };
-  using std::integral_constant;
-  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
-  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
-  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast 15 into rows 1 and 3
-  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast 31 into rows 2 and 3
-  return (u32)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 template <int SRC>
