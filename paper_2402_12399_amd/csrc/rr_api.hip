@@ -110,6 +110,7 @@ static int make_dims(const rr_config *c, bool need_ffn, Dims *D) {
   D->NCAT = D->NR * c->E;
   D->NL = D->NCAT * Gq;
   D->NB = (c->T + kTokBlock - 1) / kTokBlock;
+  D->Ts = select_direct(*D) ? round_up(c->T, 16) : c->T;
   D->cb = 1;
   D->NBc = D->NB;
   D->dtype = c->dtype; D->act = c->act;
@@ -145,7 +146,8 @@ struct Carver {
 static size_t carve(const Dims &D, bool forward, void *ws, Work *W) {
   Carver cv{static_cast<char *>(ws), 0};
   size_t T = D.T, NR = D.NR, E = D.E;
-  W->key = cv.take<u32>(T * NR);
+  W->key = cv.take<u32>((size_t)D.Ts * NR);
+  W->rank8 = select_direct(D) ? cv.take<uint8_t>((size_t)D.Ts * NR) : nullptr;
   W->ir_score = cv.take<float>(T);
   W->ir_cand = cv.take<int32_t>(T);
   W->blk_cnt = cv.take<int32_t>((size_t)D.NCAT * D.NB * router_count_blocks(D));

@@ -37,6 +37,7 @@ struct Dims {
   int NCAT;    // NR * E candidate arrays (one per round and expert, ascending token index)
   int NL;      // NCAT * Gq selection lists: list id = (round * E + expert) * Gq + block
   int NB;      // token blocks of kTokBlock
+  int Ts;      // row length of the per-round arrays: T, select_direct rounds it up to 16
   int cb;      // candidate-count blocks per token block (1, or 4 when the small-batch router counts per 32 tokens)
   int NBc;     // candidate-count blocks: blk_cnt is [NCAT, NBc]
   int ir, fr, arrival;
@@ -53,10 +54,15 @@ struct __attribute__((aligned(32))) TileInfo {
   int32_t expert, row0, rbase, rows, fill, ir_offset, pad0, pad1;
 };
 
+// Batches whose selection lists are not materialised (rr_dispatch.hip, select_direct_kernel).
+constexpr int kDirectMaxT = 16384;
+inline bool select_direct(const Dims &D) { return D.Gq == 1 && D.T <= kDirectMaxT; }
+
 // Device pointers carved out of the caller's workspace.
 struct Work {
   // routing
-  u32     *key;          // [T, NR]   order-preserving key of the score of the r-th choice
+  u32     *key;          // [NR, Ts]  order-preserving key of the score of the r-th choice
+  uint8_t *rank8;        // [NR, Ts]  its expert (select_direct only, else NULL)
   float   *ir_score;     // [T]       score of the best expert of the token's own group
   int32_t *ir_cand;      // [T]       that expert
   int32_t *blk_cnt;      // [NCAT, NBc] candidates per (list, count block); scanned in place

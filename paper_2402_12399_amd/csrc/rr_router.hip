@@ -96,11 +96,12 @@ __device__ inline f32x16 mfma5(const Frag &xh, const Frag &xl, const Frag &wh, c
 
 struct RankOut {
   int32_t *rank_expert, *slot;  // [T,k+1]
-  u32 *key;                     // [T,NR]
+  u32 *key;                     // [NR,Ts]
+  uint8_t *rank8;               // [NR,Ts] the rounds' experts, where select_direct_kernel reads them; else NULL
   float *ir_score;              // [T]
   int32_t *ir_cand;             // [T]
   int32_t *blk_cnt;             // [NCAT, NBc]
-  int k, NR, fr, Eg, Tg, NCAT, NBc;
+  int k, NR, fr, Eg, Tg, NCAT, NBc, Ts;
 };
 
 // Two lanes rank one token from its finished row of logits (LDS): lanes l and l + 32 of a wave
@@ -134,7 +135,8 @@ __device__ inline void rank_row(const float *row, int tok, int half, int E, int 
         const int e = rank_key_expert(key);  // -1 past the number of experts
         if (q <= k) ranks[(size_t)tok * (k + 1) + q] = (q < n) ? e : -1;
         if (FUSE && q < R.NR) {
-          R.key[(size_t)tok * R.NR + q] = rank_key_score(key);
+          R.key[(size_t)q * R.Ts + tok] = rank_key_score(key);
+          if (R.rank8) R.rank8[(size_t)q * R.Ts + tok] = (uint8_t)e;
           atomicAdd(&cnt[q * E + e], 1);
         }
       }
@@ -188,7 +190,8 @@ __device__ inline void rank_row_shared(const float *row, int tok, int sub, int E
       const int e = rank_key_expert(key);  // -1 past the number of experts
       if (q <= k) ranks[(size_t)tok * (k + 1) + q] = (q < n) ? e : -1;
       if (FUSE && q < R.NR) {
-        R.key[(size_t)tok * R.NR + q] = rank_key_score(key);
+        R.key[(size_t)q * R.Ts + tok] = rank_key_score(key);
+        if (R.rank8) R.rank8[(size_t)q * R.Ts + tok] = (uint8_t)e;
         atomicAdd(&cnt[q * E + e], 1);
       }
     }
@@ -238,7 +241,8 @@ __device__ inline void rank_tile(const float *tile, int TS, int ntok, int t0, in
     if (rank < n) {
       ranks[(size_t)tok * (k + 1) + rank] = e;
       if (FUSE && rank < R.NR) {
-        R.key[(size_t)tok * R.NR + rank] = score_key(v);
+        R.key[(size_t)rank * R.Ts + tok] = score_key(v);
+        if (R.rank8) R.rank8[(size_t)rank * R.Ts + tok] = (uint8_t)e;
         atomicAdd(&cnt[rank * E + e], 1);
       }
     }
@@ -920,8 +924,8 @@ hipError_t launch_router(const Dims &D, const void *x, const float *w_router, co
   prof_begin(K_ROUTER, s);
   RankOut R{};
   if (tb && W)  // D.NBc is then the count-block grid of this router (see router_count_blocks)
-    R = RankOut{tb->rank_expert, tb->slot, W->key, W->ir_score, W->ir_cand, W->blk_cnt,
-                D.k, D.NR, D.fr, D.Eg, D.Tg, D.NCAT, D.NBc};
+    R = RankOut{tb->rank_expert, tb->slot, W->key, W->rank8, W->ir_score, W->ir_cand, W->blk_cnt,
+                D.k, D.NR, D.fr, D.Eg, D.Tg, D.NCAT, D.NBc, D.Ts};
   if (small) {
     const RankOut *Rp = tb && W ? &R : nullptr;
     if (D.dtype == RR_BF16) launch_small<true>(D, x, w_router, bias, logits, probs, rank_expert, Rp, s);

@@ -824,3 +824,27 @@ def test_forward_cut_row_tiles(T, d, F, E, parts):
     left = int((-(-rows // 256)).sum()) * -(-F // 128) % 256
     assert min(256 // left, 8) == parts
     _forward_case(w, (), inputs)
+
+
+# Lists that their workgroup finds by itself, up to 16384 tokens: every number of tokens per thread (4, 8, 12, 16) with a
+# last quadruple that is whole or ragged, the most rounds, and the first size past the limit.  The keys that the digit
+# select meets: spread over the whole range of their type, all equal, and equal but for the last bits.
+DIRECT_LISTS = [
+    # T, E, k, cf, arrival, scores
+    (1025, 2, 1, 0.5, False, "wide"), (4096, 6, 2, 0.75, False, "normal"), (4099, 8, 4, 0.6, True, "ties"),
+    (8190, 8, 4, 0.5, False, "close"), (12289, 16, 2, 0.5, False, "wide"), (16384, 4, 2, 0.5, False, "normal"),
+    (16383, 5, 3, 0.4, False, "equal"), (16385, 8, 2, 0.5, False, "close"), (5, 64, 2, 7000.0, False, "normal"),
+]
+
+
+@pytest.mark.parametrize("T,E,k,cf,arrival,scores", DIRECT_LISTS)
+def test_dispatch_lists_found_by_their_workgroup(T, E, k, cf, arrival, scores):
+    a = wl.synthetic_logits(T, E, seed=T + E, ties=scores == "ties")
+    if scores == "wide":
+        a = (np.sign(a) * np.exp2(4 * np.abs(a) - 12)).astype(np.float32)
+    if scores == "equal":
+        a[:] = -0.25
+    if scores == "close":
+        a = (1.0 + np.float32(2.0 ** -20) * np.round(a)).astype(np.float32)
+    cfg = rr.RRConfig(T, 64, 0, E, k, 1, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), arrival))
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), arrival, False))
