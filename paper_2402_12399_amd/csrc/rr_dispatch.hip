@@ -1314,19 +1314,38 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
   if constexpr (SRC != ROUTE_RANKED) {
     // (all loads of an element, or of several, in flight together: one CU's latency is what this kernel consists of)
     if constexpr (SRC == ROUTE_PARTS) {
-      for (int idx = tid; idx < T * E; idx += OR_THREADS) {  // the partial sums in order, then the bias
-        float p[kMaxParts];
+      // The partial sums in order, then the bias; `elements` scores at a time, of up to `parts` parts each, about 32
+      // loads in flight.  (One score at a time: 5.2 us of an 18 us kernel at 300 tokens x 16 experts; kernel 20.3 ->
+      // 18.9 between events, 256 x 8 one part 15.8 -> 15.1 and the layer 28.5 -> 27.6.)
+      auto sum_parts = [&](auto parts, auto elements) {
+        constexpr int PN = decltype(parts)::value, EN = decltype(elements)::value;
+        for (int i0 = tid; i0 < T * E; i0 += EN * OR_THREADS) {
+          float p[EN][PN], b[EN];
 #pragma unroll
-        for (int q = 0; q < kMaxParts; ++q) p[q] = part[(size_t)(q < kparts ? q : 0) * T * E + idx];
-        const int row = idx / E, e = idx - row * E;
-        const float b = bias ? bias[e] : 0.0f;
-        float v = p[0];
+          for (int u = 0; u < EN; ++u) {
+            const int idx = min(i0 + u * OR_THREADS, T * E - 1);
+            b[u] = bias ? bias[idx % E] : 0.0f;
 #pragma unroll
-        for (int q = 1; q < kMaxParts; ++q) v += q < kparts ? p[q] : 0.0f;
-        v += b;
-        logits[idx] = v;
-        tile[row * (E + 1) + e] = v;
-      }
+            for (int q = 0; q < PN; ++q) p[u][q] = part[(size_t)(q < kparts ? q : 0) * T * E + idx];
+          }
+#pragma unroll
+          for (int u = 0; u < EN; ++u) {
+            const int idx = i0 + u * OR_THREADS, row = idx / E, e = idx - row * E;
+            float v = p[u][0];
+#pragma unroll
+            for (int q = 1; q < PN; ++q) v += q < kparts ? p[u][q] : 0.0f;
+            v += b[u];
+            if (idx < T * E) {
+              logits[idx] = v;
+              tile[row * (E + 1) + e] = v;
+            }
+          }
+        }
+      };
+      using std::integral_constant;
+      if (kparts == 1) sum_parts(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+      else if (kparts <= 8) sum_parts(integral_constant<int, 8>{}, integral_constant<int, 4>{});
+      else sum_parts(integral_constant<int, kMaxParts>{}, integral_constant<int, 2>{});
     } else {
       constexpr int AHEAD = 8;
       for (int i0 = tid; i0 < T * E; i0 += AHEAD * OR_THREADS) {
