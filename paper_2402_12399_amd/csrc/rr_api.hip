@@ -244,6 +244,14 @@ int rr_workspace_bytes(const rr_config *cfg, size_t *bytes) {
   return RR_OK;
 }
 
+// Host function for tests: which tiles the grouped GEMMs of this layer use (see FfnShapes).
+int rr_ffn_shapes(const rr_config *cfg, FfnShapes *out) {
+  Dims D;
+  const int rc = make_dims(cfg, true, &D);
+  if (rc == RR_OK) ffn_describe(D, out);
+  return rc;
+}
+
 int rr_router_scores(const rr_config *cfg, const void *x, const float *w_router, const float *bias, float *logits,
                      float *probs, int32_t *rank_expert, void *stream) {
   Dims D;

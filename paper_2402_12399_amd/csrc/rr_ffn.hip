@@ -854,6 +854,7 @@ constexpr float kAct256 = 4.0f, kAct128 = 3.0f;
 long long expected_row_tiles(const Dims &D, int bm) {
   // dispatched rows: the top-k assignments (a dropped token's re-routed row stands for its dropped ones)
   const long long want = (long long)D.T * D.k, R = want < D.Rmax ? want : D.Rmax, used = R < D.E ? R : D.E;
+  if (used == 1) return (R + bm - 1) / bm;  // all rows are one expert's
   // a popular expert: its capacity and three times an even share of re-routed tokens; one expert in eight is one
   const long long popular = std::min((long long)D.T, D.C + (D.ir ? 3ll * D.T / D.E : 0)), n_popular = (used + 7) / 8;
   return 4 * R <= 3ll * bm * used ? used + n_popular * ((popular - 1) / bm) : R / bm + used / 2;
@@ -907,7 +908,7 @@ FfnPlan ffn_plan(const Dims &D) {
   }
   for (int u = q0; u <= q1; ++u)
     for (int w = q0; w <= q1; ++w) {
-      if (up[u] < 0.0f || down[w] < 0.0f) continue;
+      if (!(up[u] >= 0.0f) || !(down[w] >= 0.0f)) continue;
       const int bm = std::max(kShape[u].bm, kShape[w].bm);
       const float cost = up[u] + down[w] + empty(u, D.F, D.act == RR_ACT_SWIGLU, bm) + empty(w, D.d, false, bm);
       if (least < 0.0f || cost <= least) { least = cost; best = {(FfnShape)u, (FfnShape)w}; }
@@ -1006,6 +1007,16 @@ hipError_t ffn_kernel_attributes() {
 int ffn_row_tile(const Dims &D) {
   const FfnPlan plan = ffn_plan(D);
   return std::max(kShape[plan.up].bm, kShape[plan.down].bm);
+}
+
+void ffn_describe(const Dims &D, FfnShapes *out) {
+  const FfnPlan plan = ffn_plan(D);
+  const FfnShape q[2] = {plan.up, plan.down};
+  for (int i = 0; i < 2; ++i) {
+    out->bm[i] = kShape[q[i]].bm;
+    out->brows[i] = kShape[q[i]].brows;
+    out->cost[i] = shape_cost(D, i ? D.F : D.d, i ? D.d : D.F, i == 0, q[i]);
+  }
 }
 
 bool ffn_fuses_gather(const Dims &D) { return (long long)D.T * D.d * (D.dtype == RR_BF16 ? 2 : 4) < 0x7ffffff0ll; }

@@ -141,6 +141,10 @@ hipError_t launch_gather(const Dims &D, const void *x, const rr_tables &tb, cons
 hipError_t router_kernel_attributes();  // raises the dynamic-LDS limit of the streaming router on the current device
 hipError_t ffn_kernel_attributes();     // raises the dynamic-LDS limit of the bf16 GEMM kernels on the current device
 int ffn_row_tile(const Dims &D);          // row-tile height of the layer's GEMMs (Dims::BM)
+// The tiles that the layer's up [0] and down [1] projection are computed in, and their estimated time in us: for tests
+// (rr_ffn_shapes, exported by the library but no part of its C ABI).
+struct FfnShapes { int32_t bm[2], brows[2]; float cost[2]; };
+void ffn_describe(const Dims &D, FfnShapes *out);
 bool ffn_fuses_gather(const Dims &D);     // the up projection reads x through the dispatch tables: no gather pass
 hipError_t launch_ffn(const Dims &D, const void *x, const rr_tables &tb, const void *w1, const void *w3,
                       const void *w2, const Work &W, void *out, hipStream_t s);

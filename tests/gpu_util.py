@@ -1,4 +1,6 @@
 """Helpers for the GPU parity tests: host <-> device marshalling and table comparison."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -26,6 +28,17 @@ def config_of(w: wl.Workload, mode=("ir", "fr"), arrival=False, T=None, quota=Fa
     return rr.RRConfig(T or w.T, w.d_model, w.d_ff, w.E, w.k, w.G, w.capacity_factor,
                        rr.RR_F32 if w.dtype == "f32" else rr.RR_BF16,
                        rr.RR_ACT_GELU if w.act == "gelu" else rr.RR_ACT_SWIGLU, flags_of(mode, arrival, quota))
+
+
+class _FfnShapes(C.Structure):
+    _fields_ = [("bm", C.c_int32 * 2), ("brows", C.c_int32 * 2), ("cost", C.c_float * 2)]
+
+
+def ffn_shapes(cfg: rr.RRConfig) -> _FfnShapes:
+    """The tiles of the layer's up [0] and down [1] projection and their estimated times (host-only query)."""
+    out, cc = _FfnShapes(), cfg.c()
+    assert rr.load_library().rr_ffn_shapes(C.byref(cc), C.byref(out)) == 0
+    return out
 
 
 def to_device(a, dtype):

@@ -10,6 +10,7 @@ import pytest
 import paper_2402_12399_amd as rr
 from oracle import rectify_router as orc
 from paper_2402_12399_amd import binding
+from tests import gpu_util as gu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 RR_OK, INVALID, UNSUPPORTED, WORKSPACE = 0, -1, -2, -3
@@ -117,6 +118,19 @@ def test_workspace_size_properties(lib):
     cc = _cfg().c()
     assert lib.rr_workspace_bytes(C.byref(cc), None) == INVALID
     assert lib.rr_workspace_bytes(None, C.byref(C.c_size_t(0))) == INVALID
+
+
+@pytest.mark.parametrize("dtype,sizes", [(rr.RR_BF16, (24, 60, 97, 120, 192, 193, 220, 255, 256, 300)),
+                                         (rr.RR_F32, (24, 30, 40, 49, 56, 63, 64, 100))])
+def test_one_expert_layers_get_the_least_estimated_tiles(lib, dtype, sizes):
+    """With one expert the number of row tiles is known; just under a tile's height it is one, not none."""
+    costs = []
+    for T in sizes:
+        s = gu.ffn_shapes(_cfg(T=T, E=1, k=1, G=1, d_model=2048, d_ff=5632, dtype=dtype, flags=0))
+        assert all(np.isfinite(c) and c > 0 for c in s.cost), (T, list(s.cost))
+        assert all(bm < 2 * max(T, 32) for bm in s.bm), (T, list(s.bm))  # no tile of which most rows are padding
+        costs.append(sum(s.cost))
+    assert all(a <= b * 1.001 for a, b in zip(costs, costs[1:])), costs  # more tokens never look cheaper
 
 
 def test_entry_points_reject_bad_arguments_on_the_host(lib):

@@ -760,6 +760,15 @@ def test_forward_tile_shapes(case):
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
 
 
+# One expert: all tokens are its rows (no (k+1)-th choice, so no Fill-in), at sizes just under and over a tile's height.
+@pytest.mark.parametrize("T,d,F,dtype,act", [(220, 256, 392, "bf16", "swiglu"), (257, 264, 384, "bf16", "gelu"),
+                                             (56, 96, 200, "f32", "swiglu"), (65, 72, 264, "f32", "gelu")])
+def test_forward_one_expert(T, d, F, dtype, act):
+    for cf in (1.0, 0.4):  # everybody kept; most re-routed to the same expert
+        w = wl.Workload("one expert", T, d, F, 1, 1, 1, cf, dtype, act, "none", 60 + T)
+        _forward_case(w, ("ir",), wl.make_inputs(w))
+
+
 # Batches whose tables one workgroup builds, and their borders: one token, a wave and one more or less, the most tokens
 # (and one more), lists of one candidate and of all tokens, ranks shared by 1, 2, 4 and 8 lanes, every source of the ranking
 # (logits; the router's partial scores or its own ranking in the forward call).
