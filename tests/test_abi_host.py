@@ -133,6 +133,19 @@ def test_one_expert_layers_get_the_least_estimated_tiles(lib, dtype, sizes):
     assert all(a <= b * 1.001 for a, b in zip(costs, costs[1:])), costs  # more tokens never look cheaper
 
 
+@pytest.mark.parametrize("T,d,F,E,G,k,quota,cf,whole", [
+    (1024, 3904, 11840, 32, 8, 1, True, 1.25, True),    # weights bound it, 30 to 60 rows per expert
+    (896, 2112, 6016, 24, 8, 2, False, 0.5, True),
+    (1424, 1792, 5632, 64, 8, 1, False, 1.5, False),    # 22 rows per expert: a short tile holds them
+    (1024, 256, 768, 32, 8, 1, True, 1.25, False),      # the weights stay in the last-level cache
+    (16, 4096, 11008, 8, 2, 2, False, 1.25, False),
+])
+def test_weight_bound_layers_get_one_tile_per_expert(lib, T, d, F, E, G, k, quota, cf, whole):
+    flags = gu.flags_of(("ir", "fr"), False, quota)
+    s = gu.ffn_shapes(_cfg(T=T, d_model=d, d_ff=F, E=E, k=k, G=G, capacity_factor=cf, flags=flags))
+    assert ((s.bm[0], s.brows[0], s.bm[1], s.brows[1]) == (256, 256, 256, 256)) == whole
+
+
 def test_entry_points_reject_bad_arguments_on_the_host(lib):
     """Nothing here reaches a kernel launch: every call fails validation first."""
     cfg = _cfg()
