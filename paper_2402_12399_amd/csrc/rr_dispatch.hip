@@ -328,13 +328,16 @@ __device__ inline u32 wave_min(u32 v) {
 // l % kHistCopies (consecutive words, different banks), and the copies are added up before the bins are scanned.
 // passes: at most that many digits; the result is then a lower bound of the m-th largest key, off by less than
 // one step of the last digit taken (need_eq is meaningless then).
-template <class Each>
+// COMMON false: the digits start at the highest bit.  Where `each` reads memory (lists past the registers) finding the
+// common prefix is a pass of its own and saves none as a rule: 400 K tokens, 8 experts, top-2, lists of up to 190 K
+// candidates, select_slot_kernel 464 us without it, 504 with it.
+template <bool COMMON, class Each>
 __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq, int passes = 4) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   u32 *copies = hist + 256;  // [256][kHistCopies]
-  u32 prefix, remaining = (u32)m;
-  int left;  // bits below the prefix
-  {
+  u32 prefix = 0, remaining = (u32)m;
+  int left = 32;  // bits below the prefix
+  if constexpr (COMMON) {
     u32 lo = 0xffffffffu, nhi = 0xffffffffu;  // smallest key, smallest complement
     each([&](u32 kx, bool valid) {
       if (valid) {
@@ -446,7 +449,7 @@ __device__ inline void select_in_registers(const DispatchArgs &A, int n, int m, 
   }
   u32 thr = 0, need_eq = 0;
   if (by_score)
-    thr = radix_select(m, [&](auto f) {
+    thr = radix_select<true>(m, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < SS_PER; ++u)
         if (u < nu) f(kreg[u], u * SS_THREADS + tid < n);
@@ -513,7 +516,7 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, boo
   const unsigned long long below = (1ull << lane) - 1ull;
   u32 thr = 0, need_eq = 0;
   if (by_score)
-    thr = radix_select(m, [&](auto f) {
+    thr = radix_select<false>(m, [&](auto f) {
       for (int base = 0; base < n; base += SS_THREADS) {
         const int idx = base + tid;
         f(idx < n ? keys[idx] : 0u, idx < n);
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     u32 dummy;
     // two digits are enough: L only has to lie below the list's m-th highest key, and the keys of one step of the
     // second (2^-16 of the sample's range) are a handful of candidates more
-    L = radix_select(qsel, [&](auto f) {
+    L = radix_select<false>(qsel, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kSegPer; ++u) f(sk[u], true);
     }, S.hist, S.pick, dummy, 2);
@@ -946,7 +949,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
   const int mode = m == 0 ? 0 : (m == n ? 1 : (by_score ? 3 : 2));
   u32 thr = 0, need_eq = 0;
   if (mode == 3)
-    thr = radix_select(m, [&](auto f) {
+    thr = radix_select<true>(m, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kDirectPer; ++u)
         if (u < per) f(kreg[u], (member >> u) & 1u);
