@@ -838,18 +838,22 @@ void launch_split(const Dims &D, const void *x, const float *w_router, const flo
   } while (0)
   if (D.E <= 16) RR_LAUNCH_SPLIT(0);
   else if (D.E <= 32) RR_LAUNCH_SPLIT(1);
-  else RR_LAUNCH_SPLIT(2);
+  else if constexpr (BF16 || NW < 16) RR_LAUNCH_SPLIT(2);
 #undef RR_LAUNCH_SPLIT
 }
 
 // Waves that split K: as many as leave each of them two macro-steps, and as a full chip holds (16 waves per CU).
-// 4096 tokens x 4096 bf16, 8 experts: 4 waves 28 us, 16 waves 20; 8192 x 2048, 16 experts: 18, 16.
+// 4096 tokens x 4096 bf16, 8 experts: 4 waves 28 us, 16 waves 20; 8192 x 2048, 16 experts: 18, 16.  With more workgroups
+// than CUs and more than 16 experts, 4: two workgroups with their larger partial tiles and operand registers otherwise do not
+// share a CU (13140 x 2752 bf16, 42 experts: 8 waves 65 us, 4 waves 52).  fp32 with two column
+// fragments stops at 8 (4192 x 2560, 48 experts: 16 waves 37 us, 8 waves 33).
 template <bool BF16>
 void launch_small(const Dims &D, const void *x, const float *w_router, const float *bias, float *logits, float *probs,
                   int32_t *rank_expert, const RankOut *R, hipStream_t s) {
   const int steps = (D.d + (BF16 ? 63 : 31)) / (BF16 ? 64 : 32);
-  if (steps >= 32 && D.T <= 8192) launch_split<BF16, 16>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
-  else if (steps >= 16) launch_split<BF16, 8>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
+  const bool all_resident = D.T <= 256 * RS_TB;
+  if (steps >= 32 && all_resident && (BF16 || D.E <= 32)) launch_split<BF16, 16>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
+  else if (steps >= 16 && (all_resident || D.E <= 16)) launch_split<BF16, 8>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
   else launch_split<BF16, 4>(D, x, w_router, bias, logits, probs, rank_expert, R, 1, s);
 }
 
@@ -892,8 +896,10 @@ hipError_t router_kernel_attributes() {
     constexpr int NW = decltype(nw)::value, NJ = decltype(nj)::value;
     set(router_kernel<true, NW, NJ, true>, rs_smem(NW, NJ));
     set(router_kernel<true, NW, NJ, false>, rs_smem(NW, NJ));
-    set(router_kernel<false, NW, NJ, true>, rs_smem(NW, NJ));
-    set(router_kernel<false, NW, NJ, false>, rs_smem(NW, NJ));
+    if constexpr (NW < 16 || NJ < 2) {
+      set(router_kernel<false, NW, NJ, true>, rs_smem(NW, NJ));
+      set(router_kernel<false, NW, NJ, false>, rs_smem(NW, NJ));
+    }
   };
   split(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
   split(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});

@@ -169,6 +169,14 @@ def test_router_scores(dtype, T, d, E, k):
         assert clear.mean() > 0.99
 
 
+# The K-split router's numbers of waves: 16, 8 and 4, on both sides of one workgroup per CU (8192 tokens), for every
+# number of column fragments; rows that are no multiple of a macro-step.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,d,E,k", [(8192, 2056, 33, 2), (8193, 2056, 33, 2), (8193, 1032, 17, 1), (8193, 1032, 5, 1), (300, 1032, 64, 3)])
+def test_router_scores_waves(dtype, T, d, E, k):
+    test_router_scores(dtype, T, d, E, k)
+
+
 # ------------------------------------------------------------------ whole layer
 def _forward_case(w, mode, inputs, sample=None, arrival=False, quota=False):
     cfg = gu.config_of(w, mode, arrival, T=inputs["x"].shape[0], quota=quota)
