@@ -21,7 +21,9 @@
 // Plans that are a few dozen numbers (array bases, kept counts, row layout) are recomputed by every
 // workgroup that needs them instead of being a launch of their own: a dependent launch costs about
 // 6 us on this part, more than any of these kernels needs for a small batch.
-// Batches of up to 1024 tokens skip all of it: one workgroup builds every table (route_small_kernel).
+// Small batches (one_is_cheaper: up to 1024 tokens, fewer with more experts and rounds) skip all of it: one workgroup
+// builds every table (route_small_kernel), from the router's scores or ranks, or from logits - where those are more than
+// kOneTile, topk_rank ranks them first.
 // Every table is a deterministic function of the logits: integer atomics are only used for counts.
 #include <algorithm>
 #include <type_traits>
@@ -1233,7 +1235,7 @@ __global__ __launch_bounds__(kTokBlock) void ir_weights_kernel(DispatchArgs A, c
 }
 
 // ------------------------------------------------------------------ small batches: all tables in one workgroup
-// Up to kOneT tokens (and kOneEntries candidates) one workgroup of 1024 threads builds every table: a batch of
+// Up to kOneT tokens (one_is_cheaper) one workgroup of 1024 threads builds every table: a batch of
 // a few hundred tokens is three or four dependent launches of 4 - 14 us otherwise, most of it latency.  Thread
 // tid owns tokens u * 1024 + tid, so (u, wave) is token order.  Steps, a barrier between any two:
 //   ranking (SRC: by the router already; or from logits; or from partial scores, which are summed here)
@@ -1671,20 +1673,26 @@ static DispatchArgs dispatch_args(const Dims &D) {
           select_direct(D) ? 1 : 0, D.Ts};
 }
 
-// One CU's throughput sets the limits: at 1024 tokens and 64 experts one workgroup takes as long as the launches it
-// replaces (tables from logits, us, before -> now: 256 x 8, k 1: 22 -> 12; 512 x 16, k 2: 24 -> 17; 1024 x 16, k 4:
-// 27 -> 27; 256 x 64, k 2: 30 -> 20).
-bool route_in_one(const Dims &D) {
-  return D.T <= kOneT && (long long)D.E * D.C <= kOneSlots;
+// One workgroup or the chain of launches?  One CU works through the lists (a wave each) and the candidates; the chain pays
+// for its launches, one more with Intra-GPU lists and three more with several capacity blocks.  `saved`: us that one
+// workgroup saves apart from those.  The costs are a fit to 1200 batches of 8 to 1024 tokens, 1 to 64 experts, k 1 to 4,
+// tables from logits and from ranks: with a line that the sizes of the LDS arrays alone set, 235 of them were up to 1.5 times
+// as fast the other way; with this one the choice is 0.6 % off the better way on average.  Us, one workgroup / chain:
+// 256 x 8, k 1: 12 / 22; 512 x 16, k 2: 17 / 24; 944 x 16, k 4: 30 / 22; 760 x 64, k 3, no Intra-GPU lists: 32 / 27; 1024 x 16, k 4: 47 / 32.
+static bool one_is_cheaper(const Dims &D, float saved) {
+  if (D.T > kOneT || (long long)D.E * D.C > kOneSlots) return false;
+  return (float)D.NL * 0.013f + (float)(D.T * D.NR) * 0.003f <= saved + (D.ir ? 2.9f : 0.0f) + (D.Gq > 1 ? 8.5f : 0.0f);
 }
+bool route_in_one(const Dims &D) { return one_is_cheaper(D, 6.0f); }
 
 // The forward call's router splits K over workgroups (of four waves) while they leave most CUs idle and the partial
 // scores, which one workgroup reads, stay small: 16 tokens x 4096, 8 experts, router + tables 34 us with the router
 // that ranks (one workgroup) and three table kernels, 26 us with it and one, 15 us with K split; 300 tokens x 2048,
 // 16 experts 46, 31, 27 us.  Short rows gain less from the split, so that it ends at half as many scores for them.
+// The split saves some 4 us more than the tables' launches do by themselves.
 int router_parts(const Dims &D) {
   const int tiles = (D.T + 31) / 32, steps = (D.d + (D.dtype == RR_BF16 ? 63 : 31)) / (D.dtype == RR_BF16 ? 64 : 32);
-  if (!route_in_one(D) || D.T * D.E > (steps >= 32 ? 8192 : 4096)) return 0;
+  if (D.T > kOneT || D.T * D.E > (steps >= 32 ? 8192 : 4096) || !one_is_cheaper(D, 10.0f)) return 0;
   return std::max(1, std::min({kMaxParts, 256 / tiles, steps / 4, 65536 / (D.T * D.E)}));
 }
 

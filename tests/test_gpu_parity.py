@@ -819,6 +819,42 @@ def test_small_batch_tables(T, E, G, k, cf, quota):
         gu.assert_tables_equal(tables.to_host(), _oracle_tables(a, cfg, ("ir", "fr"), False, quota))
 
 
+# The line between one workgroup for all tables and the chain of launches: a batch on either side of it, for the terms it
+# is made of (lists, candidates, Intra-GPU lists, capacity blocks), from logits, from the router's ranks and from its partial scores.
+ONE_OR_CHAIN = [
+    # T, E, G, k, mode, quota, d (0: from logits), one workgroup
+    (430, 16, 1, 4, (), False, 0, True), (431, 16, 1, 4, (), False, 0, False),
+    (919, 16, 1, 2, ("ir", "fr"), False, 0, True), (920, 16, 1, 2, ("ir", "fr"), False, 0, False),
+    (1024, 32, 2, 2, ("ir", "fr"), True, 0, True), (1024, 64, 8, 4, ("ir", "fr"), True, 0, False),
+    (919, 16, 1, 2, ("ir", "fr"), False, 1024, True), (920, 16, 1, 2, ("ir", "fr"), False, 1024, False),
+    (128, 64, 1, 4, (), False, 2048, True), (400, 5, 1, 4, ("fr",), False, 64, True), (1000, 8, 1, 4, ("ir", "fr"), False, 2048, False),
+]
+
+
+@pytest.mark.parametrize("T,E,G,k,mode,quota,d,one", ONE_OR_CHAIN)
+def test_tables_in_one_workgroup_or_by_launches(T, E, G, k, mode, quota, d, one):
+    cfg = rr.RRConfig(T, d or 64, 0, E, k, G, 0.75, rr.RR_BF16, rr.RR_ACT_SWIGLU, gu.flags_of(mode, False, quota))
+    tables, ws = rr.alloc_tables(cfg), rr.alloc_workspace(cfg)
+    rr.rr_profile_enable(True)
+    try:
+        if d:
+            rng = np.random.default_rng(T + d)
+            x = (rng.integers(-8, 9, (T, d)) / 8.0).astype(np.float32)  # dyadic: the scores are exact in any order
+            wr = (rng.integers(-8, 9, (E, d)) / 16.0).astype(np.float32)
+            logits = torch.empty((T, E), device="cuda")
+            rr.rr_moe_forward(cfg, torch.from_numpy(x).cuda().bfloat16(), torch.from_numpy(wr).cuda(), None, None, None,
+                              None, None, tables, logits, ws)
+            a = (x.astype(np.float64) @ wr.astype(np.float64).T).astype(np.float32)
+            assert np.array_equal(logits.cpu().numpy(), a)
+        else:
+            a = wl.synthetic_logits(T, E, seed=T, bias_std=1.0, ties=True)
+            rr.rr_rectified_dispatch(cfg, torch.from_numpy(a).cuda(), tables, ws)
+        assert (rr.rr_profile_read()["route_small"][0] == 1) == one
+    finally:
+        rr.rr_profile_enable(False)
+    gu.assert_tables_equal(tables.to_host(), _oracle_tables(a, cfg, mode, False, quota))
+
+
 # The 256 x 256 kernel's last round: its tiles are cut by rows into as many parts as leave no CU idle.  First choices
 # only, capacity T / E: the experts' rows, and so the cut of the up projection, follow from the tables.
 CUT_TILES = [
