@@ -768,6 +768,52 @@ def test_forward_tile_shapes(case):
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
 
 
+def _activation_of(g, act, d, F):
+    """bf16 layer output act(g) for fp32 arguments g: one expert, g as the sum of its three bf16 parts (exact in fp32, so
+    the pre-activation is g itself), an up projection of 1, and a down projection that passes one inner unit on."""
+    g = torch.from_numpy(g)
+    hi = g.bfloat16()
+    lo = (g - hi.float()).bfloat16()
+    x = torch.zeros(len(g), d, dtype=torch.bfloat16)
+    x[:, 0], x[:, 1], x[:, 2] = hi, lo, (g - hi.float() - lo.float()).bfloat16()
+    x[g.isinf(), :3] = 3e38  # finite tokens, an infinite sum (the other inner units have weights 0)
+    x[:, 3] = 1
+    w1 = torch.zeros(1, F, d, dtype=torch.bfloat16)
+    w1[0, 0, :3] = 1
+    w3 = torch.zeros_like(w1)
+    w3[0, 0, 3] = 1
+    w2 = torch.zeros(1, d, F, dtype=torch.bfloat16)
+    w2[0, 0, 0] = 1
+    cfg = rr.RRConfig(len(g), d, F, 1, 1, 1, 1.0, rr.RR_BF16, act, 0)
+    out = torch.empty(len(g), d, dtype=torch.bfloat16, device="cuda")
+    rr.rr_moe_forward(cfg, x.cuda(), torch.zeros(1, d, device="cuda"), None, w1.cuda(),
+                      w3.cuda() if act == rr.RR_ACT_SWIGLU else None, w2.cuda(), out, None, None, rr.alloc_workspace(cfg))
+    torch.cuda.synchronize()
+    return out[:, 0].float().cpu()
+
+
+# Small tiles and the 256 x 256 kernel.  An fp32 value with relative error r (rms) rounds to the wrong bf16 neighbour with
+# probability 2 r sqrt(2 / pi) / 2^-7.5 or so: for r = 4e-8 - half an ulp of the last operation and the erf's - 12 of 2^20
+# arguments; twice that is allowed.  (Where 1 + erf cancels, g < -3, the error of g Phi(g) is absolute: not counted.)
+@pytest.mark.parametrize("d,F", [(8, 8), (256, 256)])
+@pytest.mark.parametrize("sigma", [0.3, 1.0])
+def test_gelu_rounds_like_the_exact_function(d, F, sigma):
+    g = (np.random.default_rng(3).standard_normal(1 << 20) * sigma).astype(np.float32)
+    phi = 0.5 * torch.erfc(torch.from_numpy(g).double() * -(0.5 ** 0.5))
+    want = (torch.from_numpy(g).double() * phi).bfloat16().float()
+    wrong = (_activation_of(g, rr.RR_ACT_GELU, d, F) != want) & torch.from_numpy(g > -3)
+    assert int(wrong.sum()) <= (24 if sigma < 1 else 36), int(wrong.sum())  # (negative arguments past -1 carry the cancellation)
+
+
+@pytest.mark.parametrize("d,F", [(8, 8), (256, 256)])
+def test_gelu_of_large_and_infinite_arguments(d, F):
+    g = torch.tensor([1e30, 3e38, 100.0, 13.0] * 40).bfloat16().float().numpy()
+    assert torch.equal(_activation_of(g, rr.RR_ACT_GELU, d, F), torch.from_numpy(g).bfloat16().float())
+    g[3::7] = np.inf
+    got = _activation_of(g, rr.RR_ACT_GELU, d, F)
+    assert torch.equal(got[3::7], torch.full_like(got[3::7], float("inf")))  # not NaN
+
+
 # One expert: all tokens are its rows (no (k+1)-th choice, so no Fill-in), at sizes just under and over a tile's height.
 @pytest.mark.parametrize("T,d,F,dtype,act", [(220, 256, 392, "bf16", "swiglu"), (257, 264, 384, "bf16", "gelu"),
                                              (56, 96, 200, "f32", "swiglu"), (65, 72, 264, "f32", "gelu")])
