@@ -72,7 +72,9 @@ __device__ __forceinline__ void sched_step() {
   }
 }
 
-// for results that are rounded to bf16 right away: hardware reciprocal (1 ulp) instead of a division
+__device__ inline float silu(float g) { return g / (1.0f + __expf(-g)); }
+// for results that are rounded to bf16 right away, in the 256 x 256 kernel's whole-chunk layers: hardware reciprocal (1 ulp;
+// 0 for arguments below -87.4, where the result is below 2e-36) instead of a division
 __device__ inline float silu_fast(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -136,7 +138,7 @@ __device__ inline void store_tile_t(f32x4 (&acc)[WM][WN], uint16_t *Cb, int rbas
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         c[u] = acc[i][j][u];
-        if (GATED) c[u] = silu_fast(c[u]) * acc[i][j + NJ][u];
+        if (GATED) c[u] = (ACT == RR_ACT_SWIGLU ? silu(c[u]) : silu_fast(c[u])) * acc[i][j + NJ][u];
         if (ACT == RR_ACT_GELU) c[u] = gelu_erf(c[u]);
       }
       if (cols_in || wcol0 + j * 16 + 4 * fg < N) {
@@ -764,7 +766,7 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         c[u] = acc[i][j][u];
-        if (GATED) c[u] = (S::BF16 ? silu_fast(c[u]) : c[u] / (1.0f + expf(-c[u]))) * acc[i][j + NJ][u];
+        if (GATED) c[u] = (S::BF16 ? silu(c[u]) : c[u] / (1.0f + expf(-c[u]))) * acc[i][j + NJ][u];
         if (ACT == RR_ACT_GELU) c[u] = gelu_erf(c[u]);
       }
       if (col < N) {  // N % 8 == 0: a group of four columns is inside or outside as a whole
@@ -964,7 +966,10 @@ void launch_gemm(FfnShape shape, const Dims &D, GemmArgs g, bool fuse, hipStream
       g.NT = gated ? (g.N + 127) / 128 : (g.N + 255) / 256;
       const int cus = cu_count();
       if constexpr (UP) {
-        if (gated && fuse) gemm_bf16_persistent_kernel<true, -1, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        const bool ragged = g.K % GB_BK != 0;  // (ACT RR_ACT_SWIGLU: with the division)
+        if (gated && fuse && ragged) gemm_bf16_persistent_kernel<true, RR_ACT_SWIGLU, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        else if (gated && ragged) gemm_bf16_persistent_kernel<true, RR_ACT_SWIGLU, false><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
+        else if (gated && fuse) gemm_bf16_persistent_kernel<true, -1, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
         else if (gated) gemm_bf16_persistent_kernel<true, -1, false><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
         else if (fuse) gemm_bf16_persistent_kernel<false, RR_ACT_GELU, true><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
         else gemm_bf16_persistent_kernel<false, RR_ACT_GELU, false><<<cus, PK_THREADS, PK_SMEM, s>>>(g);
@@ -993,6 +998,8 @@ hipError_t ffn_kernel_attributes() {
   auto set = [&e](auto kern, int bytes) {
     if (e == hipSuccess) e = set_lds(kern, bytes);
   };
+  set(gemm_bf16_persistent_kernel<true, RR_ACT_SWIGLU, true>, PK_SMEM);
+  set(gemm_bf16_persistent_kernel<true, RR_ACT_SWIGLU, false>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<true, -1, true>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<true, -1, false>, PK_SMEM);
   set(gemm_bf16_persistent_kernel<false, RR_ACT_GELU, true>, PK_SMEM);

@@ -805,6 +805,16 @@ def test_gelu_rounds_like_the_exact_function(d, F, sigma):
     assert int(wrong.sum()) <= (24 if sigma < 1 else 36), int(wrong.sum())  # (negative arguments past -1 carry the cancellation)
 
 
+# SwiGLU divides in small tiles and where K is ragged: its tail stays down to the smallest normal numbers, where a
+# reciprocal of 1 + exp(-g) is flushed to zero (g < -87.4).  __expf(-g): the exponent's rounding, 88 * 2^-24 relative.
+@pytest.mark.parametrize("T,d,F", [(256, 8, 8), (256, 72, 64), (65536, 264, 256)])  # the last: 256 x 256 tiles
+def test_swiglu_tail_of_ragged_layers(T, d, F):
+    g = np.linspace(-88.0, -80.0, T).astype(np.float32)
+    want = (torch.from_numpy(g).double() * torch.special.expit(torch.from_numpy(g).double()))
+    got = _activation_of(g, rr.RR_ACT_SWIGLU, d, F).double()
+    assert (got / want - 1).abs().max() <= 2.0 ** -8  # bf16 rounding
+
+
 @pytest.mark.parametrize("d,F", [(8, 8), (256, 256)])
 def test_gelu_of_large_and_infinite_arguments(d, F):
     g = torch.tensor([1e30, 3e38, 100.0, 13.0] * 40).bfloat16().float().numpy()
