@@ -611,7 +611,8 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
   // tiles, column tiles inside a panel, row tiles inside a column: neighbours share weights
   // (the table's row tiles are P.sub times as high as this kernel's)
   const int MT = P.ctl[0] * P.sub, NT = P.NT, total = MT * NT;
-  const int per = (total + 7) >> 3, run = blockIdx.x >> 3, t = (blockIdx.x & 7) * per + run;
+  const unsigned g = blockIdx.y * gridDim.x + blockIdx.x;  // rows of whole XCD runs (tile_grid)
+  const int per = (total + 7) >> 3, run = (int)(g >> 3), t = (int)(g & 7) * per + run;
   if (run >= per || t >= total) return;
   const int panel = t / (kPanel * NT), r = t - panel * kPanel * NT, h = min(kPanel, MT - panel * kPanel);
   const int nt = r / h, mt = panel * kPanel + r - nt * h;
@@ -940,14 +941,24 @@ void for_each_tile_kernel(F f) {
   shape(Tag<TileB32n>{});
 }
 
-// One GEMM (UP or down) with tiles of shape S; grid: the most tiles there can be, in whole XCD runs.
+// Grid of the small-tile kernel for `tiles` tiles: a grid dimension holds fewer than 2^32 threads (a layer of 2^20 fp32 tokens,
+// d_ff 32768, in 32 x 64 outputs has 2^24 tiles of 256 threads), so more tiles make rows of whole XCD runs.
+dim3 tile_grid(long long tiles) {
+  constexpr long long kRow = 1ll << 20;
+  return dim3((unsigned)((std::min(tiles, kRow) + 7) / 8 * 8), (unsigned)((tiles + kRow - 1) / kRow));
+}
+int column_tiles(const ShapeInfo &s, int N, bool gated) {
+  const int bn = gated ? s.brows / 2 : s.brows;
+  return (int)(((long long)N + bn - 1) / bn);
+}
+
+// One GEMM (UP or down) with tiles of shape S; grid: the most tiles there can be.
 template <class S, bool UP>
 void launch_tiles(const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
   const bool gated = UP && D.act == RR_ACT_SWIGLU;
-  const int bn = gated ? S::BROWS / 2 : S::BROWS;
-  g.NT = (g.N + bn - 1) / bn;
+  g.NT = column_tiles(ShapeInfo{S::BM, S::BROWS, 0.0f, 0.0f}, g.N, gated);
   g.sub = D.BM / S::BM;
-  const dim3 grid((unsigned)(((long long)g.NT * D.max_mtiles * g.sub + 7) / 8 * 8));
+  const dim3 grid = tile_grid((long long)g.NT * D.max_mtiles * g.sub);
   if constexpr (UP) {
     if (gated && fuse) gemm_tile_kernel<S, true, -1, true, false><<<grid, S::THREADS, S::SMEM, s>>>(g);
     else if (gated) gemm_tile_kernel<S, true, -1, false, false><<<grid, S::THREADS, S::SMEM, s>>>(g);

@@ -768,6 +768,16 @@ def test_forward_tile_shapes(case):
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
 
 
+def test_forward_more_tiles_than_a_grid_row():
+    """2^24 tiles of the up projection: more workgroups than one grid dimension takes (128 GiB of inner activations)."""
+    w = wl.Workload("many tiles", 1 << 20, 320, 32832, 1, 1, 1, 1.0, "f32", "swiglu", "none", 71)
+    shapes = gu.ffn_shapes(gu.config_of(w, ()))
+    assert shapes.bm[0] == 32 and (1 << 15) * (w.d_ff * 2 // shapes.brows[0]) * 256 > 1 << 32
+    torch.cuda.empty_cache()
+    _forward_case(w, (), wl.make_inputs(w), sample=np.random.default_rng(0).choice(w.T, 256, replace=False))
+    torch.cuda.empty_cache()
+
+
 def _activation_of(g, act, d, F):
     """bf16 layer output act(g) for fp32 arguments g: one expert, g as the sum of its three bf16 parts (exact in fp32, so
     the pre-activation is g itself), an up projection of 1, and a down projection that passes one inner unit on."""
