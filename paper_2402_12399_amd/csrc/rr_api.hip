@@ -126,7 +126,6 @@ static int make_dims(const rr_config *c, bool need_ffn, Dims *D) {
     if (rows_max * kmax * 2 >= ((int64_t)1 << 31) || (int64_t)c->d_model * c->d_ff * 2 >= ((int64_t)1 << 31))
       return RR_ERR_UNSUPPORTED;
   }
-  if (need_ffn && (c->d_model >= 1 << 23 || c->d_ff >= 1 << 23)) return RR_ERR_UNSUPPORTED;  // a GEMM tile's rows: 32-bit byte offsets
   D->BM = need_ffn ? ffn_row_tile(*D) : 0;
   D->max_mtiles = need_ffn ? D->Rmax / D->BM + c->E : 0;  // routing-only calls cut no GEMM row tiles
   return RR_OK;

@@ -786,6 +786,105 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
 #endif
 }
 
+// ------------------------------------------------------------------ rows or columns of 2^23 elements and more, bf16 and fp32
+// The kernels above address a tile's rows with 32-bit byte offsets.  Past kLongRow elements this one takes over, with
+// 64-bit addresses: 32 rows x 16 columns (gated: of both matrices) per workgroup, its waves split K, fragments come
+// straight from global memory (a lane's 16 bytes are its operand, as above), the partial tiles are summed through
+// LDS in a fixed order.  Bound by the latency of its loads; such layers are one or two tiles wide in the
+// other dimension, so that splitting K is what fills the chip (6 rows, 2^23 + 8 -> 8 bf16: one tile).
+constexpr int kLongRow = 1 << 23;
+constexpr int LG_NW = 16, LG_THREADS = LG_NW * 64, LG_ROWS = 32, LG_COLS = 16;
+
+template <bool BF16, bool GATED, int ACT, bool GATHER, bool DIRECT>
+__global__ __launch_bounds__(LG_THREADS) void gemm_long_kernel(GemmArgs P) {
+  constexpr int ES = BF16 ? 2 : 4, PE = 16 / ES, KM = 4 * PE, NB = GATED ? 2 : 1;
+  using Frag = typename std::conditional<BF16, bf16x8, f32x4>::type;
+  __shared__ float red[LG_NW][2 * NB * 4][64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 15, q = lane >> 4;
+  const int N = P.N, NT = P.NT;
+  const long long K = P.K, t = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+  if (t >= (long long)P.ctl[0] * NT) return;
+  const TileInfo ti = P.tiles[t / NT];
+  const int n0 = (int)(t % NT) * LG_COLS;
+  const char *a[2], *b[NB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int lr = min(ti.row0 + i * 16 + r, ti.rows - 1);  // rows past the last one repeat it and are not stored
+    long long row = ti.rbase + lr;
+    if (GATHER) row = P.row_token ? P.row_token[row] : (lr < ti.fill ? P.slot_token[(size_t)ti.expert * P.C + lr] : P.ir_token[ti.ir_offset + lr - ti.fill]);
+    a[i] = static_cast<const char *>(P.A) + (size_t)row * K * ES;
+  }
+#pragma unroll
+  for (int m = 0; m < NB; ++m)
+    b[m] = static_cast<const char *>(m ? P.B1 : P.B0) + ((size_t)ti.expert * N + min(n0 + r, N - 1)) * K * ES;
+  f32x4 acc[2][NB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int m = 0; m < NB; ++m) acc[i][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto fetch = [&](long long k, Frag (&fa)[2], Frag (&fb)[NB]) {
+    const bool in = k + q * PE < K;  // K % 8 == 0: a lane's piece is inside or outside as a whole
+    const size_t off = (size_t)(in ? k + q * PE : 0) * ES;
+    const Frag zero = {};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) fa[i] = in ? *reinterpret_cast<const Frag *>(a[i] + off) : zero;
+#pragma unroll
+    for (int m = 0; m < NB; ++m) fb[m] = in ? *reinterpret_cast<const Frag *>(b[m] + off) : zero;
+  };
+  Frag fa[2], fb[NB], na[2], nb[NB];
+  const long long step = (long long)LG_NW * KM;
+  fetch((long long)w * KM, fa, fb);
+  for (long long k = (long long)w * KM; k < K; k += step) {
+    fetch(k + step, na, nb);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int m = 0; m < NB; ++m) {
+        // B fragment first, as in the other kernels: lane owns row (lane & 15), columns 4 * (lane >> 4) .. + 3
+        if constexpr (BF16) {
+          acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[m], fa[i], acc[i][m], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[m][u], fa[i][u], acc[i][m], 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) fa[i] = na[i];
+#pragma unroll
+    for (int m = 0; m < NB; ++m) fb[m] = nb[m];
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int m = 0; m < NB; ++m)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) red[w][(i * NB + m) * 4 + u][lane] = acc[i][m][u];
+  __syncthreads();
+  if (tid >= LG_ROWS * LG_COLS) return;
+  const int i = w >> 2, u = w & 3;  // wave w < 8 finishes element u of row fragment i
+  float c[NB];
+#pragma unroll
+  for (int m = 0; m < NB; ++m) {
+    c[m] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < LG_NW; ++s) c[m] += red[s][(i * NB + m) * 4 + u][lane];
+  }
+  if (GATED) c[0] = (BF16 ? silu(c[0]) : c[0] / (1.0f + expf(-c[0]))) * c[NB - 1];
+  if (ACT == RR_ACT_GELU) c[0] = gelu_erf(c[0]);
+  const int row = ti.row0 + i * 16 + r, col = n0 + 4 * q + u;
+  if (row >= ti.rows || col >= N) return;
+  const int dest = DIRECT ? P.row_dest[ti.rbase + row] : -1;
+  const size_t at = (size_t)(ti.rbase + row) * N + col, to = (size_t)max(dest, 0) * N + col;
+  if constexpr (BF16) {
+    const uint16_t v = (uint16_t)pack_bf16(c[0], 0.0f);
+    static_cast<uint16_t *>(P.Cout)[at] = v;
+    if (DIRECT && dest >= 0) static_cast<uint16_t *>(P.Out)[to] = v;
+  } else {
+    static_cast<float *>(P.Cout)[at] = c[0];
+    if (DIRECT && dest >= 0) static_cast<float *>(P.Out)[to] = c[0];
+  }
+}
+
 template <typename Kern>
 hipError_t set_lds(Kern kern, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -825,11 +924,12 @@ using TileB32n = TileShape<true, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
 // 32 x 128 92, 64 x 128 108 (one expert has more than 64 rows: 272 tiles), 128 x 128 74; fp32, up / down: 64 x 128
 // 213 / 238, 32 x 128 188 / 213, 32 x 64 165 / 168; 16 tokens, 8 experts, down 11008 -> 4096: 32 x 128 141, 32 x 64 133;
 // 8 experts 4096 x 11008, K = 11008: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255.
-enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_F64, FFN_F32, FFN_F32N };
+enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_F64, FFN_F32, FFN_F32N, FFN_LONG };
 struct ShapeInfo { int bm, brows; float cost, fixed; };
 constexpr ShapeInfo kShape[] = {{256, 256, 1.45f, 5.0f}, {256, 128, 1.0f, 3.0f}, {128, 128, 0.62f, 2.0f},
                                 {64, 128, 0.5f, 1.0f},   {32, 128, 0.4f, 1.0f},  {32, 64, 0.3f, 0.3f},
-                                {64, 128, 1.05f, 1.0f},  {32, 128, 0.5f, 0.7f},  {32, 64, 0.26f, 0.5f}};
+                                {64, 128, 1.05f, 1.0f},  {32, 128, 0.5f, 0.7f},  {32, 64, 0.26f, 0.5f},
+                                {LG_ROWS, LG_COLS, 0.0f, 0.0f}};
 constexpr float kCuFetch = 26e3f, kHbm = 5.9e6f;  // bytes per us
 // the 256 x 256 kernel: its start, and a chunk of a tile of which a 1 / n share of the rows is there, n = 1 .. PK_MAX_CUT
 constexpr float kPersistentStart = 6.0f, kCutCost[] = {1.0f, 0.72f, 0.6f, 0.53f, 0.5f, 0.47f, 0.45f, 0.43f};
@@ -855,7 +955,7 @@ float shape_cost(const Dims &D, int K, int N, bool up, int q, bool by_rows = fal
   const ShapeInfo &s = kShape[q];
   if (q == FFN_P256 && !persistent_ok(K)) return -1.0f;
   const int es = bf16 ? 2 : 4, KT = (int)(((long long)K * es + GB_ROW_BYTES - 1) / GB_ROW_BYTES);
-  // a tile's rows are addressed with 32-bit byte offsets (rr_config bounds rows so that the narrowest shape always fits)
+  // a tile's rows are addressed with 32-bit byte offsets (below kLongRow elements the narrowest shape always fits)
   if ((long long)K * std::max(s.bm, s.brows) * es >= 1ll << 31) return -1.0f;
   const float used = (float)std::min<long long>({(long long)D.T * D.k, D.Rmax, D.E});
   const float stream = used * N * K * es * (gated ? 2 : 1) / kHbm;
@@ -881,6 +981,7 @@ struct FfnPlan { FfnShape up, down; };
 // lower shape cuts every row tile of the table (GemmArgs::sub) and launches a workgroup for the cuts that turn out
 // to be empty too, about 30 ns each (300 tokens, up 2048 -> 5632: 32-row tiles in a table of 128 rows 269 us, 140 alone).
 FfnPlan ffn_plan(const Dims &D) {
+  if (std::max(D.d, D.F) >= kLongRow) return {FFN_LONG, FFN_LONG};
   constexpr float kEmpty = 0.031f;
   const int q0 = D.dtype == RR_BF16 ? FFN_P256 : FFN_F64, q1 = D.dtype == RR_BF16 ? FFN_32N : FFN_F32N;
   auto empty = [&](int q, int N, bool gated, int bm) {
@@ -969,6 +1070,21 @@ void launch_tiles(const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
   }
 }
 
+template <bool BF16, bool UP>
+void launch_long(const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
+  g.NT = (int)(((long long)g.N + LG_COLS - 1) / LG_COLS);
+  const dim3 grid = tile_grid((long long)g.NT * D.max_mtiles);
+  if constexpr (UP) {
+    const bool gated = D.act == RR_ACT_SWIGLU;
+    if (gated && fuse) gemm_long_kernel<BF16, true, -1, true, false><<<grid, LG_THREADS, 0, s>>>(g);
+    else if (gated) gemm_long_kernel<BF16, true, -1, false, false><<<grid, LG_THREADS, 0, s>>>(g);
+    else if (fuse) gemm_long_kernel<BF16, false, RR_ACT_GELU, true, false><<<grid, LG_THREADS, 0, s>>>(g);
+    else gemm_long_kernel<BF16, false, RR_ACT_GELU, false, false><<<grid, LG_THREADS, 0, s>>>(g);
+  } else {
+    gemm_long_kernel<BF16, false, -1, false, true><<<grid, LG_THREADS, 0, s>>>(g);
+  }
+}
+
 template <bool UP>
 void launch_gemm(FfnShape shape, const Dims &D, GemmArgs g, bool fuse, hipStream_t s) {
   switch (shape) {
@@ -997,6 +1113,10 @@ void launch_gemm(FfnShape shape, const Dims &D, GemmArgs g, bool fuse, hipStream
     case FFN_F64: launch_tiles<TileF64, UP>(D, g, fuse, s); break;
     case FFN_F32: launch_tiles<TileF32, UP>(D, g, fuse, s); break;
     case FFN_F32N: launch_tiles<TileF32n, UP>(D, g, fuse, s); break;
+    case FFN_LONG:
+      if (D.dtype == RR_BF16) launch_long<true, UP>(D, g, fuse, s);
+      else launch_long<false, UP>(D, g, fuse, s);
+      break;
   }
 }
 

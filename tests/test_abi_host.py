@@ -101,6 +101,9 @@ def _ws_status(lib, cfg):
     # bf16 FFN: one expert's rows (up to C + T) or one weight matrix past 32-bit byte offsets
     (dict(T=1 << 20, d_model=1024, d_ff=4096, E=64, G=8), UNSUPPORTED), (dict(d_model=32768, d_ff=32768), UNSUPPORTED),
     (dict(T=1 << 17, d_model=1024, d_ff=4096, E=64, G=8), RR_OK),
+    # rows or columns of 2^23 elements and more: fp32 without a limit, bf16 up to the same 32-bit offsets
+    (dict(T=4, d_model=8, d_ff=1 << 24, dtype=rr.RR_F32), RR_OK), (dict(T=4, d_model=1 << 24, d_ff=8, dtype=rr.RR_F32), RR_OK),
+    (dict(T=4, d_model=8, d_ff=1 << 24), RR_OK), (dict(T=4, d_model=16, d_ff=1 << 26), UNSUPPORTED),
     (dict(flags=rr.RR_QUOTA_PER_GROUP | rr.RR_INTRA_GPU | rr.RR_FILL_IN), RR_OK),   # 512 tokens per group
     (dict(flags=rr.RR_QUOTA_PER_GROUP, T=1000), UNSUPPORTED),                      # groups must hold whole token blocks
     (dict(flags=rr.RR_QUOTA_PER_GROUP, T=1024, G=8, E=8), RR_OK),

@@ -178,7 +178,7 @@ def test_router_scores_waves(dtype, T, d, E, k):
 
 
 # ------------------------------------------------------------------ whole layer
-def _forward_case(w, mode, inputs, sample=None, arrival=False, quota=False):
+def _forward_case(w, mode, inputs, sample=None, arrival=False, quota=False, logits_l2=1e-5):
     cfg = gu.config_of(w, mode, arrival, T=inputs["x"].shape[0], quota=quota)
     dev = {n: (torch.from_numpy(inputs[n]).cuda() if n in ("w_router", "bias") and inputs[n] is not None
                else gu.to_device(inputs[n], w.dtype)) for n in ("x", "w_router", "bias", "w1", "w3", "w2")}
@@ -186,7 +186,7 @@ def _forward_case(w, mode, inputs, sample=None, arrival=False, quota=False):
     f32 = lambda n: None if inputs[n] is None else wl.values_f32(inputs[n], w.dtype)
     policy = orc.POLICY_ARRIVAL if arrival else orc.POLICY_SCORE
     a = orc.router_scores(f32("x"), inputs["w_router"], inputs["bias"])
-    assert gu.rel_l2(logits.astype(np.float64), a.astype(np.float64)) <= 1e-5
+    assert gu.rel_l2(logits.astype(np.float64), a.astype(np.float64)) <= logits_l2
     # identical logits: the oracle routes the library's own logits
     want_tables = orc.route(logits, w.k, w.G, w.capacity_factor, "ir" in mode, "fr" in mode, policy, quota)
     gu.assert_tables_equal(tables, want_tables, cw_atol=1e-6)
@@ -776,6 +776,20 @@ def test_forward_more_tiles_than_a_grid_row():
     torch.cuda.empty_cache()
     _forward_case(w, (), wl.make_inputs(w), sample=np.random.default_rng(0).choice(w.T, 256, replace=False))
     torch.cuda.empty_cache()
+
+
+# Rows and columns of 2^23 elements and more (64-bit addresses), both sides of the line, both types and activations, up
+# projections that gather through slots, Intra-GPU lists and per-group rows.  fp32: K sums of 2^23 terms in 16 partial
+# sums, each a chain of 2^17 MFMAs whose roundings add up to sqrt(2^17) * 2^-25 = 1.1e-5 of the sum, for the scores
+# as well; two such sums make an inner unit (3e-5 of the row), and of 5e7 elements the worst is six deviations off.
+@pytest.mark.parametrize("T,d,F,E,G,dtype,act,quota", [
+    (6, 8, (1 << 23) - 8, 1, 1, "bf16", "swiglu", False), (6, 8, 1 << 23, 2, 1, "bf16", "swiglu", False),
+    (40, 8, (1 << 23) + 8, 2, 2, "f32", "gelu", False), (6, (1 << 23) + 40, 8, 2, 1, "f32", "swiglu", False),
+    (6, (1 << 23) + 40, 24, 1, 1, "bf16", "gelu", False), (128, 8, 1 << 23, 1, 1, "f32", "gelu", True)])
+def test_forward_long_rows(monkeypatch, T, d, F, E, G, dtype, act, quota):
+    monkeypatch.setitem(OUT_BOUNDS, "f32", dict(l2=3e-5, row=1e-4, elem_atol=2e-4, elem_rtol=1e-4))
+    w = wl.Workload("long", T, d, F, E, G, 1, 0.5, dtype, act, "none", 80 + T)
+    _forward_case(w, ("ir",), wl.make_inputs(w), quota=quota, sample=np.arange(0, T, 1 + T // 8), logits_l2=3e-5)
 
 
 def _activation_of(g, act, d, F):
