@@ -2,6 +2,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -142,19 +143,23 @@ struct Carver {
   }
 };
 
-static size_t carve(const Dims &D, bool forward, void *ws, Work *W) {
+// What a workspace is for: the tables from logits; a routing-only forward call as well; a layer with its experts.
+enum Use { USE_DISPATCH, USE_ROUTING, USE_LAYER };
+
+// A workspace that is large enough for one batch is large enough for every smaller one of the same layer (up to the batch size
+// from which the router counts per 128 tokens instead of 32): whatever a size rule gives small batches only is laid over
+// arrays that it does not use, or reserved for all.
+static size_t carve(const Dims &D, Use use, void *ws, Work *W) {
   Carver cv{static_cast<char *>(ws), 0};
   size_t T = D.T, NR = D.NR, E = D.E;
   W->key = cv.take<u32>((size_t)D.Ts * NR);
-  W->rank8 = select_direct(D) ? cv.take<uint8_t>((size_t)D.Ts * NR) : nullptr;
   W->ir_score = cv.take<float>(T);
   W->ir_cand = cv.take<int32_t>(T);
   W->blk_cnt = cv.take<int32_t>((size_t)D.NCAT * D.NB * router_count_blocks(D));
   W->cat_cnt = cv.take<int32_t>(D.NCAT);
-  W->grp_fill = cv.take<int32_t>(E * D.Gq);
-  W->grp_off = cv.take<int32_t>(E * D.Gq);
-  W->row_token = D.quota ? cv.take<int32_t>(D.Rmax) : nullptr;
   W->cand_key = cv.take<u32>(T * NR);
+  // (the candidates of select_direct are not materialised; 16 tokens' ranks fit the smallest array, 256 bytes)
+  W->rank8 = select_direct(D) ? reinterpret_cast<uint8_t *>(W->cand_key) : nullptr;
   W->cand_tok = cv.take<int32_t>(T * NR);
   const bool splits = select_splits(D.T, D.NR, D.NL);
   W->comp_key = splits ? cv.take<u32>(T * NR) : nullptr;
@@ -163,11 +168,16 @@ static size_t carve(const Dims &D, bool forward, void *ws, Work *W) {
   W->list_done = splits ? cv.take<int32_t>(D.NL) : nullptr;
   W->ir_blk_cnt = cv.take<int32_t>(E * D.NB);
   W->ir_cnt = cv.take<int32_t>(E);
+  // where the router splits K, the workgroup that sums its parts builds the tables without any of the arrays so far
+  W->part = static_cast<float *>(ws);
+  if (use != USE_DISPATCH) cv.off = std::max(cv.off, router_parts_reserve(D) * sizeof(float));
+  W->grp_fill = cv.take<int32_t>(E * D.Gq);
+  W->grp_off = cv.take<int32_t>(E * D.Gq);
+  W->row_token = D.quota ? cv.take<int32_t>(D.Rmax) : nullptr;
   W->row_base = cv.take<int32_t>(E + 1);
-  W->tiles = cv.take<TileInfo>(D.max_mtiles + 1);
+  W->tiles = cv.take<TileInfo>(use == USE_LAYER ? (size_t)D.Rmax / kMinRowTile + E + 1 : 1);
   W->tile_ctl = cv.take<int32_t>(4);
-  W->part = cv.take<float>(T * E * router_parts(D));
-  if (forward) {
+  if (use == USE_LAYER) {
     size_t K1 = D.k + 1, es = D.dtype == RR_BF16 ? 2 : 4;
     W->logits = cv.take<float>(T * E);
     W->tables.rank_expert = cv.take<int32_t>(T * K1);
@@ -181,7 +191,7 @@ static size_t carve(const Dims &D, bool forward, void *ws, Work *W) {
     W->tables.ir_token = cv.take<int32_t>(T);
     W->tables.combine_w = cv.take<float>(T * (D.k + 2));
     W->row_dest = cv.take<int32_t>(D.Rmax);
-    W->x_disp = cv.take<char>((size_t)D.Rmax * D.d * es);
+    W->x_disp = cv.take<char>(ffn_fuses_gather(D) ? 0 : (size_t)D.Rmax * D.d * es);
     W->h = cv.take<char>((size_t)D.Rmax * D.F * es);
     W->y = cv.take<char>((size_t)D.Rmax * D.d * es);
   }
@@ -204,12 +214,12 @@ static bool tables_complete(const rr_tables *t) {
          t->ir_row && t->ir_offset && t->ir_token && t->combine_w;
 }
 
-static int check_ws(const Dims &D, bool forward, void *ws, size_t ws_bytes, Work *W) {
+static int check_ws(const Dims &D, Use use, void *ws, size_t ws_bytes, Work *W) {
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255)) return RR_ERR_WORKSPACE;
   Work probe;
-  size_t need = carve(D, forward, nullptr, &probe);
+  size_t need = carve(D, use, nullptr, &probe);
   if (ws_bytes < need) return RR_ERR_WORKSPACE;
-  carve(D, forward, ws, W);
+  carve(D, use, ws, W);
   return RR_OK;
 }
 
@@ -239,7 +249,7 @@ int rr_workspace_bytes(const rr_config *cfg, size_t *bytes) {
   int rc = make_dims(cfg, cfg && cfg->d_ff > 0, &D);
   if (rc != RR_OK) return rc;
   Work W;
-  *bytes = carve(D, D.F > 0, nullptr, &W);
+  *bytes = carve(D, D.F > 0 ? USE_LAYER : USE_ROUTING, nullptr, &W);
   return RR_OK;
 }
 
@@ -275,12 +285,12 @@ int rr_rectified_dispatch_static(const rr_config *cfg, const float *logits, cons
   if (!logits || !tables_complete(out)) return RR_ERR_INVALID_ARG;
   if (!aligned16(logits) || !tables_aligned(out)) return RR_ERR_INVALID_ARG;
   Work probe;
-  if (carve(D, false, nullptr, &probe) > (size_t)RR_STATIC_WORKSPACE_BYTES) return RR_ERR_TOO_LARGE;
+  if (carve(D, USE_DISPATCH, nullptr, &probe) > (size_t)RR_STATIC_WORKSPACE_BYTES) return RR_ERR_TOO_LARGE;
   const int dev = device_setup();
   if (dev < 0 || !g_scratch_ptr[dev]) return RR_ERR_HIP;
   Work W;
   memset(&W, 0, sizeof(W));
-  carve(D, false, g_scratch_ptr[dev], &W);
+  carve(D, USE_DISPATCH, g_scratch_ptr[dev], &W);
   hipError_t e = launch_dispatch(D, logits, *out, W, false, nullptr, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? RR_OK : RR_ERR_HIP;
 }
@@ -294,7 +304,7 @@ int rr_rectified_dispatch(const rr_config *cfg, const float *logits, const rr_ta
   if (!aligned16(logits) || !tables_aligned(out)) return RR_ERR_INVALID_ARG;
   Work W;
   memset(&W, 0, sizeof(W));
-  rc = check_ws(D, false, workspace, workspace_bytes, &W);
+  rc = check_ws(D, USE_DISPATCH, workspace, workspace_bytes, &W);
   if (rc != RR_OK) return rc;
   if (device_setup() < 0) return RR_ERR_HIP;
   hipError_t e = launch_dispatch(D, logits, *out, W, false, nullptr, static_cast<hipStream_t>(stream));
@@ -321,7 +331,7 @@ int rr_moe_forward(const rr_config *cfg, const void *x, const float *w_router, c
   if (!routing_only && (!aligned16(w1) || !aligned16(w3) || !aligned16(w2) || !aligned16(out))) return RR_ERR_INVALID_ARG;
   Work W;
   memset(&W, 0, sizeof(W));
-  rc = check_ws(D, !routing_only, workspace, workspace_bytes, &W);
+  rc = check_ws(D, routing_only ? USE_ROUTING : USE_LAYER, workspace, workspace_bytes, &W);
   if (rc != RR_OK) return rc;
   if (device_setup() < 0) return RR_ERR_HIP;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -361,7 +371,7 @@ int rr_router_backward(const rr_config *cfg, const void *dout, const float *logi
   if (!aligned16(dout) || !aligned4(logits) || !aligned4(dcombine_w) || !aligned4(dlogits)) return RR_ERR_INVALID_ARG;
   Work W;
   memset(&W, 0, sizeof(W));
-  rc = check_ws(D, true, workspace, workspace_bytes, &W);
+  rc = check_ws(D, USE_LAYER, workspace, workspace_bytes, &W);
   if (rc != RR_OK) return rc;
   const rr_tables &tb = tables ? *tables : W.tables;
   const float *lg = logits ? logits : W.logits;

@@ -1247,7 +1247,8 @@ __global__ __launch_bounds__(kTokBlock) void ir_weights_kernel(DispatchArgs A, c
 enum { ROUTE_RANKED = 0, ROUTE_LOGITS = 1, ROUTE_PARTS = 2 };
 constexpr int OR_THREADS = 1024, OR_WAVES = OR_THREADS / kWave;
 constexpr int kOneT = OR_THREADS, kOneSlots = 32768, kOneTile = 16384;  // kOneTile: T * E with the ranking done here
-constexpr int kMaxParts = 16;  // parts of the router's K
+constexpr int kMaxParts = 16;            // parts of the router's K
+constexpr int kMaxPartFloats = 65536;    // partial scores in all
 
 struct OneLayout {  // dynamic LDS: the score tile, later the candidate arrays; slots; counts
   int tops, ctok, slot, wcnt, wir, plan, plan_topk, total;
@@ -1693,8 +1694,9 @@ bool route_in_one(const Dims &D) { return one_is_cheaper(D, 6.0f); }
 int router_parts(const Dims &D) {
   const int tiles = (D.T + 31) / 32, steps = (D.d + (D.dtype == RR_BF16 ? 63 : 31)) / (D.dtype == RR_BF16 ? 64 : 32);
   if (D.T > kOneT || D.T * D.E > (steps >= 32 ? 8192 : 4096) || !one_is_cheaper(D, 10.0f)) return 0;
-  return std::max(1, std::min({kMaxParts, 256 / tiles, steps / 4, 65536 / (D.T * D.E)}));
+  return std::max(1, std::min({kMaxParts, 256 / tiles, steps / 4, kMaxPartFloats / (D.T * D.E)}));
 }
+size_t router_parts_reserve(const Dims &D) { return std::min((size_t)kMaxPartFloats, (size_t)D.T * D.E * kMaxParts); }
 
 static void launch_row_token(const Dims &D, const DispatchArgs &A, const rr_tables &tb, const Work &W, hipStream_t s) {
   if (D.quota && D.max_mtiles > 0)  // the forward pass addresses dispatched rows through row_token

@@ -913,6 +913,8 @@ using TileB64 = TileShape<true, 2, 2, 2, 4, 3, 2>;      // bf16, 64 x 128
 using TileB32 = TileShape<true, 1, 2, 2, 4, 4, 2>;      // bf16, 32 x 128
 using TileB32n = TileShape<true, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
 
+static_assert(TileB32::BM == kMinRowTile && TileB32n::BM == kMinRowTile && TileF32::BM == kMinRowTile && TileF32n::BM == kMinRowTile && LG_ROWS == kMinRowTile);
+
 // Which tiles a GEMM uses: the shape with the least estimated time.  A CU works through ceil(tiles / CUs) tiles of
 // (K chunks x time of a chunk + prologue and epilogue); a chunk takes the longer of
 //   cost     its MFMAs and LDS traffic, us per chunk with the CU full, and

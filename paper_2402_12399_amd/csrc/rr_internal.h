@@ -14,6 +14,7 @@ constexpr int kMaxK = 4;
 constexpr int kMaxRounds = kMaxK + 1;   // k top-k rounds + the Fill-in round
 constexpr int kTokBlock = 128;          // tokens per workgroup in the per-token routing kernels
 constexpr int kWave = 64;
+constexpr int kMinRowTile = 32;         // lowest row tile of the grouped GEMM
 // Selection lists (rr_dispatch.hip): up to kSelectRegMax candidates are one workgroup's registers;
 // longer lists are cut into segments of kSelectSegLen candidates, one workgroup each, when the batch
 // can hold such a list at all and the lists are few enough for the segment map (kept in LDS).
@@ -62,7 +63,7 @@ inline bool select_direct(const Dims &D) { return D.Gq == 1 && D.T <= kDirectMax
 struct Work {
   // routing
   u32     *key;          // [NR, Ts]  order-preserving key of the score of the r-th choice
-  uint8_t *rank8;        // [NR, Ts]  its expert (select_direct only, else NULL)
+  uint8_t *rank8;        // [NR, Ts]  its expert (select_direct only, in cand_key's place; else NULL)
   float   *ir_score;     // [T]       score of the best expert of the token's own group
   int32_t *ir_cand;      // [T]       that expert
   int32_t *blk_cnt;      // [NCAT, NBc] candidates per (list, count block); scanned in place
@@ -83,7 +84,7 @@ struct Work {
   int32_t *tile_ctl;     // [4] [0] = number of row tiles
   // forward only
   float   *logits;       // [T,E] when the caller passes none
-  float   *part;         // [parts,T,E] partial scores of a small batch (router_parts)
+  float   *part;         // [parts,T,E] partial scores of a small batch (router_parts), in place of the routing arrays up to ir_cnt
   rr_tables tables;      // storage when the caller passes none
   int32_t *row_dest;     // [Rmax] token whose ONLY processed row this is (its output row is written by the down projection), else -1
   void    *x_disp;       // [Rmax, d]
@@ -128,6 +129,7 @@ hipError_t launch_router(const Dims &D, const void *x, const float *w_router, co
 // forward call's router then splits K into (0: it ranks the tokens itself).
 bool route_in_one(const Dims &D);
 int router_parts(const Dims &D);
+size_t router_parts_reserve(const Dims &D);  // at least the floats of the parts of this batch and of every smaller one
 hipError_t launch_router_parts(const Dims &D, const void *x, const float *w_router, float *part, int kparts, hipStream_t s);
 // logits: source of the ranking; or, with kparts > 0, destination of the scores: part[kparts][T][E] summed, plus bias.
 // ranked: the router has ranked the tokens (neither is read).

@@ -149,6 +149,24 @@ def test_weight_bound_layers_get_one_tile_per_expert(lib, T, d, F, E, G, k, quot
     assert ((s.bm[0], s.brows[0], s.bm[1], s.brows[1]) == (256, 256, 256, 256)) == whole
 
 
+def test_a_workspace_fits_every_smaller_batch(lib):
+    """A program that sizes its workspace at its largest batch may call with smaller ones (up to 16384 tokens: the router's
+    candidate counts are four times as many there as above)."""
+    rng = np.random.default_rng(8)
+    for _ in range(400):
+        E = int(rng.choice([1, 2, 6, 8, 16, 32, 64]))
+        k = int(rng.integers(1, min(E, 4) + 1))
+        flags = int(rng.integers(0, 8)) & (7 if E > k else ~rr.RR_FILL_IN)
+        c = dict(E=E, k=k, G=1, flags=flags, d_model=8 * int(2 ** rng.uniform(0, 9)), dtype=int(rng.integers(0, 2)),
+                 d_ff=0 if rng.integers(0, 2) else 8 * int(2 ** rng.uniform(0, 9)), capacity_factor=float(rng.choice([0.3, 1.0, 1.25, 40.0])))
+        top = int(2 ** rng.uniform(3, 14))
+        sizes = sorted({max(1, int(top * f)) for f in rng.uniform(0, 1, 24)} | {top})
+        got = [_ws_status(lib, _cfg(T=T, **c)) for T in sizes]
+        assert all(rc == RR_OK for rc, _ in got)
+        need = [n for _, n in got]
+        assert need == sorted(need), (c, list(zip(sizes, need)))
+
+
 def test_entry_points_reject_bad_arguments_on_the_host(lib):
     """Nothing here reaches a kernel launch: every call fails validation first."""
     cfg = _cfg()
