@@ -228,7 +228,7 @@ def run_forward(rr, wl, torch, w, mode, steps, warmup, quota=False, dev=None, ba
                "frac": round(bwd_gbs / PEAK_HBM_GBS, 4), "bytes_per_launch": bwd_bytes}
     ffn_ms = kernels.get("ffn_gate_up", 0) + kernels.get("ffn_down", 0)
     routing_names = ("router_scores", "topk_rank", "scan_candidates", "scatter_candidates",
-                     "select_slot", "ir_count", "ir_scan", "ir_weights")
+                     "select_slot", "ir_count", "ir_scan", "ir_weights", "route_small")
     routing_ms = sum(kernels.get(n, 0.0) for n in routing_names)
     return {
         "dev": dev, "capacity": C, "ms_per_step": ms_per_step, "tokens_per_s": T / (ms_per_step * 1e-3),

@@ -30,7 +30,7 @@
 //   * While a tile's epilogue stores drain, the first K chunk of the workgroup's next tile is
 //     already in flight (its tile id and table entries were fetched during the K loop).
 // Layers with few rows or short rows, and all fp32 layers: gemm_tile_kernel, smaller tiles of several shapes
-// (pick_shape chooses per GEMM).
+// (ffn_plan chooses the pair).
 #include <algorithm>
 #include <type_traits>
 
@@ -581,8 +581,8 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 //   * bf16: v_mfma_f32_16x16x32_bf16.  fp32: v_mfma_f32_16x16x4_f32, fp32 products and accumulation; a
 //     lane's 16-byte piece is its operand of four MFMAs - the K order inside a chunk is then a
 //     permutation, the same for both operands.
-// Measured, before (register-staged bf16 kernel, fp32 FMA kernel) -> now: 6161 rows, 1000 x 2728, bf16 GELU: up 169 -> 58 us,
-// down 120 -> 66; 3931 rows, 1024 x 2816, fp32 SwiGLU: up 612 -> 354 us (128 TFLOP/s; the fp32 MFMA pipe sustains 154),
+// Measured, before (register-staged bf16 kernel, fp32 FMA kernel) -> now: 6161 rows, 1000 x 2728, bf16 GELU, down 118 -> 47 us
+// (the up projection runs on 256 x 256 tiles: 163 -> 58); 3931 rows, 1024 x 2816, fp32 SwiGLU: up 612 -> 354 us (128 TFLOP/s; the fp32 MFMA pipe sustains 154),
 // down 397 -> 184.  bf16 tiles of this size are bound by the operand bytes per flop (L2 -> LDS), fp32 ones by the MFMAs.
 // WM x WN: 16-row fragments of a wave.
 template <bool BF16_, int WAVES_M_, int WAVES_N_, int WM_, int WN_, int ST_, int OCC_>
@@ -952,7 +952,7 @@ long long expected_row_tiles(const Dims &D, int bm) {
 // Estimated time of a GEMM with tiles of shape q, us; < 0: not possible.  by_rows: 256 x 256 tiles of which only a share of
 // the rows is there are priced like the parts of a cut tile (their K loop leaves the missing fragments out).
 float shape_cost(const Dims &D, int K, int N, bool up, int q, bool by_rows = false) {
-  constexpr int kCUs = 256;
+  constexpr int kCUs = 256;  // of the part: a host function, which cannot ask a device (the launch does, see cu_count)
   const bool bf16 = D.dtype == RR_BF16, gated = up && D.act == RR_ACT_SWIGLU;
   const ShapeInfo &s = kShape[q];
   if (q == FFN_P256 && !persistent_ok(K)) return -1.0f;

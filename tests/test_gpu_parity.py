@@ -9,6 +9,7 @@ differently (near-ties flipped by rounding) is printed, not asserted; layer outp
 a wrong store mask on a ragged tile cannot hide in the norm.
 """
 import dataclasses
+import re
 
 import numpy as np
 import pytest
@@ -596,9 +597,9 @@ def test_quota_forward_c1_fp32(mode):
 
 QUOTA_SMALL = [w for w in SMALL_BF16 if (w.T // w.G) * w.G == w.T and (w.T // w.G) % 128 == 0]
 QUOTA_SMALL += [
-    # bf16 shape that takes the register-staged GEMM and the separate gather kernel (d % 64 != 0), E not a power of two
+    # bf16 rows that are no whole K chunks, E not a power of two
     wl.Workload("q1", 1024, 136, 264, 6, 2, 1, 0.5, "bf16", "swiglu", "zipf:1.5", 31),
-    # fp32 path (plain FMA GEMM), top-2, three groups
+    # fp32 tiles, top-2, three groups
     wl.Workload("q2", 1152, 72, 200, 6, 3, 2, 1.0, "f32", "swiglu", "normal:1.0", 32),
 ]
 
@@ -765,6 +766,9 @@ TILE_SHAPES = [
 def test_forward_tile_shapes(case):
     name, T, d, F, E, G, k, dtype, act = case
     w = wl.Workload(name, T, d, F, E, G, k, 1.0, dtype, act, "zipf:1.1", 40 + T % 97)
+    shapes = gu.ffn_shapes(gu.config_of(w))
+    for i, (bm, brows) in enumerate(re.findall(r"(\d+)x(\d+)", name)):  # the up projection's tiles, and the down projection's
+        assert (shapes.bm[i], shapes.brows[i]) == (int(bm), int(brows))
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
 
 
@@ -956,7 +960,48 @@ def test_forward_cut_row_tiles(T, d, F, E, parts):
     rows = np.minimum(np.bincount(first, minlength=E), -(-T // E))
     left = int((-(-rows // 256)).sum()) * -(-F // 128) % 256
     assert min(256 // left, 8) == parts
+    shapes = gu.ffn_shapes(gu.config_of(w, ()))
+    assert (shapes.bm[0], shapes.brows[0]) == (256, 256)
     _forward_case(w, (), inputs)
+
+
+# The same with the down projection in 256 x 256 tiles (256 output columns, the second store of single rows), the GELU up
+# projection (256 columns), and rows through the per-group table.
+CUT_DOWN_TILES = [
+    # T, d_model, d_ff, E, G, act, quota, parts of a tile of the up / down projection's last round (1: not cut)
+    (7815, 2288, 888, 3, 1, "swiglu", False, (1, 8)),
+    (4096, 2040, 1512, 8, 2, "swiglu", True, (1, 2)),
+    (4035, 2024, 1872, 8, 1, "gelu", False, (2, 2)),
+    (4096, 1912, 1832, 8, 2, "gelu", True, (2, 2)),
+]
+
+
+@pytest.mark.parametrize("T,d,F,E,G,act,quota,parts", CUT_DOWN_TILES)
+def test_forward_cut_row_tiles_of_the_down_projection(T, d, F, E, G, act, quota, parts):
+    w = wl.Workload("cut down", T, d, F, E, G, 1, 1.0, "bf16", act, "normal:0.5", 40 + T % 97)
+    inputs = wl.make_inputs(w)
+    first = orc.router_scores(wl.values_f32(inputs["x"], "bf16"), inputs["w_router"], inputs["bias"]).argmax(axis=1)
+    groups = first.reshape(G if quota else 1, -1)
+    rows = sum(np.minimum(np.bincount(g, minlength=E), -(-groups.shape[1] // E)) for g in groups)
+    row_tiles = int((-(-rows // 256)).sum())
+    left = [row_tiles * -(-n // cols) % 256 for n, cols in ((F, 128 if act == "swiglu" else 256), (d, 256))]
+    assert tuple(min(256 // n, 8) if n else 1 for n in left) == parts
+    shapes = gu.ffn_shapes(gu.config_of(w, (), quota=quota))
+    assert list(shapes.bm) == [256, 256] and list(shapes.brows) == [256, 256]
+    _forward_case(w, (), inputs, quota=quota, sample=np.sort(np.random.default_rng(1).choice(T, 1024, replace=False)))
+
+
+# x of 2 GiB and more: the dispatch gather is a pass of its own (32-bit buffer offsets), from slots and Intra-GPU lists and,
+# with quotas, from the per-group rows.
+@pytest.mark.parametrize("T,E,F,dtype,mode,quota", [(1 << 19, 4, 64, "f32", ("ir", "fr"), False), (1 << 20, 8, 192, "bf16", ("fr",), True)])
+def test_forward_separate_gather(T, E, F, dtype, mode, quota):
+    w = wl.Workload("gather", T, 1024, F, E, 2, 1, 1.0, dtype, "swiglu", "normal:0.5", 91)
+    rr.rr_profile_enable(True)
+    try:
+        _full_size_case(w, mode, n_sample=256, quota=quota, report_flips=False)
+        assert rr.rr_profile_read()["dispatch_gather"][0] == 1
+    finally:
+        rr.rr_profile_enable(False)
 
 
 # Lists that their workgroup finds by itself, up to 16384 tokens: every number of tokens per thread (4, 8, 12, 16) with a
