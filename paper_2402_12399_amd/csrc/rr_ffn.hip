@@ -791,7 +791,8 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
 // 64-bit addresses: 32 rows x 16 columns (gated: of both matrices) per workgroup, its waves split K, fragments come
 // straight from global memory (a lane's 16 bytes are its operand, as above), the partial tiles are summed through
 // LDS in a fixed order.  Bound by the latency of its loads; such layers are one or two tiles wide in the
-// other dimension, so that splitting K is what fills the chip (6 rows, 2^23 + 8 -> 8 bf16: one tile).
+// other dimension, so that splitting K is what fills the chip: 6 rows, 2 experts, 8 x 2^23 bf16: down 10.5 ms, up 5.5 (256 x 256
+// tiles: 117 and 5.4); the layer of 2^23 x 24 in fp32 84 ms (64 x 64 tiles of FMAs: 1047).
 constexpr int kLongRow = 1 << 23;
 constexpr int LG_NW = 16, LG_THREADS = LG_NW * 64, LG_ROWS = 32, LG_COLS = 16;
 
