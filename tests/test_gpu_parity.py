@@ -833,7 +833,7 @@ def test_gelu_rounds_like_the_exact_function(d, F, sigma):
     assert int(wrong.sum()) <= (24 if sigma < 1 else 36), int(wrong.sum())  # (negative arguments past -1 carry the cancellation)
 
 
-# SwiGLU divides in small tiles and where K is ragged: its tail stays down to the smallest normal numbers, where a
+# SwiGLU divides where K is ragged or shorter than three chunks: its tail stays down to the smallest normal numbers, where a
 # reciprocal of 1 + exp(-g) is flushed to zero (g < -87.4).  __expf(-g): the exponent's rounding, 88 * 2^-24 relative.
 @pytest.mark.parametrize("T,d,F", [(256, 8, 8), (256, 72, 64), (65536, 264, 256)])  # the last: 256 x 256 tiles
 def test_swiglu_tail_of_ragged_layers(T, d, F):
