@@ -1270,6 +1270,12 @@ __host__ __device__ inline OneLayout one_layout(int T, int E, int NR, int Gq, bo
   return L;
 }
 
+// Lanes that rank a token together (a power of two; at least eight experts each).
+__host__ __device__ inline int rank_lanes(int T, int E) {
+  const int threads = T <= 128 ? 8 : (T <= 256 ? 4 : (T <= 512 ? 2 : 1)), share = E >> 3 < threads ? E >> 3 : threads;
+  return share >= 8 ? 8 : (share >= 4 ? 4 : (share >= 2 ? 2 : 1));
+}
+
 template <int SRC>
 __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
     DispatchArgs A, const float *__restrict__ part, int kparts, const float *__restrict__ bias, float *__restrict__ logits,
@@ -1368,8 +1374,7 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
     __syncthreads();
     // Ranking.  With fewer tokens than threads several lanes share a token: each ranks a part of its row (at
     // least eight experts), the lists are merged by shuffles and handed to the token's thread through LDS.
-    const int share = min(E >> 3, T <= 128 ? 8 : (T <= 256 ? 4 : (T <= 512 ? 2 : 1)));
-    const int lpt = share >= 8 ? 8 : (share >= 4 ? 4 : (share >= 2 ? 2 : 1)), per = (E + lpt - 1) / lpt;
+    const int lpt = rank_lanes(T, E), per = (E + lpt - 1) / lpt;
     auto rank = [&](auto tag) {
       constexpr int N = decltype(tag)::value;  // list length: at least k + 1 and NR
       const int n = min(A.k + 1, E);
@@ -1676,21 +1681,29 @@ static DispatchArgs dispatch_args(const Dims &D) {
 
 // One workgroup or the chain of launches?  One CU works through the lists (a wave each) and the candidates; the chain pays
 // for its launches, one more with Intra-GPU lists and three more with several capacity blocks.  `saved`: us that one
-// workgroup saves apart from those.  The costs are a fit to 1200 batches of 8 to 1024 tokens, 1 to 64 experts, k 1 to 4,
-// tables from logits and from ranks: with a line that the sizes of the LDS arrays alone set, 235 of them were up to 1.5 times
-// as fast the other way; with this one the choice is 0.6 % off the better way on average.  Us, one workgroup / chain:
-// 256 x 8, k 1: 12 / 22; 512 x 16, k 2: 17 / 24; 944 x 16, k 4: 30 / 22; 760 x 64, k 3, no Intra-GPU lists: 32 / 27; 1024 x 16, k 4: 47 / 32.
+// workgroup saves apart from those - more from logits that it ranks itself, less what the longest run of one lane's
+// insertions takes.  The costs are a fit to 3100 batches of 8 to 1024 tokens, 1 to 64 experts, k 1 to 4, tables from logits
+// and from ranks: with a line that the sizes of the LDS arrays alone set, one in five of them was up to 1.5 times as fast the
+// other way; with this one the choice is 0.8 % off the better way on average.  Us, one workgroup / chain:
+// 256 x 8, k 1: 12 / 22; 998 x 4, k 2: 22 / 29; 944 x 16, k 4: 30 / 22; 760 x 64, k 3, no Intra-GPU lists: 32 / 27; 1024 x 16, k 4: 47 / 32.
 static bool one_is_cheaper(const Dims &D, float saved) {
   if (D.T > kOneT || (long long)D.E * D.C > kOneSlots) return false;
-  return (float)D.NL * 0.013f + (float)(D.T * D.NR) * 0.003f <= saved + (D.ir ? 2.9f : 0.0f) + (D.Gq > 1 ? 8.5f : 0.0f);
+  return (float)D.NL * 0.01375f + (float)(D.T * D.NR) * 0.00212f <= saved + (D.ir ? 3.16f : 0.0f) + (D.Gq > 1 ? 8.93f : 0.0f);
 }
-bool route_in_one(const Dims &D) { return one_is_cheaper(D, 6.0f); }
+bool route_in_one(const Dims &D, bool ranked) {
+  float saved = 3.66f;
+  if (!ranked && D.T * D.E <= kOneTile) {
+    const int lanes = rank_lanes(D.T, D.E), list = D.k == 1 ? 2 : (D.k == 2 ? 3 : kMaxRank);
+    saved += 2.95f - 0.04f * (float)((D.E + lanes - 1) / lanes * list);
+  }
+  return one_is_cheaper(D, saved);
+}
 
 // The forward call's router splits K over workgroups (of four waves) while they leave most CUs idle and the partial
 // scores, which one workgroup reads, stay small: 16 tokens x 4096, 8 experts, router + tables 34 us with the router
 // that ranks (one workgroup) and three table kernels, 26 us with it and one, 15 us with K split; 300 tokens x 2048,
 // 16 experts 46, 31, 27 us.  Short rows gain less from the split, so that it ends at half as many scores for them.
-// The split saves some 4 us more than the tables' launches do by themselves.
+// With the split one workgroup saves some 6 us more.
 int router_parts(const Dims &D) {
   const int tiles = (D.T + 31) / 32, steps = (D.d + (D.dtype == RR_BF16 ? 63 : 31)) / (D.dtype == RR_BF16 ? 64 : 32);
   if (D.T > kOneT || D.T * D.E > (steps >= 32 ? 8192 : 4096) || !one_is_cheaper(D, 10.0f)) return 0;
@@ -1740,7 +1753,7 @@ hipError_t dispatch_kernel_attributes() {
 hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &tb, const Work &W, bool ranked,
                            int32_t *row_dest, hipStream_t s) {
   const DispatchArgs A = dispatch_args(D);
-  const bool in_one = route_in_one(D);
+  const bool in_one = route_in_one(D, ranked);
   if (in_one && !ranked && D.T * D.E <= kOneTile)
     return launch_route_small(D, nullptr, 0, nullptr, const_cast<float *>(logits), tb, W, false, row_dest, s);
   if (!ranked) {  // otherwise the router's epilogue has already written what topk_rank writes

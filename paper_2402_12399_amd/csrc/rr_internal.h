@@ -127,7 +127,7 @@ hipError_t launch_router(const Dims &D, const void *x, const float *w_router, co
                          hipStream_t s);
 // Batches whose routing tables one workgroup builds (rr_dispatch.hip, route_small_kernel), and the parts that the
 // forward call's router then splits K into (0: it ranks the tokens itself).
-bool route_in_one(const Dims &D);
+bool route_in_one(const Dims &D, bool ranked);  // ranked: by the router already
 int router_parts(const Dims &D);
 size_t router_parts_reserve(const Dims &D);  // at least the floats of the parts of this batch and of every smaller one
 hipError_t launch_router_parts(const Dims &D, const void *x, const float *w_router, float *part, int kparts, hipStream_t s);

@@ -907,11 +907,11 @@ def test_small_batch_tables(T, E, G, k, cf, quota):
 # is made of (lists, candidates, Intra-GPU lists, capacity blocks), from logits, from the router's ranks and from its partial scores.
 ONE_OR_CHAIN = [
     # T, E, G, k, mode, quota, d (0: from logits), one workgroup
-    (430, 16, 1, 4, (), False, 0, True), (431, 16, 1, 4, (), False, 0, False),
-    (919, 16, 1, 2, ("ir", "fr"), False, 0, True), (920, 16, 1, 2, ("ir", "fr"), False, 0, False),
+    (480, 16, 1, 4, (), False, 0, True), (495, 16, 1, 4, (), False, 0, False),
+    (660, 16, 1, 3, ("ir", "fr"), False, 0, True), (680, 16, 1, 3, ("ir", "fr"), False, 0, False),
     (1024, 32, 2, 2, ("ir", "fr"), True, 0, True), (1024, 64, 8, 4, ("ir", "fr"), True, 0, False),
-    (919, 16, 1, 2, ("ir", "fr"), False, 1024, True), (920, 16, 1, 2, ("ir", "fr"), False, 1024, False),
-    (128, 64, 1, 4, (), False, 2048, True), (400, 5, 1, 4, ("fr",), False, 64, True), (1000, 8, 1, 4, ("ir", "fr"), False, 2048, False),
+    (960, 16, 1, 2, ("ir", "fr"), False, 1024, True), (976, 16, 1, 2, ("ir", "fr"), False, 1024, False),
+    (128, 64, 1, 4, (), False, 2048, True), (400, 5, 1, 4, ("fr",), False, 64, True), (1000, 8, 1, 4, ("fr",), False, 2048, False),
 ]
 
 
