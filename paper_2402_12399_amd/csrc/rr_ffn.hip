@@ -570,6 +570,28 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 #endif
 }
 
+// Four fp32 values as sums of three bf16 values, each the nearest of what the ones before it leave (8 mantissa bits and
+// a sign: three of them hold all 24): plane[p] gets part p of the four.  Conversions and subtractions only:
+// v_dot2c_f32_bf16 with (-1, 0) would subtract a packed value from its fp32 one without unpacking it (7 instructions for two
+// values, not 11), but does not run beside MFMAs (22 cycles each, v_sub_f32 8).
+__device__ __forceinline__ void split3(const f32x4 &x, uint2 (&plane)[3]) {
+  u32 w[3][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float a = x[2 * q], b = x[2 * q + 1];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      w[p][q] = pack_bf16(a, b);
+      if (p < 2) {
+        a -= __builtin_bit_cast(float, w[p][q] << 16);
+        b -= __builtin_bit_cast(float, w[p][q] & 0xffff0000u);
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) plane[p] = make_uint2(w[p][0], w[p][1]);
+}
+
 // ------------------------------------------------------------------ small tiles, bf16 and fp32, any K % 8 == 0
 // Everything the 256 x 256 kernel is not made for: fp32 layers, row lengths that are no multiple of the
 // K chunk or shorter than three of them, and batches whose experts get few rows.  One workgroup per tile,
@@ -582,17 +604,29 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 //   * bf16: v_mfma_f32_16x16x32_bf16.  fp32: v_mfma_f32_16x16x4_f32, fp32 products and accumulation; a
 //     lane's 16-byte piece is its operand of four MFMAs - the K order inside a chunk is then a
 //     permutation, the same for both operands.
+//   * fp32 rows of five chunks and more that fill their tiles (TILE_SPLIT): every operand is split into three bf16 parts
+//     that hold its 24 bits, and the six products down to 2^-18 of the leading one run on the bf16 pipe, accumulated in
+//     fp32 (a split of Dekker's kind, as the router's): 96 cycles of MFMAs per pair of fragments and chunk instead of 256.
+//     The parts are made once per workgroup, on the way to LDS (a wave that splits its own fragments does it two to four
+//     times over, and conversions run at half speed beside MFMAs: 285 us instead of 265 for the layer below).  Error
+//     against 64 bits below that of the fp32 MFMAs, which round as often (1024 tokens, 1024 x 2816 SwiGLU 1.09e-6
+//     of the output's norm, 1.29e-6; 4096 x 4096 1.80e-6, 2.09e-6; 64 x 128 GELU 1.8e-7, 2.6e-7).
+//     3931 rows, 1024 x 2816 SwiGLU: up 355 -> 270 us (1.0 PFLOP/s on the bf16 pipe), down 187 -> 190 (1.1 tiles per CU);
+//     7900 rows, 2112 x 4224 GELU: 1077 -> 745, 1075 -> 773.  Bound by the bf16 pipe (57 % of the cycles at 2.03 GHz)
+//     and the splitting beside it.
 // Measured, before (register-staged bf16 kernel, fp32 FMA kernel) -> now: 6161 rows, 1000 x 2728, bf16 GELU, down 118 -> 47 us
 // (the up projection runs on 256 x 256 tiles: 163 -> 58); 3931 rows, 1024 x 2816, fp32 SwiGLU: up 612 -> 354 us (128 TFLOP/s; the fp32 MFMA pipe sustains 154),
 // down 397 -> 184.  bf16 tiles of this size are bound by the operand bytes per flop (L2 -> LDS), fp32 ones by the MFMAs.
 // WM x WN: 16-row fragments of a wave.
-template <bool BF16_, int WAVES_M_, int WAVES_N_, int WM_, int WN_, int ST_, int OCC_>
+enum TileMath { TILE_BF16, TILE_F32, TILE_SPLIT };  // TILE_SPLIT: fp32 operands as three bf16 parts each
+template <TileMath MATH_, int WAVES_M_, int WAVES_N_, int WM_, int WN_, int ST_, int OCC_>
 struct TileShape {
-  static constexpr bool BF16 = BF16_;
+  static constexpr TileMath MATH = MATH_;
+  static constexpr bool BF16 = MATH == TILE_BF16;
   static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, WM = WM_, WN = WN_, ST = ST_, OCC = OCC_;
   static constexpr int NW = WAVES_M * WAVES_N, THREADS = NW * 64;
   static constexpr int BM = WAVES_M * WM * 16, BROWS = WAVES_N * WN * 16;
-  static constexpr int STAGE = (BM + BROWS) * GB_ROW_BYTES, SMEM = ST * STAGE;
+  static constexpr int STAGE = (BM + BROWS) * (MATH == TILE_SPLIT ? 3 * GB_ROW_BYTES / 2 : GB_ROW_BYTES), SMEM = ST * STAGE;
 };
 
 // ACT: RR_ACT_GELU, RR_ACT_SWIGLU (bf16: with the division), or -1
@@ -631,7 +665,7 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
 
   // ---- operands: buffers that start at the tile's first row (GATHER: at x) and end with its last one
   const int lrow = w * 8 + (lane >> 3);            // stage row of this lane in instruction 0
-  const int piece = (lane & 7) ^ swz(lrow);        // 16-byte piece of the row's chunk that belongs at its position
+  const int piece = S::MATH == TILE_SPLIT ? lane & 7 : (lane & 7) ^ swz(lrow);  // 16-byte piece of the row's chunk that belongs at its position
   const unsigned rowb = (unsigned)K * ES;
   const unsigned rstep = NW * 8 * rowb;            // between the rows of consecutive instructions
   auto rsrc = [](const char *base, size_t off, long long range) {
@@ -645,16 +679,19 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
   const __amdgpu_buffer_rsrc_t rsA =
       GATHER ? rsrc(static_cast<const char *>(P.A), 0, P.a_bytes)
              : rsrc(static_cast<const char *>(P.A), (size_t)(rbase + m0) * rowb, (long long)min(BM, rows_e - m0) * rowb);
+  auto load16 = [](const __amdgpu_buffer_rsrc_t &rs, unsigned off, int koff) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, koff, 0));
+  };
+  auto token_of = [&](int lr) {  // row within the expert: capacity slots first, then its Intra-GPU rows
+    const int32_t *src = lr < ti.fill ? P.slot_token + ((size_t)e * P.C + lr) : P.ir_token + (ti.ir_offset + lr - ti.fill);
+    if (P.row_token) src = P.row_token + (rbase + lr);
+    if (lr >= rows_e) src = P.slot_token;  // a valid dummy: the lookups of all instructions are in flight together
+    return *src;
+  };
   unsigned va[GATHER ? NIA : 1];
   if (GATHER) {
 #pragma unroll
-    for (int i = 0; i < NIA; ++i) {
-      const int lr = m0 + i * NW * 8 + lrow;  // row within the expert: capacity slots first, then its Intra-GPU rows
-      const int32_t *src = lr < ti.fill ? P.slot_token + ((size_t)e * P.C + lr) : P.ir_token + (ti.ir_offset + lr - ti.fill);
-      if (P.row_token) src = P.row_token + (rbase + lr);
-      if (lr >= rows_e) src = P.slot_token;  // a valid dummy: the lookups of all instructions are in flight together
-      va[i] = (unsigned)*src;
-    }
+    for (int i = 0; i < NIA; ++i) va[i] = (unsigned)token_of(m0 + i * NW * 8 + lrow);
 #pragma unroll
     for (int i = 0; i < NIA; ++i) va[i] = m0 + i * NW * 8 + lrow < rows_e ? va[i] * rowb + piece * 16 : PAST;
   } else {
@@ -725,8 +762,9 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
     }
   };
 
+  if constexpr (S::MATH != TILE_SPLIT)
 #pragma unroll
-  for (int q = 0; q < ST - 1; ++q) issue(q, q);
+    for (int q = 0; q < ST - 1; ++q) issue(q, q);
   int dest[WM];
 #pragma unroll
   for (int i = 0; i < WM; ++i) {
@@ -734,23 +772,106 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
     if (DIRECT) dest[i] = P.row_dest[rbase + min(m0 + (wm * WM + i) * 16 + fr, rows_e - 1)];
   }
   int cur = 0, fill = ST - 1;
-  for (int kt = 0; kt < KT; ++kt) {
-    // own loads of chunk kt have landed (ST - 2 younger chunks may be on their way), own reads of chunk kt - 1 too
-    dma_barrier<(ST - 2) * NI>();
-    const char *st = smem + cur * S::STAGE;
-    // software pipeline: the fragments of the next k-step are read under the MFMAs of this one
-    load_frags(st, 0);
-    if (kt > 0) mfma_step(1);  // last k-step of chunk kt - 1
-    issue(kt + ST - 1, fill);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(st, 1);
-    mfma_step(0);
-    if constexpr (S::BF16) sched_mfma_lds_read<(WM + WN < WM * WN ? WM + WN : WM * WN)>();
-    __builtin_amdgcn_sched_barrier(0);
-    cur = cur == ST - 1 ? 0 : cur + 1;
-    fill = fill == ST - 1 ? 0 : fill + 1;
+  if constexpr (S::MATH == TILE_SPLIT) {
+    // Chunks go through registers: a lane holds four elements of NI rows, splits them and writes 8 bytes to each of the
+    // three planes in LDS, 64 bytes per row and chunk; the next chunk is requested before this one is multiplied.
+    f32x4 raw[NI];
+    auto fetch = [&](int kt) {
+      const bool past = kt * CE + piece * PE >= K;
+      const int koff = min(kt, KT - 1) * GB_ROW_BYTES;
+#pragma unroll
+      for (int i = 0; i < NIB; ++i) {
+        const unsigned v = vb + (GATED && i >= NIB0 ? i - NIB0 : i) * rstep;
+        raw[NIA + i] = load16(!GATED || i < NIB0 ? rsB0 : rsB1, past ? PAST : v, koff);
+      }
+#pragma unroll
+      for (int i = 0; i < NIA; ++i) {
+        const unsigned v = GATHER ? va[GATHER ? i : 0] : va[0] + i * rstep;
+        raw[i] = load16(rsA, past ? PAST : v, koff);
+      }
+    };
+    // 16-byte piece c of a plane's row sits at c ^ ((row >> 2) & 3): the 16 rows of a fragment then fill all 64 banks
+    constexpr int PLANE = (BM + S::BROWS) * GB_ROW_BYTES / 2;
+    char *const wr = smem + lrow * 64 + (((piece >> 1) ^ ((lrow >> 2) & 3)) << 4) + (piece & 1) * 8;
+    const int fpos = fr * 64 + ((fg ^ (fr >> 2)) << 4);
+    fetch(0);
+    for (int kt = 0; kt < KT; ++kt) {
+      if (kt > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everybody has read chunk kt - 1
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        uint2 q[3];
+        split3(raw[i], q);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(wr + p * PLANE + i * NW * 8 * 64) = q[p];
+      }
+      fetch(kt + 1);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // chunk kt is written
+      bf16x8 b3[WN][3];
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          b3[j][p] = *reinterpret_cast<const bf16x8 *>(smem + p * PLANE + (b_off[j] / GB_ROW_BYTES - fr) * 64 + fpos);
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        bf16x8 a3[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          a3[p] = *reinterpret_cast<const bf16x8 *>(smem + p * PLANE + (wm * WM + i) * 16 * 64 + fpos);
+        // the products of parts down to 2^-18 of the leading one, smallest first
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+          for (int j = 0; j < WN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b3[j][PB[q]], a3[PA[q]], acc[i][j], 0, 0, 0);
+      }
+    }
+    // An infinity, or a value that rounds to one in bf16, leaves NaN behind its first part: a fragment of which any
+    // element is not finite is computed again from fp32 operands.
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      const int arow = (wm * WM + i) * 16 + fr;  // of the tile
+      unsigned ao = arow * rowb;
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        bool finite = true;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) finite = finite && __builtin_isfinite(acc[i][j][u]);
+        if (__all(finite)) continue;
+        if (GATHER) ao = m0 + arow < rows_e ? (unsigned)token_of(m0 + arow) * rowb : PAST;
+        const bool up = GATED && j >= WN / 2;
+        const unsigned bo = (unsigned)(GATED ? (wn * (WN / 2) + j % (WN / 2)) * 16 + fr : (wn * WN + j) * 16 + fr) * rowb;
+        f32x4 c = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = 0; k < K; k += 16) {
+          const unsigned kb = (k + 4 * fg) * ES;
+          const bool past = kb >= rowb;
+          const f32x4 a = load16(rsA, past || ao == PAST ? PAST : ao + kb, 0), b = load16(up ? rsB1 : rsB0, past ? PAST : bo + kb, 0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u], a[u], c, 0, 0, 0);
+        }
+        acc[i][j] = c;
+      }
+    }
+  } else {
+    for (int kt = 0; kt < KT; ++kt) {
+      // own loads of chunk kt have landed (ST - 2 younger chunks may be on their way), own reads of chunk kt - 1 too
+      dma_barrier<(ST - 2) * NI>();
+      const char *st = smem + cur * S::STAGE;
+      // software pipeline: the fragments of the next k-step are read under the MFMAs of this one
+      load_frags(st, 0);
+      if (kt > 0) mfma_step(1);  // last k-step of chunk kt - 1
+      issue(kt + ST - 1, fill);
+      __builtin_amdgcn_sched_barrier(0);
+      load_frags(st, 1);
+      mfma_step(0);
+      if constexpr (S::BF16) sched_mfma_lds_read<(WM + WN < WM * WN ? WM + WN : WM * WN)>();
+      __builtin_amdgcn_sched_barrier(0);
+      cur = cur == ST - 1 ? 0 : cur + 1;
+      fill = fill == ST - 1 ? 0 : fill + 1;
+    }
+    mfma_step(1);
   }
-  mfma_step(1);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // loads past the last chunk still write this LDS
 
   // ---- epilogue
@@ -907,14 +1028,16 @@ int cu_count() {
 bool persistent_ok(int K) { return K % GB_BK == 0 ? K >= 3 * GB_BK : K > 3 * GB_BK; }
 
 //                         BF16   waves  frags ring waves per SIMD
-using TileF64 = TileShape<false, 2, 2, 2, 4, 2, 2>;     // fp32, 64 rows x 128 staged weight rows
-using TileF32 = TileShape<false, 2, 2, 1, 4, 2, 2>;     // fp32, 32 x 128
-using TileF32n = TileShape<false, 2, 2, 1, 2, 3, 2>;    // fp32, 32 x 64
-using TileB256 = TileShape<true, 4, 2, 4, 4, 3, 2>;     // bf16, 256 x 128, 8 waves
-using TileB128 = TileShape<true, 2, 4, 4, 2, 4, 2>;     // bf16, 128 x 128, 8 waves
-using TileB64 = TileShape<true, 2, 2, 2, 4, 3, 2>;      // bf16, 64 x 128
-using TileB32 = TileShape<true, 1, 2, 2, 4, 4, 2>;      // bf16, 32 x 128
-using TileB32n = TileShape<true, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
+using TileS128 = TileShape<TILE_SPLIT, 2, 2, 4, 4, 1, 3>;  // fp32, 128 rows x 128 staged weight rows
+using TileS64 = TileShape<TILE_SPLIT, 2, 2, 2, 4, 1, 4>;   // fp32, 64 x 128
+using TileF64 = TileShape<TILE_F32, 2, 2, 2, 4, 2, 2>;     // fp32, 64 x 128
+using TileF32 = TileShape<TILE_F32, 2, 2, 1, 4, 2, 2>;     // fp32, 32 x 128
+using TileF32n = TileShape<TILE_F32, 2, 2, 1, 2, 3, 2>;    // fp32, 32 x 64
+using TileB256 = TileShape<TILE_BF16, 4, 2, 4, 4, 3, 2>;     // bf16, 256 x 128, 8 waves
+using TileB128 = TileShape<TILE_BF16, 2, 4, 4, 2, 4, 2>;     // bf16, 128 x 128, 8 waves
+using TileB64 = TileShape<TILE_BF16, 2, 2, 2, 4, 3, 2>;      // bf16, 64 x 128
+using TileB32 = TileShape<TILE_BF16, 1, 2, 2, 4, 4, 2>;      // bf16, 32 x 128
+using TileB32n = TileShape<TILE_BF16, 1, 2, 2, 2, 5, 2>;     // bf16, 32 x 64
 
 static_assert(TileB32::BM == kMinRowTile && TileB32n::BM == kMinRowTile && TileF32::BM == kMinRowTile && TileF32n::BM == kMinRowTile && LG_ROWS == kMinRowTile);
 
@@ -929,11 +1052,14 @@ static_assert(TileB32::BM == kMinRowTile && TileB32n::BM == kMinRowTile && TileF
 // 32 x 128 92, 64 x 128 108 (one expert has more than 64 rows: 272 tiles), 128 x 128 74; fp32, up / down: 64 x 128
 // 213 / 238, 32 x 128 188 / 213, 32 x 64 165 / 168; 16 tokens, 8 experts, down 11008 -> 4096: 32 x 128 141, 32 x 64 133;
 // 8 experts 4096 x 11008, K = 11008: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255.
-enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_F64, FFN_F32, FFN_F32N, FFN_LONG };
-struct ShapeInfo { int bm, brows; float cost, fixed; };
+// fp32: the split shapes' numbers are a fit to 260 layers timed in every pair of shapes (1e8 to 5e11 flop): the plan is 1.8 %
+// off the best pair on average, 6.6 % faster than the three fp32 shapes were (up to 1.45 times; three layers 5 - 13 % slower,
+// whose rows per expert the estimate gets wrong).
+enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_S128, FFN_S64, FFN_F64, FFN_F32, FFN_F32N, FFN_LONG };
+struct ShapeInfo { int bm, brows; float cost, fixed, alone; };  // alone: of a chunk, where the CU has one workgroup (0: cost)
 constexpr ShapeInfo kShape[] = {{256, 256, 1.45f, 5.0f}, {256, 128, 1.0f, 3.0f}, {128, 128, 0.62f, 2.0f},
                                 {64, 128, 0.5f, 1.0f},   {32, 128, 0.4f, 1.0f},  {32, 64, 0.3f, 0.3f},
-                                {64, 128, 1.05f, 1.0f},  {32, 128, 0.5f, 0.7f},  {32, 64, 0.26f, 0.5f},
+                                {128, 128, 1.37f, 1.1f, 2.8f}, {64, 128, 0.74f, 1.0f, 2.2f},  {64, 128, 1.05f, 1.0f},  {32, 128, 0.5f, 0.7f},  {32, 64, 0.26f, 0.5f},
                                 {LG_ROWS, LG_COLS, 0.0f, 0.0f}};
 constexpr float kCuFetch = 26e3f, kHbm = 5.9e6f;  // bytes per us
 // the 256 x 256 kernel: its start, and a chunk of a tile of which a 1 / n share of the rows is there, n = 1 .. PK_MAX_CUT
@@ -959,20 +1085,29 @@ float shape_cost(const Dims &D, int K, int N, bool up, int q, bool by_rows = fal
   const bool bf16 = D.dtype == RR_BF16, gated = up && D.act == RR_ACT_SWIGLU;
   const ShapeInfo &s = kShape[q];
   if (q == FFN_P256 && !persistent_ok(K)) return -1.0f;
+  const bool split = q == FFN_S128 || q == FFN_S64;
   const int es = bf16 ? 2 : 4, KT = (int)(((long long)K * es + GB_ROW_BYTES - 1) / GB_ROW_BYTES);
   // a tile's rows are addressed with 32-bit byte offsets (below kLongRow elements the narrowest shape always fits)
   if ((long long)K * std::max(s.bm, s.brows) * es >= 1ll << 31) return -1.0f;
+  // fp32 rows of up to four chunks: fp32 MFMAs (a tile is mostly its start and end); longer ones: split operands or 32 x 64
+  constexpr int kSplitChunks = 5;
+  if (split && KT < kSplitChunks) return -1.0f;
+  if ((q == FFN_F64 || q == FFN_F32) && KT >= kSplitChunks) return -1.0f;
   const float used = (float)std::min<long long>({(long long)D.T * D.k, D.Rmax, D.E});
   const float stream = used * N * K * es * (gated ? 2 : 1) / kHbm;
   const int bn = gated ? s.brows / 2 : s.brows;
   const long long mt = expected_row_tiles(D, s.bm), tiles = mt * ((N + bn - 1) / bn), rounds = tiles / kCUs, left = tiles - rounds * kCUs;
+  if (split && tiles > 1ll << 20) return -1.0f;  // (grids of more than one row: not measured, a pass takes seconds)
   const float fetch = (float)(s.brows * GB_ROW_BYTES) / kCuFetch * used / (float)mt;
   const float filled = std::min(1.0f, (float)std::min<long long>((long long)D.T * D.k, D.Rmax) / (float)(mt * s.bm));
   const float fixed = s.fixed + filled * (up && q == FFN_256 ? kAct256 : (up && q == FFN_128 ? kAct128 : 0.0f));
   auto part_cost = [&](long long n) { return s.cost * kCutCost[std::min<long long>(n, PK_MAX_CUT) - 1]; };
   const float cost = by_rows ? part_cost((long long)(1.0f / filled)) : s.cost, chunk = std::max(cost, fetch);
   float busy = (float)rounds * (KT * chunk + fixed);
-  if (q == FFN_P256) {
+  if (split) {  // three or four workgroups per CU: their number evens out half of the last round
+    const float all = (float)tiles / kCUs;
+    busy = std::max((0.56f * all + 0.44f * ceilf(all)) * (KT * chunk + fixed), KT * s.alone + fixed);
+  } else if (q == FFN_P256) {
     busy += kPersistentStart;
     if (left > 0) busy += KT * std::max(std::min(cost, part_cost(kCUs / left)), fetch) + fixed;
   } else if (left > 0) {  // several workgroups per CU: a round that is nearly empty runs partly under the one before
@@ -988,7 +1123,7 @@ struct FfnPlan { FfnShape up, down; };
 FfnPlan ffn_plan(const Dims &D) {
   if (std::max(D.d, D.F) >= kLongRow) return {FFN_LONG, FFN_LONG};
   constexpr float kEmpty = 0.031f;
-  const int q0 = D.dtype == RR_BF16 ? FFN_P256 : FFN_F64, q1 = D.dtype == RR_BF16 ? FFN_32N : FFN_F32N;
+  const int q0 = D.dtype == RR_BF16 ? FFN_P256 : FFN_S128, q1 = D.dtype == RR_BF16 ? FFN_32N : FFN_F32N;
   auto empty = [&](int q, int N, bool gated, int bm) {
     const ShapeInfo &s = kShape[q];
     const int bn = gated ? s.brows / 2 : s.brows;
@@ -1041,6 +1176,8 @@ void for_each_tile_kernel(F f) {
     f(gemm_tile_kernel<S, false, RR_ACT_GELU, false, false>, S::SMEM);
     f(gemm_tile_kernel<S, false, -1, false, true>, S::SMEM);
   };
+  shape(Tag<TileS128>{});
+  shape(Tag<TileS64>{});
   shape(Tag<TileF64>{});
   shape(Tag<TileF32>{});
   shape(Tag<TileF32n>{});
@@ -1129,6 +1266,8 @@ void launch_gemm(FfnShape shape, const Dims &D, GemmArgs g, bool fuse, hipStream
     case FFN_64: launch_tiles<TileB64, UP>(D, g, fuse, s); break;
     case FFN_32: launch_tiles<TileB32, UP>(D, g, fuse, s); break;
     case FFN_32N: launch_tiles<TileB32n, UP>(D, g, fuse, s); break;
+    case FFN_S128: launch_tiles<TileS128, UP>(D, g, fuse, s); break;
+    case FFN_S64: launch_tiles<TileS64, UP>(D, g, fuse, s); break;
     case FFN_F64: launch_tiles<TileF64, UP>(D, g, fuse, s); break;
     case FFN_F32: launch_tiles<TileF32, UP>(D, g, fuse, s); break;
     case FFN_F32N: launch_tiles<TileF32n, UP>(D, g, fuse, s); break;

@@ -772,6 +772,65 @@ def test_forward_tile_shapes(case):
     _forward_case(w, ("ir", "fr"), wl.make_inputs(w))
 
 
+# fp32 in split tiles: ragged rows, columns and K (a last chunk of one piece; whole chunks), both tiles for both GEMMs, rows
+# through slots, Intra-GPU lists and per-group rows.
+SPLIT_SHAPES = [
+    # tile of the up / down projection, T, d_model, d_ff, E, G, k, act, quota
+    ("64x128 64x128", 4097, 520, 264, 3, 1, 2, "swiglu", False),
+    ("64x128 128x128", 4097, 776, 264, 3, 1, 2, "swiglu", False),
+    ("128x128 64x128", 4097, 520, 1032, 3, 1, 2, "gelu", False),
+    ("128x128 128x128", 4097, 776, 392, 3, 1, 2, "swiglu", False),
+    ("128x128 128x128", 4096, 800, 1032, 4, 4, 2, "gelu", True),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_SHAPES, ids=[f"{c[0]} {c[7]}{' quota' * c[8]}" for c in SPLIT_SHAPES])
+def test_forward_split_tiles(case):
+    name, T, d, F, E, G, k, act, quota = case
+    w = wl.Workload(name, T, d, F, E, G, k, 1.0, "f32", act, "zipf:1.1", 40 + T % 97)
+    shapes = gu.ffn_shapes(gu.config_of(w, quota=quota))
+    assert [f"{m}x{n}" for m, n in zip(shapes.bm, shapes.brows)] == name.split()
+    _forward_case(w, ("ir", "fr"), wl.make_inputs(w), quota=quota, sample=np.arange(0, T, 4))
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_forward_split_tiles_of_values_without_bf16_parts(act):
+    """Weights that a bf16 part cannot hold (rounding to an infinity), infinities and NaN, and denormal ones: what fp32
+    arithmetic makes of them, and nothing else in the layer's output moves."""
+    T, d, F = 4097, 1032, 1032
+    w = wl.Workload("special", T, d, F, 1, 1, 1, 1.0, "f32", act, "none", 92)
+    assert list(gu.ffn_shapes(gu.config_of(w, ())).brows) == [128, 128]
+    inp = wl.make_inputs(w)
+    inp["x"][:, 5] *= np.float32(1e-38)          # times a weight of 3.4e38: an ordinary term
+    inp["w1"][0, 40, 5] = inp["w1"][0, 700, 5] = np.float32(3.4e38)
+    inp["x"][:, 77] *= np.float32(1e30)          # times a denormal weight
+    inp["w1"][0, :, 77] = np.float32(1e-40)
+    inp["w_router"][:, 77] = 0.0
+    clean, clean_ref = _whole_layer(w, inp)
+    assert np.linalg.norm(clean - clean_ref) <= 1e-5 * np.linalg.norm(clean_ref)
+    inp["w2"][0, 300, 9] = np.inf                # output column 300: +-inf by the sign of inner unit 9, column 801: NaN
+    inp["w2"][0, 801, 11] = np.nan
+    got, ref = _whole_layer(w, inp)
+    assert np.isinf(ref[:, 300]).mean() > 0.99   # (a unit that is zero makes NaN of an infinity)
+    assert np.array_equal(np.where(np.isfinite(ref), 0, ref), np.where(np.isfinite(got), 0, got), equal_nan=True)
+    others = np.setdiff1d(np.arange(d), [300, 801])
+    assert np.linalg.norm(got[:, others] - ref[:, others]) <= 1e-5 * np.linalg.norm(ref[:, others])
+    whole = np.array([c for c in others if c // 16 not in (300 // 16, 801 // 16)])  # a fragment is computed again as a whole
+    assert np.array_equal(got[:, whole], clean[:, whole])
+
+
+def _whole_layer(w, inp):
+    """(output of a layer of one expert and room for every token, the same in float64)"""
+    cfg, dev = gu.config_of(w, ()), {n: gu.to_device(v, "f32") for n, v in inp.items()}
+    out = torch.empty((w.T, w.d_model), dtype=torch.float32, device="cuda")
+    rr.rr_moe_forward(cfg, dev["x"], dev["w_router"], dev["bias"], dev["w1"], dev["w3"], dev["w2"], out, None, None,
+                      rr.alloc_workspace(cfg))
+    x, w1, w2 = (torch.from_numpy(v).double() for v in (inp["x"], inp["w1"][0], inp["w2"][0]))
+    g = x @ w1.T
+    h = torch.nn.functional.gelu(g) if w.act == "gelu" else torch.nn.functional.silu(g) * (x @ torch.from_numpy(inp["w3"][0]).double().T)
+    return out.cpu().numpy().astype(np.float64), (h @ w2.T).numpy()
+
+
 def test_forward_more_tiles_than_a_grid_row():
     """2^24 tiles of the up projection: more workgroups than one grid dimension takes (128 GiB of inner activations)."""
     w = wl.Workload("many tiles", 1 << 20, 320, 32832, 1, 1, 1, 1.0, "f32", "swiglu", "none", 71)
