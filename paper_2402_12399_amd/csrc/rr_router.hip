@@ -119,19 +119,16 @@ __device__ inline void rank_row(const float *row, int tok, int half, int E, int 
   int32_t *ranks = FUSE ? R.rank_expert : rank_expert;
   auto rank = [&](auto tag) {
     constexpr int N = decltype(tag)::value;  // list length: at least n
-    unsigned long long b[N], o[N];
+    rank_t b[N], o[N];
     top_keys_of_range<N>(row, half ? h : 0, half ? E : h, b);
 #pragma unroll
-    for (int q = 0; q < N; ++q) {  // the other half's list (fetched whole before this lane's own list changes)
-      const u32 lo = __shfl_xor((u32)b[q], 32), hi = __shfl_xor((u32)(b[q] >> 32), 32);
-      o[q] = ((unsigned long long)hi << 32) | lo;
-    }
+    for (int q = 0; q < N; ++q) o[q] = rank_of_lane(b[q], 32);  // the other half's list, fetched whole before this one changes
 #pragma unroll
     for (int q = 0; q < N; ++q) insert_key(b, o[q]);
     if (half == 0) {
 #pragma unroll
       for (int q = 0; q < kMaxRank; ++q) {
-        const unsigned long long key = q < N ? b[q < N ? q : 0] : 0ull;
+        const rank_t key = q < N ? b[q < N ? q : 0] : 0.0;
         const int e = rank_key_expert(key);  // -1 past the number of experts
         if (q <= k) ranks[(size_t)tok * (k + 1) + q] = (q < n) ? e : -1;
         if (FUSE && q < R.NR) {
@@ -162,15 +159,11 @@ __device__ inline void rank_row_shared(const float *row, int tok, int sub, int E
                                        const RankOut &R, int *cnt) {
   const int n = min(k + 1, E);
   int32_t *ranks = FUSE ? R.rank_expert : rank_expert;
-  auto fetch = [&](unsigned long long v, int off) {
-    const u32 lo = __shfl_xor((u32)v, off), hi = __shfl_xor((u32)(v >> 32), off);
-    return ((unsigned long long)hi << 32) | lo;
-  };
   auto rank = [&](auto tag) {
     constexpr int N = decltype(tag)::value;  // list length: at least n
-    unsigned long long b[N], o[N];
+    rank_t b[N], o[N];
 #pragma unroll
-    for (int q = 0; q < N; ++q) b[q] = 0ull;
+    for (int q = 0; q < N; ++q) b[q] = 0.0;
 #pragma unroll
     for (int m = 0; m < kMaxE / LPT; ++m) {
       const int e = sub + m * LPT;
@@ -179,14 +172,14 @@ __device__ inline void rank_row_shared(const float *row, int tok, int sub, int E
 #pragma unroll
     for (int off = 1; off < LPT; off <<= 1) {
 #pragma unroll
-      for (int q = 0; q < N; ++q) o[q] = fetch(b[q], off);  // the other list, fetched whole before this one changes
+      for (int q = 0; q < N; ++q) o[q] = rank_of_lane(b[q], off);  // the other list, fetched whole before this one changes
 #pragma unroll
       for (int q = 0; q < N; ++q) insert_key(b, o[q]);
     }
 #pragma unroll
     for (int q = 0; q < kMaxRank; ++q) {
       if (sub != q % LPT) continue;  // all lanes hold the list: each writes its entries
-      const unsigned long long key = q < N ? b[q < N ? q : 0] : 0ull;
+      const rank_t key = q < N ? b[q < N ? q : 0] : 0.0;
       const int e = rank_key_expert(key);  // -1 past the number of experts
       if (q <= k) ranks[(size_t)tok * (k + 1) + q] = (q < n) ? e : -1;
       if (FUSE && q < R.NR) {
@@ -201,16 +194,10 @@ __device__ inline void rank_row_shared(const float *row, int tok, int sub, int E
   else rank(std::integral_constant<int, kMaxRank>{});
   if (FUSE) {
     const int e0 = tok / R.Tg * R.Eg;
-    unsigned long long best = 0ull;
-    for (int m = sub; m < R.Eg; m += LPT) {
-      const unsigned long long key = rank_key(row[e0 + m], e0 + m);
-      best = key > best ? key : best;
-    }
+    rank_t best = 0.0;
+    for (int m = sub; m < R.Eg; m += LPT) best = rank_max(best, rank_key(row[e0 + m], e0 + m));
 #pragma unroll
-    for (int off = 1; off < LPT; off <<= 1) {
-      const unsigned long long o = fetch(best, off);
-      best = o > best ? o : best;
-    }
+    for (int off = 1; off < LPT; off <<= 1) best = rank_max(best, rank_of_lane(best, off));
     if (sub == 0) {
       R.ir_score[tok] = key_score(rank_key_score(best));
       R.ir_cand[tok] = rank_key_expert(best);
