@@ -64,6 +64,23 @@ __device__ inline int lanes_below(unsigned long long mask) {
   return __popcll(mask & ((1ull << lane) - 1ull));
 }
 
+// Inclusive sum over the lanes of the wave (data-parallel moves).
+__device__ inline int wave_scan(int v) {
+  auto step = [&](auto ctrl, auto row_mask) {
+    v += __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, decltype(row_mask)::value, 0xf, false);
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr 1, 2, 4, 8
+  step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast 15 into rows 1 and 3
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+__device__ inline int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); }
+
 // ------------------------------------------------------------------ topk_rank
 // One token block per workgroup, two lanes per token: lanes l and l + 32 of a wave each rank half of token l's experts
 // and merge, as in the router's epilogue.  What bounds it is the instructions of a token's insertions, so half the
@@ -174,12 +191,7 @@ __global__ __launch_bounds__(SC_THREADS) void scan_blocks_kernel(int32_t *__rest
       v[u] = sum;
       sum += t;
     }
-    int incl = sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      int t = __shfl_up(incl, off);
-      if (lane >= off) incl += t;
-    }
+    const int incl = wave_scan(sum);
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
     int before = 0, total = 0;
@@ -244,12 +256,7 @@ __global__ __launch_bounds__(kTokBlock) void scatter_candidates_kernel(DispatchA
   // in expert order (a dozen counts: recomputed by every workgroup rather than by a launch of its own)
   for (int r = w; r < A.NR; r += NW) {
     const int c = lane < A.E ? cat_cnt[r * A.E + lane] : 0;
-    int incl = c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      int t = __shfl_up(incl, off);
-      if (lane >= off) incl += t;
-    }
+    const int incl = wave_scan(c);
     if (lane < A.E) s_base[r * A.E + lane] = r * A.T + incl - c;
   }
   // the plan of the lists that this block's tokens can be candidates of: capacity block g of every
@@ -341,20 +348,18 @@ __device__ inline u32 wave_min(u32 v) {
 // equal to it are kept (the first ones in token order).  `each(f)` calls f(key, valid) for every key slot of the
 // calling thread, the same number of times in every lane of a wave (invalid slots with valid = false);
 // all threads of the workgroup call this together.
-// A digit pass is four barriers and an LDS histogram, 1.6 us; a few thousand scores differ in 24 or 25 bits, and
+// For lists streamed from memory, and what value_select leaves over.  A digit pass is four barriers and an LDS histogram, 1.6 us; a few thousand scores differ in 24 or 25 bits, and
 // two digits below their common prefix as a rule leave a bin of which every key is kept: the threshold is then
 // the key below the bin, and the passes end (3001 tokens, 6 experts: four fixed passes 6.5 us, now 4.2; all of
 // select_slot_kernel at 4096 tokens with per-group capacity 21.0 -> 17.5).
 // Most lanes of a wave can hit the same histogram bin (scores tied or close), and LDS atomics of one instruction on
 // one address are served one lane after the other: every bin has kHistCopies counters, lane l adds to copy
 // l % kHistCopies (consecutive words, different banks), and the copies are added up before the bins are scanned.
-// passes: at most that many digits; the result is then a lower bound of the m-th largest key, off by less than
-// one step of the last digit taken (need_eq is meaningless then).
 // COMMON false: the digits start at the highest bit.  Where `each` reads memory (lists past the registers) finding the
 // common prefix is a pass of its own and saves none as a rule: 400 K tokens, 8 experts, top-2, lists of up to 190 K
 // candidates, select_slot_kernel 464 us without it, 504 with it.
 template <bool COMMON, class Each>
-__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq, int passes = 4) {
+__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   u32 *copies = hist + 256;  // [256][kHistCopies]
   u32 prefix = 0, remaining = (u32)m;
@@ -383,7 +388,7 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
     left = diff ? 32 - __clz((int)diff) : 0;
     prefix = left < 32 ? lo >> left << left : 0u;
   }  // (hist is next written two barriers from here)
-  while (left > 0 && passes-- > 0) {
+  while (left > 0) {
     const int bits = min(left, 8), shift = left - bits;
 #pragma unroll
     for (int q = 0; q < 256 * kHistCopies / SS_THREADS; ++q) copies[q * SS_THREADS + tid] = 0;
@@ -407,13 +412,7 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
     if (w == 0) {
       // lane l owns bins 255-4l .. 252-4l, i.e. bins in descending order across lanes
       u32 c0 = hist[255 - 4 * lane], c1 = hist[254 - 4 * lane], c2 = hist[253 - 4 * lane], c3 = hist[252 - 4 * lane];
-      u32 sum = c0 + c1 + c2 + c3, incl = sum;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        u32 t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-      u32 excl = incl - sum;
+      const u32 sum = c0 + c1 + c2 + c3, incl = (u32)wave_scan((int)sum), excl = incl - sum;
       if (excl < remaining && remaining <= incl) {
         u32 rem = remaining - excl, in_bin = c0;
         int bkt = 255 - 4 * lane;
@@ -438,94 +437,181 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
   return prefix;
 }
 
+// The same as radix_select for keys held in registers, by one histogram of the scores themselves: kValueBins bins of equal width
+// between the lowest and the highest (score - lowest, scaled and rounded, never decreases with the key).  Scores spread
+// over such bins, where the leading digits of their keys - sign and exponent - are a handful of values: the bin
+// with the m-th highest holds a few keys as a rule, which every wave ranks for itself.  Five barriers, where
+// three digit passes are thirteen.  3001 tokens, 6 experts: select_direct_kernel 11.8 -> 9.6 us.
+// Scores whose range is no ordinary number, and bins of more than a wave of keys, are left to the digits.
+constexpr int kValueBins = 4 * SS_THREADS;
+static_assert(kValueBins + kWave + 2 * SS_WAVES + 1 <= kHistWords, "bins, the bin's keys, wave results, their number");
+template <class Each>
+__device__ inline u32 value_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  u32 *const few = hist + kValueBins, *const wres = few + kWave, *const n_few = wres + 2 * SS_WAVES;
+  u32 lo = 0xffffffffu, nhi = 0xffffffffu;  // smallest key, smallest complement
+  each([&](u32 kx, bool valid) {
+    if (valid) {
+      lo = min(lo, kx);
+      nhi = min(nhi, ~kx);
+    }
+  });
+  lo = wave_min(lo);
+  nhi = wave_min(nhi);
+  if (lane == 0) {
+    wres[w] = lo;
+    wres[SS_WAVES + w] = nhi;
+  }
+  reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
+  if (tid == 0) *n_few = 0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < SS_WAVES; ++q) {
+    lo = min(lo, wres[q]);
+    nhi = min(nhi, wres[SS_WAVES + q]);
+  }
+  if (lo == ~nhi) {  // all scores are equal
+    need_eq = (u32)m;
+    return lo;
+  }
+  const float low = key_score(lo), width = key_score(~nhi) - low, scale = (float)kValueBins / width;
+  if (!(width < INFINITY) || !(scale < INFINITY)) {  // (uniform over the workgroup)
+    __syncthreads();
+    return radix_select<true>(m, each, hist, s_pick, need_eq);
+  }
+  auto bin_of = [&](u32 kx) { return min((int)((key_score(kx) - low) * scale), kValueBins - 1); };
+  each([&](u32 kx, bool valid) {
+    if (valid) atomicAdd(&hist[bin_of(kx)], 1u);
+  });
+  __syncthreads();
+  // thread t owns four bins, t = 0 the highest
+  const uint4 c = reinterpret_cast<const uint4 *>(hist)[SS_THREADS - 1 - tid];
+  const int sum = (int)(c.x + c.y + c.z + c.w), incl = wave_scan(sum);
+  if (lane == 63) wres[w] = (u32)incl;  // (the extremes were read before the last barrier)
+  __syncthreads();
+  int excl = incl - sum;
+#pragma unroll
+  for (int q = 0; q < SS_WAVES; ++q) excl += q < w ? (int)wres[q] : 0;
+  if (excl < m && m <= excl + sum) {
+    u32 rem = (u32)(m - excl), in_bin = c.w;
+    int bin = 4 * (SS_THREADS - 1 - tid) + 3;
+    if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.z;
+      if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.y;
+        if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.x; } } }
+    s_pick[0] = (u32)bin;
+    s_pick[1] = rem;
+    s_pick[2] = in_bin;
+  }
+  __syncthreads();
+  const int bin = (int)s_pick[0], rem = (int)s_pick[1], in_bin = (int)s_pick[2];
+  if (in_bin > kWave) {
+    __syncthreads();
+    return radix_select<true>(m, each, hist, s_pick, need_eq);
+  }
+  each([&](u32 kx, bool valid) {
+    if (valid && bin_of(kx) == bin) few[atomicAdd(n_few, 1u)] = kx;
+  });
+  __syncthreads();
+  const u32 mine = lane < in_bin ? few[lane] : 0u;  // (a key is never 0)
+  int above = 0, equal = 0;
+  for (int q = 0; q < in_bin; ++q) {
+    const u32 other = (u32)__builtin_amdgcn_readlane((int)mine, q);
+    above += other > mine;
+    equal += other == mine;
+  }
+  const unsigned long long at = __ballot(lane < in_bin && above < rem && rem <= above + equal);
+  const int src = __ffsll((long long)at) - 1;
+  need_eq = (u32)(rem - __builtin_amdgcn_readlane(above, src));
+  return (u32)__builtin_amdgcn_readlane((int)mine, src);
+}
+
 // Shared memory of the selection kernels.
-struct SelectSmem {
+struct __attribute__((aligned(16))) SelectSmem {
   u32 hist[kHistWords];
   u32 pick[3];
-  int2 wtot[SS_PER][SS_WAVES];  // (kept-for-sure, equal-to-threshold) counts per (trip, wave)
-  int2 wsum[8];
+  int wtot[SS_PER][SS_WAVES];  // counts per (trip, wave): kept for sure, and equal to the threshold << 16
+  int wsum[8];
 };
 
-// Selection and slotting of a list of n <= SS_THREADS * SS_PER candidates held in registers: candidate
+// Selection and slotting of a list of n <= SS_THREADS * NU candidates held in registers: candidate
 // idx = u * SS_THREADS + tid is element u of thread tid (`load(idx, key, tok)` fetches it), so the
-// candidates are met in token order.  by_score: the m highest keys are kept, equal keys in token order
-// (radix select of the threshold, digit passes on registers); otherwise the first m in token
-// order.  Kept candidates take slots fill0, fill0 + 1, ... in token order: one scan over the
-// (trip, wave) totals of the kept flags.  Only kept candidates are written (every slot entry starts
-// as -1).
-template <class Load>
-__device__ inline void select_in_registers(const DispatchArgs &A, int n, int m, bool by_score, int r, int j, int fill0,
-                                           Load load, SelectSmem &S, int32_t *__restrict__ slot,
-                                           int32_t *__restrict__ slot_token) {
+// candidates are met in token order.  The m < n highest keys are kept, equal keys in token order.  Kept candidates take slots
+// fill0, fill0 + 1, ... in token order: one scan over the (trip, wave) totals of the kept flags.
+// Only kept candidates are written (every slot entry starts as -1).
+template <int NU, class Load>
+__device__ inline void select_trips(const DispatchArgs &A, int n, int m, int r, int j, int fill0, Load load, SelectSmem &S,
+                                    int32_t *__restrict__ slot, int32_t *__restrict__ slot_token) {
+  static_assert(SS_THREADS * NU < 1 << 16, "two counts in a word");
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const unsigned long long below = (1ull << lane) - 1ull;
   const int nu = (n + SS_THREADS - 1) / SS_THREADS;
-  u32 kreg[SS_PER];
-  int treg[SS_PER];
+  u32 kreg[NU];
+  int treg[NU];
 #pragma unroll
-  for (int u = 0; u < SS_PER; ++u) {
+  for (int u = 0; u < NU; ++u) {
     const int idx = u * SS_THREADS + tid;
     kreg[u] = 0;
     treg[u] = 0;
     if (u < nu && idx < n) load(idx, kreg[u], treg[u]);
   }
-  u32 thr = 0, need_eq = 0;
-  if (by_score)
-    thr = radix_select<true>(m, [&](auto f) {
+  u32 need_eq = 0;
+  const u32 thr = value_select(m, [&](auto f) {
 #pragma unroll
-      for (int u = 0; u < SS_PER; ++u)
-        if (u < nu) f(kreg[u], u * SS_THREADS + tid < n);
-    }, S.hist, S.pick, need_eq);
+    for (int u = 0; u < NU; ++u)
+      if (u < nu) f(kreg[u], u * SS_THREADS + tid < n);
+  }, S.hist, S.pick, need_eq);
 
-  int pre[SS_PER];  // lanes of this wave before this one: kept-for-sure | equal << 8
+  int pre[NU];  // lanes of this wave before this one: kept-for-sure | equal << 8
 #pragma unroll
-  for (int u = 0; u < SS_PER; ++u) {
+  for (int u = 0; u < NU; ++u) {
     pre[u] = 0;
     if (u < nu) {
-      const int idx = u * SS_THREADS + tid;
-      const bool valid = idx < n;
-      bool gt, eq = false;
-      if (by_score) { gt = valid && kreg[u] > thr; eq = valid && kreg[u] == thr; }
-      else gt = valid && idx < m;
+      const bool valid = u * SS_THREADS + tid < n;
+      const bool gt = valid && kreg[u] > thr, eq = valid && kreg[u] == thr;
       const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
       pre[u] = __popcll(bgt & below) | (__popcll(beq & below) << 8) | (gt ? 1 << 16 : 0) | (eq ? 1 << 17 : 0);
-      if (lane == 0) S.wtot[u][w] = make_int2(__popcll(bgt), __popcll(beq));
+      if (lane == 0) S.wtot[u][w] = __popcll(bgt) | __popcll(beq) << 16;
     }
   }
   __syncthreads();
   // exclusive scan of the nu * SS_WAVES totals in (trip, wave) order = token order
+  constexpr int kScanWaves = (NU * SS_WAVES + kWave - 1) / kWave;
+  static_assert(kScanWaves <= 8, "wsum");
   const int ne = nu * SS_WAVES;
-  int2 mine = make_int2(0, 0), incl = mine;
-  if (tid < ne) mine = (&S.wtot[0][0])[tid];
-  if (tid < 8 * kWave) {  // SS_PER * SS_WAVES = 384 entries fit 6 waves
-    incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int tx = __shfl_up(incl.x, off), ty = __shfl_up(incl.y, off);
-      if (lane >= off) { incl.x += tx; incl.y += ty; }
-    }
-    if (lane == 63) S.wsum[w] = incl;
+  int mine = 0, incl = 0;
+  if (tid < kScanWaves * kWave) {
+    if (tid < ne) mine = (&S.wtot[0][0])[tid];
+    incl = wave_scan(mine);
+    if (kScanWaves > 1 && lane == 63) S.wsum[w] = incl;
   }
-  __syncthreads();
+  if constexpr (kScanWaves > 1) __syncthreads();
   if (tid < ne) {
-    int2 before = make_int2(0, 0);
-    for (int q = 0; q < w; ++q) { before.x += S.wsum[q].x; before.y += S.wsum[q].y; }
-    (&S.wtot[0][0])[tid] = make_int2(before.x + incl.x - mine.x, before.y + incl.y - mine.y);
+    int before = 0;
+    if constexpr (kScanWaves > 1)
+      for (int q = 0; q < w; ++q) before += S.wsum[q];
+    (&S.wtot[0][0])[tid] = before + incl - mine;
   }
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < SS_PER; ++u) {
+  for (int u = 0; u < NU; ++u) {
     if (u < nu && u * SS_THREADS + tid < n) {
-      const int2 base = S.wtot[u][w];
+      const int base = S.wtot[u][w];
       const bool gt = (pre[u] >> 16) & 1, eq = (pre[u] >> 17) & 1;
-      const int eqs = base.y + ((pre[u] >> 8) & 255);  // equal keys before this one
+      const int eqs = (int)((u32)base >> 16) + ((pre[u] >> 8) & 255);  // equal keys before this one
       if (gt || (eq && (u32)eqs < need_eq)) {
-        const int sl = fill0 + base.x + (pre[u] & 255) + min(eqs, (int)need_eq);
+        const int sl = fill0 + (base & 0xffff) + (pre[u] & 255) + min(eqs, (int)need_eq);
         slot[(size_t)treg[u] * (A.k + 1) + r] = sl;
         slot_token[(size_t)j * A.C + sl] = treg[u];
       }
     }
   }
+}
+// (lists of up to 4096 candidates without the other twenty trips' tests)
+template <class Load>
+__device__ inline void select_in_registers(const DispatchArgs &A, int n, int m, int r, int j, int fill0, Load load, SelectSmem &S,
+                                           int32_t *__restrict__ slot, int32_t *__restrict__ slot_token) {
+  if (n <= 4 * SS_THREADS) select_trips<4>(A, n, m, r, j, fill0, load, S, slot, slot_token);
+  else select_trips<SS_PER>(A, n, m, r, j, fill0, load, S, slot, slot_token);
 }
 
 // The same for a list of any length, streamed from memory by one workgroup: the threshold by digit
@@ -556,14 +642,14 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, boo
     else gt = valid && idx < m;
     unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
     int gt_before = __popcll(bgt & below), eq_before = __popcll(beq & below);
-    if (lane == 0) S.wtot[0][w] = make_int2(__popcll(bgt), __popcll(beq));
+    if (lane == 0) S.wtot[0][w] = __popcll(bgt) | __popcll(beq) << 16;
     __syncthreads();
     int tot_gt = 0, tot_eq = 0;
 #pragma unroll
     for (int q = 0; q < SS_WAVES; ++q) {
-      const int2 t = S.wtot[0][q];
-      if (q < w) { gt_before += t.x; eq_before += t.y; }
-      tot_gt += t.x; tot_eq += t.y;
+      const int gts = S.wtot[0][q] & 0xffff, eqs = S.wtot[0][q] >> 16;
+      if (q < w) { gt_before += gts; eq_before += eqs; }
+      tot_gt += gts; tot_eq += eqs;
     }
     if (valid) {
       int eqs = run_eq + eq_before;                       // equal keys before this one
@@ -589,7 +675,7 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, boo
 // writes the expert's fill counts.
 //
 // Lists of up to SS_THREADS * SS_PER candidates are one workgroup's work (select_in_registers).  A
-// longer list - a skewed router sends most tokens to a few experts - is cut into segments of
+// longer list - a skewed router sends most tokens to a few experts - and one that keeps few of many is cut into segments of
 // kSegLen candidates, one workgroup each (the first workgroups of the grid are the segments after a
 // list's first; each derives its (list, segment) from the candidate counts):
 //   * nobody, everybody or the first m in token order kept: scatter_candidates has handed out the
@@ -602,21 +688,13 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, boo
 //     number at least m and fit the registers, the kept set is among them and it finishes the
 //     list with select_in_registers; otherwise (the sample misled, or the scores are tied en
 //     masse) it streams the original list.  The result is exact either way.
-constexpr int kSegLen = kSelectSegLen;           // 16384
-constexpr int kSegPer = kSegLen / SS_THREADS;    // candidates per thread of a segment workgroup
-constexpr int kSampleLen = kSegLen;              // keys in the sample
 constexpr int kRegMax = kSelectRegMax;           // candidates that fit the registers of one workgroup
 constexpr int kMapLists = 2048;                  // lists up to which long lists are split (the map is kept in LDS)
 
 // Exclusive scan of one value per thread over the workgroup (two barriers); total = sum over all threads.
 __device__ inline int block_scan_exclusive(int v, int *s_wave, int &total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int t = __shfl_up(incl, off);
-    if (lane >= off) incl += t;
-  }
+  const int incl = wave_scan(v);
   if (lane == 63) s_wave[w] = incl;
   __syncthreads();
   int before = 0;
@@ -631,6 +709,11 @@ __device__ inline int block_scan_exclusive(int v, int *s_wave, int &total) {
   return before + incl - v;
 }
 
+// kSegLen: 16384, or 4096 where that makes at most 256 further segments (kSelectShortMax candidates in all).  Short segments and
+// a sample of a quarter pay for lists from kLong candidates on if two thirds or more of them fall away:
+// 100000 tokens, 64 experts Zipf(1.1), top-2 (longest list 73 K, next 17 K): 35.5 -> 29.4 us, with the histogram of
+// scores and trips for 4096 candidates 19.1; 32768 tokens, 32 experts, capacity 512 of 18 K: 26.5 -> 21.2.
+template <int kSegLen>
 __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A, const int32_t *__restrict__ cat_cnt,
                                                                  const int32_t *__restrict__ blk_off,
                                                                  const u32 *__restrict__ cand_key,
@@ -638,6 +721,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
                                                                  u32 *__restrict__ comp_key,
                                                                  int32_t *__restrict__ comp_tok,
                                                                  int32_t *__restrict__ seg_cnt,
+                                                                 int32_t *__restrict__ seg_more,
                                                                  int32_t *__restrict__ list_done,
                                                                  int32_t *__restrict__ slot,
                                                                  int32_t *__restrict__ slot_token,
@@ -645,6 +729,9 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
                                                                  int32_t *__restrict__ grp_off,
                                                                  int32_t *__restrict__ fill_topk,
                                                                  int32_t *__restrict__ fill_total) {
+  constexpr int kSegPer = kSegLen / SS_THREADS;  // candidates per thread of a segment workgroup
+  constexpr int kSampleLen = kSegLen;            // keys in the sample
+  constexpr int kLong = kSegLen == kSelectSegLen ? kRegMax : 2 * kSegLen;  // candidates up to which a list has one segment
   __shared__ SelectSmem S;
   __shared__ int s_extra[kMapLists + 1];  // exclusive scan over the lists of their segments after the first
   __shared__ int s_wave[SS_WAVES];
@@ -673,7 +760,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
         const int c = l / A.Gq, gg = l - c * A.Gq, rr = c / A.E;
         int lo, hi;
         piece(rr, c - rr * A.E, gg, lo, hi);
-        ex = hi - lo > kRegMax ? (hi - lo + kSegLen - 1) / kSegLen - 1 : 0;
+        ex = hi - lo > kLong ? (hi - lo + kSegLen - 1) / kSegLen - 1 : 0;
       }
       int total;
       const int excl = block_scan_exclusive(ex, s_wave, total);
@@ -699,16 +786,24 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
   // ---- the list: (round r, expert j, capacity block g); n candidates, m of them kept, in slots fill0 ..
   const int cat = lst / A.Gq, g = lst - cat * A.Gq, r = cat / A.E, j = cat - r * A.E;
   int n = 0, m = 0, fill = 0, lo = 0;
-  for (int rr = 0; rr <= r; ++rr) {
-    int hi;
-    fill += m;
-    piece(rr, j, g, lo, hi);
-    n = hi - lo;
-    m = min(n, A.Cq - fill);
+  const int before_j = lane < A.E ? cat_cnt[r * A.E + lane] : 0;  // (every load of the plan in one round trip)
+  int lo_r[kMaxRounds], hi_r[kMaxRounds];
+#pragma unroll
+  for (int rr = 0; rr < kMaxRounds; ++rr) {
+    lo_r[rr] = hi_r[rr] = 0;
+    if (rr <= r) piece(rr, j, g, lo_r[rr], hi_r[rr]);
   }
+#pragma unroll
+  for (int rr = 0; rr < kMaxRounds; ++rr)
+    if (rr <= r) {
+      fill += m;
+      lo = lo_r[rr];
+      n = hi_r[rr] - lo;
+      m = min(n, A.Cq - fill);
+    }
   const int fill0 = g * A.Cq + fill;
-  int base = r * A.T + lo;  // round r's arrays tile [r T, (r+1) T) in expert order
-  for (int jj = 0; jj < j; ++jj) base += cat_cnt[r * A.E + jj];
+  // round r's arrays tile [r T, (r+1) T) in expert order
+  const int base = r * A.T + lo + __builtin_amdgcn_readlane(wave_scan(before_j) - before_j, j);
   const u32 *keys = cand_key + base;
   const int32_t *toks = cand_tok + base;
   if (seg == 0) {
@@ -723,14 +818,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
           if (rr == A.k - 1) topk = total;
         }
       }
-      int incl = total, sum_topk = topk;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum_topk += __shfl_xor(sum_topk, off);
+      const int incl = wave_scan(total), sum_topk = wave_sum(topk);
       if (lane < A.Gq) {
         grp_fill[j * A.Gq + lane] = total;
         grp_off[j * A.Gq + lane] = incl - total;
@@ -745,22 +833,21 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
   if (m == 0) return;  // nobody kept: every slot entry already says so
   const bool by_score = !A.arrival || r == A.k;  // the Fill-in round always selects by score (Sec. 4.2)
   if (m == n || !by_score) return;  // everybody, or the first m in token order: settled by scatter_candidates
-  const bool is_long = n > kRegMax;          // then, if can_split, the list has a workgroup per segment
-  if (!is_long) {
-    select_in_registers(A, n, m, true, r, j, fill0, [&](int idx, u32 &kx, int &tok) { kx = keys[idx]; tok = toks[idx]; },
-                        S, slot, slot_token);
-    return;
-  }
-
-  // ---- long list, the m highest scores: sample, copy the candidates that may be kept, last one finishes
+  // ---- long list (more than kLong candidates: then, if can_split, it has a workgroup per segment), the m highest scores: sample, copy the candidates that may be kept, last one finishes
   const int nseg = (n + kSegLen - 1) / kSegLen;
   // rank in the sample: the expected number of sampled keys among the list's m highest, plus five
   // standard deviations and a few; the candidates with key >= L then number about n / kSampleLen times that
   const float expect = (float)m * (float)kSampleLen / (float)n;
   const int qsel = (int)(expect + 5.0f * sqrtf(expect) + 16.0f);
-  const bool split = can_split && qsel < kSampleLen && (long long)qsel * n / kSampleLen <= kRegMax * 7 / 8;
+  const long long survivors = (long long)qsel * n / kSampleLen;
+  const bool split = can_split && n > kLong && qsel < kSampleLen && survivors <= (n <= kRegMax ? n / 3 : kRegMax * 7 / 8);
   if (!split) {
-    if (seg == 0) select_streaming(A, n, m, true, r, j, fill0, keys, toks, S, slot, slot_token);
+    if (seg > 0) return;
+    if (n <= kRegMax)
+      select_in_registers(A, n, m, r, j, fill0, [&](int idx, u32 &kx, int &tok) { kx = keys[idx]; tok = toks[idx]; },
+                          S, slot, slot_token);
+    else
+      select_streaming(A, n, m, true, r, j, fill0, keys, toks, S, slot, slot_token);
     return;
   }
   u32 L;
@@ -769,17 +856,15 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     // instruction then reads one run - two cache lines - where single candidates a stride apart would
     // touch 64 lines: 19 -> 5 us for a list of 900 K candidates)
     static_assert(kSegPer * SS_WAVES * kWave == kSampleLen, "one run per (trip, wave)");
-    const int run = n / (kSampleLen / kWave);  // > 64: n > kRegMax
+    const int run = n / (kSampleLen / kWave);  // > 64: n > kLong >= 1.5 kSampleLen
     u32 sk[kSegPer];
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) sk[u] = keys[(size_t)(u * SS_WAVES + w) * run + lane];
     u32 dummy;
-    // two digits are enough: L only has to lie below the list's m-th highest key, and the keys of one step of the
-    // second (2^-16 of the sample's range) are a handful of candidates more
-    L = radix_select<false>(qsel, [&](auto f) {
+    L = value_select(qsel, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kSegPer; ++u) f(sk[u], true);
-    }, S.hist, S.pick, dummy, 2);
+    }, S.hist, S.pick, dummy);
   }
   {
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -793,34 +878,29 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
       const bool ge = idx < len && kreg[u] >= L;
       const unsigned long long bge = __ballot(ge);
       pre[u] = __popcll(bge & below) | (ge ? 1 << 16 : 0);
-      if (lane == 0) S.wtot[u][w] = make_int2(__popcll(bge), 0);
+      if (lane == 0) S.wtot[u][w] = __popcll(bge);
     }
     __syncthreads();
     // exclusive scan of the kSegPer * SS_WAVES wave totals in (trip, wave) order = token order
     int mine = 0, incl = 0;
-    if (tid < kSegPer * SS_WAVES) mine = (&S.wtot[0][0])[tid].x;
-    if (tid < 4 * kWave) {  // kSegPer * SS_WAVES = 256 entries = 4 waves
-      incl = mine;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-      if (lane == 63) S.wsum[w].x = incl;
+    if (tid < kSegPer * SS_WAVES) mine = (&S.wtot[0][0])[tid];
+    if (tid < 4 * kWave) {  // kSegPer * SS_WAVES is at most 256 entries = 4 waves
+      incl = wave_scan(mine);
+      if (lane == 63) S.wsum[w] = incl;
     }
     __syncthreads();
     int count = 0;
     if (tid < kSegPer * SS_WAVES) {
       int before = 0;
-      for (int q = 0; q < w; ++q) before += S.wsum[q].x;
-      (&S.wtot[0][0])[tid].x = before + incl - mine;
+      for (int q = 0; q < w; ++q) before += S.wsum[q];
+      (&S.wtot[0][0])[tid] = before + incl - mine;
     }
-    count = S.wsum[0].x + S.wsum[1].x + S.wsum[2].x + S.wsum[3].x;
+    count = S.wsum[0] + S.wsum[1] + S.wsum[2] + S.wsum[3];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) {
       if ((pre[u] >> 16) & 1) {
-        const int idx = u * SS_THREADS + tid, pos = base + i0 + S.wtot[u][w].x + (pre[u] & 255);
+        const int idx = u * SS_THREADS + tid, pos = base + i0 + S.wtot[u][w] + (pre[u] & 255);
         comp_key[pos] = kreg[u];
         comp_tok[pos] = toks[i0 + idx];
       }
@@ -829,11 +909,11 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     // store counts as done when the L2 has it), the barrier collects the waves, and ONE device-scope
     // fence (a write-back of the L2, which the other XCDs do not see into) goes before the ticket.
     // Whoever draws the last ticket fences once more before it reads the other segments' copies.
-    const int seg_id = seg == 0 ? lst : A.NL + extra_base + seg - 1;
+    int32_t *const my_cnt = seg == 0 ? seg_cnt + lst : seg_more + extra_base + seg - 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-      seg_cnt[seg_id] = count;
+      *my_cnt = count;
       __threadfence();
       s_bcast = atomicAdd(&list_done[lst], 1);
       if (s_bcast == nseg - 1) __threadfence();
@@ -848,7 +928,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     int carry = 0;
     for (int q0 = 0; q0 < nseg; q0 += SS_THREADS) {  // nseg <= 2^24 / kSegLen + 1 fits s_extra
       const int q = q0 + tid;
-      const int c = q < nseg ? seg_cnt[q == 0 ? lst : A.NL + extra_base + q - 1] : 0;
+      const int c = q < nseg ? (q == 0 ? seg_cnt[lst] : seg_more[extra_base + q - 1]) : 0;
       int tot;
       const int excl = block_scan_exclusive(c, s_wave, tot);
       if (q < nseg) s_extra[q] = carry + excl;
@@ -862,7 +942,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     return;
   }
   const int *s_off = s_extra;  // first copy of every segment
-  select_in_registers(A, total, m, true, r, j, fill0, [&](int idx, u32 &kx, int &tok) {
+  select_in_registers(A, total, m, r, j, fill0, [&](int idx, u32 &kx, int &tok) {
     int a = 0, b = nseg - 1;  // segment whose copies hold position idx
     while (a < b) {
       const int mid = (a + b + 1) >> 1;
@@ -895,7 +975,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
                                                                    int32_t *__restrict__ grp_off,
                                                                    int32_t *__restrict__ fill_topk,
                                                                    int32_t *__restrict__ fill_total) {
-  __shared__ u32 hist[kHistWords];
+  __shared__ __attribute__((aligned(16))) u32 hist[kHistWords];
   __shared__ u32 s_pick[3];
   __shared__ u32 s_wave[SS_WAVES];
   __shared__ int s_cnt[kMaxRounds];
@@ -940,12 +1020,9 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
         }
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    c01 += __shfl_xor(c01, off);
-    if (r >= 2) c23 += __shfl_xor(c23, off);
-    if (r >= 4) c4 += __shfl_xor(c4, off);
-  }
+  c01 = (u32)wave_sum((int)c01);
+  if (r >= 2) c23 = (u32)wave_sum((int)c23);
+  if (r >= 4) c4 = (u32)wave_sum((int)c4);
   if (lane <= r) {  // lane rr adds the wave's count of round rr
     const u32 both = lane < 2 ? c01 : (lane < 4 ? c23 : c4);
     const int v = lane & 1 ? both >> 16 : both & 0xffffu;
@@ -971,7 +1048,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
   const int mode = m == 0 ? 0 : (m == n ? 1 : (by_score ? 3 : 2));
   u32 thr = 0, need_eq = 0;
   if (mode == 3)
-    thr = radix_select<true>(m, [&](auto f) {
+    thr = value_select(m, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kDirectPer; ++u)
         if (u < per) f(kreg[u], (member >> u) & 1u);
@@ -991,12 +1068,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
   eq &= member;
   // exclusive scan over the threads of both counts, 16 bits each (at most kDirectMaxT candidates)
   const u32 mine = (u32)__popc(gt) | (u32)__popc(eq) << 16;
-  u32 incl = mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const u32 t = __shfl_up(incl, off);
-    if (lane >= off) incl += t;
-  }
+  const u32 incl = (u32)wave_scan((int)mine);
   if (lane == 63) s_wave[w] = incl;
   __syncthreads();
   u32 before = incl - mine;
@@ -1056,12 +1128,7 @@ __device__ inline void row_plan_wave(const DispatchArgs &A, bool writes, const i
   const int fill = on ? fill_total[e] : 0;
   const int rows = fill + nir;
   const int ntile = A.max_mtiles > 0 ? (rows + A.BM - 1) / A.BM : 0;
-  int s_ir = nir, s_rows = rows, s_tiles = ntile;  // inclusive scans over experts
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int a = __shfl_up(s_ir, off), b = __shfl_up(s_rows, off), c = __shfl_up(s_tiles, off);
-    if (e >= off) { s_ir += a; s_rows += b; s_tiles += c; }
-  }
+  const int s_ir = wave_scan(nir), s_rows = wave_scan(rows), s_tiles = wave_scan(ntile);  // inclusive, over experts
   if (on) {
     s_off[e] = s_ir - nir;
     s_rbase[e] = s_rows - rows;
@@ -1486,12 +1553,7 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
   };
   if (w < NR) {
     const int c = lane < E ? s_cnt[w * E + lane] : 0;
-    int incl = c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int t = __shfl_up(incl, off);
-      if (lane >= off) incl += t;
-    }
+    const int incl = wave_scan(c);
     if (lane < E) s_base[w * E + lane] = w * T + incl - c;
   } else {
     for (int c = OR_THREADS - 1 - tid; c < E * A.Gq; c += OR_THREADS - NR * kWave) {
@@ -1523,14 +1585,7 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
     for (int j = w; j < E; j += OR_WAVES) {
       const u32 v = lane < A.Gq ? plan_topk[j * A.Gq + lane] : 0u;
       const int total = v >> 16;
-      int incl = total, sum_topk = v & 0xffffu;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum_topk += __shfl_xor(sum_topk, off);
+      const int incl = wave_scan(total), sum_topk = wave_sum(v & 0xffffu);
       if (lane < A.Gq) grp_off[j * A.Gq + lane] = incl - total;
       if (lane == 63) {
         fill_total[j] = incl;
@@ -1796,10 +1851,16 @@ hipError_t launch_dispatch(const Dims &D, const float *logits, const rr_tables &
     prof_end(K_SCATTER_CAND, s);
     prof_begin(K_SELECT_SLOT, s);
     // one workgroup per list, plus one for every further segment that a long list can have
-    const int sel_grid = D.NL + (select_splits(D.T, D.NR, D.NL) ? (int)((long long)D.T * D.NR / kSelectSegLen) : 0);
-    select_slot_kernel<<<sel_grid, SS_THREADS, 0, s>>>(A, W.cat_cnt, W.blk_cnt, W.cand_key, W.cand_tok, W.comp_key,
-                                                       W.comp_tok, W.seg_cnt, W.list_done, tb.slot, tb.slot_token,
-                                                       W.grp_fill, W.grp_off, tb.fill_topk, tb.fill_total);
+    const bool splits = select_splits(D.T, D.NR, D.NL);
+    auto select = [&](auto kern, int seg_len, int32_t *seg_more) {
+      const int grid = D.NL + (splits ? (int)((long long)D.T * D.NR / seg_len) : 0);
+      kern<<<grid, SS_THREADS, 0, s>>>(A, W.cat_cnt, W.blk_cnt, W.cand_key, W.cand_tok, W.comp_key, W.comp_tok, W.seg_cnt,
+                                       seg_more, W.list_done, tb.slot, tb.slot_token, W.grp_fill, W.grp_off, tb.fill_topk,
+                                       tb.fill_total);
+    };
+    // The counts of the further segments: one per kSelectShortLen candidates fits the Intra-GPU counts, which are written later.
+    if (splits && (long long)D.T * D.NR <= kSelectShortMax) select(select_slot_kernel<kSelectShortLen>, kSelectShortLen, W.ir_blk_cnt);
+    else select(select_slot_kernel<kSelectSegLen>, kSelectSegLen, W.seg_cnt + (splits ? D.NL : 0));
     prof_end(K_SELECT_SLOT, s);
   }
   if (D.ir) {

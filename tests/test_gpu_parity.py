@@ -118,6 +118,35 @@ def test_dispatch_deterministic():
             assert np.array_equal(first[name], again[name]), name
 
 
+# The selection's histogram of score values: scores whose range is no fp32 number, that lie within a few ulps, that are denormal,
+# spread over many powers of two (nearly all in one bin), or tied en masse; lists of one register trip, of several,
+# and cut into short segments, with a capacity that keeps few and one that keeps most.
+def _odd_scores(kind, T, E):
+    rng = np.random.default_rng(T + E)
+    if kind == "wide":
+        return (rng.uniform(-1, 1, (T, E)) * 3.3e38).astype(np.float32)
+    if kind == "ulps":
+        return (1.0 + rng.integers(0, 40, (T, E)) * 2.0 ** -23).astype(np.float32)
+    if kind == "denormal":
+        return (rng.integers(-3000, 3000, (T, E)) * 1e-42).astype(np.float32)
+    if kind == "geometric":
+        return (rng.choice([-1.0, 1.0], (T, E)) * 2.0 ** rng.uniform(-120, 100, (T, E))).astype(np.float32)
+    a = rng.standard_normal((T, E)).astype(np.float32)  # "ties": most scores one of five values
+    return np.where(rng.random((T, E)) < 0.9, np.round(a), a).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["wide", "ulps", "denormal", "geometric", "ties"])
+@pytest.mark.parametrize("T,E,G,k,cf,quota", [
+    (3000, 6, 1, 2, 0.5, False), (16385, 2, 1, 1, 0.9, False), (33000, 4, 2, 1, 0.05, False), (33000, 2, 1, 1, 0.3, False),
+    (4 * 2560, 4, 4, 1, 0.7, True)])
+def test_dispatch_odd_scores_bit_exact(kind, T, E, G, k, cf, quota):
+    a = _odd_scores(kind, T, E)
+    cfg = rr.RRConfig(T, 64, 0, E, k, G, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), False, quota))
+    # (scores hundreds apart: the oracle's weights, ratios of exponentials over all experts, are 0 / 0 there)
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), False, quota),
+                           cw_atol=1.0 if kind in ("wide", "geometric") else 1e-6)
+
+
 LONG_LIST_CASES = [
     # T, E, G, k, cf, bias of expert 1, ties, arrival, quota
     (300000, 8, 2, 2, 0.5, 4.0, False, False, False),   # one expert draws ~all first choices: a list of ~290 K candidates, split
