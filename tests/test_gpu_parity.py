@@ -147,6 +147,14 @@ def test_dispatch_odd_scores_bit_exact(kind, T, E, G, k, cf, quota):
                            cw_atol=1.0 if kind in ("wide", "geometric") else 1e-6)
 
 
+# Intra-GPU counts per 1024 tokens: from 4096 experts x 128-token blocks on, up to 8192 experts x 1024-token blocks; ragged ends.
+@pytest.mark.parametrize("T,E", [(8192, 64), (8196, 64), (9220, 60), (131072, 64), (131076, 64)])
+def test_dispatch_intra_gpu_blocks_bit_exact(T, E):
+    a = wl.synthetic_logits(T, E, seed=T % 1000, bias_std=1.0, ties=False)
+    cfg = rr.RRConfig(T, 64, 0, E, 1, 4, 0.6, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir",)))
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir",)))
+
+
 LONG_LIST_CASES = [
     # T, E, G, k, cf, bias of expert 1, ties, arrival, quota
     (300000, 8, 2, 2, 0.5, 4.0, False, False, False),   # one expert draws ~all first choices: a list of ~290 K candidates, split
