@@ -1361,8 +1361,14 @@ constexpr int kOneT = OR_THREADS, kOneSlots = 32768, kOneTile = 16384;  // kOneT
 constexpr int kMaxParts = 16;            // parts of the router's K
 constexpr int kMaxPartFloats = 65536;    // partial scores in all
 
+// Who is kept: a wave per list searches for a threshold; or, for up to 128 tokens and more lists than two per wave, a thread per
+// candidate counts the keys of its list that beat its own.  Us for the call, search / counting: 16 tokens, 96 lists
+// 28.3 / 25.2; 64, 64 lists 37.4 / 35.0; 128, 64 lists 37.1 / 35.3; but 88 tokens, 12 lists 26.3 / 26.9 and 256, 16 lists (of up
+// to 100 candidates) 27.0 / 29.8: one list per wave is searched in the time that the longest list takes to be counted.
+__host__ __device__ inline bool counts_candidates(int T, int NL) { return T <= 128 && NL > 2 * OR_WAVES; }
+
 struct OneLayout {  // dynamic LDS: the score tile, later the candidate arrays; slots; counts
-  int tops, ctok, slot, wcnt, wir, plan, plan_topk, total;
+  int tops, ctok, slot, wcnt, wir, plan, plan_topk, clist, kept, total;
 };
 __host__ __device__ inline OneLayout one_layout(int T, int E, int NR, int Gq, bool tile) {
   const int rows = (T + kWave - 1) / kWave, n = NR * T;
@@ -1377,7 +1383,10 @@ __host__ __device__ inline OneLayout one_layout(int T, int E, int NR, int Gq, bo
   L.wir = L.wcnt + (NR * rows * E * 2 + 3) / 4 * 4;
   L.plan = L.wir + (rows * E * 2 + 3) / 4 * 4;
   L.plan_topk = L.plan + NR * E * Gq * 4;
-  L.total = L.plan_topk + (Gq > 1 ? E * Gq * 4 : 0);
+  L.clist = L.plan_topk + (Gq > 1 ? E * Gq * 4 : 0);
+  const bool count = counts_candidates(T, NR * E * Gq);
+  L.kept = L.clist + (count ? (n * 2 + 3) / 4 * 4 : 0);
+  L.total = L.kept + (count ? (n + 31) / 32 * 4 : 0);
   return L;
 }
 
@@ -1414,6 +1423,9 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
   uint16_t *const wcnt = reinterpret_cast<uint16_t *>(lds + L.wcnt);  // [NR][rows][E] candidates, scanned over rows
   uint16_t *const wir = reinterpret_cast<uint16_t *>(lds + L.wir);    // [rows][E] the same for the Intra-GPU lists
   u32 *const plan = reinterpret_cast<u32 *>(lds + L.plan);            // [NL] kept count << 16 | slots of earlier rounds
+  const bool count = counts_candidates(T, A.NL);
+  uint16_t *const clist = reinterpret_cast<uint16_t *>(lds + L.clist);  // [NR][T] (count) list of the candidate
+  u32 *const kept_bits = reinterpret_cast<u32 *>(lds + L.kept);         // (count) a bit per candidate
   u32 *const plan_topk = reinterpret_cast<u32 *>(lds + L.plan_topk);  // [E][Gq] (quotas) occupied after all rounds << 16 | after the top-k ones
 
   // ---- everything from global memory first: one round trip
@@ -1625,8 +1637,10 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
         const int at = s_base[r * E + e_r[r]] + wcnt[(r * rows + row) * E + e_r[r]] + below[r];
         ckey[at] = key_r[r];
         ctok[at] = (uint16_t)i;
+        if (count) clist[at] = (uint16_t)((r * E + e_r[r]) * A.Gq + (A.Gq == 1 ? 0 : i / A.Tg));
       }
   }
+  if (count && tid < (NR * T + 31) / 32) kept_bits[tid] = 0;
   __syncthreads();
   // ---- the lists.  A slot is kept in LDS as its offset from the first slot of the list's capacity block.
   for (int c = tid; c < E * A.C; c += OR_THREADS) {  // zero padding (Sec. 3)
@@ -1634,7 +1648,52 @@ __global__ __launch_bounds__(OR_THREADS) void route_small_kernel(
     const u32 last = plan[((NR - 1) * E + j) * A.Gq + g];
     if (sl - g * A.Cq >= (int)((last >> 16) + (last & 0xffffu))) slot_token[c] = -1;
   }
-  for (int lst = w; lst < A.NL; lst += OR_WAVES) {
+  if (count) {
+    // candidate at position `at`: its list's first position, length, plan
+    struct Cand { int start, n, m, fill, r, j, g; };
+    auto cand_of = [&](int at) {
+      const int lst = clist[at], cat = A.Gq == 1 ? lst : lst / A.Gq, g = lst - cat * A.Gq;
+      int r = 0;
+#pragma unroll
+      for (int q = 1; q < kMaxRounds; ++q) r += at >= q * T;
+      int lo, hi;
+      piece(r, cat - r * E, g, lo, hi);
+      return Cand{s_base[cat] + lo, hi - lo, (int)(plan[lst] >> 16), (int)(plan[lst] & 0xffffu), r, cat - r * E, g};
+    };
+    for (int at = tid; at < NR * T; at += OR_THREADS) {
+      const Cand c = cand_of(at);
+      const int pos = at - c.start;
+      bool kept = c.m == c.n;
+      if (c.m > 0 && c.m < c.n) {
+        if (A.arrival && c.r < A.k) {
+          kept = pos < c.m;
+        } else {
+          const u32 mine = ckey[at];  // (a key is never 0)
+          int better = 0;
+#pragma unroll 8
+          for (int q = 0; q < c.n; ++q) better += ckey[c.start + q] > (q < pos ? mine - 1 : mine);  // ties: the earlier token
+          kept = better < c.m;
+        }
+      }
+      if (kept) atomicOr(&kept_bits[at >> 5], 1u << (at & 31));
+    }
+    __syncthreads();
+    for (int at = tid; at < NR * T; at += OR_THREADS) {
+      if (!((kept_bits[at >> 5] >> (at & 31)) & 1u)) continue;
+      const Cand c = cand_of(at);
+      int sl = c.fill;  // and one for every kept candidate between the list's first and this one
+      const int w0 = c.start >> 5, w1 = at >> 5;
+      for (int q = w0; q <= w1; ++q) {
+        u32 bits = kept_bits[q];
+        if (q == w0) bits &= ~0u << (c.start & 31);
+        if (q == w1) bits &= (1u << (at & 31)) - 1u;
+        sl += __popc(bits);
+      }
+      const int tok = ctok[at];
+      s_slot[c.r * T + tok] = (uint16_t)sl;
+      slot_token[(size_t)c.j * A.C + c.g * A.Cq + sl] = tok;
+    }
+  } else for (int lst = w; lst < A.NL; lst += OR_WAVES) {
     const int cat = lst / A.Gq, g = lst - cat * A.Gq, r = cat / E, j = cat - r * E;
     int lo, hi;
     piece(r, j, g, lo, hi);

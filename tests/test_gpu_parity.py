@@ -155,6 +155,22 @@ def test_dispatch_intra_gpu_blocks_bit_exact(T, E):
     gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir",)))
 
 
+# Small batches whose candidates count the keys that beat theirs (up to 128 tokens, more than 32 lists), and their neighbours:
+# every token on few experts, ties, arrival order, per-group capacity, one token.
+@pytest.mark.parametrize("T,E,G,k,cf,arrival,quota", [
+    (128, 16, 4, 2, 0.5, False, False), (129, 16, 4, 2, 0.5, False, False), (128, 11, 1, 2, 0.25, False, False),
+    (128, 64, 8, 4, 1.0, False, False), (1, 64, 1, 4, 1.0, False, False), (100, 32, 2, 1, 0.3, True, False),
+    (128, 34, 1, 2, 0.5, False, True)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_dispatch_counted_candidates_bit_exact(T, E, G, k, cf, arrival, quota, ties):
+    if T % G:
+        G = 1
+    a = wl.synthetic_logits(T, E, seed=T + E, bias_std=2.0, ties=ties)
+    a[:, E // 2] += np.float32(4.0)  # one list with nearly every token
+    cfg = rr.RRConfig(T, 64, 0, E, k, G, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), arrival, quota))
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), arrival, quota))
+
+
 LONG_LIST_CASES = [
     # T, E, G, k, cf, bias of expert 1, ties, arrival, quota
     (300000, 8, 2, 2, 0.5, 4.0, False, False, False),   # one expert draws ~all first choices: a list of ~290 K candidates, split
