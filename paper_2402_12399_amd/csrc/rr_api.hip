@@ -341,7 +341,11 @@ int rr_moe_forward(const rr_config *cfg, const void *x, const float *w_router, c
     if (!routing_only) {
       if (e == hipSuccess && !ffn_fuses_gather(D)) e = launch_gather(D, x, tb, W, s);
       if (e == hipSuccess) e = launch_ffn(D, x, tb, w1, w3, w2, W, out, s);
-      if (e == hipSuccess) e = launch_combine(D, tb, W, out, s);
+      // Top-1 with Intra-GPU Rectification and without Fill-in: every token has exactly one processed row - its first
+      // choice's, or the re-routed one - and the down projection has stored it.   64 tokens, 512 x 1536, 16 experts: the layer
+      // 31.1 us with the combine launch, 29.0 without; 2048 tokens, 1024 x 2816: 88.6, 85.5.
+      const bool all_stored = D.k == 1 && D.ir && !D.fr;
+      if (e == hipSuccess && !all_stored) e = launch_combine(D, tb, W, out, s);
     }
     return e == hipSuccess ? RR_OK : RR_ERR_HIP;
   };
