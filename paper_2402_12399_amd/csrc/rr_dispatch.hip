@@ -13,7 +13,7 @@
 //                      lists whose kept set follows from the counts (nobody, everybody, the first m
 //                      in token order) get their slots here and are not materialised
 //   select_slot        per remaining list: kept count and first free slot from the counts,
-//                      radix-select of the score threshold of the kept set (ties -> lower token
+//                      select the score threshold of the kept set (ties -> lower token
 //                      index), then a prefix scan in token order hands out consecutive slots
 //   ir_count / ir_scan / ir_weights
 //                      per-expert Intra-GPU lists (stable, token order), dispatched-row layout and
@@ -618,52 +618,62 @@ __device__ inline void select_in_registers(const DispatchArgs &A, int n, int m, 
 }
 
 // The same for a list of any length, streamed from memory by one workgroup: the threshold by digit
-// passes over the keys, then a pass that hands out the slots 1024 candidates at a time.  The
-// path for lists that fit neither the registers nor the split scheme below; exact for any input.
-__device__ inline void select_streaming(const DispatchArgs &A, int n, int m, bool by_score, int r, int j, int fill0,
+// passes over the keys, then a pass that hands out the slots.  The path for lists that fit neither the registers nor the
+// split scheme below; exact for any input.  Bound by the latency of its loads and barriers, so 8192 candidates are in
+// flight at a time: 326862 tokens, 8 experts Zipf(1.5), top-4: select_slot_kernel
+// 381 -> 150 us (1024 at a time with two barriers each before).
+__device__ inline void select_streaming(const DispatchArgs &A, int n, int m, int r, int j, int fill0,
                                         const u32 *__restrict__ keys, const int32_t *__restrict__ toks, SelectSmem &S,
                                         int32_t *__restrict__ slot, int32_t *__restrict__ slot_token) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NU = 8;
+  static_assert(NU * SS_WAVES == 2 * kWave, "two totals per lane");
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned long long below = (1ull << lane) - 1ull;
-  u32 thr = 0, need_eq = 0;
-  if (by_score)
-    thr = radix_select<false>(m, [&](auto f) {
-      for (int base = 0; base < n; base += SS_THREADS) {
-        const int idx = base + tid;
-        f(idx < n ? keys[idx] : 0u, idx < n);
-      }
-    }, S.hist, S.pick, need_eq);
-  int run_gt = 0, run_eq = 0;
-  for (int base = 0; base < n; base += SS_THREADS) {
-    const int idx = base + tid;
-    const bool valid = idx < n;
-    u32 kx = 0;
-    int tok = 0;
-    if (valid) { kx = keys[idx]; tok = toks[idx]; }
-    bool gt, eq = false;
-    if (by_score) { gt = valid && kx > thr; eq = valid && kx == thr; }
-    else gt = valid && idx < m;
-    unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
-    int gt_before = __popcll(bgt & below), eq_before = __popcll(beq & below);
-    if (lane == 0) S.wtot[0][w] = __popcll(bgt) | __popcll(beq) << 16;
-    __syncthreads();
-    int tot_gt = 0, tot_eq = 0;
+  u32 need_eq = 0;
+  const u32 thr = radix_select<false>(m, [&](auto f) {
+    for (int base = tid; base - tid < n; base += NU * SS_THREADS) {
+      u32 kx[NU];
 #pragma unroll
-    for (int q = 0; q < SS_WAVES; ++q) {
-      const int gts = S.wtot[0][q] & 0xffff, eqs = S.wtot[0][q] >> 16;
-      if (q < w) { gt_before += gts; eq_before += eqs; }
-      tot_gt += gts; tot_eq += eqs;
+      for (int u = 0; u < NU; ++u) kx[u] = base + u * SS_THREADS < n ? keys[base + u * SS_THREADS] : 0u;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) f(kx[u], base + u * SS_THREADS < n);
     }
-    if (valid) {
-      int eqs = run_eq + eq_before;                       // equal keys before this one
+  }, S.hist, S.pick, need_eq);
+  int run_gt = 0, run_eq = 0;
+  for (int base = tid; base - tid < n; base += NU * SS_THREADS) {
+    u32 kreg[NU];
+    int treg[NU], pre[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int idx = base + u * SS_THREADS;
+      kreg[u] = idx < n ? keys[idx] : 0u;
+      treg[u] = idx < n ? toks[idx] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const bool valid = base + u * SS_THREADS < n, gt = valid && kreg[u] > thr, eq = valid && kreg[u] == thr;
+      const unsigned long long bgt = __ballot(gt), beq = __ballot(eq);
+      pre[u] = __popcll(bgt & below) | (__popcll(beq & below) << 8) | (gt ? 1 << 16 : 0) | (eq ? 1 << 17 : 0);
+      if (lane == 0) S.wtot[u][w] = __popcll(bgt) | __popcll(beq) << 16;
+    }
+    __syncthreads();
+    // every wave scans the totals in (trip, wave) order = token order, two per lane
+    const int t0 = (&S.wtot[0][0])[2 * lane], t1 = (&S.wtot[0][0])[2 * lane + 1], incl = wave_scan(t0 + t1), excl = incl - t0 - t1;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int e = u * SS_WAVES + w;  // uniform
+      const int before = __builtin_amdgcn_readlane(e & 1 ? excl + t0 : excl, e >> 1);
+      const bool gt = (pre[u] >> 16) & 1, eq = (pre[u] >> 17) & 1;
+      const int eqs = run_eq + (int)((u32)before >> 16) + ((pre[u] >> 8) & 255);  // equal keys before this one
       if (gt || (eq && (u32)eqs < need_eq)) {
-        int sl = fill0 + run_gt + gt_before + min(eqs, (int)need_eq);
-        slot[(size_t)tok * (A.k + 1) + r] = sl;
-        slot_token[(size_t)j * A.C + sl] = tok;
+        const int sl = fill0 + run_gt + (before & 0xffff) + (pre[u] & 255) + min(eqs, (int)need_eq);
+        slot[(size_t)treg[u] * (A.k + 1) + r] = sl;
+        slot_token[(size_t)j * A.C + sl] = treg[u];
       }
     }
-    run_gt += tot_gt;
-    run_eq += tot_eq;
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    run_gt += total & 0xffff;
+    run_eq += (int)((u32)total >> 16);
     __syncthreads();
   }
 }
@@ -850,7 +860,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
       select_in_registers(A, n, m, r, j, fill0, [&](int idx, u32 &kx, int &tok) { kx = keys[idx]; tok = toks[idx]; },
                           S, slot, slot_token);
     else
-      select_streaming(A, n, m, true, r, j, fill0, keys, toks, S, slot, slot_token);
+      select_streaming(A, n, m, r, j, fill0, keys, toks, S, slot, slot_token);
     return;
   }
   u32 L;
@@ -941,7 +951,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     __syncthreads();
   }
   if (total < m || total > kRegMax) {
-    select_streaming(A, n, m, true, r, j, fill0, keys, toks, S, slot, slot_token);
+    select_streaming(A, n, m, r, j, fill0, keys, toks, S, slot, slot_token);
     return;
   }
   const int *s_off = s_extra;  // first copy of every segment
