@@ -585,15 +585,21 @@ __global__ __launch_bounds__(PK_THREADS) void gemm_bf16_persistent_kernel(GemmAr
 #endif
 }
 
-// Four fp32 values as sums of three bf16 values, each the nearest of what the ones before it leave (8 mantissa bits and
-// a sign: three of them hold all 24): plane[p] gets part p of the four.  Conversions and subtractions only:
-// v_dot2c_f32_bf16 with (-1, 0) would subtract a packed value from its fp32 one without unpacking it (7 instructions for two
-// values, not 11), but does not run beside MFMAs (22 cycles each, v_sub_f32 8).
-__device__ __forceinline__ void split3(const f32x4 &x, uint2 (&plane)[3]) {
+// Four fp32 values, times kSplitScale, as sums of three bf16 values, each the nearest of what the ones before it leave (8
+// mantissa bits and a sign: three of them hold all 24): plane[p] gets part p of the four.  bf16 counts down to 2^-133, so the
+// parts of values below 2^-110 would lose bits: the scale lifts fp32's smallest step, 2^-149, to there, and the sum of
+// products is brought back by kSplitUnscale (powers of two: nothing is rounded).  Values from 2^89 and sums from 2^50 on
+// become infinities and are computed again (see the end of the K loop).  2048 tokens, 1024 x 2816, 8 experts: 510 us without the
+// scale (tokens at 2^-122: an error of 8e-4), 503 with it as a 4-byte multiplication and 4-byte subtractions, 519 as 8-byte ones.
+// Conversions and subtractions only: v_dot2c_f32_bf16 with (-1, 0) would subtract a packed value from its fp32 one without unpacking
+// it (7 instructions for two values, not 11 and the 2 of the scale), but does not run beside MFMAs (22 cycles each, v_sub_f32 8).
+constexpr float kSplitScale = 0x1p39f, kSplitUnscale = 0x1p-78f;
+__device__ __forceinline__ void split3(const f32x4 &x, float scale, uint2 (&plane)[3]) {
+#pragma clang fp contract(off)  // (the first subtraction as a fused one is 8 bytes long too)
   u32 w[3][2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    float a = x[2 * q], b = x[2 * q + 1];
+    float a = x[2 * q] * scale, b = x[2 * q + 1] * scale;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       w[p][q] = pack_bf16(a, b);
@@ -621,7 +627,8 @@ __device__ __forceinline__ void split3(const f32x4 &x, uint2 (&plane)[3]) {
 //     permutation, the same for both operands.
 //   * fp32 rows of five chunks and more that fill their tiles (TILE_SPLIT): every operand is split into three bf16 parts
 //     that hold its 24 bits, and the six products down to 2^-18 of the leading one run on the bf16 pipe, accumulated in
-//     fp32 (a split of Dekker's kind, as the router's): 96 cycles of MFMAs per pair of fragments and chunk instead of 256.
+//     fp32 (a split of Dekker's kind, as the router's; the three left out are up to 2^-24.2 of a product, so a lone product is
+//     off by up to 0.94 ulp, where an fp32 MFMA rounds it to 0.5): 96 cycles of MFMAs per pair of fragments and chunk instead of 256.
 //     The parts are made once per workgroup, on the way to LDS (a wave that splits its own fragments does it two to four
 //     times over, and conversions run at half speed beside MFMAs: 285 us instead of 265 for the layer below).  Error
 //     against 64 bits below that of the fp32 MFMAs, which round as often (1024 tokens, 1024 x 2816 SwiGLU 1.09e-6
@@ -809,13 +816,15 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
     constexpr int PLANE = (BM + S::BROWS) * GB_ROW_BYTES / 2;
     char *const wr = smem + lrow * 64 + (((piece >> 1) ^ ((lrow >> 2) & 3)) << 4) + (piece & 1) * 8;
     const int fpos = fr * 64 + ((fg ^ (fr >> 2)) << 4);
+    float scale;  // in a register: a multiplication of 4 bytes instead of 8
+    asm("s_mov_b32 %0, %1" : "=s"(scale) : "i"(__builtin_bit_cast(int, kSplitScale)));
     fetch(0);
     for (int kt = 0; kt < KT; ++kt) {
       if (kt > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everybody has read chunk kt - 1
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         uint2 q[3];
-        split3(raw[i], q);
+        split3(raw[i], scale, q);
 #pragma unroll
         for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(wr + p * PLANE + i * NW * 8 * 64) = q[p];
       }
@@ -842,8 +851,8 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b3[j][PB[q]], a3[PA[q]], acc[i][j], 0, 0, 0);
       }
     }
-    // An infinity, or a value that rounds to one in bf16, leaves NaN behind its first part: a fragment of which any
-    // element is not finite is computed again from fp32 operands.
+    // An infinity, or a value that the scale or bf16's rounding makes one, leaves NaN behind its first part: a fragment of
+    // which any element is not finite is computed again from fp32 operands.
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
       const int arow = (wm * WM + i) * 16 + fr;  // of the tile
@@ -853,7 +862,11 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
         bool finite = true;
 #pragma unroll
         for (int u = 0; u < 4; ++u) finite = finite && __builtin_isfinite(acc[i][j][u]);
-        if (__all(finite)) continue;
+        if (__all(finite)) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[i][j][u] *= kSplitUnscale;
+          continue;
+        }
         if (GATHER) ao = m0 + arow < rows_e ? (unsigned)token_of(m0 + arow) * rowb : PAST;
         const bool up = GATED && j >= WN / 2;
         const unsigned bo = (unsigned)(GATED ? (wn * (WN / 2) + j % (WN / 2)) * 16 + fr : (wn * WN + j) * 16 + fr) * rowb;

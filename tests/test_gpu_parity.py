@@ -848,17 +848,14 @@ def test_forward_split_tiles(case):
 
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 def test_forward_split_tiles_of_values_without_bf16_parts(act):
-    """Weights that a bf16 part cannot hold (rounding to an infinity), infinities and NaN, and denormal ones: what fp32
-    arithmetic makes of them, and nothing else in the layer's output moves."""
+    """Weights that a bf16 part cannot hold (rounding to an infinity), infinities and NaN: what fp32 arithmetic makes of them,
+    and nothing else in the layer's output moves.  (Small values: the two tests below.)"""
     T, d, F = 4097, 1032, 1032
     w = wl.Workload("special", T, d, F, 1, 1, 1, 1.0, "f32", act, "none", 92)
     assert list(gu.ffn_shapes(gu.config_of(w, ())).brows) == [128, 128]
     inp = wl.make_inputs(w)
     inp["x"][:, 5] *= np.float32(1e-38)          # times a weight of 3.4e38: an ordinary term
     inp["w1"][0, 40, 5] = inp["w1"][0, 700, 5] = np.float32(3.4e38)
-    inp["x"][:, 77] *= np.float32(1e30)          # times a denormal weight
-    inp["w1"][0, :, 77] = np.float32(1e-40)
-    inp["w_router"][:, 77] = 0.0
     clean, clean_ref = _whole_layer(w, inp)
     assert np.linalg.norm(clean - clean_ref) <= 1e-5 * np.linalg.norm(clean_ref)
     inp["w2"][0, 300, 9] = np.inf                # output column 300: +-inf by the sign of inner unit 9, column 801: NaN
@@ -870,6 +867,52 @@ def test_forward_split_tiles_of_values_without_bf16_parts(act):
     assert np.linalg.norm(got[:, others] - ref[:, others]) <= 1e-5 * np.linalg.norm(ref[:, others])
     whole = np.array([c for c in others if c // 16 not in (300 // 16, 801 // 16)])  # a fragment is computed again as a whole
     assert np.array_equal(got[:, whole], clean[:, whole])
+
+
+# fp32's whole range goes through the split tiles with all its bits: tokens and weights down to the smallest steps, and sums and
+# operands beyond what the parts take (computed again).  x and the first weights are drawn at 2^ex and 2^ew, every fourth
+# token at 2^(ex - 6): rows of one fragment differ.  Bounds per row: fp32 arithmetic on K = 1032 terms as elsewhere, 3e-5 of the row's norm,
+# and half a step of 2^-149 for every term and result that is itself among the denormals: sqrt(1032) of them, far below the
+# rows here (2^-126 at least, 2^-23 of it).
+SPLIT_RANGES = [
+    # act, ex, ew
+    ("gelu", -116, 0), ("gelu", -118, 2), ("swiglu", -116, 80), ("swiglu", 76, -126), ("gelu", 84, -140), ("gelu", -138, 80),
+    ("gelu", 20, 34), ("gelu", 95, -90), ("swiglu", -90, 100), ("swiglu", 0, 0),
+]
+
+
+@pytest.mark.parametrize("act,ex,ew", SPLIT_RANGES)
+def test_forward_split_tiles_keep_the_range_of_fp32(act, ex, ew):
+    T, d, F = 4097, 1032, 1032
+    w = wl.Workload("range", T, d, F, 1, 1, 1, 1.0, "f32", act, "none", 93)
+    assert list(gu.ffn_shapes(gu.config_of(w, ())).brows) == [128, 128]
+    inp = wl.make_inputs(w)
+    inp["x"] = np.ldexp(inp["x"], ex)
+    inp["x"][::4] = np.ldexp(inp["x"][::4], -6)
+    inp["w1"] = np.ldexp(inp["w1"], ew)
+    if act == "swiglu":
+        inp["w3"] = np.ldexp(inp["w3"], ew)
+    got, ref = _whole_layer(w, inp)
+    rows = np.linalg.norm(ref, axis=1)
+    assert rows.min() > 2.0 ** -126 and np.isfinite(ref).all()
+    err = np.linalg.norm(got - ref, axis=1) / rows
+    assert err.max() <= 3e-5, (int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("small,large", [(1e-38, 3e38), (1e-40, 3e38), (1e-38, 1e25)])
+def test_forward_split_tiles_of_a_small_and_a_large_column(small, large):
+    """One inner column of tiny activations (1e-40: denormal) against large weights: the terms that decide every inner unit."""
+    T, d, F = 4097, 1032, 1032
+    w = wl.Workload("column", T, d, F, 1, 1, 1, 1.0, "f32", "gelu", "none", 94)
+    inp = wl.make_inputs(w)
+    inp["x"] *= np.float32(small * large / 100.0)
+    inp["x"][:, 77] = np.random.default_rng(5).standard_normal(T).astype(np.float32) * np.float32(small)
+    inp["w1"][0, :, 77] = np.sign(inp["w1"][0, :, 77]) * np.float32(large)
+    got, ref = _whole_layer(w, inp)
+    x, w1 = inp["x"].astype(np.float64), inp["w1"][0, :64].astype(np.float64)
+    assert np.linalg.norm(x[:, [77]] * w1[:, 77]) > 0.99 * np.linalg.norm(x @ w1.T)
+    err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 3e-5, float(err.max())
 
 
 def _whole_layer(w, inp):
