@@ -358,39 +358,21 @@ __device__ inline u32 wave_min(u32 v) {
 // Most lanes of a wave can hit the same histogram bin (scores tied or close), and LDS atomics of one instruction on
 // one address are served one lane after the other: every bin has kHistCopies counters, lane l adds to copy
 // l % kHistCopies (consecutive words, different banks), and the copies are added up before the bins are scanned.
-// COMMON false: the digits start at the highest bit.  Where `each` reads memory (lists past the registers) finding the
-// common prefix is a pass of its own and saves none as a rule: 400 K tokens, 8 experts, top-2, lists of up to 190 K
+// IN_RANGE: of the keys in [lo, hi] only, from the highest bit in which lo and hi differ; the caller knows how many keys
+// of the list lie above hi.  Otherwise the digits start at the highest bit: where `each` reads memory (lists past the registers)
+// finding the extremes is a pass of its own and saves none as a rule: 400 K tokens, 8 experts, top-2, lists of up to 190 K
 // candidates, select_slot_kernel 464 us without it, 504 with it.
-template <bool COMMON, class Each>
-__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
+template <bool IN_RANGE, class Each>
+__device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq, u32 lo = 0, u32 hi = 0xffffffffu) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   u32 *copies = hist + 256;  // [256][kHistCopies]
   u32 prefix = 0, remaining = (u32)m;
   int left = 32;  // bits below the prefix
-  if constexpr (COMMON) {
-    u32 lo = 0xffffffffu, nhi = 0xffffffffu;  // smallest key, smallest complement
-    each([&](u32 kx, bool valid) {
-      if (valid) {
-        lo = min(lo, kx);
-        nhi = min(nhi, ~kx);
-      }
-    });
-    lo = wave_min(lo);
-    nhi = wave_min(nhi);
-    if (lane == 0) {
-      hist[w] = lo;
-      hist[SS_WAVES + w] = nhi;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < SS_WAVES; ++q) {
-      lo = min(lo, hist[q]);
-      nhi = min(nhi, hist[SS_WAVES + q]);
-    }
-    const u32 diff = lo ^ ~nhi;
+  if constexpr (IN_RANGE) {
+    const u32 diff = lo ^ hi;
     left = diff ? 32 - __clz((int)diff) : 0;
     prefix = left < 32 ? lo >> left << left : 0u;
-  }  // (hist is next written two barriers from here)
+  }
   while (left > 0) {
     const int bits = min(left, 8), shift = left - bits;
 #pragma unroll
@@ -398,7 +380,7 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
     __syncthreads();
     each([&](u32 kx, bool valid) {
       const u32 digit = (kx ^ prefix) >> shift;  // (the prefix has zeros there: past 8 bits only in keys of another prefix)
-      if (valid && digit >> bits == 0) atomicAdd(&copies[digit * kHistCopies + (lane & (kHistCopies - 1))], 1u);
+      if (valid && digit >> bits == 0 && (!IN_RANGE || kx - lo <= hi - lo)) atomicAdd(&copies[digit * kHistCopies + (lane & (kHistCopies - 1))], 1u);
     });
     __syncthreads();
     {  // thread t adds up a quarter of the copies of bin t / 4
@@ -431,9 +413,9 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
     prefix |= s_pick[0] << shift;
     remaining = s_pick[1];
     left = shift;
-    if (s_pick[2] == remaining && prefix > 0) {  // the whole bin is kept
+    if (s_pick[2] == remaining && max(prefix, lo) > 0) {  // the whole bin is kept
       need_eq = 0;
-      return prefix - 1;
+      return max(prefix, lo) - 1;  // (keys below lo can share the bin's digits)
     }
   }
   need_eq = remaining;
@@ -441,91 +423,142 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
 }
 
 // The same as radix_select for keys held in registers, by one histogram of the scores themselves: kValueBins bins of equal width
-// between the lowest and the highest (score - lowest, scaled and rounded, never decreases with the key).  Scores spread
+// (score - lowest, scaled, rounded and clamped to the bins, never decreases with the key).  Scores spread
 // over such bins, where the leading digits of their keys - sign and exponent - are a handful of values: the bin
 // with the m-th highest holds a few keys as a rule, which every wave ranks for itself.  Five barriers, where
 // three digit passes are thirteen.  3001 tokens, 6 experts: select_direct_kernel 11.8 -> 9.6 us.
-// Scores whose range is no ordinary number, and bins of more than a wave of keys, are left to the digits.
+//   * The bins span three times the range between the waves' usual extremes (of the lowest keys of two waves the higher one, of
+//     eight such the lowest, and the mirror image), as far as there are scores: a few that lie far from all others
+//     share the bins at the ends.  (Bins as wide as their distance would hold all other keys in one, by LDS atomics on one address.)
+//   * Where half of the waves have their first key in one bin all the same, scores are spread in no such way and the digits select.
+//   * More keys in the bin than a wave has lanes: one score, many times (done), or the digits go on among its keys.
+// Us of the selecting kernel, digits alone / bins from the lowest to the highest score, then digits over again / now, for scores
+// that are normal, with one of 1e4, with every hundredth times 1e6, multiples of 1/4: 16384 tokens, 2 experts 22.2 / 20.0 / 20.1, 22.0 /
+// 29.0 / 20.4, 22.5 / 29.1 / 21.8, 24.4 / 26.5 / 20.8; 32768 tokens 23.1 / 20.3 / 19.3, 22.8 / 35.6 / 21.0, 23.0 / 35.3 / 22.6,
+// 25.4 / 27.7 / 21.8.
 constexpr int kValueBins = 4 * SS_THREADS;
-static_assert(kValueBins + kWave + 2 * SS_WAVES + 1 <= kHistWords, "bins, the bin's keys, wave results, their number");
+static_assert(kValueBins + 2 * kWave + 1 <= kHistWords, "bins, the bin's keys, wave results, their number");
+static_assert(SS_WAVES == 16, "a row of 16 lanes for each of the waves' results");
 template <class Each>
 __device__ inline u32 value_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  u32 *const few = hist + kValueBins, *const wres = few + kWave, *const n_few = wres + 2 * SS_WAVES;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  u32 *const few = hist + kValueBins, *const wres = few + kWave, *const n_few = wres + kWave;
+  // v of another lane of the row of 16
+  auto row_step = [](auto ctrl, u32 v) { return (u32)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xf, 0xf, false); };
+  using std::integral_constant;
+  const integral_constant<int, 0xb1> quad1; const integral_constant<int, 0x4e> quad2;    // lane ^ 1, ^ 2
+  const integral_constant<int, 0x124> ror4; const integral_constant<int, 0x128> ror8;
+  auto wave_results = [&](u32 lo, u32 nhi, u32 probe) {  // (one LDS access per wave, whatever the number of waves)
+    lo = wave_min(lo);
+    nhi = wave_min(nhi);
+    if (lane == 0) {
+      wres[w] = lo;
+      wres[SS_WAVES + w] = nhi;
+      wres[2 * SS_WAVES + w] = probe;
+    }
+  };
+  auto row_min = [&](u32 v) {
+    v = min(v, row_step(quad1, v));
+    v = min(v, row_step(quad2, v));
+    v = min(v, row_step(ror4, v));
+    return min(v, row_step(ror8, v));
+  };
+  auto lane_value = [](u32 v, int l) { return (u32)__builtin_amdgcn_readlane((int)v, l); };
   u32 lo = 0xffffffffu, nhi = 0xffffffffu;  // smallest key, smallest complement
-  each([&](u32 kx, bool valid) {
+  auto extremes = [&](u32 kx, bool valid) {
     if (valid) {
       lo = min(lo, kx);
       nhi = min(nhi, ~kx);
     }
-  });
-  lo = wave_min(lo);
-  nhi = wave_min(nhi);
-  if (lane == 0) {
-    wres[w] = lo;
-    wres[SS_WAVES + w] = nhi;
-  }
+  };
+  each(extremes);
+  const unsigned long long have = __ballot(lo != 0xffffffffu);
+  wave_results(lo, nhi, have ? lane_value(lo, __ffsll((long long)have) - 1) : 0u);  // (a key is never 0)
   reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
   if (tid == 0) *n_few = 0;
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < SS_WAVES; ++q) {
-    lo = min(lo, wres[q]);
-    nhi = min(nhi, wres[SS_WAVES + q]);
-  }
-  if (lo == ~nhi) {  // all scores are equal
+  const u32 wave_v = wres[lane];  // lanes 0 .. 15: lowest keys of the waves, 16 .. 31: complements of the highest, 32 .. 47: a key
+  u32 ends = max(wave_v, row_step(quad1, wave_v)), all = row_min(wave_v);  // (a wave without keys: all ones, and so its pair)
+  ends = min(ends, row_step(quad2, ends));
+  ends = min(ends, row_step(ror4, ends));
+  ends = min(ends, row_step(ror8, ends));
+  lo = lane_value(all, 0);
+  nhi = lane_value(all, SS_WAVES);
+  u32 hi = ~nhi;
+  if (lo == hi) {  // all scores are equal
     need_eq = (u32)m;
     return lo;
   }
-  const float low = key_score(lo), width = key_score(~nhi) - low, scale = (float)kValueBins / width;
-  if (!(width < INFINITY) || !(scale < INFINITY)) {  // (uniform over the workgroup)
+  const float lowest = key_score(lo), highest = key_score(hi);
+  const float usual_low = key_score(lane_value(ends, 0)), usual_high = key_score(~lane_value(ends, SS_WAVES));
+  const float margin = usual_high - usual_low;  // (neighbouring tokens' scores can be alike, and the waves' extremes then lie close)
+  const bool usual = margin > 0.0f;
+  const float low = usual ? fmaxf(lowest, usual_low - margin) : lowest;
+  const float width = (usual ? fminf(highest, usual_high + margin) : highest) - low, scale = (float)kValueBins / width;
+  auto bin_of = [&](u32 kx) { return (int)__builtin_amdgcn_fmed3f((key_score(kx) - low) * scale, 0.0f, (float)(kValueBins - 1)); };
+  bool digits = !(width < INFINITY) || !(scale < INFINITY) || isnan(lowest) || isnan(highest);  // (uniform over the workgroup)
+  if (!digits) {
+    const bool probe = (lane & 48) == 2 * SS_WAVES && wave_v != 0;
+    const int bin = probe ? bin_of(wave_v) : -1 - lane, probes = __popcll(__ballot(probe));
+    auto sharers = [&](int q) { return __popcll(__ballot(bin == __builtin_amdgcn_readlane(bin, 2 * SS_WAVES + q))); };
+    digits = max(sharers(0), sharers(2)) >= max(3, (probes + 1) / 2);
+  }
+  if (!digits) {
+    each([&](u32 kx, bool valid) {
+      if (valid) atomicAdd(&hist[bin_of(kx)], 1u);
+    });
     __syncthreads();
-    return radix_select<true>(m, each, hist, s_pick, need_eq);
-  }
-  auto bin_of = [&](u32 kx) { return min((int)((key_score(kx) - low) * scale), kValueBins - 1); };
-  each([&](u32 kx, bool valid) {
-    if (valid) atomicAdd(&hist[bin_of(kx)], 1u);
-  });
-  __syncthreads();
-  // thread t owns four bins, t = 0 the highest
-  const uint4 c = reinterpret_cast<const uint4 *>(hist)[SS_THREADS - 1 - tid];
-  const int sum = (int)(c.x + c.y + c.z + c.w), incl = wave_scan(sum);
-  if (lane == 63) wres[w] = (u32)incl;  // (the extremes were read before the last barrier)
-  __syncthreads();
-  int excl = incl - sum;
-#pragma unroll
-  for (int q = 0; q < SS_WAVES; ++q) excl += q < w ? (int)wres[q] : 0;
-  if (excl < m && m <= excl + sum) {
-    u32 rem = (u32)(m - excl), in_bin = c.w;
-    int bin = 4 * (SS_THREADS - 1 - tid) + 3;
-    if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.z;
-      if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.y;
-        if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.x; } } }
-    s_pick[0] = (u32)bin;
-    s_pick[1] = rem;
-    s_pick[2] = in_bin;
-  }
-  __syncthreads();
-  const int bin = (int)s_pick[0], rem = (int)s_pick[1], in_bin = (int)s_pick[2];
-  if (in_bin > kWave) {
+    // thread t owns four bins, t = 0 the highest
+    const uint4 c = reinterpret_cast<const uint4 *>(hist)[SS_THREADS - 1 - tid];
+    const int sum = (int)(c.x + c.y + c.z + c.w), incl = wave_scan(sum);
+    if (lane == 63) wres[w] = (u32)incl;  // (the extremes were read before the last barrier)
     __syncthreads();
-    return radix_select<true>(m, each, hist, s_pick, need_eq);
+    const int waves = wave_scan(lane < SS_WAVES ? (int)wres[lane] : 0);
+    const int excl = incl - sum + (w ? (int)lane_value((u32)waves, w - 1) : 0);
+    if (excl < m && m <= excl + sum) {
+      u32 rem = (u32)(m - excl), in_bin = c.w;
+      int bin = 4 * (SS_THREADS - 1 - tid) + 3;
+      if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.z;
+        if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.y;
+          if (rem > in_bin) { rem -= in_bin; --bin; in_bin = c.x; } } }
+      s_pick[0] = (u32)bin;
+      s_pick[1] = rem;
+      s_pick[2] = in_bin;
+    }
+    __syncthreads();
+    const int bin = (int)s_pick[0], in_bin = (int)s_pick[2];
+    m = (int)s_pick[1];  // of the bin's keys
+    if (in_bin <= kWave) {
+      each([&](u32 kx, bool valid) {
+        if (valid && bin_of(kx) == bin) few[atomicAdd(n_few, 1u)] = kx;
+      });
+      __syncthreads();
+      const u32 mine = lane < in_bin ? few[lane] : 0u;  // (a key is never 0)
+      int above = 0, equal = 0;
+      for (int q = 0; q < in_bin; ++q) {
+        const u32 other = lane_value(mine, q);
+        above += other > mine;
+        equal += other == mine;
+      }
+      const unsigned long long at = __ballot(lane < in_bin && above < m && m <= above + equal);
+      const int src = __ffsll((long long)at) - 1;
+      need_eq = (u32)(m - __builtin_amdgcn_readlane(above, src));
+      return lane_value(mine, src);
+    }
+    lo = nhi = 0xffffffffu;  // the bin's extremes
+    each([&](u32 kx, bool valid) { extremes(kx, valid && bin_of(kx) == bin); });
+    wave_results(lo, nhi, 0);  // (the sums were read before the last barrier)
+    __syncthreads();
+    const u32 ext = row_min(wres[lane]);
+    lo = lane_value(ext, 0);
+    hi = ~lane_value(ext, SS_WAVES);
+    if (lo == hi) {
+      need_eq = (u32)m;
+      return lo;
+    }
   }
-  each([&](u32 kx, bool valid) {
-    if (valid && bin_of(kx) == bin) few[atomicAdd(n_few, 1u)] = kx;
-  });
   __syncthreads();
-  const u32 mine = lane < in_bin ? few[lane] : 0u;  // (a key is never 0)
-  int above = 0, equal = 0;
-  for (int q = 0; q < in_bin; ++q) {
-    const u32 other = (u32)__builtin_amdgcn_readlane((int)mine, q);
-    above += other > mine;
-    equal += other == mine;
-  }
-  const unsigned long long at = __ballot(lane < in_bin && above < rem && rem <= above + equal);
-  const int src = __ffsll((long long)at) - 1;
-  need_eq = (u32)(rem - __builtin_amdgcn_readlane(above, src));
-  return (u32)__builtin_amdgcn_readlane((int)mine, src);
+  return radix_select<true>(m, each, hist, s_pick, need_eq, lo, hi);
 }
 
 // Shared memory of the selection kernels.

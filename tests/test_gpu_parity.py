@@ -142,9 +142,70 @@ def _odd_scores(kind, T, E):
 def test_dispatch_odd_scores_bit_exact(kind, T, E, G, k, cf, quota):
     a = _odd_scores(kind, T, E)
     cfg = rr.RRConfig(T, 64, 0, E, k, G, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), False, quota))
-    # (scores hundreds apart: the oracle's weights, ratios of exponentials over all experts, are 0 / 0 there)
-    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), False, quota),
-                           cw_atol=1.0 if kind in ("wide", "geometric") else 1e-6)
+    want = _oracle_tables(a, cfg, ("ir", "fr"), False, quota)
+    want["combine_w"] = _weights_of(a, want, k)
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), want)
+
+
+def _weights_of(a, tables, k):
+    """Eq. 2 / Eq. 3 weights of oracle tables with the softmax over the processed experts alone: the oracle's, ratios of
+    exponentials over all experts, are 0 / 0 where scores lie hundreds apart."""
+    rank, slot, ir = tables["rank_expert"], tables["slot"], tables["ir_expert"]
+    s = np.full((len(a), k + 2), -np.inf)
+    rows = np.arange(len(a))
+    for r in range(k + 1):
+        s[:, r] = np.where(slot[:, r] >= 0, a[rows, rank[:, r]].astype(np.float64), -np.inf)
+    s[:, k + 1] = np.where(ir >= 0, a[rows, ir].astype(np.float64), -np.inf)
+    count = np.ones_like(s)
+    count[:, k + 1] = k - (slot[:, :k] >= 0).sum(axis=1)  # Eq. 3: the dropped choices
+    top = s.max(axis=1, keepdims=True)
+    e = np.where(np.isfinite(s), count * np.exp(s - np.where(np.isfinite(top), top, 0.0)), 0.0)
+    return e / np.maximum(e.sum(axis=1, keepdims=True), 1e-300)
+
+
+# Scores that crowd a histogram of equal bins: one far from all others, many far away, two clusters, a grid (one score in the
+# bin, many times), a cluster of many scores in one bin; lists held by one workgroup, by segments, and of per-group capacity.
+def _crowded_scores(kind, T, E):
+    rng = np.random.default_rng(T + E)
+    a = rng.standard_normal((T, E))
+    if kind == "one high":
+        a[T // 3] = 1e4 * np.arange(1, E + 1)
+    if kind == "one low":
+        a[T // 3] = -1e4 * np.arange(1, E + 1)
+    if kind == "many far":
+        a[::50] *= 1e6
+    if kind == "two clusters":
+        a += 1e6 * (rng.random((T, E)) < 0.5)
+    if kind == "grid":
+        a = np.round(a * 4) / 4
+    if kind == "one bin":
+        a = np.where(rng.random((T, E)) < 0.7, 1 + rng.integers(0, 8192, (T, E)) * 2.0 ** -20, 8 * rng.random((T, E)))
+    return a.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["one high", "one low", "many far", "two clusters", "grid", "one bin"])
+@pytest.mark.parametrize("T,E,G,k,cf,quota", [
+    (1500, 3, 1, 1, 0.4, False), (8190, 4, 1, 2, 0.5, False), (20001, 2, 1, 1, 0.6, False), (33000, 2, 1, 1, 0.2, False),
+    (60000, 4, 2, 2, 0.3, False), (4 * 2560, 4, 4, 1, 0.5, True)])
+def test_dispatch_crowded_scores_bit_exact(kind, T, E, G, k, cf, quota):
+    a = _crowded_scores(kind, T, E)
+    cfg = rr.RRConfig(T, 64, 0, E, k, G, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr"), False, quota))
+    want = _oracle_tables(a, cfg, ("ir", "fr"), False, quota)
+    want["combine_w"] = _weights_of(a, want, k)
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), want)
+
+
+# The threshold at the lowest key of a crowded bin, and one to either side: keys of the bin below share its leading digits.
+@pytest.mark.parametrize("kept", [1943, 3133, 4307, 5427])
+def test_dispatch_threshold_at_the_end_of_a_bin(kept):
+    rng = np.random.default_rng(9)
+    T = 6000
+    s = np.where(rng.random(T) < 0.8, 1 + rng.integers(0, 8192, T) * 2.0 ** -20, 8 * rng.random(T))
+    a = np.stack([s, np.full(T, -1.0)], axis=1).astype(np.float32)
+    for m in (kept - 1, kept, kept + 1):
+        cfg = rr.RRConfig(T, 64, 0, 2, 1, 1, (m - 0.5) * 2 / T, rr.RR_F32, rr.RR_ACT_SWIGLU, 0)
+        assert rr.rr_slots_per_expert(cfg) == m
+        gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ()))
 
 
 # Intra-GPU counts per 1024 tokens: from 4096 experts x 128-token blocks on, up to 8192 experts x 1024-token blocks; ragged ends.
