@@ -721,7 +721,7 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, int
 // writes the expert's fill counts.
 //
 // Lists of up to SS_THREADS * SS_PER candidates are one workgroup's work (select_in_registers).  A
-// longer list - a skewed router sends most tokens to a few experts - and one that keeps few of many is cut into segments of
+// longer list - a skewed router sends most tokens to a few experts - is cut into segments of
 // kSegLen candidates, one workgroup each (the first workgroups of the grid are the segments after a
 // list's first; each derives its (list, segment) from the candidate counts):
 //   * nobody, everybody or the first m in token order kept: scatter_candidates has handed out the
@@ -755,10 +755,11 @@ __device__ inline int block_scan_exclusive(int v, int *s_wave, int &total) {
   return before + incl - v;
 }
 
-// kSegLen: 16384, or 4096 where that makes at most 256 further segments (kSelectShortMax candidates in all).  Short segments and
-// a sample of a quarter pay for lists from kLong candidates on if two thirds or more of them fall away:
-// 100000 tokens, 64 experts Zipf(1.1), top-2 (longest list 73 K, next 17 K): 35.5 -> 29.4 us, with the histogram of
-// scores and trips for 4096 candidates 19.1; 32768 tokens, 32 experts, capacity 512 of 18 K: 26.5 -> 21.2.
+// kSegLen: 16384, or 4096 where that makes at most 256 further segments (kSelectShortMax candidates in all); the sample is as long.
+// 100000 tokens, 64 experts Zipf(1.1), top-2 (longest list 73 K): 35.5 -> 29.4 us, with the histogram of scores and trips for 4096
+// candidates 19.1.  (Lists that fit the registers are not cut, though with independent scores the few kept of 18 K would be found 3 us
+// sooner - 32768 tokens, 32 experts Zipf(1.1), 512 kept of each: 18.3, not 21.5; digits alone 24.9 -: 10 K lists are 2.5 us
+// slower cut, and where ties or the order of the tokens defeat the sample 24 K ones 31, not 20.)
 template <int kSegLen>
 __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A, const int32_t *__restrict__ cat_cnt,
                                                                  const int32_t *__restrict__ blk_off,
@@ -777,7 +778,6 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
                                                                  int32_t *__restrict__ fill_total) {
   constexpr int kSegPer = kSegLen / SS_THREADS;  // candidates per thread of a segment workgroup
   constexpr int kSampleLen = kSegLen;            // keys in the sample
-  constexpr int kLong = kSegLen == kSelectSegLen ? kRegMax : 2 * kSegLen;  // candidates up to which a list has one segment
   __shared__ SelectSmem S;
   __shared__ int s_extra[kMapLists + 1];  // exclusive scan over the lists of their segments after the first
   __shared__ int s_wave[SS_WAVES];
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
         const int c = l / A.Gq, gg = l - c * A.Gq, rr = c / A.E;
         int lo, hi;
         piece(rr, c - rr * A.E, gg, lo, hi);
-        ex = hi - lo > kLong ? (hi - lo + kSegLen - 1) / kSegLen - 1 : 0;
+        ex = hi - lo > kRegMax ? (hi - lo + kSegLen - 1) / kSegLen - 1 : 0;
       }
       int total;
       const int excl = block_scan_exclusive(ex, s_wave, total);
@@ -879,21 +879,22 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
   if (m == 0) return;  // nobody kept: every slot entry already says so
   const bool by_score = !A.arrival || r == A.k;  // the Fill-in round always selects by score (Sec. 4.2)
   if (m == n || !by_score) return;  // everybody, or the first m in token order: settled by scatter_candidates
-  // ---- long list (more than kLong candidates: then, if can_split, it has a workgroup per segment), the m highest scores: sample, copy the candidates that may be kept, last one finishes
+  if (n <= kRegMax) {
+    select_in_registers(A, n, m, r, j, fill0, [&](int idx, u32 &kx, int &tok) { kx = keys[idx]; tok = toks[idx]; }, S, slot,
+                        slot_token);
+    return;
+  }
+
+  // ---- long list (if can_split it has a workgroup per segment), the m highest scores: sample, copy the candidates that may be
+  // kept, last one finishes
   const int nseg = (n + kSegLen - 1) / kSegLen;
   // rank in the sample: the expected number of sampled keys among the list's m highest, plus five
   // standard deviations and a few; the candidates with key >= L then number about n / kSampleLen times that
   const float expect = (float)m * (float)kSampleLen / (float)n;
   const int qsel = (int)(expect + 5.0f * sqrtf(expect) + 16.0f);
-  const long long survivors = (long long)qsel * n / kSampleLen;
-  const bool split = can_split && n > kLong && qsel < kSampleLen && survivors <= (n <= kRegMax ? n / 3 : kRegMax * 7 / 8);
+  const bool split = can_split && qsel < kSampleLen && (long long)qsel * n / kSampleLen <= kRegMax * 7 / 8;
   if (!split) {
-    if (seg > 0) return;
-    if (n <= kRegMax)
-      select_in_registers(A, n, m, r, j, fill0, [&](int idx, u32 &kx, int &tok) { kx = keys[idx]; tok = toks[idx]; },
-                          S, slot, slot_token);
-    else
-      select_streaming(A, n, m, r, j, fill0, keys, toks, S, slot, slot_token);
+    if (seg == 0) select_streaming(A, n, m, r, j, fill0, keys, toks, S, slot, slot_token);
     return;
   }
   u32 L;
@@ -902,7 +903,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
     // instruction then reads one run - two cache lines - where single candidates a stride apart would
     // touch 64 lines: 19 -> 5 us for a list of 900 K candidates)
     static_assert(kSegPer * SS_WAVES * kWave == kSampleLen, "one run per (trip, wave)");
-    const int run = n / (kSampleLen / kWave);  // > 64: n > kLong >= 1.5 kSampleLen
+    const int run = n / (kSampleLen / kWave);  // > 64: n > kRegMax >= 1.5 kSampleLen
     u32 sk[kSegPer];
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) sk[u] = keys[(size_t)(u * SS_WAVES + w) * run + lane];

@@ -16,9 +16,8 @@ constexpr int kTokBlock = 128;          // tokens per workgroup in the per-token
 constexpr int kWave = 64;
 constexpr int kMinRowTile = 32;         // lowest row tile of the grouped GEMM
 // Selection lists (rr_dispatch.hip): up to kSelectRegMax candidates are one workgroup's registers;
-// longer lists - and lists from 2 kSelectShortLen on of which most candidates fall away - are cut into segments of kSelectSegLen or
-// kSelectShortLen candidates, one workgroup each, when the batch can hold a list past the registers at all and the lists
-// are few enough for the segment map (kept in LDS).
+// longer lists are cut into segments of kSelectSegLen or kSelectShortLen candidates, one workgroup each, when the batch
+// can hold such a list at all and the lists are few enough for the segment map (kept in LDS).
 constexpr int kSelectRegMax = 24576;
 constexpr int kSelectSegLen = 16384;
 constexpr int kSelectShortLen = 4096, kSelectShortMax = 1 << 20;  // segments of batches of up to that many candidates

@@ -253,6 +253,25 @@ def test_dispatch_long_lists_bit_exact(T, E, G, k, cf, hot, ties, arrival, quota
     gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr"), arrival, quota))
 
 
+# Token orders that defeat a sample of 64 evenly spaced runs of 64 candidates: the highest scores all in those runs, or none; and
+# runs of neighbours with nearly the same score.  Lists just under and over what one workgroup holds, and long ones.
+@pytest.mark.parametrize("T,cf", [(20000, 0.5), (24576, 0.2), (24577, 0.2), (60000, 0.2)])
+@pytest.mark.parametrize("kind", ["in the runs", "outside", "alike"])
+def test_dispatch_misleading_token_order_bit_exact(T, cf, kind):
+    rng = np.random.default_rng(T)
+    s = rng.standard_normal(T)
+    runs = (np.arange(64)[:, None] * (T // 64) + np.arange(64)).ravel()
+    if kind == "in the runs":
+        s[runs] += 8
+    if kind == "outside":
+        s[runs] -= 8
+    if kind == "alike":
+        s = np.repeat(rng.standard_normal(T // 64 + 1), 64)[:T] + 0.01 * s
+    a = np.stack([s, np.full(T, -40.0)], axis=1).astype(np.float32)  # all tokens choose expert 0
+    cfg = rr.RRConfig(T, 64, 0, 2, 1, 1, cf, rr.RR_F32, rr.RR_ACT_SWIGLU, gu.flags_of(("ir", "fr")))
+    gu.assert_tables_equal(gu.run_dispatch(cfg, a), _oracle_tables(a, cfg, ("ir", "fr")))
+
+
 # ------------------------------------------------------------------ router scores
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T,d,E,k", [(256, 64, 8, 1), (1000, 264, 6, 2), (513, 1024, 64, 2), (2048, 2048, 16, 1)])
