@@ -84,7 +84,7 @@ static int make_dims(const rr_config *c, bool need_ffn, Dims *D) {
   if ((c->flags & RR_FILL_IN) && c->k + 1 > c->E) return RR_ERR_INVALID_ARG;
   if (!(c->capacity_factor > 0.0f) || !isfinite(c->capacity_factor)) return RR_ERR_INVALID_ARG;
   if (c->flags & ~(uint32_t)(RR_INTRA_GPU | RR_FILL_IN | RR_POLICY_ARRIVAL | RR_QUOTA_PER_GROUP)) return RR_ERR_INVALID_ARG;
-  if (c->E > kMaxE || c->k > kMaxK || c->T > (1 << 24)) return RR_ERR_UNSUPPORTED;
+  if (c->E > kMaxE || c->k > kMaxK || c->T > kMaxTokens) return RR_ERR_UNSUPPORTED;
   if (c->dtype != RR_F32 && c->dtype != RR_BF16) return RR_ERR_UNSUPPORTED;
   if (c->d_model % 8) return RR_ERR_UNSUPPORTED;
   if (need_ffn) {

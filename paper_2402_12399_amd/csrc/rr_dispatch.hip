@@ -37,8 +37,11 @@ namespace {
 constexpr int TS = kMaxE + 1;  // LDS row stride of a [token][expert] tile
 
 // Experts x count blocks up to which ir_weights adds up the counts of the Intra-GPU lists itself, in workgroups of 128 tokens;
-// past it in workgroups of 1024, which make an eighth of the blocks and add eight times as fast.  100000 tokens, 64 experts: count, scan and
-// weights 14.2 us, count and weights 11.3.
+// past it in workgroups of 1024, which make an eighth of the blocks and add eight times as fast, up to kIrLargeSelfMax; then the scan
+// launch, behind blocks of 128.  64 experts, the Intra-GPU kernels / the whole call, us: 100000 tokens 14.2 with the scan, 11.3 without;
+// 131072 tokens (the line) 20.1 / 59 and 15.9 / 55; past it, 163840 tokens 20.3 / 65.3 and 16.5 / 65.4, 262144 tokens 21.1 / 76.1 and 18.9 / 77.5,
+// 524288 tokens 24.4 / 117 and 27.1 / 122: the adding up, of all blocks in every workgroup, takes what the launch would.  (The lower line is not
+// where both sides are equal: 8192 tokens, just under it, 20.7 / 33.7 and in workgroups of 1024 13.7 / 26.8; 4096 tokens 16.9 / 27.7.)
 constexpr int kIrSelfMax = 4096, kIrLargeBlock = 1024, kIrLargeSelfMax = 8192;
 
 struct DispatchArgs {
@@ -735,7 +738,7 @@ __device__ inline void select_streaming(const DispatchArgs &A, int n, int m, int
 //     list with select_in_registers; otherwise (the sample misled, or the scores are tied en
 //     masse) it streams the original list.  The result is exact either way.
 constexpr int kRegMax = kSelectRegMax;           // candidates that fit the registers of one workgroup
-constexpr int kMapLists = 2048;                  // lists up to which long lists are split (the map is kept in LDS)
+constexpr int kMapLists = kSelectMapLists;       // lists up to which long lists are split (the map is kept in LDS)
 
 // Exclusive scan of one value per thread over the workgroup (two barriers); total = sum over all threads.
 __device__ inline int block_scan_exclusive(int v, int *s_wave, int &total) {
@@ -778,6 +781,9 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
                                                                  int32_t *__restrict__ fill_total) {
   constexpr int kSegPer = kSegLen / SS_THREADS;  // candidates per thread of a segment workgroup
   constexpr int kSampleLen = kSegLen;            // keys in the sample
+  // candidates of the longest list: tokens of a batch, or what the launch takes for short segments
+  constexpr int kMaxList = kSegLen == kSelectShortLen ? kSelectShortMax : kMaxTokens;
+  static_assert(kMaxList / kSegLen + 1 <= kMapLists + 1, "the offsets of a list's segments take the map's place");
   __shared__ SelectSmem S;
   __shared__ int s_extra[kMapLists + 1];  // exclusive scan over the lists of their segments after the first
   __shared__ int s_wave[SS_WAVES];
@@ -973,7 +979,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
   int total = 0;
   {
     int carry = 0;
-    for (int q0 = 0; q0 < nseg; q0 += SS_THREADS) {  // nseg <= 2^24 / kSegLen + 1 fits s_extra
+    for (int q0 = 0; q0 < nseg; q0 += SS_THREADS) {  // (nseg fits s_extra)
       const int q = q0 + tid;
       const int c = q < nseg ? (q == 0 ? seg_cnt[lst] : seg_more[extra_base + q - 1]) : 0;
       int tot;
@@ -1146,7 +1152,7 @@ __device__ inline int drops_of_token(const int32_t *slot, int i, int k) {
 }
 
 // TB tokens per workgroup and count block: kTokBlock, or kIrLargeBlock where ir_weights can then add up the counts of every
-// block itself but not those of the small blocks (ir_block).
+// block itself but not those of the small blocks (ir_large).
 template <int TB>
 __global__ __launch_bounds__(TB) void ir_count_kernel(DispatchArgs A, const int32_t *__restrict__ slot,
                                                              const int32_t *__restrict__ ir_cand,

@@ -12,6 +12,7 @@ namespace rr {
 constexpr int kMaxE = 64;
 constexpr int kMaxK = 4;
 constexpr int kMaxRounds = kMaxK + 1;   // k top-k rounds + the Fill-in round
+constexpr int kMaxTokens = 1 << 24;
 constexpr int kTokBlock = 128;          // tokens per workgroup in the per-token routing kernels
 constexpr int kWave = 64;
 constexpr int kMinRowTile = 32;         // lowest row tile of the grouped GEMM
@@ -19,11 +20,12 @@ constexpr int kMinRowTile = 32;         // lowest row tile of the grouped GEMM
 // longer lists are cut into segments of kSelectSegLen or kSelectShortLen candidates, one workgroup each, when the batch
 // can hold such a list at all and the lists are few enough for the segment map (kept in LDS).
 constexpr int kSelectRegMax = 24576;
+constexpr int kSelectMapLists = 2048;
 constexpr int kSelectSegLen = 16384;
 constexpr int kSelectShortLen = 4096, kSelectShortMax = 1 << 20;  // segments of batches of up to that many candidates
 static_assert(kSelectShortLen >= kTokBlock * kMaxRounds, "a batch's short segments fit its Intra-GPU counts, [E, token blocks]");
 __host__ __device__ inline bool select_splits(long long T, int NR, int NL) {
-  return T * NR > kSelectRegMax && NL <= 2048;
+  return T * NR > kSelectRegMax && NL <= kSelectMapLists;
 }
 
 typedef uint32_t u32;
@@ -79,7 +81,8 @@ struct Work {
   int32_t *comp_tok;     // [NR*T]
   int32_t *seg_cnt;      // [NL + NR*T / kSelectSegLen] how many of those every segment has
   int32_t *list_done;    // [NL]      segments of a list that have finished (tickets)
-  int32_t *ir_blk_cnt;   // [E, NB]   Intra-GPU tokens per (expert, token block); scanned in place
+  int32_t *ir_blk_cnt;   // [E, NB]   Intra-GPU tokens per (expert, block of 128 tokens), scanned in place; or [blocks, E], blocks of 128 or 1024
+                         //           tokens, added up by ir_weights; before that the candidate counts of select_slot's short segments
   int32_t *ir_cnt;       // [E]
   int32_t *row_base;     // [E+1]     first dispatched row of each expert (slot rows, then IR rows)
   TileInfo *tiles;       // [max_mtiles] row tiles of the grouped GEMM
