@@ -827,6 +827,9 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
         split3(raw[i], scale, q);
 #pragma unroll
         for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2 *>(wr + p * PLANE + i * NW * 8 * 64) = q[p];
+        // (128 x 128: all rows' parts at once do not fit the registers.  9048 tokens, 768 x 1344, 64 experts: 690 us, two rows at a time 662;
+        // 64 x 128 has the room: 2048 tokens, 1024 x 2816, 8 experts 504, two rows at a time 514)
+        if (WM == 4 && i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       }
       fetch(kt + 1);
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // chunk kt is written
