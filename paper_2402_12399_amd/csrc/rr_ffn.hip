@@ -1097,9 +1097,9 @@ static_assert(TileB32::BM == kMinRowTile && TileB32n::BM == kMinRowTile && TileF
 // 32 x 128 92, 64 x 128 108 (one expert has more than 64 rows: 272 tiles), 128 x 128 74; fp32, up / down: 64 x 128
 // 213 / 238, 32 x 128 188 / 213, 32 x 64 165 / 168; 16 tokens, 8 experts, down 11008 -> 4096: 32 x 128 141, 32 x 64 133;
 // 8 experts 4096 x 11008, K = 11008: 1230 rows 256 x 256 256, 256 x 128 178, 64 x 128 255.
-// fp32: the split shapes' numbers are a fit to 260 layers timed in every pair of shapes (1e8 to 5e11 flop): the plan is 1.8 %
-// off the best pair on average, 6.6 % faster than the three fp32 shapes were (up to 1.45 times; three layers 5 - 13 % slower,
-// whose rows per expert the estimate gets wrong).
+// fp32: the split shapes' numbers are a fit to 260 layers timed in every pair of shapes (1e8 to 5e11 flop).  Of 600 others (5e7 to 3e11)
+// the plan is 1.2 % off the best pair on average and 8.5 % faster than the three fp32 shapes were; 16 are 2 - 7 % slower than
+// those: their rows per expert are not what the estimate expects, or each weight serves a row or two.
 enum FfnShape { FFN_P256, FFN_256, FFN_128, FFN_64, FFN_32, FFN_32N, FFN_S128, FFN_S64, FFN_F64, FFN_F32, FFN_F32N, FFN_LONG };
 struct ShapeInfo { int bm, brows; float cost, fixed, alone; };  // alone: of a chunk, where the CU has one workgroup (0: cost)
 constexpr ShapeInfo kShape[] = {{256, 256, 1.45f, 5.0f}, {256, 128, 1.0f, 3.0f}, {128, 128, 0.62f, 2.0f},
@@ -1134,15 +1134,18 @@ float shape_cost(const Dims &D, int K, int N, bool up, int q, bool by_rows = fal
   const int es = bf16 ? 2 : 4, KT = (int)(((long long)K * es + GB_ROW_BYTES - 1) / GB_ROW_BYTES);
   // a tile's rows are addressed with 32-bit byte offsets (below kLongRow elements the narrowest shape always fits)
   if ((long long)K * std::max(s.bm, s.brows) * es >= 1ll << 31) return -1.0f;
-  // fp32 rows of up to four chunks: fp32 MFMAs (a tile is mostly its start and end); longer ones: split operands or 32 x 64
+  // fp32 rows of up to four chunks: fp32 MFMAs (a tile is mostly its start and end); longer ones: split operands or 32 x 64.  Past 2^20 split
+  // tiles, passes of a tenth of a second, nothing was timed: fp32 MFMAs in any of their shapes, as for short rows.
   constexpr int kSplitChunks = 5;
-  if (split && KT < kSplitChunks) return -1.0f;
-  if ((q == FFN_F64 || q == FFN_F32) && KT >= kSplitChunks) return -1.0f;
+  constexpr long long kSplitTiles = 1ll << 20;
+  auto tiles_of = [&](int bm, int brows) { return expected_row_tiles(D, bm) * ((N + (gated ? brows / 2 : brows) - 1) / (gated ? brows / 2 : brows)); };
+  const bool can_split = KT >= kSplitChunks && tiles_of(kShape[FFN_S128].bm, kShape[FFN_S128].brows) <= kSplitTiles;
+  if (split && (!can_split || tiles_of(s.bm, s.brows) > kSplitTiles)) return -1.0f;
+  if ((q == FFN_F64 || q == FFN_F32) && can_split) return -1.0f;
   const float used = (float)std::min<long long>({(long long)D.T * D.k, D.Rmax, D.E});
   const float stream = used * N * K * es * (gated ? 2 : 1) / kHbm;
   const int bn = gated ? s.brows / 2 : s.brows;
   const long long mt = expected_row_tiles(D, s.bm), tiles = mt * ((N + bn - 1) / bn), rounds = tiles / kCUs, left = tiles - rounds * kCUs;
-  if (split && tiles > 1ll << 20) return -1.0f;  // (grids of more than one row: not measured, a pass takes seconds)
   const float fetch = (float)(s.brows * GB_ROW_BYTES) / kCuFetch * used / (float)mt;
   const float filled = std::min(1.0f, (float)std::min<long long>((long long)D.T * D.k, D.Rmax) / (float)(mt * s.bm));
   const float fixed = s.fixed + filled * (up && q == FFN_256 ? kAct256 : (up && q == FFN_128 ? kAct128 : 0.0f));
@@ -1175,17 +1178,24 @@ FfnPlan ffn_plan(const Dims &D) {
     const long long cuts = expected_row_tiles(D, bm) * (bm / s.bm) - expected_row_tiles(D, s.bm);
     return kEmpty * (float)(std::max(0ll, cuts) * ((N + bn - 1) / bn));
   };
+  // One GEMM in split tiles and the other, though it could be too, in 32 x 64 fp32 ones: only if well ahead.  256 tokens, 6 experts of
+  // 77 - 123 rows, 1600 x 5696: 373 us, 329 in 32 x 64 tiles alone; 656 tokens, 12 experts, 1808 x 6632: 671, 642.  Of the 600 layers 23
+  // are more than 2 % slower than in fp32 shapes without the margin (up to 12 %), 16 with it, and the mean of all gains 0.2 %.
+  constexpr float kMixed = 1.1f;
+  auto split = [](int q) { return q == FFN_S128 || q == FFN_S64; };
   FfnPlan best{(FfnShape)q1, (FfnShape)q1};
   float least = -1.0f, up[FFN_F32N + 1], down[FFN_F32N + 1];
   for (int q = q0; q <= q1; ++q) {
     up[q] = shape_cost(D, D.d, D.F, true, q);
     down[q] = shape_cost(D, D.F, D.d, false, q);
   }
+  const bool both = D.dtype != RR_BF16 && up[FFN_S64] >= 0.0f && down[FFN_S64] >= 0.0f;
   for (int u = q0; u <= q1; ++u)
     for (int w = q0; w <= q1; ++w) {
       if (!(up[u] >= 0.0f) || !(down[w] >= 0.0f)) continue;
       const int bm = std::max(kShape[u].bm, kShape[w].bm);
-      const float cost = up[u] + down[w] + empty(u, D.F, D.act == RR_ACT_SWIGLU, bm) + empty(w, D.d, false, bm);
+      const float sure = both && split(u) != split(w) ? kMixed : 1.0f;
+      const float cost = sure * (up[u] + down[w]) + empty(u, D.F, D.act == RR_ACT_SWIGLU, bm) + empty(w, D.d, false, bm);
       if (least < 0.0f || cost <= least) { least = cost; best = {(FfnShape)u, (FfnShape)w}; }
     }
   // Layers that their weights bound - more than the last-level cache holds, and some dozen to a tile's height of rows
