@@ -89,10 +89,11 @@ def run_dispatch(cfg: rr.RRConfig, logits_np: np.ndarray) -> dict:
 
 
 def run_forward(cfg: rr.RRConfig, dev: dict, want_tables=True):
-    """dev: device tensors x, w_router, bias, w1, w3, w2.  Returns (out tensor, tables dict, logits np)."""
+    """dev: device tensors x, w_router, bias, w1, w3, w2.  Returns (out tensor, tables dict, logits np).  Outputs start as NaN, so
+    that an element that the call leaves unwritten cannot hold an earlier call's result."""
     tdt = torch.float32 if cfg.dtype == rr.RR_F32 else torch.bfloat16
-    out = torch.empty((cfg.T, cfg.d_model), dtype=tdt, device="cuda")
-    logits = torch.empty((cfg.T, cfg.E), dtype=torch.float32, device="cuda")
+    out = torch.full((cfg.T, cfg.d_model), float("nan"), dtype=tdt, device="cuda")
+    logits = torch.full((cfg.T, cfg.E), float("nan"), dtype=torch.float32, device="cuda")
     tb = rr.alloc_tables(cfg) if want_tables else None
     ws = rr.alloc_workspace(cfg)
     rr.rr_moe_forward(cfg, dev["x"], dev["w_router"], dev["bias"], dev["w1"], dev["w3"], dev["w2"], out, tb, logits, ws)

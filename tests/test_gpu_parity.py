@@ -329,6 +329,7 @@ def _forward_case(w, mode, inputs, sample=None, arrival=False, quota=False, logi
         _flipped_decisions(want_tables, orc.route(a, w.k, w.G, w.capacity_factor, "ir" in mode, "fr" in mode, policy, quota))))
     want_out = orc.moe_output(f32("x"), want_tables, w.k, f32("w1"), f32("w3"), f32("w2"), w.act, tokens=sample)
     got = gu.to_host_f64(out)
+    assert np.isfinite(got).all()  # every row is written, also those that no sample looks at
     if sample is not None:
         got = got[sample]
     err = _assert_output_close(got, want_out, w.dtype, w.name)
@@ -394,6 +395,7 @@ def _full_size_case(w, mode, n_sample=1024, quota=False, report_flips=True):
 
     want_out = orc.moe_output(x, want, w.k, PerExpert(dev["w1"]), PerExpert(dev["w3"]), PerExpert(dev["w2"]),
                               w.act, tokens=sample)
+    assert bool(torch.isfinite(out).all())  # every row is written, also those that the sample leaves out
     got = gu.to_host_f64(out[torch.from_numpy(sample).cuda()])
     _assert_output_close(got, want_out, w.dtype, w.name)
     unprocessed = torch.from_numpy(np.flatnonzero(want["combine_w"].sum(axis=1) == 0)).cuda()
@@ -998,7 +1000,7 @@ def test_forward_split_tiles_of_a_small_and_a_large_column(small, large):
 def _whole_layer(w, inp):
     """(output of a layer of one expert and room for every token, the same in float64)"""
     cfg, dev = gu.config_of(w, ()), {n: gu.to_device(v, "f32") for n, v in inp.items()}
-    out = torch.empty((w.T, w.d_model), dtype=torch.float32, device="cuda")
+    out = torch.full((w.T, w.d_model), float("nan"), device="cuda")
     rr.rr_moe_forward(cfg, dev["x"], dev["w_router"], dev["bias"], dev["w1"], dev["w3"], dev["w2"], out, None, None,
                       rr.alloc_workspace(cfg))
     x, w1, w2 = (torch.from_numpy(v).double() for v in (inp["x"], inp["w1"][0], inp["w2"][0]))
@@ -1048,7 +1050,7 @@ def _activation_of(g, act, d, F):
     w2 = torch.zeros(1, d, F, dtype=torch.bfloat16)
     w2[0, 0, 0] = 1
     cfg = rr.RRConfig(len(g), d, F, 1, 1, 1, 1.0, rr.RR_BF16, act, 0)
-    out = torch.empty(len(g), d, dtype=torch.bfloat16, device="cuda")
+    out = torch.full((len(g), d), float("nan"), dtype=torch.bfloat16, device="cuda")
     rr.rr_moe_forward(cfg, x.cuda(), torch.zeros(1, d, device="cuda"), None, w1.cuda(),
                       w3.cuda() if act == rr.RR_ACT_SWIGLU else None, w2.cuda(), out, None, None, rr.alloc_workspace(cfg))
     torch.cuda.synchronize()
@@ -1094,6 +1096,34 @@ def test_forward_one_expert(T, d, F, dtype, act):
     for cf in (1.0, 0.4):  # everybody kept; most re-routed to the same expert
         w = wl.Workload("one expert", T, d, F, 1, 1, 1, cf, dtype, act, "none", 60 + T)
         _forward_case(w, ("ir",), wl.make_inputs(w))
+
+
+# Top-1 with Intra-GPU Rectification and without Fill-in: every token has exactly one row, which the down projection stores, and
+# nothing is combined.  Every tile that a down projection has, rows through slots, Intra-GPU lists and per-group rows, tables
+# by one workgroup and by launches, ragged sizes; much and little dropped.
+ONE_ROW_LAYERS = [
+    # tile of the down projection, T, d_model, d_ff, E, G, cf, dtype, act, quota
+    ("64x128 f32", 8194, 520, 264, 2, 1, 0.5, "f32", "swiglu", False), ("128x128 f32", 6001, 1032, 264, 2, 1, 1.0, "f32", "swiglu", False),
+    ("32x64 f32", 130, 800, 264, 4, 2, 0.5, "f32", "swiglu", False), ("128x128 f32", 5632, 1032, 264, 4, 4, 0.5, "f32", "gelu", True),
+    ("32x64 bf16", 40, 72, 136, 4, 2, 0.25, "bf16", "gelu", False), ("32x128 bf16", 700, 776, 264, 4, 1, 0.5, "bf16", "swiglu", False),
+    ("64x128 bf16", 4097, 264, 264, 2, 1, 0.5, "bf16", "swiglu", False), ("128x128 bf16", 6001, 264, 264, 2, 1, 1.0, "bf16", "swiglu", False),
+    ("256x128 bf16", 4097, 1032, 264, 2, 1, 0.5, "bf16", "swiglu", False), ("256x256 bf16", 7815, 2288, 888, 3, 1, 0.5, "bf16", "swiglu", False),
+    ("256x256 bf16", 4096, 2040, 1512, 8, 2, 1.0, "bf16", "swiglu", True),
+]
+
+
+@pytest.mark.parametrize("case", ONE_ROW_LAYERS, ids=[f"{c[0]} T={c[1]}{' quota' * c[9]}" for c in ONE_ROW_LAYERS])
+def test_forward_one_row_per_token(case):
+    name, T, d, F, E, G, cf, dtype, act, quota = case
+    w = wl.Workload(name, T, d, F, E, G, 1, cf, dtype, act, "zipf:1.1", 50 + T % 97)
+    shapes = gu.ffn_shapes(gu.config_of(w, ("ir",), quota=quota))
+    assert f"{shapes.bm[1]}x{shapes.brows[1]} {dtype}" == name
+    rr.rr_profile_enable(True)
+    try:
+        _forward_case(w, ("ir",), wl.make_inputs(w), quota=quota)
+        assert rr.rr_profile_read()["combine"][0] == 0
+    finally:
+        rr.rr_profile_enable(False)
 
 
 # Batches whose tables one workgroup builds, and their borders: one token, a wave and one more or less, the most tokens
