@@ -435,6 +435,7 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
 //     share the bins at the ends.  (Bins as wide as their distance would hold all other keys in one, by LDS atomics on one address.)
 //   * Where half of the waves have their first key in one bin all the same, scores are spread in no such way and the digits select.
 //   * More keys in the bin than a wave has lanes: one score, many times (done), or the digits go on among its keys.
+//   * Lists of no more keys than that need no bins (1024 tokens, 64 experts, 8 groups of quotas, lists of a few keys: the layer 54.4 us with, 52.1).
 // Us of the selecting kernel, digits alone / bins from the lowest to the highest score, then digits over again / now, for scores
 // that are normal, with one of 1e4, with every hundredth times 1e6, multiples of 1/4: 16384 tokens, 2 experts 22.2 / 20.0 / 20.1, 22.0 /
 // 29.0 / 20.4, 22.5 / 29.1 / 21.8, 24.4 / 26.5 / 20.8; 32768 tokens 23.1 / 20.3 / 19.3, 22.8 / 35.6 / 21.0, 23.0 / 35.3 / 22.6,
@@ -443,7 +444,7 @@ constexpr int kValueBins = 4 * SS_THREADS;
 static_assert(kValueBins + 2 * kWave + 1 <= kHistWords, "bins, the bin's keys, wave results, their number");
 static_assert(SS_WAVES == 16, "a row of 16 lanes for each of the waves' results");
 template <class Each>
-__device__ inline u32 value_select(int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
+__device__ inline u32 value_select(int n, int m, Each each, u32 *hist, u32 *s_pick, u32 &need_eq) {
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   u32 *const few = hist + kValueBins, *const wres = few + kWave, *const n_few = wres + kWave;
   // v of another lane of the row of 16
@@ -474,11 +475,33 @@ __device__ inline u32 value_select(int m, Each each, u32 *hist, u32 *s_pick, u32
       nhi = min(nhi, ~kx);
     }
   };
+  // the m-th highest of `count` keys, at most a wave's lanes, that `is_in` tells: every wave ranks them for itself
+  auto ranked = [&](int count, auto is_in) {
+    each([&](u32 kx, bool valid) {
+      if (valid && is_in(kx)) few[atomicAdd(n_few, 1u)] = kx;
+    });
+    __syncthreads();
+    const u32 mine = lane < count ? few[lane] : 0u;  // (a key is never 0)
+    int above = 0, equal = 0;
+    for (int q = 0; q < count; ++q) {
+      const u32 other = lane_value(mine, q);
+      above += other > mine;
+      equal += other == mine;
+    }
+    const unsigned long long at = __ballot(lane < count && above < m && m <= above + equal);
+    const int src = __ffsll((long long)at) - 1;
+    need_eq = (u32)(m - __builtin_amdgcn_readlane(above, src));
+    return lane_value(mine, src);
+  };
+  if (tid == 0) *n_few = 0;
+  if (n <= kWave) {  // (uniform over the workgroup)
+    __syncthreads();
+    return ranked(n, [](u32) { return true; });
+  }
   each(extremes);
   const unsigned long long have = __ballot(lo != 0xffffffffu);
   wave_results(lo, nhi, have ? lane_value(lo, __ffsll((long long)have) - 1) : 0u);  // (a key is never 0)
   reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
-  if (tid == 0) *n_few = 0;
   __syncthreads();
   const u32 wave_v = wres[lane];  // lanes 0 .. 15: lowest keys of the waves, 16 .. 31: complements of the highest, 32 .. 47: a key
   u32 ends = max(wave_v, row_step(quad1, wave_v)), all = row_min(wave_v);  // (a wave without keys: all ones, and so its pair)
@@ -531,23 +554,7 @@ __device__ inline u32 value_select(int m, Each each, u32 *hist, u32 *s_pick, u32
     __syncthreads();
     const int bin = (int)s_pick[0], in_bin = (int)s_pick[2];
     m = (int)s_pick[1];  // of the bin's keys
-    if (in_bin <= kWave) {
-      each([&](u32 kx, bool valid) {
-        if (valid && bin_of(kx) == bin) few[atomicAdd(n_few, 1u)] = kx;
-      });
-      __syncthreads();
-      const u32 mine = lane < in_bin ? few[lane] : 0u;  // (a key is never 0)
-      int above = 0, equal = 0;
-      for (int q = 0; q < in_bin; ++q) {
-        const u32 other = lane_value(mine, q);
-        above += other > mine;
-        equal += other == mine;
-      }
-      const unsigned long long at = __ballot(lane < in_bin && above < m && m <= above + equal);
-      const int src = __ffsll((long long)at) - 1;
-      need_eq = (u32)(m - __builtin_amdgcn_readlane(above, src));
-      return lane_value(mine, src);
-    }
+    if (in_bin <= kWave) return ranked(in_bin, [&](u32 kx) { return bin_of(kx) == bin; });
     lo = nhi = 0xffffffffu;  // the bin's extremes
     each([&](u32 kx, bool valid) { extremes(kx, valid && bin_of(kx) == bin); });
     wave_results(lo, nhi, 0);  // (the sums were read before the last barrier)
@@ -594,7 +601,7 @@ __device__ inline void select_trips(const DispatchArgs &A, int n, int m, int r, 
     if (u < nu && idx < n) load(idx, kreg[u], treg[u]);
   }
   u32 need_eq = 0;
-  const u32 thr = value_select(m, [&](auto f) {
+  const u32 thr = value_select(n, m, [&](auto f) {
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       if (u < nu) f(kreg[u], u * SS_THREADS + tid < n);
@@ -914,7 +921,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) sk[u] = keys[(size_t)(u * SS_WAVES + w) * run + lane];
     u32 dummy;
-    L = value_select(qsel, [&](auto f) {
+    L = value_select(kSampleLen, qsel, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kSegPer; ++u) f(sk[u], true);
     }, S.hist, S.pick, dummy);
@@ -1101,7 +1108,7 @@ __global__ __launch_bounds__(SS_THREADS) void select_direct_kernel(DispatchArgs 
   const int mode = m == 0 ? 0 : (m == n ? 1 : (by_score ? 3 : 2));
   u32 thr = 0, need_eq = 0;
   if (mode == 3)
-    thr = value_select(m, [&](auto f) {
+    thr = value_select(n, m, [&](auto f) {
 #pragma unroll
       for (int u = 0; u < kDirectPer; ++u)
         if (u < per) f(kreg[u], (member >> u) & 1u);
