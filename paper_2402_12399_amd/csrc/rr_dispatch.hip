@@ -430,17 +430,20 @@ __device__ inline u32 radix_select(int m, Each each, u32 *hist, u32 *s_pick, u32
 // over such bins, where the leading digits of their keys - sign and exponent - are a handful of values: the bin
 // with the m-th highest holds a few keys as a rule, which every wave ranks for itself.  Five barriers, where
 // three digit passes are thirteen.  3001 tokens, 6 experts: select_direct_kernel 11.8 -> 9.6 us.
-//   * The bins span three times the range between the waves' usual extremes (of the lowest keys of two waves the higher one, of
-//     eight such the lowest, and the mirror image), as far as there are scores: a few that lie far from all others
-//     share the bins at the ends.  (Bins as wide as their distance would hold all other keys in one, by LDS atomics on one address.)
-//   * Where half of the waves have their first key in one bin all the same, scores are spread in no such way and the digits select.
+//   * The bins span the list's scores, or - lists of more than kShortList keys, and shorter ones that half of whose waves have their first
+//     key in one bin - three times the range between the waves' usual extremes (of the lowest keys of two waves the higher one, of
+//     eight such the lowest, and the mirror image): a few scores that lie far from all others then share the bins at the ends.
+//     (Bins as wide as their distance would hold all other keys in one, by LDS atomics on one address.  Waves of short lists hold runs of
+//     neighbouring tokens, whose scores can be alike: their extremes say little.)
+//   * Where half of the waves' first keys share a bin all the same, scores are spread in no such way and the digits select.
 //   * More keys in the bin than a wave has lanes: one score, many times (done), or the digits go on among its keys.
-//   * Lists of no more keys than that need no bins (1024 tokens, 64 experts, 8 groups of quotas, lists of a few keys: the layer 54.4 us with, 52.1).
+//   * Lists of up to kTinyList keys need no bins: 1024 tokens, 64 experts, top-2, lists of 32: the kernel 10.7 -> 9.7 us.  (Every wave goes
+//     over the keys one by one, 64 of them 2.7 us: 1024 tokens, 16 experts, top-4, lists of 64: 10.5 us, 12.4 without bins.)
 // Us of the selecting kernel, digits alone / bins from the lowest to the highest score, then digits over again / now, for scores
-// that are normal, with one of 1e4, with every hundredth times 1e6, multiples of 1/4: 16384 tokens, 2 experts 22.2 / 20.0 / 20.1, 22.0 /
-// 29.0 / 20.4, 22.5 / 29.1 / 21.8, 24.4 / 26.5 / 20.8; 32768 tokens 23.1 / 20.3 / 19.3, 22.8 / 35.6 / 21.0, 23.0 / 35.3 / 22.6,
-// 25.4 / 27.7 / 21.8.
-constexpr int kValueBins = 4 * SS_THREADS;
+// that are normal, with one of 1e4, with every hundredth times 1e6, multiples of 1/4: 3001 tokens, 6 experts 13.5 / 10.8 / 10.8, 13.3 /
+// 13.5 / 10.9, 13.1 / 14.3 / 11.8, 14.7 / 15.3 / 12.0; 16384 tokens, 2 experts 22.5 / 19.9 / 20.1, 22.2 / 29.0 / 20.3, 22.2 / 29.2 / 21.9, 24.5 /
+// 26.6 / 22.9; 32768 tokens 22.7 / 20.7 / 19.3, 23.0 / 35.8 / 21.0, 22.8 / 35.4 / 22.7, 25.4 / 27.8 / 21.9.
+constexpr int kValueBins = 4 * SS_THREADS, kTinyList = 32, kShortList = 4096;
 static_assert(kValueBins + 2 * kWave + 1 <= kHistWords, "bins, the bin's keys, wave results, their number");
 static_assert(SS_WAVES == 16, "a row of 16 lanes for each of the waves' results");
 template <class Each>
@@ -494,7 +497,7 @@ __device__ inline u32 value_select(int n, int m, Each each, u32 *hist, u32 *s_pi
     return lane_value(mine, src);
   };
   if (tid == 0) *n_few = 0;
-  if (n <= kWave) {  // (uniform over the workgroup)
+  if (n <= kTinyList) {  // (uniform over the workgroup)
     __syncthreads();
     return ranked(n, [](u32) { return true; });
   }
@@ -504,10 +507,7 @@ __device__ inline u32 value_select(int n, int m, Each each, u32 *hist, u32 *s_pi
   reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
   __syncthreads();
   const u32 wave_v = wres[lane];  // lanes 0 .. 15: lowest keys of the waves, 16 .. 31: complements of the highest, 32 .. 47: a key
-  u32 ends = max(wave_v, row_step(quad1, wave_v)), all = row_min(wave_v);  // (a wave without keys: all ones, and so its pair)
-  ends = min(ends, row_step(quad2, ends));
-  ends = min(ends, row_step(ror4, ends));
-  ends = min(ends, row_step(ror8, ends));
+  const u32 all = row_min(wave_v);
   lo = lane_value(all, 0);
   nhi = lane_value(all, SS_WAVES);
   u32 hi = ~nhi;
@@ -516,20 +516,32 @@ __device__ inline u32 value_select(int n, int m, Each each, u32 *hist, u32 *s_pi
     return lo;
   }
   const float lowest = key_score(lo), highest = key_score(hi);
-  const float usual_low = key_score(lane_value(ends, 0)), usual_high = key_score(~lane_value(ends, SS_WAVES));
-  const float margin = usual_high - usual_low;  // (neighbouring tokens' scores can be alike, and the waves' extremes then lie close)
-  const bool usual = margin > 0.0f;
-  const float low = usual ? fmaxf(lowest, usual_low - margin) : lowest;
-  const float width = (usual ? fminf(highest, usual_high + margin) : highest) - low, scale = (float)kValueBins / width;
+  float low, scale;
   auto bin_of = [&](u32 kx) { return (int)__builtin_amdgcn_fmed3f((key_score(kx) - low) * scale, 0.0f, (float)(kValueBins - 1)); };
-  bool digits = !(width < INFINITY) || !(scale < INFINITY) || isnan(lowest) || isnan(highest);  // (uniform over the workgroup)
-  if (!digits) {
+  // bins between two scores; false: no ordinary range, or half of the waves' keys share a bin and the bin may be crowded (uniform over
+  // the workgroup)
+  auto bins_over = [&](float from, float to) {
+    const float width = to - from;
+    low = from;
+    scale = (float)kValueBins * __builtin_amdgcn_rcpf(width);
+    if (!(width < INFINITY) || !(scale < INFINITY)) return false;
+    if (n <= kWave) return true;
     const bool probe = (lane & 48) == 2 * SS_WAVES && wave_v != 0;
     const int bin = probe ? bin_of(wave_v) : -1 - lane, probes = __popcll(__ballot(probe));
     auto sharers = [&](int q) { return __popcll(__ballot(bin == __builtin_amdgcn_readlane(bin, 2 * SS_WAVES + q))); };
-    digits = max(sharers(0), sharers(2)) >= max(3, (probes + 1) / 2);
+    return max(sharers(0), sharers(2)) < max(3, (probes + 1) / 2);
+  };
+  bool spread = n <= kShortList && bins_over(lowest, highest);
+  if (!spread && lowest <= highest) {  // (both are numbers)
+    u32 ends = max(wave_v, row_step(quad1, wave_v));  // (a wave without keys: all ones, and so its pair)
+    ends = min(ends, row_step(quad2, ends));
+    ends = min(ends, row_step(ror4, ends));
+    ends = min(ends, row_step(ror8, ends));
+    const float usual_low = key_score(lane_value(ends, 0)), usual_high = key_score(~lane_value(ends, SS_WAVES));
+    const float apart = usual_high - usual_low, margin = apart > 0.0f ? apart : INFINITY;  // (else the list's own extremes)
+    spread = bins_over(fmaxf(lowest, usual_low - margin), fminf(highest, usual_high + margin));
   }
-  if (!digits) {
+  if (spread) {
     each([&](u32 kx, bool valid) {
       if (valid) atomicAdd(&hist[bin_of(kx)], 1u);
     });
