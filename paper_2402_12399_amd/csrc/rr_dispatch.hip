@@ -1032,9 +1032,10 @@ __global__ __launch_bounds__(SS_THREADS) void select_slot_kernel(DispatchArgs A,
 // keys of round r - and counts expert j's candidates of the earlier rounds on the way (the kept count of a
 // round is min(candidates, free slots)).  No candidate counts, no scan, no scatter: three launches fewer.
 // A thread owns `per` neighbouring tokens (4, 8, 12 or 16), so thread order is token order: one scan over the threads
-// hands out the slots.  What bounds it is what one CU reads for a list, then the digit passes: with the [T, k + 1]
-// table of 32-bit ranks and the keys of all rounds side by side it read 24 bytes per token at k = 2, now 4 + (r + 1).
-// 16384 tokens, 8 experts, top-2: reading 10.1 -> 5.6 us, kernel 29.1 -> 22.2; 4000 tokens, 16 experts: 18.9 -> 13.4.
+// hands out the slots.  What bounds it is what one CU reads for a list, then a chain of nine barriers around the LDS
+// histogram: with the [T, k + 1] table of 32-bit ranks and the keys of all rounds side by side it read 24 bytes per token at k = 2,
+// now 4 + (r + 1).  16384 tokens, 8 experts, top-2: reading 10.1 -> 5.6 us, kernel 29.1 -> 22.2, with the histogram of scores 18.0; 4000
+// tokens, 16 experts: 18.9 -> 13.4 -> 11.2; 3001, 6 experts: 13.5 -> 10.8.
 constexpr int kDirectPer = kDirectMaxT / SS_THREADS;
 static_assert(kDirectPer == 16, "a thread's tokens are quadruples, at most four");
 
